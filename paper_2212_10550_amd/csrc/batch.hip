@@ -498,7 +498,8 @@ __global__ void __launch_bounds__(kW * kWave, kMinGroups * kW / 4) render_kernel
           int bone = -1;
           float xc[3] = {0.0f, 0.0f, 0.0f};
           if (act) {
-            const dfm::InitResult q = dfm::broyden_from(A, pl.gr, x0, true, xp, pl.max_iter, pl.tol_stop);
+            dfm::GatherCorners cs(A, pl.gr);
+            const dfm::InitResult q = dfm::broyden_from(cs, pl.gr, x0, true, xp, pl.max_iter, pl.tol_stop);
             if (q.ok && q.r < pl.tol_valid && dfm::in_hbox(q.x, pl.hbox)) {
               xc[0] = q.x[0];
               xc[1] = q.x[1];
@@ -531,7 +532,8 @@ __global__ void __launch_bounds__(kW * kWave, kMinGroups * kW / 4) render_kernel
           const int sj = qa ? (int)wm.queue[q0 + h] : 0;
           float xp[3] = {0.0f, 0.0f, 0.0f};
           if (qa) sample_xp(wm, ra, rb, sb + sj, xp);
-          const dfm::Choice cc = dfm::multi_init<32>(A, pl.gr, pd.binv, pd.bok, nb, xp, qa, lane & 31, pl.hbox,
+          dfm::GatherCorners cs(A, pl.gr);
+          const dfm::Choice cc = dfm::multi_init<32>(cs, pl.gr, pd.binv, pd.bok, nb, xp, qa, lane & 31, pl.hbox,
                                                      pl.max_iter, pl.tol_stop, pl.tol_valid);
           const int sr = r < 2 ? 32 * r : 0;
           const float xs[3] = {__shfl(cc.x[0], sr, kWave), __shfl(cc.x[1], sr, kWave), __shfl(cc.x[2], sr, kWave)};

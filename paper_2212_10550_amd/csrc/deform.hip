@@ -11,7 +11,8 @@
 //  * solve kernel: eight lanes per posed sample each run a third of the nb
 //    Broyden solves in FP32 registers and pick the lowest residual with
 //    shuffles; bone inverses are staged in LDS once per block; the blended
-//    grid is read through the vector L1/L2 with float4 gathers.
+//    grid is read through the vector L1/L2 with float4 gathers, a cell's
+//    eight corners once for as long as the iterate stays in it.
 #include <mutex>
 
 #include "common.h"
@@ -58,7 +59,8 @@ __global__ void __launch_bounds__(kSolveBlock) solve_kernel(
       xp[1] = xp_soa[ld + n];
       xp[2] = xp_soa[2 * ld + n];
     }
-    const Choice c = multi_init(A, gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
+    HeldCorners cs(A, gr);
+    const Choice c = multi_init<kGroup>(cs, gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
     if (act && j == 0) write_choice(c, n, ld, 0, xc_soa, bone_out, resid_out, steps_out);
   }
 }
@@ -97,8 +99,9 @@ __global__ void __launch_bounds__(kSolveBlock) roots_kernel(
     const bool act = n < Sn;
     if (act) {
       const float xp[3] = {xp_soa[n], xp_soa[ld + n], xp_soa[2 * ld + n]};
+      HeldCorners cs(A, gr);
       for (int i = j; i < nb; i += kGroup) {
-        const InitResult q = broyden(A, gr, sBinv + 12 * i, sBok[i], xp, max_iter, tol_stop);
+        const InitResult q = broyden(cs, gr, sBinv + 12 * i, sBok[i], xp, max_iter, tol_stop);
         const bool valid = q.ok && q.r < tol_valid && in_hbox(q.x, hbox);
         cx[sl][i][0] = q.x[0];
         cx[sl][i][1] = q.x[1];
@@ -181,7 +184,8 @@ __global__ void __launch_bounds__(kSolveBlock) guided_kernel(
   for (int64_t n = (int64_t)blockIdx.x * kSolveBlock + threadIdx.x; n < Sn; n += (int64_t)gridDim.x * kSolveBlock) {
     const float xp[3] = {xp_soa[n], xp_soa[ld + n], xp_soa[2 * ld + n]};
     float x[3] = {x0_soa[n], x0_soa[ld + n], x0_soa[2 * ld + n]};
-    const InitResult q = broyden_from(A, gr, x, true, xp, max_iter, tol_stop);
+    HeldCorners cs(A, gr);
+    const InitResult q = broyden_from(cs, gr, x, true, xp, max_iter, tol_stop);
     gsteps[n] = (int16_t)q.steps;
     if (q.ok && q.r < tol_valid && in_hbox(q.x, hbox)) {
       xc_soa[n] = q.x[0];
@@ -227,7 +231,8 @@ __global__ void __launch_bounds__(kSolveBlock) fallback_kernel(
       xp[1] = xp_soa[ld + n];
       xp[2] = xp_soa[2 * ld + n];
     }
-    const Choice c = multi_init<kFbGroup>(A, gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
+    HeldCorners cs(A, gr);
+    const Choice c = multi_init<kFbGroup>(cs, gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
     if (act && j == 0) write_choice(c, n, ld, gsteps[n], xc_soa, bone_out, resid_out, steps_out);
   }
 }

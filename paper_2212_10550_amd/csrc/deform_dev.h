@@ -87,6 +87,7 @@ struct Cell {
 };
 
 __device__ __forceinline__ Cell locate(const Grid &g, const float x[3]) {
+#pragma clang fp contract(off)
   Cell c;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -113,9 +114,60 @@ __device__ __forceinline__ uint32_t cell_base(const Grid &g, const Cell &c) {
   return (((uint32_t)c.i0[2] * (uint32_t)g.D[1] + (uint32_t)c.i0[1]) * (uint32_t)g.D[0] + (uint32_t)c.i0[0]) * 48u;
 }
 
-__device__ __forceinline__ const float4 *corner_ptr(const float *A, const Grid &g, uint32_t base, int k) {
-  return reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(A) + (base + g.dc[k]));
-}
+// Sources of a cell's eight corner transforms for the residuals below: start()
+// and at() name the cell (byte offset of its base vertex), corner() gives the
+// three rows of corner k.  Both sources give the same floats.
+//  * HeldCorners keeps the last cell's 96 floats in registers and gathers
+//    only when the cell changes.  The staged kernels use it: their time went
+//    to the texture path (24 gathers of 16 bytes per residual), and Broyden's
+//    steps shrink so fast that only the start, the first step and a fifth of
+//    the second steps reach a new cell of a 64 x 64 x 32 grid.  It costs 60
+//    to 70 registers (guided solve 91 -> 160, three waves per SIMD; multi-init
+//    solve 121 -> 176, two) and pays all the same: guided solve of 875,600
+//    samples 133 -> 76 us, multi-init solve of 36,503 samples 83 -> 72 us, of
+//    a 64^3 lattice 477 -> 398 us.
+//  * GatherCorners reads them from the blended grid each time: the persistent
+//    renderer, whose other stages leave no registers to hold a cell.
+struct GatherCorners {
+  const float *A;
+  const uint32_t *dc;
+  uint32_t base;
+  __device__ __forceinline__ GatherCorners(const float *A_, const Grid &g) : A(A_), dc(g.dc), base(0) {}
+  __device__ __forceinline__ void start(uint32_t b) { base = b; }
+  __device__ __forceinline__ void at(uint32_t b) { base = b; }
+  __device__ __forceinline__ void corner(int k, float4 r[3]) const {
+    const float4 *p = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(A) + (base + dc[k]));
+    r[0] = p[0];
+    r[1] = p[1];
+    r[2] = p[2];
+  }
+};
+
+struct HeldCorners {
+  const float *A;
+  const uint32_t *dc;
+  uint32_t base;
+  float4 v[8][3];
+  __device__ __forceinline__ HeldCorners(const float *A_, const Grid &g) : A(A_), dc(g.dc) {}
+  __device__ __forceinline__ void start(uint32_t b) {
+    base = b;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float4 *p = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(A) + (b + dc[k]));
+      v[k][0] = p[0];
+      v[k][1] = p[1];
+      v[k][2] = p[2];
+    }
+  }
+  __device__ __forceinline__ void at(uint32_t b) {
+    if (b != base) start(b);
+  }
+  __device__ __forceinline__ void corner(int k, float4 r[3]) const {
+    r[0] = v[k][0];
+    r[1] = v[k][1];
+    r[2] = v[k][2];
+  }
+};
 
 // Trilinear weights of the eight corners (k = cx + 2 cy + 4 cz).
 __device__ __forceinline__ void tri_weights(const float f[3], float t[8]) {
@@ -131,26 +183,38 @@ __device__ __forceinline__ void tri_weights(const float f[3], float t[8]) {
   t[7] = f[0] * a11;
 }
 
+__device__ __forceinline__ void fma4(float t, const float4 &r, float4 &m) {
+  m.x = fmaf(t, r.x, m.x);
+  m.y = fmaf(t, r.y, m.y);
+  m.z = fmaf(t, r.z, m.z);
+  m.w = fmaf(t, r.w, m.w);
+}
+
+// The residual, its Jacobian and the Broyden iteration fix every rounding
+// (fmaf and dot3, no contraction): the staged kernels and the persistent
+// renderer hold the corner values differently and must agree bit for bit.
+
 // g = (sum_c tri_c A_c) x_h - x': the 12 blended channels are interpolated
 // first, then applied to x_h once.
-__device__ __forceinline__ void residual(const float *__restrict__ A, const Grid &gr, const float x[3],
-                                         const float xp[3], float g[3]) {
+template <class Corners>
+__device__ __forceinline__ void residual(Corners &cs, const Grid &gr, const float x[3], const float xp[3], float g[3]) {
+#pragma clang fp contract(off)
   const Cell c = locate(gr, x);
-  const uint32_t base = cell_base(gr, c);
+  cs.at(cell_base(gr, c));
   float t[8];
   tri_weights(c.f, t);
   float4 m0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), m1 = m0, m2 = m0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const float4 *p = corner_ptr(A, gr, base, k);
-    const float4 r0 = p[0], r1 = p[1], r2 = p[2];
-    m0.x += t[k] * r0.x; m0.y += t[k] * r0.y; m0.z += t[k] * r0.z; m0.w += t[k] * r0.w;
-    m1.x += t[k] * r1.x; m1.y += t[k] * r1.y; m1.z += t[k] * r1.z; m1.w += t[k] * r1.w;
-    m2.x += t[k] * r2.x; m2.y += t[k] * r2.y; m2.z += t[k] * r2.z; m2.w += t[k] * r2.w;
+    float4 r[3];
+    cs.corner(k, r);
+    fma4(t[k], r[0], m0);
+    fma4(t[k], r[1], m1);
+    fma4(t[k], r[2], m2);
   }
-  g[0] = (m0.x * x[0] + m0.y * x[1] + m0.z * x[2] + m0.w) - xp[0];
-  g[1] = (m1.x * x[0] + m1.y * x[1] + m1.z * x[2] + m1.w) - xp[1];
-  g[2] = (m2.x * x[0] + m2.y * x[1] + m2.z * x[2] + m2.w) - xp[2];
+  g[0] = (dot3(m0.x, x[0], m0.y, x[1], m0.z, x[2]) + m0.w) - xp[0];
+  g[1] = (dot3(m1.x, x[0], m1.y, x[1], m1.z, x[2]) + m1.w) - xp[1];
+  g[2] = (dot3(m2.x, x[0], m2.y, x[1], m2.z, x[2]) + m2.w) - xp[2];
 }
 
 // Derivatives of a trilinear interpolant along its cell axes, from the
@@ -158,10 +222,11 @@ __device__ __forceinline__ void residual(const float *__restrict__ A, const Grid
 // differences of neighbouring corners are taken first, so the result does
 // not cancel when the corner values are close (they are smooth fields).
 __device__ __forceinline__ void tri_grad(const float v[8], const float f[3], float d[3]) {
+#pragma clang fp contract(off)
   const float gx = 1.0f - f[0], gy = 1.0f - f[1], gz = 1.0f - f[2];
-  d[0] = gy * gz * (v[1] - v[0]) + f[1] * gz * (v[3] - v[2]) + gy * f[2] * (v[5] - v[4]) + f[1] * f[2] * (v[7] - v[6]);
-  d[1] = gx * gz * (v[2] - v[0]) + f[0] * gz * (v[3] - v[1]) + gx * f[2] * (v[6] - v[4]) + f[0] * f[2] * (v[7] - v[5]);
-  d[2] = gx * gy * (v[4] - v[0]) + f[0] * gy * (v[5] - v[1]) + gx * f[1] * (v[6] - v[2]) + f[0] * f[1] * (v[7] - v[3]);
+  d[0] = fmaf(f[1] * f[2], v[7] - v[6], dot3(gy * gz, v[1] - v[0], f[1] * gz, v[3] - v[2], gy * f[2], v[5] - v[4]));
+  d[1] = fmaf(f[0] * f[2], v[7] - v[5], dot3(gx * gz, v[2] - v[0], f[0] * gz, v[3] - v[1], gx * f[2], v[6] - v[4]));
+  d[2] = fmaf(f[0] * f[1], v[7] - v[3], dot3(gx * gy, v[4] - v[0], f[0] * gy, v[5] - v[1], gx * f[1], v[6] - v[2]));
 }
 
 __device__ __forceinline__ float tri_weight(const float f[3], int k) {
@@ -170,10 +235,12 @@ __device__ __forceinline__ float tri_weight(const float f[3], int k) {
 
 // Residual and Jacobian: with y_c = A_c x_h, g = sum_c tri_c y_c - x' and
 // J = sum_c tri_c M_c + (d/dx of the interpolant of y_c at fixed x_h).
-__device__ __forceinline__ void residual_jac(const float *__restrict__ A, const Grid &gr, const float x[3],
-                                             const float xp[3], float g[3], float J[3][3]) {
+template <class Corners>
+__device__ __forceinline__ void residual_jac(Corners &cs, const Grid &gr, const float x[3], const float xp[3], float g[3],
+                                             float J[3][3]) {
+#pragma clang fp contract(off)
   const Cell c = locate(gr, x);
-  const uint32_t base = cell_base(gr, c);
+  cs.start(cell_base(gr, c));
   float y[3][8];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -181,15 +248,15 @@ __device__ __forceinline__ void residual_jac(const float *__restrict__ A, const 
     for (int j = 0; j < 3; ++j) J[i][j] = 0.0f;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const float4 *p = corner_ptr(A, gr, base, k);
-    const float4 r[3] = {p[0], p[1], p[2]};
+    float4 r[3];
+    cs.corner(k, r);
     const float t = tri_weight(c.f, k);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      y[i][k] = r[i].x * x[0] + r[i].y * x[1] + r[i].z * x[2] + r[i].w;
-      J[i][0] += t * r[i].x;
-      J[i][1] += t * r[i].y;
-      J[i][2] += t * r[i].z;
+      y[i][k] = dot3(r[i].x, x[0], r[i].y, x[1], r[i].z, x[2]) + r[i].w;
+      J[i][0] = fmaf(t, r[i].x, J[i][0]);
+      J[i][1] = fmaf(t, r[i].y, J[i][1]);
+      J[i][2] = fmaf(t, r[i].z, J[i][2]);
     }
   }
 #pragma unroll
@@ -198,13 +265,13 @@ __device__ __forceinline__ void residual_jac(const float *__restrict__ A, const 
     tri_grad(y[i], c.f, d);
     g[i] = -xp[i];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) g[i] += tri_weight(c.f, k) * y[i][k];
+    for (int k = 0; k < 8; ++k) g[i] = fmaf(tri_weight(c.f, k), y[i][k], g[i]);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) J[i][j] += c.dp[j] * d[j];
+    for (int j = 0; j < 3; ++j) J[i][j] = fmaf(c.dp[j], d[j], J[i][j]);
   }
 }
 
-__device__ __forceinline__ float norm3(const float v[3]) { return sqrtf(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]); }
+__device__ __forceinline__ float norm3(const float v[3]) { return sqrtf(dot3(v[0], v[0], v[1], v[1], v[2], v[2])); }
 
 constexpr int kSolveBlock = 256;
 // kGroup lanes share one posed sample; lane j runs inits j, j + kGroup, ...
@@ -221,32 +288,34 @@ struct InitResult {
 };
 
 // One Broyden solve from the start point x (H0 = J(x)^{-1}).
-__device__ __forceinline__ InitResult broyden_from(const float *__restrict__ A, const Grid &gr, float x[3], bool start_ok,
+template <class Corners>
+__device__ __forceinline__ InitResult broyden_from(Corners &cs, const Grid &gr, float x[3], bool start_ok,
                                                   const float xp[3], int max_iter, float tol_stop) {
+#pragma clang fp contract(off)
   InitResult res;
   const bool bone_ok = start_ok;
   float g[3], J[3][3], H[3][3];
-  residual_jac(A, gr, x, xp, g, J);
+  residual_jac(cs, gr, x, xp, g, J);
   const float detJ = inv3(J, H);
   bool ok = bone_ok && fabsf(detJ) >= 1e-12f;
   int k = 0;
   const float tol2 = tol_stop * tol_stop;
   if (ok) {
     for (; k < max_iter; ++k) {
-      if (g[0] * g[0] + g[1] * g[1] + g[2] * g[2] < tol2) break;
+      if (dot3(g[0], g[0], g[1], g[1], g[2], g[2]) < tol2) break;
       float dx[3], xn[3], gn[3], dg[3], Hdg[3], dxH[3];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) dx[a] = -(H[a][0] * g[0] + H[a][1] * g[1] + H[a][2] * g[2]);
+      for (int a = 0; a < 3; ++a) dx[a] = -dot3(H[a][0], g[0], H[a][1], g[1], H[a][2], g[2]);
 #pragma unroll
       for (int a = 0; a < 3; ++a) xn[a] = x[a] + dx[a];
-      residual(A, gr, xn, xp, gn);
+      residual(cs, gr, xn, xp, gn);
 #pragma unroll
       for (int a = 0; a < 3; ++a) dg[a] = gn[a] - g[a];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) Hdg[a] = H[a][0] * dg[0] + H[a][1] * dg[1] + H[a][2] * dg[2];
+      for (int a = 0; a < 3; ++a) Hdg[a] = dot3(H[a][0], dg[0], H[a][1], dg[1], H[a][2], dg[2]);
 #pragma unroll
-      for (int b = 0; b < 3; ++b) dxH[b] = dx[0] * H[0][b] + dx[1] * H[1][b] + dx[2] * H[2][b];
-      const float den = dx[0] * Hdg[0] + dx[1] * Hdg[1] + dx[2] * Hdg[2];
+      for (int b = 0; b < 3; ++b) dxH[b] = dot3(dx[1], H[1][b], dx[0], H[0][b], dx[2], H[2][b]);
+      const float den = dot3(dx[1], Hdg[1], dx[0], Hdg[0], dx[2], Hdg[2]);
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
         x[a] = xn[a];
@@ -261,7 +330,7 @@ __device__ __forceinline__ InitResult broyden_from(const float *__restrict__ A, 
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) H[a][b] += (dx[a] - Hdg[a]) * dxH[b] * iden;
+        for (int b = 0; b < 3; ++b) H[a][b] = fmaf((dx[a] - Hdg[a]) * dxH[b], iden, H[a][b]);
     }
   }
 #pragma unroll
@@ -273,12 +342,13 @@ __device__ __forceinline__ InitResult broyden_from(const float *__restrict__ A, 
 }
 
 // One Broyden solve from bone init i: x0 = B_i^{-1} x'.
-__device__ __forceinline__ InitResult broyden(const float *__restrict__ A, const Grid &gr, const float *Bi, bool bone_ok,
+template <class Corners>
+__device__ __forceinline__ InitResult broyden(Corners &cs, const Grid &gr, const float *Bi, bool bone_ok,
                                              const float xp[3], int max_iter, float tol_stop) {
   float x[3];
 #pragma unroll
-  for (int a = 0; a < 3; ++a) x[a] = Bi[4 * a] * xp[0] + Bi[4 * a + 1] * xp[1] + Bi[4 * a + 2] * xp[2] + Bi[4 * a + 3];
-  return broyden_from(A, gr, x, bone_ok, xp, max_iter, tol_stop);
+  for (int a = 0; a < 3; ++a) x[a] = dot3(Bi[4 * a], xp[0], Bi[4 * a + 1], xp[1], Bi[4 * a + 2], xp[2]) + Bi[4 * a + 3];
+  return broyden_from(cs, gr, x, bone_ok, xp, max_iter, tol_stop);
 }
 
 __device__ __forceinline__ bool in_hbox(const float x[3], const Box &b) {
@@ -294,15 +364,15 @@ struct Choice {
   int bone, steps;
 };
 
-template <int kG = kGroup>
-__device__ __forceinline__ Choice multi_init(const float *__restrict__ A, const Grid &gr, const float *sBinv,
+template <int kG, class Corners>
+__device__ __forceinline__ Choice multi_init(Corners &cs, const Grid &gr, const float *sBinv,
                                              const int *sBok, int nb, const float xp[3], bool act, int j, Box hbox,
                                              int max_iter, float tol_stop, float tol_valid) {
   float best_r = INFINITY, best_x[3] = {0.0f, 0.0f, 0.0f}, x0[3] = {0.0f, 0.0f, 0.0f};
   int best = 0x7fffffff, steps = 0;
   if (act) {
     for (int i = j; i < nb; i += kG) {
-      const InitResult q = broyden(A, gr, sBinv + 12 * i, sBok[i], xp, max_iter, tol_stop);
+      const InitResult q = broyden(cs, gr, sBinv + 12 * i, sBok[i], xp, max_iter, tol_stop);
       steps += q.steps;
       if (i == 0) {
         x0[0] = q.x[0];
