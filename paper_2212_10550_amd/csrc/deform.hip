@@ -708,7 +708,9 @@ extern "C" int32_t ia355_snarf_deform_guided(const float *xp, int64_t S, const i
     guided_kernel<<<stride_grid(ceil_div(S, kSolveBlock), dev, 8192), kSolveBlock, 0, s>>>(
         xp, x0, guide_bone, S, S_dev, ld, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps, queue,
         qlen, gsteps);
-    fallback_kernel<<<stride_grid(ceil_div(S * kFbGroup, kSolveBlock), dev), kSolveBlock, 0, s>>>(
+    // bounded with a host count too (the queue is short): 109,000 empty
+    // blocks for 875,600 samples took 24 us, 2048 take 5
+    fallback_kernel<<<stride_grid(ceil_div(S * kFbGroup, kSolveBlock), true), kSolveBlock, 0, s>>>(
         xp, ld, B, nb, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps, queue, qlen, gsteps,
         n_fallback);
   } else if (n_fallback) {
