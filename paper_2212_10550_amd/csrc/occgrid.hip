@@ -8,7 +8,7 @@
 //
 // The lattice, deform, encode and MLP steps reuse the library's stages on
 // one lattice point per sample; the threshold, the dilation and the packing
-// are one kernel with a thread per output word.
+// are one kernel with a workgroup per brick of the packed layout.
 //
 // Training stage (Sec. 3.3): one shared grid, updated every few iterations
 // from the densities of one random point per cell in the posed space of a
@@ -125,37 +125,54 @@ int reg_blocks(int64_t S) {
   return (int)(b > kRegMaxBlocks ? kRegMaxBlocks : b);
 }
 
-// One thread per output word of the brick layout (32 cells: 8 along x, 4
-// along y); a cell is occupied when any density within r cells (Chebyshev
-// distance, clipped at the grid) exceeds the threshold.
+// One workgroup per brick of the packed layout (8 x 8 x 16 cells): a cell is
+// occupied when any density within r cells (Chebyshev distance, clipped at the
+// grid) exceeds the threshold.  A box dilation is the OR along one axis after
+// the other, so each row of the brick and its halo (8 + 2 r densities along x)
+// becomes one bit mask, dilated along x by shifts; then a thread per (z, y)
+// row of the brick ORs the (2 r + 1)^2 row masks around it.  Bound by the
+// latency of the halo's loads (one row per thread, its loads in flight
+// together).  A thread per output word walking 32 cells x 27 densities left
+// the chip idle: 143 us at G = 64 (r = 1, 8192 threads), 5 us this way.
+constexpr int kHaloY = 8 + 2 * kMaxDilate, kHaloZ = 16 + 2 * kMaxDilate;
+
 __global__ void __launch_bounds__(kBlock) occ_from_density_kernel(const float *__restrict__ sigma, int G,
-                                                                  float thresh, int r, uint32_t *__restrict__ bits,
-                                                                  int64_t nword) {
-  const int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (w >= nword) return;
-  const int64_t nb = (G + 7) / 8;
-  const int64_t brick = w >> 5;
-  const int q = (int)(w & 31);
-  const int x0 = (int)(brick % nb) * 8, y0 = (int)((brick / nb) % nb) * 8 + (q & 1) * 4;
-  const int z = (int)(brick / (nb * nb)) * 16 + (q >> 1);
-  uint32_t v = 0;
-  if (z < G) {
-    const int z0 = z - r < 0 ? 0 : z - r, z1 = z + r > G - 1 ? G - 1 : z + r;
-    for (int j = 0; j < 32; ++j) {
-      const int x = x0 + (j & 7), y = y0 + (j >> 3);
-      if (x >= G || y >= G) continue;
-      const int xa = x - r < 0 ? 0 : x - r, xb = x + r > G - 1 ? G - 1 : x + r;
-      const int ya = y - r < 0 ? 0 : y - r, yb = y + r > G - 1 ? G - 1 : y + r;
-      bool occ = false;
-      for (int zz = z0; zz <= z1 && !occ; ++zz)
-        for (int yy = ya; yy <= yb && !occ; ++yy) {
-          const float *row = sigma + ((int64_t)zz * G + yy) * G;
-          for (int xx = xa; xx <= xb; ++xx) occ = occ || row[xx] > thresh;
-        }
-      if (occ) v |= 1u << j;
+                                                                  float thresh, int r, uint32_t *__restrict__ bits) {
+  __shared__ uint32_t row[kHaloZ * kHaloY];  // x-dilated cells 0..7 of each halo row
+  __shared__ __attribute__((aligned(4))) uint8_t out[128];
+  const int nb = (G + 7) / 8;
+  const int64_t brick = blockIdx.x;
+  const int x0 = (int)(brick % nb) * 8, y0 = (int)((brick / nb) % nb) * 8, z0 = (int)(brick / ((int64_t)nb * nb)) * 16;
+  const int hy = 8 + 2 * r, hx = 8 + 2 * r, rows = (16 + 2 * r) * hy;
+  for (int i = threadIdx.x; i < rows; i += kBlock) {
+    const int zz = z0 - r + i / hy, yy = y0 - r + i % hy;
+    uint32_t m = 0;
+    if (zz >= 0 && zz < G && yy >= 0 && yy < G) {
+      const float *src = sigma + ((int64_t)zz * G + yy) * G;
+#pragma unroll
+      for (int j = 0; j < 8 + 2 * kMaxDilate; ++j) {
+        const int xx = x0 - r + j;
+        if (j < hx && xx >= 0 && xx < G && src[xx] > thresh) m |= 1u << j;
+      }
     }
+    uint32_t d = m;
+    for (int k = 1; k <= 2 * r; ++k) d |= m >> k;
+    row[i] = d;
   }
-  bits[w] = v;
+  __syncthreads();
+  if (threadIdx.x < 128) {
+    // byte 8 z + y of the brick's 32 words holds its cells (0..7, y, z)
+    const int y = threadIdx.x & 7, z = threadIdx.x >> 3;
+    uint32_t v = 0;
+    if (y0 + y < G && z0 + z < G) {
+      for (int dz = 0; dz <= 2 * r; ++dz)
+        for (int dy = 0; dy <= 2 * r; ++dy) v |= row[(z + dz) * hy + y + dy];
+      v &= G - x0 < 8 ? (1u << (G - x0)) - 1u : 0xffu;
+    }
+    out[threadIdx.x] = (uint8_t)v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 32) bits[brick * 32 + threadIdx.x] = reinterpret_cast<const uint32_t *>(out)[threadIdx.x];
 }
 
 struct OccWs {
@@ -195,9 +212,8 @@ OccWs occ_ws(void *base, int32_t G, int32_t L, int32_t F, int32_t mlp_dtype, int
 extern "C" int32_t ia355_occ_from_density(const float *sigma, int32_t G, float sigma_thresh, int32_t dilate,
                                           uint32_t *occ_bits, ia355_stream_t stream) {
   if (G <= 0 || G > 2048 || dilate < 0 || dilate > kMaxDilate || !sigma || !occ_bits) return IA355_ERR_INVALID_ARG;
-  const int64_t nword = occ_words(G);
-  occ_from_density_kernel<<<(unsigned)ceil_div(nword, kBlock), kBlock, 0, as_stream(stream)>>>(
-      sigma, G, sigma_thresh, dilate, occ_bits, nword);
+  const int64_t nbrick = occ_words(G) / 32;
+  occ_from_density_kernel<<<(unsigned)nbrick, kBlock, 0, as_stream(stream)>>>(sigma, G, sigma_thresh, dilate, occ_bits);
   return launch_status();
 }
 

@@ -42,6 +42,24 @@ def test_occ_from_density_bit_exact(G, r):
     assert not got[G:].any() and not got[:, G:].any() and not got[:, :, G:].any()
 
 
+@pytest.mark.parametrize("G,r", [(1, 0), (7, 4), (8, 1), (17, 4), (33, 3), (50, 4)])
+def test_occ_from_density_bricks_and_halos(G, r):
+    """Grids that end inside a brick (8 x 8 x 16 cells), halos up to the widest
+    and non-finite densities (NaN is never above the threshold)."""
+    K = _K()
+    rng = np.random.default_rng(1000 + G * 10 + r)
+    sigma = np.zeros((G, G, G), np.float32)
+    at = rng.integers(0, G, size=(max(1, G // 4), 3))
+    sigma[at[:, 0], at[:, 1], at[:, 2]] = 2.0
+    sigma[rng.random(sigma.shape) < 0.05] = np.nan
+    sigma[0, 0, G - 1] = np.inf
+    bits = torch.full((K.occ_words(G),), -1, dtype=torch.int32, device=dev())
+    K.occ_from_density(up(sigma), G, 1.5, r, bits)
+    got = unpack_bricks(host(bits), G)
+    np.testing.assert_array_equal(got[:G, :G, :G], orc.dilate(sigma > 1.5, r))
+    assert not got[G:].any() and not got[:, G:].any() and not got[:, :, G:].any()
+
+
 def _build(w, G, table, thresh, r, mlp_dtype):
     K = _K()
     Dz, Dy, Dx, nb = w.W.shape
