@@ -1,19 +1,22 @@
 // Ray marching with empty-space skipping (Sec. 3.2 ray sampling, Sec. 3.3
 // occupancy-grid skipping), as a stream compaction in four kernels:
-//   count  -- one wave per ray, one lane per midpoint sample: a ballot of
-//             the samples in occupied cells gives the ray's count, and the
-//             block's total;
-//   chunk  -- each block scans 4096 block totals (exclusive, in place) and
+//   count  -- which midpoint samples of each ray lie in occupied cells (a
+//             keep mask, 64 steps a word), the ray's count and the block's
+//             total: one wave per ray and one lane per sample for few rays,
+//             one lane per ray for many;
+//   chunk  -- each block scans 8192 block totals (exclusive, in place) and
 //             writes its chunk total;
 //   top    -- one block scans the chunk totals and writes the sample count
 //             (skipped when there is one chunk: the chunk kernel writes it);
-//   fill   -- one wave per ray again, from the keep masks the count kernel
-//             saved (one 64-bit ballot per 64 steps) and the ray's entry
-//             distance: only kept samples' positions are recomputed (the same
-//             expression, so the same floats), no cell lookups; each kept
-//             sample's slot is the ray's offset plus the popcount of kept
-//             lanes below it, so a ray's samples are written in t order by
-//             consecutive lanes (structure-of-arrays, coalesced).
+//   fill   -- from the keep masks and the ray's entry distance: only kept
+//             samples' positions are recomputed (the same expression, so the
+//             same floats), no cell lookups.  Few rays: one wave per ray, a
+//             kept sample's slot is the ray's offset plus the popcount of kept
+//             lanes below it.  Many rays: a wave takes the samples of its 64
+//             rays, which are consecutive in the output, 64 at a time, a lane
+//             finding its ray and step from its slot.  A ray's samples are
+//             written in t order by consecutive lanes either way
+//             (structure-of-arrays, coalesced).
 // The occupancy bits are stored in bricks of 8 x 8 x 16 cells, one 128-byte
 // cache line each, so the consecutive samples of a ray (one wave) touch a
 // few lines rather than one line per sample.
@@ -31,81 +34,151 @@ using namespace ia355::mch;
 
 namespace {
 
-// kRaysPerWave rays per wave, four waves per workgroup: lane l handles
-// steps k = l, l + 64, ... of each of the wave's rays, so a 128-step ray is
-// two ballots, and the occupancy loads of the wave's rays (two words at a
-// time) are in flight together.  Large ray counts take four rays per wave
-// (fewer, longer waves); small ones one ray per wave, which keeps enough
-// waves in flight.
+// Two mappings, by the ray count.  Few rays (a training step's thousands): one
+// ray per wave, four waves per workgroup, lane l takes steps l, l + 64, ...,
+// so that there are enough waves.  From kManyRays on: one ray per lane, 256
+// per workgroup.  An image's neighbouring rays walk neighbouring cells, so the
+// 64 loads of a step touch a few lines, no lane is spent on steps past the
+// box (a 128-step ray crosses a unit box in 74 steps at most), the ray clip
+// with its six divisions is done once per ray instead of once per lane, and
+// the fill's waves are full although a ray keeps only 3 samples on average.
+// 1080^2 rays, 128^3 grid, 10 % occupied: count 358 -> 56 us, fill 194 -> 29
+// us against four rays per wave.  The line lies where the two cross (whole
+// march, us, wave / lane per ray): 8192 rays 12 / 23, 16384 rays 17 / 23,
+// 32768 rays 28 / 24, 65536 rays 39 / 26, the same for images, random pixels
+// and rays in random directions.
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlock = kWavesPerBlock * kWave;
-constexpr int64_t kManyRays = 65536;  // from here on, four rays per wave
+constexpr int64_t kManyRays = 32768;
+constexpr int kManySteps = 1 << 22;  // step indices plus a half are exact in single
 
-__host__ __device__ inline int rays_per_wave(int64_t R) { return R >= kManyRays ? 4 : 1; }
-__host__ __device__ inline int rays_per_block(int64_t R) { return rays_per_wave(R) * kWavesPerBlock; }
+inline bool many_rays(int64_t R, int max_steps) { return R >= kManyRays && max_steps <= kManySteps; }
+inline int rays_per_block(int64_t R, int max_steps) { return many_rays(R, max_steps) ? kBlock : kWavesPerBlock; }
 
-template <bool kPow2Ext, int kRaysPerWave>
+template <bool kPow2Ext>
 __global__ void __launch_bounds__(kBlock) march_count(const float *ro, const float *rd, int64_t R,
                                                       const uint32_t *bits, int G, Box box, float dt_fixed,
                                                       int n_per_ray, int max_steps, int64_t *ray_off,
                                                       int32_t *ray_cnt, float *ray_dt, int64_t *block_sum,
                                                       uint64_t *masks, int nw, float *ray_tn) {
-  constexpr int kRays = kRaysPerWave * kWavesPerBlock;
-  __shared__ int cnts[kRays];
+  __shared__ int cnts[kWavesPerBlock];
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  const int64_t r0 = (int64_t)blockIdx.x * kRays + wid * kRaysPerWave;
-  float o[kRaysPerWave][3], d[kRaysPerWave][3];
-  RaySpan s[kRaysPerWave];
-#pragma unroll
-  for (int u = 0; u < kRaysPerWave; ++u) {
-    const int64_t r = r0 + u < R ? r0 + u : R - 1;  // a tail wave repeats the last ray, writes nothing for it
-    load_ray(ro, rd, r, o[u], d[u]);
-    s[u] = ray_span(o[u], d[u], box, dt_fixed, n_per_ray);
-  }
-  int cnt[kRaysPerWave];
-#pragma unroll
-  for (int u = 0; u < kRaysPerWave; ++u) cnt[u] = 0;
+  const int64_t r0 = (int64_t)blockIdx.x * kWavesPerBlock + wid;
+  float o[3], d[3];
+  load_ray(ro, rd, r0 < R ? r0 : R - 1, o, d);  // a tail wave repeats the last ray, writes nothing for it
+  const RaySpan s = ray_span(o, d, box, dt_fixed, n_per_ray);
+  int cnt = 0;
   for (int w0 = 0; w0 < nw; w0 += 2) {
-    bool keep[kRaysPerWave][2];
+    bool keep[2];
 #pragma unroll
-    for (int u = 0; u < kRaysPerWave; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = (w0 + h) * kWave + lane;
-        float t = 0.0f, x[3];
-        keep[u][h] = false;
-        // a step past t_far is not kept, so its cell is not looked up
-        if (s[u].hit && k < max_steps && step_t(s[u], k) < s[u].tf)
-          keep[u][h] = sample_at<kPow2Ext>(o[u], d[u], s[u], k, box, bits, G, &t, x) && t < s[u].tf;
-      }
-#pragma unroll
-    for (int u = 0; u < kRaysPerWave; ++u)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint64_t m = __ballot(keep[u][h]);
-        cnt[u] += __popcll(m);
-        if (lane == 0 && r0 + u < R && w0 + h < nw) masks[(r0 + u) * nw + w0 + h] = m;
-      }
-  }
-#pragma unroll
-  for (int u = 0; u < kRaysPerWave; ++u) {
-    if (lane == 0 && r0 + u < R) {
-      ray_cnt[r0 + u] = cnt[u];
-      ray_dt[r0 + u] = s[u].dt;
-      ray_tn[r0 + u] = s[u].tn;
+    for (int h = 0; h < 2; ++h) {
+      const int k = (w0 + h) * kWave + lane;
+      float t = 0.0f, x[3];
+      keep[h] = false;
+      // a step past t_far is not kept, so its cell is not looked up
+      if (s.hit && k < max_steps && step_t(s, k) < s.tf)
+        keep[h] = sample_at<kPow2Ext>(o, d, s, k, box, bits, G, &t, x) && t < s.tf;
     }
-    if (lane == 0) cnts[wid * kRaysPerWave + u] = r0 + u < R ? cnt[u] : 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint64_t m = __ballot(keep[h]);
+      cnt += __popcll(m);
+      if (lane == 0 && r0 < R && w0 + h < nw) masks[r0 * nw + w0 + h] = m;
+    }
+  }
+  if (lane == 0) {
+    if (r0 < R) {
+      ray_cnt[r0] = cnt;
+      ray_dt[r0] = s.dt;
+      ray_tn[r0] = s.tn;
+    }
+    cnts[wid] = r0 < R ? cnt : 0;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     int64_t acc = 0;
-    for (int i = 0; i < kRays; ++i) {
-      const int64_t ri = (int64_t)blockIdx.x * kRays + i;
+    for (int i = 0; i < kWavesPerBlock; ++i) {
+      const int64_t ri = (int64_t)blockIdx.x * kWavesPerBlock + i;
       if (ri < R) ray_off[ri] = acc;
       acc += cnts[i];
     }
     block_sum[blockIdx.x] = acc;
   }
+}
+
+// One lane per ray.  kStepsAhead steps' occupancy bytes (8 cells along x) are
+// loaded together.  Bound by instruction issue: about 40 per step and wave.
+constexpr int kStepsAhead = 8;
+
+template <BoxKind kBox, bool kSkip>
+__global__ void __launch_bounds__(kBlock) march_count_many(const float *__restrict__ ro, const float *__restrict__ rd,
+                                                           int64_t R, const uint8_t *__restrict__ bits, int G, Box box,
+                                                           float dt_fixed, int n_per_ray, int max_steps,
+                                                           int64_t *__restrict__ ray_off, int32_t *__restrict__ ray_cnt,
+                                                           float *__restrict__ ray_dt, int64_t *__restrict__ block_sum,
+                                                           uint64_t *__restrict__ masks, int nw,
+                                                           float *__restrict__ ray_tn) {
+#pragma clang fp contract(off)
+  __shared__ int wsum[kWavesPerBlock];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+  const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  float o[3], d[3];
+  load_ray(ro, rd, r < R ? r : R - 1, o, d);
+  const RaySpan s = ray_span(o, d, box, dt_fixed, n_per_ray);
+  const float tf = s.hit && r < R ? s.tf : -INFINITY;
+  const uint32_t nb = (uint32_t)(G + 7) >> 3, sy = nb << 7, sz = nb * sy;
+  int cnt = 0;
+  // t never falls along a ray, so once a step is past t_far for every lane
+  // all later ones are
+  bool live = true;
+  for (int w = 0; w < nw; ++w) {
+    uint32_t m[2] = {0u, 0u};
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < 32 / kStepsAhead; ++c) {
+        const int k0 = w * kWave + h * 32 + c * kStepsAhead;
+        live = live && k0 < max_steps && __any(step_t(s, k0) < tf);
+        if (!live) continue;
+        // step_t of k0 + j: k0 + 1/2 + j is exact (max_steps <= kManySteps)
+        const float kf = (float)k0 + 0.5f;
+        uint32_t v[kStepsAhead], cx[kStepsAhead];
+        bool in[kStepsAhead];
+#pragma unroll
+        for (int j = 0; j < kStepsAhead; ++j) {
+          uint32_t cell[3];
+          const float t = s.tn + (kf + (float)j) * s.dt;
+          in[j] = k0 + j < max_steps && t < tf;
+          sample_cell<kBox>(o, d, t, box, G, cell);
+          cx[j] = cell[0];
+          // read past the span too: any position is clamped to a cell
+          v[j] = kSkip ? bits[occ_byte(cell[0], cell[1], cell[2], sy, sz)] : 0xffu;
+        }
+#pragma unroll
+        for (int j = 0; j < kStepsAhead; ++j) {
+          const uint32_t bit = in[j] ? (v[j] >> (cx[j] & 7u)) & 1u : 0u;
+          m[h] |= bit << (c * kStepsAhead + j);
+        }
+      }
+    cnt += __popc(m[0]) + __popc(m[1]);
+    if (r < R) masks[r * nw + w] = (uint64_t)m[0] | (uint64_t)m[1] << 32;
+  }
+  const int incl = wave_incl_scan(cnt);
+  if (lane == kWave - 1) wsum[wid] = incl;
+  __syncthreads();
+  int base = 0, all = 0;
+#pragma unroll
+  for (int i = 0; i < kWavesPerBlock; ++i) {
+    base += i < wid ? wsum[i] : 0;
+    all += wsum[i];
+  }
+  if (r < R) {
+    ray_off[r] = base + incl - cnt;
+    ray_cnt[r] = cnt;
+    ray_dt[r] = s.dt;
+    ray_tn[r] = s.tn;
+  }
+  if (threadIdx.x == 0) block_sum[blockIdx.x] = all;
 }
 
 // Exclusive scan in one block of 1024 threads: thread t holds `v`; returns
@@ -132,7 +205,7 @@ __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t *wsum
 
 // Chunk c of the per-block totals, kScanPer per thread: exclusive scan in
 // place (offsets within the chunk) and the chunk's total.
-constexpr int kScanPer = 4;
+constexpr int kScanPer = 8;  // one chunk holds 2 M rays at 256 a block
 constexpr int64_t kScanChunk = 1024 * kScanPer;
 
 __global__ void __launch_bounds__(1024) march_scan_chunk(int64_t *block_sum, int64_t nblk, int64_t *chunk_sum,
@@ -182,58 +255,118 @@ __global__ void __launch_bounds__(1024) march_scan_top(int64_t *chunk_sum, int64
   }
 }
 
-template <int kRaysPerWave>
 __global__ void __launch_bounds__(kBlock) march_fill(const float *__restrict__ ro, const float *__restrict__ rd,
                                                      int64_t R, const uint64_t *__restrict__ masks, int nw,
                                                      const float *__restrict__ ray_tn, const int64_t *block_off,
                                                      const int64_t *chunk_off, int64_t *ray_off,
                                                      const float *__restrict__ ray_dt, float *xs, float *ts,
                                                      int32_t *ray_id, int64_t cap) {
-#pragma clang fp contract(off)
-  constexpr int kRays = kRaysPerWave * kWavesPerBlock;
   // the wave index is uniform: a ray's inputs and masks go through the
   // scalar cache
   const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-  const int64_t r0 = (int64_t)blockIdx.x * kRays + wid * kRaysPerWave;
-  if (r0 >= R) return;
-  const int64_t base = block_off[blockIdx.x] + chunk_off[blockIdx.x / kScanChunk];
+  const int64_t r = (int64_t)blockIdx.x * kWavesPerBlock + wid;
+  if (r >= R) return;
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-  // every ray's inputs first, so that their loads are in flight together
-  float o[kRaysPerWave][3], d[kRaysPerWave][3], tn[kRaysPerWave], dt[kRaysPerWave];
-  int64_t off[kRaysPerWave];
-#pragma unroll
-  for (int u = 0; u < kRaysPerWave; ++u) {
-    const int64_t r = r0 + u < R ? r0 + u : R - 1;
-    load_ray(ro, rd, r, o[u], d[u]);
-    tn[u] = ray_tn[r];
-    dt[u] = ray_dt[r];
-    off[u] = ray_off[r] + base;
-  }
+  float o[3], d[3];
+  load_ray(ro, rd, r, o, d);
+  const float tn = ray_tn[r], dt = ray_dt[r];
+  int64_t at0 = ray_off[r] + block_off[blockIdx.x] + chunk_off[blockIdx.x / kScanChunk];
   __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int u = 0; u < kRaysPerWave; ++u) {
-    const int64_t r = r0 + u;
-    if (r >= R) break;
-    if (lane == 0) ray_off[r] = off[u];
-    const uint64_t *mr = masks + r * nw;
-    int64_t at0 = off[u];
-    for (int w = 0; w < nw; ++w) {
-      const uint64_t m = mr[w];
-      if (m == 0ull) continue;
-      if ((m >> lane) & 1ull) {
-        const int64_t at = at0 + __popcll(m & below);
-        if (at < cap) {
-          float t, x[3];
-          sample_pos(o[u], d[u], tn[u], dt[u], w * kWave + lane, &t, x);
-          xs[at] = x[0];
-          xs[cap + at] = x[1];
-          xs[2 * cap + at] = x[2];
-          ts[at] = t;
-          ray_id[at] = (int32_t)r;
-        }
+  if (lane == 0) ray_off[r] = at0;
+  const uint64_t *mr = masks + r * nw;
+  for (int w = 0; w < nw; ++w) {
+    const uint64_t m = mr[w];
+    if (m == 0ull) continue;
+    if ((m >> lane) & 1ull) {
+      const int64_t at = at0 + __popcll(m & below);
+      if (at < cap) {
+        float t, x[3];
+        sample_pos(o, d, tn, dt, w * kWave + lane, &t, x);
+        xs[at] = x[0];
+        xs[cap + at] = x[1];
+        xs[2 * cap + at] = x[2];
+        ts[at] = t;
+        ray_id[at] = (int32_t)r;
       }
-      at0 += __popcll(m);
     }
+    at0 += __popcll(m);
+  }
+}
+
+// Many rays: each wave writes the samples of its 64 rays, 64 slots at a time.
+// The rays' first slots and inputs are in LDS; a lane finds its ray by binary
+// search and its step as the q-th set bit of the ray's masks (global memory,
+// read in the cache line of the neighbouring lanes' rays).
+__global__ void __launch_bounds__(kBlock) march_fill_many(const float *__restrict__ ro, const float *__restrict__ rd,
+                                                          int64_t R, const uint64_t *__restrict__ masks, int nw,
+                                                          const float *__restrict__ ray_tn,
+                                                          const int64_t *__restrict__ block_off,
+                                                          const int64_t *__restrict__ chunk_off,
+                                                          int64_t *__restrict__ ray_off,
+                                                          const int32_t *__restrict__ ray_cnt,
+                                                          const float *__restrict__ ray_dt, float *__restrict__ xs,
+                                                          float *__restrict__ ts, int32_t *__restrict__ ray_id,
+                                                          int64_t cap) {
+  __shared__ float in[kWavesPerBlock][8][kWave];        // o, d, tn, dt of the wave's rays
+  __shared__ int first[kWavesPerBlock][kWave];          // first slot of each ray, from the wave's first
+  const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int64_t r0 = (int64_t)blockIdx.x * kBlock + wid * kWave;
+  if (r0 >= R) return;  // no barrier below: a wave works alone
+  const int64_t r = r0 + lane;
+  const int cnt = r < R ? ray_cnt[r] : 0;
+  const int incl = wave_incl_scan(cnt);
+  const int n = __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
+  const int64_t base = block_off[blockIdx.x] + chunk_off[blockIdx.x / kScanChunk];
+  int64_t off = 0;
+  if (r < R) {
+    off = ray_off[r] + base;
+    ray_off[r] = off;
+  }
+  if (n == 0) return;
+  const int64_t at0 = __shfl(off, 0, kWave);  // r0 < R: lane 0 holds the wave's first slot
+  {
+    float o[3], d[3];
+    const int64_t q = r < R ? r : R - 1;
+    load_ray(ro, rd, q, o, d);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      in[wid][a][lane] = o[a];
+      in[wid][3 + a][lane] = d[a];
+    }
+    in[wid][6][lane] = ray_tn[q];
+    in[wid][7][lane] = ray_dt[q];
+    first[wid][lane] = incl - cnt;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int j = lane; j < n; j += kWave) {
+    const int64_t at = at0 + j;
+    if (at >= cap) break;
+    // the last ray whose first slot is at or before j (rays without samples
+    // share the next ray's first slot and come before it)
+    int u = 0;
+#pragma unroll
+    for (int h = kWave / 2; h > 0; h >>= 1)
+      if (first[wid][u + h] <= j) u += h;
+    int q = j - first[wid][u], k = 0;
+    const uint64_t *mr = masks + (r0 + u) * nw;
+    uint64_t m = mr[0];
+    for (int c = __popcll(m); q >= c; c = __popcll(m)) {  // the word that holds the q-th kept step
+      q -= c;
+      k += kWave;
+      m = mr[k / kWave];
+    }
+    k += select_bit64(m, q);
+    const float o[3] = {in[wid][0][u], in[wid][1][u], in[wid][2][u]};
+    const float d[3] = {in[wid][3][u], in[wid][4][u], in[wid][5][u]};
+    float t, x[3];
+    sample_pos(o, d, in[wid][6][u], in[wid][7][u], k, &t, x);
+    xs[at] = x[0];
+    xs[cap + at] = x[1];
+    xs[2 * cap + at] = x[2];
+    ts[at] = t;
+    ray_id[at] = (int32_t)(r0 + u);
   }
 }
 
@@ -250,7 +383,7 @@ struct MarchWs {
 
 static MarchWs march_ws(void *base, int64_t R, int32_t max_steps) {
   const int64_t Rp = R > 0 ? R : 1;
-  const int64_t nblk = ceil_div(Rp, rays_per_block(Rp));
+  const int64_t nblk = ceil_div(Rp, many_rays(Rp, max_steps) && Rp >= 65536 ? 16 : kWavesPerBlock);  // at least the block totals
   const int64_t nw = ceil_div(max_steps > 0 ? max_steps : 1, kWave);
   char *p = (char *)base;
   MarchWs w;
@@ -289,39 +422,41 @@ extern "C" int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d,
   bool pow2;
   if (!make_box(aabb, &box, &pow2)) return IA355_ERR_INVALID_ARG;
   hipStream_t s = as_stream(stream);
-  const int64_t nblk = ceil_div(R, rays_per_block(R));
+  const int64_t nblk = ceil_div(R, rays_per_block(R, max_steps));
   const int64_t nchunk = ceil_div(nblk, kScanChunk);
   const int nw = (int)ceil_div(max_steps, kWave);
   const MarchWs mw = march_ws(ws, R, max_steps);
   int64_t *block_sum = mw.block_sum, *chunk_sum = mw.chunk_sum;
-  const bool many = rays_per_wave(R) == 4;
+  const bool many = many_rays(R, max_steps);
   if (R > 0) {
-    if (pow2 && many)
-      march_count<true, 4><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
-                                                             max_steps, ray_off, ray_cnt, ray_dt, block_sum,
-                                                             mw.masks, nw, mw.tn);
+    if (many) {
+      const bool zero = box.lo[0] == 0.0f && box.lo[1] == 0.0f && box.lo[2] == 0.0f;
+      auto *fn = !occ_bits ? march_count_many<kGeneral, false>  // without a grid no cell is looked up
+                 : !pow2   ? march_count_many<kGeneral, true>
+                 : zero    ? march_count_many<kPow2AtZero, true>
+                           : march_count_many<kPow2, true>;
+      fn<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, reinterpret_cast<const uint8_t *>(occ_bits), G, box, dt,
+                                           n_per_ray, max_steps, ray_off, ray_cnt, ray_dt, block_sum, mw.masks, nw,
+                                           mw.tn);
+    }
     else if (pow2)
-      march_count<true, 1><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
-                                                             max_steps, ray_off, ray_cnt, ray_dt, block_sum,
-                                                             mw.masks, nw, mw.tn);
-    else if (many)
-      march_count<false, 4><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
-                                                              max_steps, ray_off, ray_cnt, ray_dt, block_sum,
-                                                              mw.masks, nw, mw.tn);
+      march_count<true><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
+                                                          max_steps, ray_off, ray_cnt, ray_dt, block_sum, mw.masks, nw,
+                                                          mw.tn);
     else
-      march_count<false, 1><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
-                                                              max_steps, ray_off, ray_cnt, ray_dt, block_sum,
-                                                              mw.masks, nw, mw.tn);
+      march_count<false><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
+                                                           max_steps, ray_off, ray_cnt, ray_dt, block_sum, mw.masks,
+                                                           nw, mw.tn);
     march_scan_chunk<<<(unsigned)nchunk, 1024, 0, s>>>(block_sum, nblk, chunk_sum, ray_off, R, n_samples);
   }
   if (nchunk != 1) march_scan_top<<<1, 1024, 0, s>>>(chunk_sum, nchunk, ray_off, R, n_samples);
   if (R > 0 && cap > 0) {
     if (many)
-      march_fill<4><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
-                                                      ray_off, ray_dt, xs, ts, ray_id, cap);
+      march_fill_many<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
+                                                        ray_off, ray_cnt, ray_dt, xs, ts, ray_id, cap);
     else
-      march_fill<1><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
-                                                      ray_off, ray_dt, xs, ts, ray_id, cap);
+      march_fill<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
+                                                   ray_off, ray_dt, xs, ts, ray_id, cap);
   }
   const int32_t st = launch_status();
   if (st != IA355_OK || !n_required) return st;

@@ -77,6 +77,54 @@ __device__ __forceinline__ bool sample_at(const float o[3], const float d[3], co
   return (bits[word] >> occ_bit(cell[0], cell[1])) & 1u;
 }
 
+// How a box maps to its grid: kGeneral divides by the extents; kPow2 (every
+// extent a power of two) multiplies by inv_ext G, which is exact and rounds
+// the same product once; kPow2AtZero is that with the low corner at zero,
+// where x - lo is x.
+enum BoxKind { kGeneral, kPow2, kPow2AtZero };
+
+// Cell of the sample at ray parameter t, as sample_at finds it.  The clamp to
+// [0, G - 1] comes before the truncation, which then equals floor and clamp
+// (v_med3_f32; a NaN ends in some cell, as it does there).
+template <BoxKind kBox>
+__device__ __forceinline__ void sample_cell(const float o[3], const float d[3], float t, const Box &b, int G,
+                                            uint32_t cell[3]) {
+#pragma clang fp contract(off)
+  const float top = (float)(G - 1);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float x = o[a] + t * d[a];
+    const float rel = kBox == kPow2AtZero ? x : x - b.lo[a];
+    const float u = kBox == kGeneral ? rel / (b.hi[a] - b.lo[a]) * (float)G : rel * (b.inv_ext[a] * (float)G);
+    cell[a] = (uint32_t)__builtin_amdgcn_fmed3f(u, 0.0f, top);
+  }
+}
+
+// Byte of the packed grid that holds cell (x, y, z) (its bit is x mod 8);
+// sy, sz: bytes of a row and of a layer of bricks (< 2^24 for G <= 2048).
+__device__ __forceinline__ uint32_t occ_byte(uint32_t x, uint32_t y, uint32_t z, uint32_t sy, uint32_t sz) {
+  const uint32_t row = __umul24(y >> 3, sy) + ((x >> 3) << 7);
+  return __umul24(z >> 4, sz) + row + (((z & 15u) << 3) | (y & 7u));
+}
+
+// Position of the q-th (from 0) set bit of m; q < the number of set bits.
+__device__ __forceinline__ int select_bit64(uint64_t m, int q) {
+  const uint32_t lo = (uint32_t)m;
+  const int c0 = __popc(lo);
+  uint32_t v = q < c0 ? lo : (uint32_t)(m >> 32);
+  int pos = q < c0 ? 0 : 32;
+  q = q < c0 ? q : q - c0;
+#pragma unroll
+  for (int w = 16; w >= 1; w >>= 1) {
+    const int c = __popc(v & ((1u << w) - 1u));
+    const bool up = q >= c;
+    q = up ? q - c : q;
+    v = up ? v >> w : v;
+    pos = up ? pos + w : pos;
+  }
+  return pos;
+}
+
 __device__ __forceinline__ void load_ray(const float *ro, const float *rd, int64_t r, float o[3], float d[3]) {
 #pragma unroll
   for (int a = 0; a < 3; ++a) {

@@ -85,6 +85,46 @@ def test_march_odd_grid_bit_exact(orc, box):
     np.testing.assert_array_equal(host(p.ray_id[:S]), m["ray_id"])
 
 
+# ray counts from 32,768 on take one ray per lane: ragged last workgroups,
+# step counts that end inside a mask word or span several, every kind of box,
+# no grid, a capacity below the count, and (2,100,000 rays) more workgroup
+# totals than one scan chunk holds
+@pytest.mark.parametrize("R,steps,box,grid,share", [
+    (32767, 128, "pow2", 37, 1.0), (32768, 128, "unit", 37, 1.0), (65537, 70, "pow2", 64, 1.0), (70001, 200, "general", 37, 1.0),
+    (65791, 1, "unit", 16, 1.0), (66000, 33, "unit", 0, 1.0), (65536, 64, "general", 128, 0.4),
+    (2100000, 3, "unit", 16, 1.0)])
+def test_march_many_rays_bit_exact(orc, R, steps, box, grid, share):
+    from paper_2212_10550_amd import lib as K
+    rng = np.random.default_rng(R + steps)
+    o = rng.uniform(-0.6, 1.6, (R, 3)).astype(np.float32)
+    d = rng.normal(size=(R, 3)).astype(np.float32)
+    d[::7, rng.integers(0, 3)] = 0.0  # parallel to two faces
+    d[5::9] = np.eye(3, dtype=np.float32)[rng.integers(0, 3, d[5::9].shape[0])]
+    aabb = {"unit": [0, 0, 0, 1, 1, 1], "pow2": [-0.5, -0.5, -0.5, 1.5, 1.5, 1.5],
+            "general": [-0.05, -0.02, -0.1, 1.05, 1.0, 1.07]}[box]
+    aabb = np.array(aabb, np.float32)
+    occ = (rng.random((grid,) * 3) < 0.2).astype(np.uint8) if grid else None
+    n_per_ray, dt = (steps, 0.0) if not grid else (0, float(np.float32(1.9 / steps)))
+    m = orc.march(o, d, occ, aabb, dt, n_per_ray, steps)
+    n = m["xs"].shape[0]
+    cap = max(1, int(n * share))
+    e = lambda *s, dt=torch.float32: torch.full(s, -7, dtype=dt, device=dev())
+    bits = None
+    if grid:
+        bits = torch.empty(K.occ_words(grid), dtype=torch.int32, device=dev())
+        K.occ_pack(up(occ), bits)
+    xs, ts, rid, off, cnt = e(3, cap), e(cap), e(cap, dt=torch.int32), e(R + 1, dt=torch.int64), e(R, dt=torch.int32)
+    rdt, ns, ws = e(R), e(1, dt=torch.int64), e(K.march_workspace_size(R, steps), dt=torch.uint8)
+    K.occgrid_march(up(o), up(d), bits, grid, aabb, dt, n_per_ray, steps, xs, ts, rid, cap, off, cnt, rdt, ns, ws)
+    torch.cuda.synchronize()
+    assert n > 0 and int(ns.item()) == n
+    np.testing.assert_array_equal(host(off), m["ray_off"])
+    np.testing.assert_array_equal(host(cnt), m["ray_cnt"])
+    np.testing.assert_array_equal(host(xs).T, m["xs"][:cap])
+    np.testing.assert_array_equal(host(rid), m["ray_id"][:cap])
+    np.testing.assert_array_equal(host(ts), m["ts"][:cap])
+
+
 def test_march_empty_and_capacity(orc):
     w = synth.train_step()
     w0 = synth.ray_subset(w, np.arange(64))
