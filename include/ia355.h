@@ -62,12 +62,11 @@ extern "C" {
  * slices of grad_table, so they may run concurrently on two streams. */
 #define IA355_TABLE_COARSE 2u
 #define IA355_TABLE_FINE 4u
-/* Two-phase use of ia355_hashgrid_table_grad: IA355_TABLE_PLAN runs only
- * the passes that depend on the positions (binning the corner updates by
- * table tile); a later call with IA355_TABLE_REUSE_PLAN, the same workspace
- * and the same positions, bones, count, sizes and level-group flags runs the
- * rest.  The plan can so run as soon as the positions are known (during the
- * forward), off the backward's critical path. */
+/* Two-phase use of ia355_hashgrid_table_grad: a call with IA355_TABLE_PLAN,
+ * then one with IA355_TABLE_REUSE_PLAN, the same workspace and the same
+ * positions, bones, count, sizes and level-group flags.  Nothing is left to
+ * prepare from the positions alone: the plan call only checks its arguments
+ * and the reuse call does the whole work. */
 #define IA355_TABLE_PLAN 8u
 #define IA355_TABLE_REUSE_PLAN 16u
 
@@ -360,15 +359,16 @@ int32_t ia355_hashgrid_encode_bwd(const float *grad_feat, const float *xc, const
 /* Table gradient of the encoding (the grad_table output of
  * ia355_hashgrid_encode_bwd, same arguments, flags and result) computed
  * without global atomics on almost every entry: the corner updates are
- * binned by (level, table tile of 4096 entries), written once as 12-byte
- * records (the two FP32 values, the entry in the tile) and summed per tile
- * in LDS as exact 64-bit fixed point (a power-of-two scale per group of at
+ * binned by (level, table tile of 4096 entries), written once as 16-byte
+ * records of the two corners that neighbour in x (12-byte ones where a tile
+ * boundary separates them) and summed per tile in LDS as exact 64-bit fixed point (a power-of-two scale per group of at
  * most 4096 records, chosen from its largest |value| m), then converted back
  * and written with plain stores.  Accuracy is absolute, relative to m: each
  * record is rounded to a quantum below m 2^-46, so an entry's error is at
  * most its record count times m 2^-47 plus one FP32 rounding of the entry
- * (values below m 2^-48 contribute zero).  A tile whose bin holds more than 4096
- * records is summed by several workgroups that add their nonzero entries
+ * (values below m 2^-48 contribute zero).  A tile with many more records than
+ * others (more than 8192, and than half of what an even spread would give a
+ * workgroup) is summed by several workgroups that add their nonzero entries
  * with FP32 atomics.  Every tile of the selected levels is written, so
  * IA355_OVERWRITE needs no separate clear.  A tile summed by one workgroup
  * does not depend on the order of its records; split tiles may vary in the
@@ -382,10 +382,8 @@ int32_t ia355_hashgrid_encode_bwd(const float *grad_feat, const float *xc, const
  *       workspaces.
  * flags: IA355_OVERWRITE, a level group (IA355_TABLE_COARSE or _FINE) and
  * IA355_TABLE_PLAN (grad_feat and grad_table may then be NULL; nothing is
- * written but the workspace) or IA355_TABLE_REUSE_PLAN (xc, bone, S, S_dev
- * must be those of the plan; their contents must not have changed).  A
- * reuse without a matching plan gives wrong values; device-side checks keep
- * every access inside the workspace and the selected slice of grad_table.
+ * written) or IA355_TABLE_REUSE_PLAN (xc, bone, S, S_dev
+ * must be those of the plan; their contents must not have changed).
  * Limits: L <= 16, L * 2^log2T <= 2^26 entries (at most 16384 tiles),
  * 8 L S < 2^32; otherwise IA355_ERR_INVALID_ARG (the workspace size is then
  * 0).  A workspace below the size returns IA355_ERR_WORKSPACE. */

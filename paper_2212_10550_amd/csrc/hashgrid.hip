@@ -356,120 +356,132 @@ __global__ void __launch_bounds__(kDgBlock) table_grad_dense_kernel(const float 
 // ---------------------------------------------------------------------------
 // Table gradient without global atomics (binned).  Each level's table is cut
 // into tiles of E = 2^tb entries (2 E 8-byte sums fit in LDS); a corner update
-// (level, entry, w_c dL/dfeat_l) belongs to bin (level, tile), bins in
-// level-major order.  Five passes:
-//  1. count: every block counts its updates per bin in LDS and writes its
-//     row of the histogram hist[block][bin] (contiguous: a column per block
-//     would cost a 32-byte sector per 4-byte count, written and read back);
-//  2. scan: exclusive scan of the histogram in bin-major order (bin, then
-//     block), in chunks of 4096 (offsets inside the chunk, chunk totals),
-//     each count replaced by its offset in place;
-//  3. plan (one block): offsets of the chunks, the record range of every bin
-//     and the number of accumulation chunks it needs (<= kAccChunk records
-//     each);
-//  4. scatter: the same blocks regenerate the same updates (same items, same
-//     arithmetic) and append them to their run inside their bin's records,
-//     one 12-byte record each (the two values, the entry inside the tile);
-//  5. accumulate: one workgroup per chunk sums its records into an LDS copy
-//     of the tile and writes the tile with plain vector stores; a bin split
-//     over several chunks (only bins with many updates, on the coarse
-//     levels) adds its nonzero entries with global atomics instead, after a
-//     pass that clears those tiles when overwriting.
+// (entry, w_c dL/dfeat_l) belongs to the tile of its entry.  Three passes:
+//  1. sort: a workgroup takes one level and kSortChunk samples, counts its
+//     updates per tile in LDS (keeping each update's rank in a register),
+//     scans the counts and writes its updates in tile order into the chunk's
+//     own part of the workspace, and each tile's run into the run table.  A
+//     chunk's part is sized for its samples, so no pass has to agree on
+//     offsets across workgroups.
+//  2. plan: from the run table, a work item for each tile with records, or
+//     several, by chunks, for one with many (coarse levels, whose samples
+//     crowd on the subject).
+//  3. accumulate: a workgroup takes an item at a time, sums its runs into an
+//     LDS copy of the tile and writes it with plain vector stores, or adds its
+//     nonzero entries with global atomics where several share the tile.
+// The two x-neighbouring corners of a cell are adjacent entries or differ in
+// their low index bits (the x prime is 1), so they nearly always fall in one
+// tile and travel as one 16-byte record: the two features' (w_y w_z) dL/dfeat,
+// the x fraction and both entries.  Corners of a pair that a tile boundary
+// separates are 12-byte records at the end of the chunk's part; a sample's
+// eight updates take at most 96 bytes either way.
 // The LDS sums are 64-bit fixed point, added exactly: LDS float atomic adds run at
-// about a sixteenth of the rate of integer ones on gfx950, so each chunk
-// scales its values by a power of two 2^s chosen from its largest |value| m
-// and record count (no overflow), adds them as integers and converts each
+// about a sixteenth of the rate of integer ones on gfx950, so each window of
+// at most 4096 records scales its values by a power of two 2^s chosen from its
+// largest |value| m (no overflow), adds them as integers and converts each
 // entry back once.  Each record is rounded to the quantum 2^-s < m 2^-46, so
-// an entry's error is at most (its records) x m 2^-47 plus one FP32
-// rounding: an absolute bound relative to the chunk's largest value.  An
+// an entry's error is at most (its records) x m 2^-47 plus one FP32 rounding
+// per window: an absolute bound relative to the window's largest value.  An
 // entry near m is as accurate as FP32 adds leave it or better; one far
 // below m (under about m 2^-24) is less accurate than FP32 adds, and a
 // record below m 2^-48 rounds to zero.  Integer addition is associative, so
 // a tile summed by one workgroup does not depend on the order of its records.
-// Every tile of the selected levels is written, so an overwrite needs no
-// separate clear.  The HBM traffic is the records (12 bytes per corner
-// update, written once and read once) and one pass over the table slice.
-constexpr int kBinBlock = 1024;       // count / scatter
-constexpr int kBinMaxBlocks = 256;    // one block per CU
-constexpr int kBinUnroll = 4;         // items per thread whose loads are in flight together
-constexpr int kMaxBins = 16384;       // LDS counters of one block: 64 KB
-constexpr int kTileLog2Max = 12;      // 4096 entries x 2 x 8 B = 64 KB of LDS
-constexpr int kHsPer = 4;
-constexpr int kHsChunk = 1024 * kHsPer;
-constexpr int kMaxHsChunks = 4096;
-constexpr int kAccBlock = 1024;
-constexpr uint32_t kAccChunk = 4096;  // records per accumulation workgroup
-constexpr int kAccPer = kAccChunk / kAccBlock;  // records per thread, held in registers
+// The traffic is the records (64 bytes per sample and level, written once and
+// read once) and one pass over the table slice.
+// 16 levels of 2^19 entries, field gradients (traced: sort, plan,
+// accumulate): 18 + 10 + 45 us for 36,503 samples, 81 + 13 + 149 us for
+// 262,143.  Counting, scanning and placing 12-byte single records across all
+// workgroups took six passes, 85 and 422 us: four of them only to agree on
+// offsets, and every 4096 records flushed a tile with global atomics.  A fixed
+// share of a level's tiles per item in place of the plan left the accumulate
+// pass 62 and 243 us (the largest items ran on alone for half of it).
+constexpr int kSortBlock = 320;
+constexpr int kSortPer = 4;                        // samples per thread
+constexpr int kSortChunk = kSortBlock * kSortPer;  // at 128 tiles a hashed level's runs average 40 pairs
+constexpr int kSampleBytes = 96;   // record space of one sample and level
+constexpr int kMaxBins = 16384;    // tiles over all levels
+constexpr int kTileLog2Max = 12;   // 4096 entries x 2 x 8 B = 64 KB of LDS
+constexpr int kAccBlock = 512;
+constexpr int kAccWaves = kAccBlock / kWave;
+constexpr int kAccPer = 8;         // records per thread and window
+constexpr int kRunWaves = 4;       // waves that load a batch's runs, one per lane
+constexpr int kAccRuns = kRunWaves * kWave;
+constexpr uint32_t kAccTarget = 8192;  // records of a work item at least, where a tile has more
+constexpr int kPlanBlock = 1024;
+constexpr uint32_t kNoItem = 0xffffffffu;
 constexpr int kAccWr = (1 << (kTileLog2Max - 1)) / kAccBlock;  // float4 of a tile per thread
-constexpr int kAccMaxGrid = 2048;
-static_assert(kAccChunk <= (1u << 12) && kAccChunk % kAccBlock == 0, "bin_accum_kernel: scale and record slots");
+constexpr int kAccMaxGrid = 512;   // two workgroups per CU by LDS
+static_assert(8 * kSortChunk < 65536, "16-bit run places");
+static_assert(kAccPer * kAccBlock <= (1 << 12), "fixed-point head room");
 
 struct BinGeom {
-  int tb;         // log2 entries per tile
-  int tpl_log2;   // log2 tiles per level
-  int nbins;
-  int P;          // count / scatter blocks
-  int64_t H;      // histogram entries nbins * P
-  int nchunk;     // histogram scan chunks
-  int64_t rmax;   // record capacity: levels * S * 8
-  int64_t qmax;   // accumulation chunks at most
+  int tb;        // log2 entries per tile
+  int tpl_log2;  // log2 tiles per level
+  int64_t chunks;  // sort chunks of the capacity
 };
 
 inline bool bin_geom(int nl, int64_t S, int log2T, BinGeom *g) {
   if (nl <= 0 || S < 0 || log2T < 1 || log2T > 30) return false;
   g->tb = log2T < kTileLog2Max ? log2T : kTileLog2Max;
   g->tpl_log2 = log2T - g->tb;
-  const int64_t nb = (int64_t)nl << g->tpl_log2;
-  if (nb > kMaxBins) return false;
-  g->nbins = (int)nb;
-  int64_t p = ceil_div((int64_t)nl * (S > 0 ? S : 1), (int64_t)kBinBlock);
-  g->P = (int)(p < 1 ? 1 : (p > kBinMaxBlocks ? kBinMaxBlocks : p));
-  g->H = (int64_t)g->nbins * g->P;
-  g->nchunk = (int)ceil_div(g->H, kHsChunk);
-  g->rmax = (int64_t)nl * S * 8;
-  g->qmax = g->nbins + ceil_div(g->rmax, (int64_t)kAccChunk);
-  return g->nchunk <= kMaxHsChunks && g->rmax < 0xffffffffLL;
+  if (((int64_t)nl << g->tpl_log2) > kMaxBins) return false;
+  g->chunks = ceil_div(S > 0 ? S : 1, (int64_t)kSortChunk);
+  return (int64_t)nl * S * 8 < 0xffffffffLL;
 }
 
+// runs[level][tile][chunk]: x the first pair record and their number << 16, y
+// the same for single records; rec: chunk c of level lr has the bytes from
+// (lr S + c kSortChunk) 96, pair records upwards from its start, single
+// records downwards from its end.
+struct BinQueue {
+  uint32_t next;          // the accumulate pass's next work item
+  uint32_t split, whole;  // work items of tiles that several share, of whole tiles
+};
+
+// A work item of the accumulate pass: a range of chunks of a tile.
+struct AccItem {
+  uint32_t bin;     // level << tpl_log2 | tile
+  uint32_t c0, c1;  // chunks
+  uint32_t split;   // summed with atomics
+};
+
 struct BinWs {
-  uint32_t *hist, *csum, *chunk_first;
-  uint4 *chunk_info;  // per accumulation chunk: bin, first record, end, chunks of the bin
-  float3 *rec;  // (value 0, value 1, entry inside the tile as bits)
+  BinQueue *queue;
+  AccItem *items;  // shared tiles' from the start on, whole tiles' from the end down
+  int64_t cap;     // of items: a tile of n records has at most n / kAccTarget + 1
+  uint2 *runs;
+  char *rec;
   size_t bytes;
 };
 
-inline BinWs bin_ws(const BinGeom &g, void *base) {
+inline BinWs bin_ws(int nl, int64_t S, const BinGeom &g, void *base) {
   BinWs w;
   char *p = (char *)base;
   size_t o = 0;
-  w.hist = (uint32_t *)(p + o);
-  o += align256(sizeof(uint32_t) * (size_t)g.H);
-  w.csum = (uint32_t *)(p + o);
-  o += align256(sizeof(uint32_t) * (size_t)g.nchunk);
-  w.chunk_first = (uint32_t *)(p + o);
-  o += align256(sizeof(uint32_t) * ((size_t)g.nbins + 1));
-  w.chunk_info = (uint4 *)(p + o);
-  o += align256(sizeof(uint4) * (size_t)g.qmax);
-  w.rec = (float3 *)(p + o);
-  o += align256(sizeof(float3) * (size_t)(g.rmax > 0 ? g.rmax : 1));
+  w.queue = (BinQueue *)(p + o);
+  o += 256;
+  w.items = (AccItem *)(p + o);
+  w.cap = ((int64_t)nl << g.tpl_log2) + (int64_t)nl * S * 8 / kAccTarget;
+  o += align256(sizeof(AccItem) * (size_t)w.cap);
+  w.rec = p + o;
+  o += align256((size_t)kSampleBytes * (size_t)nl * (size_t)(S > 0 ? S : 1));
+  w.runs = (uint2 *)(p + o);  // after the records: a single record is loaded with the four bytes behind it
+  o += align256(sizeof(uint2) * (((size_t)nl * (size_t)g.chunks) << g.tpl_log2));
   w.bytes = o;
   return w;
 }
 
-// Exclusive scan of one value per thread over a 1024-thread block; *total
+// Exclusive scan of one value per thread over a block of kThreads; *total
 // gets the block's sum (the same in every thread).
+template <int kThreads>
 __device__ __forceinline__ uint32_t block_scan_u32(uint32_t v, uint32_t *wsum, uint32_t *total) {
   const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  uint32_t incl = v;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const uint32_t t = __shfl_up(incl, o, kWave);
-    if (lane >= o) incl += t;
-  }
+  const uint32_t incl = (uint32_t)wave_incl_scan((int)v);
   if (lane == kWave - 1) wsum[wid] = incl;
   __syncthreads();
   uint32_t base = 0, all = 0;
-  for (int w = 0; w < 1024 / kWave; ++w) {
+#pragma unroll
+  for (int w = 0; w < kThreads / kWave; ++w) {
     base += w < wid ? wsum[w] : 0u;
     all += wsum[w];
   }
@@ -478,421 +490,579 @@ __device__ __forceinline__ uint32_t block_scan_u32(uint32_t v, uint32_t *wsum, u
   return base + incl - v;
 }
 
-// Adds 1 to the LDS counter c[bin] for each lane with act and returns the
-// counter's old value plus the lane's rank among the wave's lanes with the
-// same bin.  When every active lane has the same bin (coarse levels: one
-// tile per level, consecutive samples) the wave does one add of the lane
-// count instead of 64 adds serialised on one LDS address.
-__device__ __forceinline__ uint32_t wave_reserve(uint32_t *c, int bin, bool act) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const uint64_t am = __ballot(act);
-  if (am == 0ull) return 0u;
-  const int first = __ffsll((unsigned long long)am) - 1;
-  const int b0 = __shfl(bin, first, kWave);
-  const uint64_t same = __ballot(act && bin == b0);
-  if (same == am) {
-    uint32_t base = 0u;
-    if (lane == first) base = atomicAdd(&c[bin], (uint32_t)__popcll(am));
-    base = __shfl(base, first, kWave);
-    return base + (uint32_t)__popcll(am & ((1ull << lane) - 1ull));
+// Adds 1 to the LDS counter c[bin[k]] for each lane with act[k], k < 4, and
+// gives the counter's value before the lane's own add.  few: the wave's bins
+// are likely one or two (dense levels: neighbouring samples); the lanes that
+// share the first lane's bin then make one add of their number, instead of
+// that many serialised on one LDS address.
+__device__ __forceinline__ void wave_reserve4(uint32_t *c, const int bin[4], const bool act[4], bool few,
+                                              uint32_t rank[4]) {
+  if (!few) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rank[k] = act[k] ? atomicAdd(&c[bin[k]], 1u) : 0u;
+    return;
   }
-  return act ? atomicAdd(&c[bin], 1u) : 0u;
+  const int lane = threadIdx.x & (kWave - 1);
+  uint64_t same[4];
+  uint32_t own[4], base[4];
+  int first[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {  // every add in flight before the first is used
+    const uint64_t am = __ballot(act[k]);
+    first[k] = am ? __ffsll((unsigned long long)am) - 1 : 0;
+    const int b0 = __builtin_amdgcn_readlane(bin[k], first[k]);
+    same[k] = __ballot(act[k] && bin[k] == b0);
+    const bool lead = lane == first[k] && same[k] != 0ull, alone = act[k] && bin[k] != b0;
+    base[k] = own[k] = 0u;
+    if (lead || alone) own[k] = atomicAdd(&c[bin[k]], lead ? (uint32_t)__popcll(same[k]) : 1u);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    base[k] = (uint32_t)__builtin_amdgcn_readlane((int)own[k], first[k]);
+    const bool mine = (same[k] >> lane) & 1ull;
+    rank[k] = mine ? base[k] + (uint32_t)__popcll(same[k] & ((1ull << lane) - 1ull)) : own[k];
+  }
 }
 
-// Items of the count and scatter passes: item it = level (l0 + it / Sn),
-// sample it % Sn; thread t of block b takes items b * 1024 + t + j * stride
-// (stride = blocks * 1024), kBinUnroll of them per round with their loads
-// issued together.  Both passes visit the same items in the same blocks and
-// compute the corner entries with the same code, so their per-(bin, block)
-// counts agree.
-struct BinItem {
-  int lr;
-  bool act;
-  float x[3];
-  float2 g;
+struct SingleRec {
+  float a, b;
+  uint32_t entry;
 };
 
-template <bool kWithGrad>
-__device__ __forceinline__ void load_items(int64_t i0, int64_t stride, int64_t items, int64_t Sn,
-                                           const float *__restrict__ xc, const int16_t *__restrict__ bone,
-                                           const float *__restrict__ gfeat, int64_t ld, int l0,
-                                           BinItem (&b)[kBinUnroll]) {
-#pragma unroll
-  for (int j = 0; j < kBinUnroll; ++j) {
-    const int64_t it = i0 + j * stride;
-    const bool in = it < items;
-    // items < 2^32 (the record count is), so 32-bit division suffices
-    const uint32_t lr = in ? (uint32_t)it / (uint32_t)Sn : 0u;
-    const int64_t n = in ? it - (int64_t)lr * Sn : 0;
-    b[j].lr = (int)lr;
-    // all loads issued together; n < Sn keeps them in bounds
-    const bool valid = !bone || bone[n] >= 0;
-    b[j].x[0] = xc[n];
-    b[j].x[1] = xc[ld + n];
-    b[j].x[2] = xc[2 * ld + n];
-    b[j].g = kWithGrad ? reinterpret_cast<const float2 *>(gfeat)[(int64_t)(l0 + b[j].lr) * ld + n]
-                       : make_float2(0.0f, 0.0f);
-    b[j].act = in && valid;
-  }
+// Single record i of the chunk whose part ends at `end`.
+__device__ __forceinline__ SingleRec *single_at(char *end, uint32_t i) {
+  return reinterpret_cast<SingleRec *>(end) - 1 - i;
 }
 
-__global__ void __launch_bounds__(kBinBlock) bin_count_kernel(const float *__restrict__ xc,
-                                                             const int16_t *__restrict__ bone, int64_t S,
-                                                             const int64_t *__restrict__ S_dev, int64_t ld, int l0,
-                                                             int nl, int log2T, int tb, Levels lv, Box box,
-                                                             uint32_t *__restrict__ hist) {
-  extern __shared__ uint32_t cnt[];
-  const int tpl_log2 = log2T - tb;
-  const int nbins = nl << tpl_log2;
-  for (int i = threadIdx.x; i < nbins; i += kBinBlock) cnt[i] = 0u;
-  __syncthreads();
-  const int64_t Sn = count_of(S, S_dev);
-  const int64_t items = (int64_t)nl * Sn;
-  const uint32_t T = 1u << log2T;
-  const int64_t stride = (int64_t)gridDim.x * kBinBlock;
-  // the loop bound is wave-uniform at kBinUnroll granularity: lanes past the
-  // end stay in with act = false (the reservations use wave ballots)
-  for (int64_t w0 = (int64_t)blockIdx.x * kBinBlock + (threadIdx.x & ~(kWave - 1)); w0 < items;
-       w0 += stride * kBinUnroll) {
-    BinItem b[kBinUnroll];
-    load_items<false>(w0 + (threadIdx.x & (kWave - 1)), stride, items, Sn, xc, bone, nullptr, ld, l0, b);
-#pragma unroll
-    for (int j = 0; j < kBinUnroll; ++j) {
-      const int level = l0 + b[j].lr;
-      const int N = lv.res[level];
-      const CellPos cp = level_pos(b[j].x, box, N);
-      const bool dense = lv.dense[level] != 0;
-      // dense levels: few tiles, neighbouring samples share them (one add
-      // per wave); hashed levels: bins spread over the tiles (plain adds)
-      if (__ballot(b[j].act && dense) != 0ull) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const uint32_t idx = corner_index(cp, k, N, dense, T - 1u);
-          wave_reserve(cnt, (b[j].lr << tpl_log2) + (int)(idx >> tb), b[j].act);
-        }
-      } else if (b[j].act) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const uint32_t idx = corner_index(cp, k, N, dense, T - 1u);
-          atomicAdd(&cnt[(b[j].lr << tpl_log2) + (int)(idx >> tb)], 1u);
-        }
-      }
-    }
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nbins; i += kBinBlock) hist[(int64_t)blockIdx.x * nbins + i] = cnt[i];
-}
-
-// Exclusive scan of one chunk of the histogram in bin-major order (element
-// j = bin P + block), in place in hist[block][bin].  The chunk's elements
-// sit in a rectangle of rows (blocks) by a few bins; they are read and
-// written row by row (neighbouring threads, neighbouring bins) through an
-// LDS copy in j order, whose rows of P are padded by one word so a row
-// walk does not fall on one bank.  H = nbins P < 2^23.
-__global__ void __launch_bounds__(1024) bin_hist_scan_kernel(uint32_t *__restrict__ hist, int64_t H, int P, int nbins,
-                                                            uint32_t *__restrict__ csum) {
-  __shared__ uint32_t wsum[1024 / kWave];
-  __shared__ uint32_t sv[2 * kHsChunk + 1];  // e + e / P for e < kHsChunk
-  const uint32_t up = (uint32_t)P;
-  const uint32_t j0 = (uint32_t)blockIdx.x * kHsChunk;
-  const uint32_t j1 = (int64_t)j0 + kHsChunk < H ? j0 + kHsChunk : (uint32_t)H;
-  const uint32_t b_lo = j0 / up, nb = (j1 - 1) / up - b_lo + 1;  // bins the chunk touches
-  const uint32_t R = up * nb;                                     // rectangle: P rows by nb bins
-  for (uint32_t r = threadIdx.x; r < R; r += 1024) {
-    const uint32_t p = r / nb, b = b_lo + r % nb, j = b * up + p;
-    if (j >= j0 && j < j1) {
-      const uint32_t e = j - j0;
-      sv[e + e / up] = hist[(int64_t)p * nbins + b];
-    }
-  }
-  __syncthreads();
-  const uint32_t e0 = threadIdx.x * kHsPer;
-  uint32_t v[kHsPer], run = 0;
-#pragma unroll
-  for (int q = 0; q < kHsPer; ++q) {
-    const uint32_t e = e0 + q;
-    v[q] = j0 + e < j1 ? sv[e + e / up] : 0u;
-    run += v[q];
-  }
-  uint32_t total;
-  uint32_t off = block_scan_u32(run, wsum, &total);  // its barriers order the reads above and the writes below
-#pragma unroll
-  for (int q = 0; q < kHsPer; ++q) {
-    const uint32_t e = e0 + q;
-    if (j0 + e < j1) sv[e + e / up] = off;
-    off += v[q];
-  }
-  __syncthreads();
-  for (uint32_t r = threadIdx.x; r < R; r += 1024) {
-    const uint32_t p = r / nb, b = b_lo + r % nb, j = b * up + p;
-    if (j >= j0 && j < j1) {
-      const uint32_t e = j - j0;
-      hist[(int64_t)p * nbins + b] = sv[e + e / up];
-    }
-  }
-  if (threadIdx.x == 0) csum[blockIdx.x] = total;
-}
-
-__global__ void __launch_bounds__(1024) bin_plan_kernel(const uint32_t *__restrict__ hist, uint32_t *__restrict__ csum,
-                                                       int nchunk, int nbins, int P,
-                                                       uint32_t *__restrict__ chunk_first,
-                                                       uint4 *__restrict__ chunk_info) {
-  __shared__ uint32_t wsum[1024 / kWave];
-  __shared__ uint32_t coff[kMaxHsChunks];
-  uint32_t carry = 0;
-  for (int c0 = 0; c0 < nchunk; c0 += 1024) {
-    const int i = c0 + threadIdx.x;
-    const uint32_t v = i < nchunk ? csum[i] : 0u;
-    uint32_t total;
-    const uint32_t off = block_scan_u32(v, wsum, &total);
-    if (i < nchunk) coff[i] = carry + off;
-    carry += total;
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nchunk; i += 1024) csum[i] = coff[i];  // chunk offsets for the scatter pass
-  const uint32_t n_rec = carry;
-  uint32_t ccarry = 0;
-  for (int b0 = 0; b0 < nbins; b0 += 1024) {
-    const int b = b0 + threadIdx.x;
-    uint32_t nch = 0, st = 0, en = 0;
-    if (b < nbins) {
-      // block 0's offset of bin b (row 0 of hist[block][bin])
-      const int64_t j = (int64_t)b * P;
-      st = hist[b] + coff[j / kHsChunk];
-      en = n_rec;
-      if (b + 1 < nbins) {
-        const int64_t j1 = j + P;
-        en = hist[b + 1] + coff[j1 / kHsChunk];
-      }
-      nch = en > st ? (en - st + kAccChunk - 1) / kAccChunk : 1u;
-    }
-    uint32_t total;
-    const uint32_t off = block_scan_u32(nch, wsum, &total);
-    if (b < nbins) {
-      chunk_first[b] = ccarry + off;
-      for (uint32_t c = 0; c < nch; ++c) {
-        const uint32_t rb = st + c * kAccChunk;
-        chunk_info[ccarry + off + c] = make_uint4((uint32_t)b, rb, en - rb > kAccChunk ? rb + kAccChunk : en, nch);
-      }
-    }
-    ccarry += total;
-  }
-  if (threadIdx.x == 0) {
-    chunk_first[nbins] = ccarry;
-  }
-}
-
-__global__ void __launch_bounds__(kBinBlock) bin_scatter_kernel(
+__global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
     const float *__restrict__ gfeat, const float *__restrict__ xc, const int16_t *__restrict__ bone, int64_t S,
     const int64_t *__restrict__ S_dev, int64_t ld, int l0, int nl, int log2T, int tb, Levels lv, Box box,
-    const uint32_t *__restrict__ hist, const uint32_t *__restrict__ coff, float3 *__restrict__ rec, uint32_t rmax) {
-  extern __shared__ uint32_t cur[];
-  const int tpl_log2 = log2T - tb;
-  const int nbins = nl << tpl_log2;
-  const int P = gridDim.x;
-  for (int i = threadIdx.x; i < nbins; i += kBinBlock) {
-    const int64_t j = (int64_t)i * P + blockIdx.x;  // bin-major position
-    cur[i] = hist[(int64_t)blockIdx.x * nbins + i] + coff[j / kHsChunk];
-  }
-  __syncthreads();
+    int64_t chunk_cap, BinQueue *__restrict__ queue, uint2 *__restrict__ runs, char *__restrict__ rec) {
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    *queue = BinQueue{kAccMaxGrid, 0u, 0u};  // the accumulate pass's first items go by block
+  extern __shared__ uint32_t cnt[];  // per tile: pair records, single records << 16
+  __shared__ uint32_t wsum[kSortBlock / kWave];
+  const int tpl_log2 = log2T - tb, tiles = 1 << tpl_log2;
+  const int lr = blockIdx.x % nl, level = l0 + lr;
+  const int N = lv.res[level];
+  const bool dense = lv.dense[level] != 0;
+  const uint32_t Tmask = (1u << log2T) - 1u, emask = (1u << tb) - 1u;
   const int64_t Sn = count_of(S, S_dev);
-  const int64_t items = (int64_t)nl * Sn;
-  const uint32_t T = 1u << log2T;
-  const uint32_t emask = (1u << tb) - 1u;
-  const int64_t stride = (int64_t)gridDim.x * kBinBlock;
-  for (int64_t w0 = (int64_t)blockIdx.x * kBinBlock + (threadIdx.x & ~(kWave - 1)); w0 < items;
-       w0 += stride * kBinUnroll) {
-    BinItem b[kBinUnroll];
-    load_items<true>(w0 + (threadIdx.x & (kWave - 1)), stride, items, Sn, xc, bone, gfeat, ld, l0, b);
+  const int64_t chunks = ceil_div(Sn, (int64_t)kSortChunk);
+  // Consecutive lanes take consecutive samples, but on dense levels samples a
+  // sixty-fourth of the chunk apart: those of a ray share coarse cells, and
+  // their records, which follow in lane order, would meet on one LDS address
+  // in the accumulate pass.
+  const int sample0 = dense ? (int)(threadIdx.x % kWave) * (kSortChunk / kWave) + (int)(threadIdx.x / kWave) * kSortPer
+                            : (int)threadIdx.x;
+  const int sstep = dense ? 1 : kSortBlock;
+  for (int64_t c = blockIdx.x / nl; c < chunks; c += gridDim.x / nl) {
+    for (int i = threadIdx.x; i < tiles; i += kSortBlock) cnt[i] = 0u;
+    float x[kSortPer][3];
+    bool act[kSortPer];
 #pragma unroll
-    for (int j = 0; j < kBinUnroll; ++j) {
-      const int level = l0 + b[j].lr;
-      const int N = lv.res[level];
-      const CellPos cp = level_pos(b[j].x, box, N);
-      const bool dense = lv.dense[level] != 0;
-      if (__ballot(b[j].act && dense) != 0ull) {
+    for (int j = 0; j < kSortPer; ++j) {
+      const int64_t n = c * kSortChunk + sample0 + j * sstep, q = n < Sn ? n : 0;
+      x[j][0] = xc[q];
+      x[j][1] = xc[ld + q];
+      x[j][2] = xc[2 * ld + q];
+      act[j] = n < Sn && (!bone || bone[q] >= 0);
+    }
+    __syncthreads();
+    // rank of each pair within its tile's run, 16 bits each
+    uint2 rank[kSortPer];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const uint32_t idx = corner_index(cp, k, N, dense, T - 1u);
-          const float w = corner_weight(cp, k);
-          const uint32_t pos = wave_reserve(cur, (b[j].lr << tpl_log2) + (int)(idx >> tb), b[j].act);
-          if (b[j].act && pos < rmax)
-            rec[pos] = make_float3(w * b[j].g.x, w * b[j].g.y, __uint_as_float(idx & emask));
+    for (int j = 0; j < kSortPer; ++j) {
+      const CellPos p = level_pos(x[j], box, N);
+      int t0[4], t1[4];
+      bool pair[4];
+      uint32_t r[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        t0[k] = (int)(corner_index(p, 2 * k, N, dense, Tmask) >> tb);
+        t1[k] = (int)(corner_index(p, 2 * k + 1, N, dense, Tmask) >> tb);
+        pair[k] = act[j] && t0[k] == t1[k];
+      }
+      wave_reserve4(cnt, t0, pair, dense, r);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (act[j] && !pair[k]) {
+          atomicAdd(&cnt[t0[k]], 1u << 16);
+          atomicAdd(&cnt[t1[k]], 1u << 16);
         }
-      } else if (b[j].act) {
-        uint32_t idx[8], pos[8];
+      rank[j] = make_uint2((r[0] & 0xffffu) | r[1] << 16, (r[2] & 0xffffu) | r[3] << 16);
+    }
+    __syncthreads();
+    // counts -> offsets, in place and into the run table
+    uint32_t carry = 0;
+    for (int b0 = 0; b0 < tiles; b0 += kSortBlock) {
+      const int i = b0 + threadIdx.x;
+      const uint32_t v = i < tiles ? cnt[i] : 0u;
+      uint32_t total;
+      const uint32_t off = carry + block_scan_u32<kSortBlock>(v, wsum, &total);  // the halves do not overflow
+      if (i < tiles) {
+        cnt[i] = off;
+        runs[(((int64_t)lr << tpl_log2) + i) * chunk_cap + c] =
+            make_uint2((off & 0xffffu) | v << 16, (off >> 16) | (v & 0xffff0000u));
+      }
+      carry += total;
+    }
+    __syncthreads();
+    char *region = rec + ((int64_t)lr * S + c * kSortChunk) * kSampleBytes;
+    uint4 *pairs = reinterpret_cast<uint4 *>(region);
+    char *end = region + (Sn - c * kSortChunk < kSortChunk ? Sn - c * kSortChunk : kSortChunk) * kSampleBytes;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          idx[k] = corner_index(cp, k, N, dense, T - 1u);
-          pos[k] = atomicAdd(&cur[(b[j].lr << tpl_log2) + (int)(idx[k] >> tb)], 1u);
-        }
+    for (int j = 0; j < kSortPer; ++j) {
+      if (!act[j]) continue;
+      // the cell is found again: kept for four samples since the count, it
+      // would cost a hundred registers
+      asm volatile("" : "+v"(x[j][0]), "+v"(x[j][1]), "+v"(x[j][2]));
+      const float2 g = reinterpret_cast<const float2 *>(
+          gfeat)[(int64_t)level * ld + c * kSortChunk + sample0 + j * sstep];
+      const CellPos p = level_pos(x[j], box, N);
+      const float w0 = 1.0f - p.f[0], w1 = p.f[0];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const float w = corner_weight(cp, k);
-          if (pos[k] < rmax) rec[pos[k]] = make_float3(w * b[j].g.x, w * b[j].g.y, __uint_as_float(idx[k] & emask));
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t i0 = corner_index(p, 2 * k, N, dense, Tmask), i1 = corner_index(p, 2 * k + 1, N, dense, Tmask);
+        const float wyz = ((k & 1) ? p.f[1] : 1.0f - p.f[1]) * ((k & 2) ? p.f[2] : 1.0f - p.f[2]);
+        const float a = wyz * g.x, b = wyz * g.y;
+        const uint32_t t0 = i0 >> tb, t1 = i1 >> tb, e0 = i0 & emask, e1 = i1 & emask;
+        if (t0 == t1) {
+          const uint32_t r = ((k & 2 ? rank[j].y : rank[j].x) >> (k & 1 ? 16 : 0)) & 0xffffu;
+          pairs[(cnt[t0] & 0xffffu) + r] =
+              make_uint4(__float_as_uint(a), __float_as_uint(b), __float_as_uint(w1), e0 | e1 << 16);
+        } else {  // the singles' next places are counted in the high halves
+          *single_at(end, atomicAdd(&cnt[t0], 1u << 16) >> 16) = SingleRec{w0 * a, w0 * b, e0};
+          *single_at(end, atomicAdd(&cnt[t1], 1u << 16) >> 16) = SingleRec{w1 * a, w1 * b, e1};
         }
       }
     }
+    __syncthreads();  // the counters are cleared for the next chunk
   }
 }
 
-// Base of bin b's tile in the table gradient.
-__device__ __forceinline__ float4 *tile_ptr(float *gtable, int b, int l0, int log2T, int tb) {
-  const int tpl_log2 = log2T - tb;
-  const int64_t level = l0 + (b >> tpl_log2);
-  const int64_t tile = b & ((1 << tpl_log2) - 1);
-  return reinterpret_cast<float4 *>(gtable + 2 * ((level << log2T) + (tile << tb)));
+// v 2^s rounded to an integer (ties to even), as two's complement bits
+// (|v| 2^s < 2^50): the sum with 1.5 2^52 has it in its low bits.
+__device__ __forceinline__ unsigned long long to_fixed(float v, double scale) {
+  const double magic = 6755399441055744.0;
+  return (unsigned long long)(__double_as_longlong(fma((double)v, scale, magic)) - __double_as_longlong(magic));
 }
 
-// Clears the tiles of bins split over several chunks (they are then summed
-// with atomics); overwrite only.
-__global__ void __launch_bounds__(256) bin_clear_split_kernel(const uint32_t *__restrict__ chunk_first, int nbins,
-                                                             int l0, int log2T, int tb, float *__restrict__ gtable) {
-  const int n4 = 1 << (tb - 1);  // float4 per tile (2 entries each)
-  for (int b = blockIdx.x; b < nbins; b += gridDim.x) {
-    if (chunk_first[b + 1] - chunk_first[b] <= 1u) continue;
-    float4 *dst = tile_ptr(gtable, b, l0, log2T, tb);
-    for (int j = threadIdx.x; j < n4; j += 256) dst[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  }
+// A fixed-point sum back to FP32 (one rounding).
+__device__ __forceinline__ float from_fixed(unsigned long long a, int s) {
+  return (float)ldexp((double)(long long)a, -s);
 }
 
-// Block-wide max of v and OR of flag (1024 threads).
-__device__ __forceinline__ float block_max(float v, bool flag, float *red, int *redf, bool *any) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  const bool wf = __ballot(flag) != 0ull;
-  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  if (lane == 0) {
-    red[wid] = v;
-    redf[wid] = wf;
+// Sixteen bytes at a multiple of four.
+__device__ __forceinline__ uint4 load16(const char *p) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+  const u4 v = *reinterpret_cast<const u4 *>(p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// The two features of a record's first and second entry (raw: a, b, x
+// fraction, entries), or of a single record's entry (a, b, entry; kind 1).
+__device__ __forceinline__ float4 values(const uint4 &raw, int kind) {
+  const float x = kind ? 0.0f : __uint_as_float(raw.z), a = __uint_as_float(raw.x), b = __uint_as_float(raw.y);
+  return make_float4((1.0f - x) * a, (1.0f - x) * b, x * a, x * b);
+}
+
+// Keeps the compiler from carrying what it computed of raw before (the values
+// are cheaper to find again than to hold).
+__device__ __forceinline__ void opaque(uint4 &raw) { asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w)); }
+
+// The work items of the accumulate pass, a wave per tile.  A tile without
+// records is cleared here when overwriting, and one with more than `target`
+// is split at the chunks where about as many are reached; its workgroups add
+// to the table with atomics, so it is cleared as well.  The items so hold at
+// most target records and a chunk's, whatever the samples crowd on.  Reads the
+// run table once or twice (0.5 MB for 36,503 samples, 3.4 MB for 262,143).
+__global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__restrict__ runs, int64_t S,
+                                                              const int64_t *__restrict__ S_dev, int64_t chunk_cap,
+                                                              int l0, int nl, int log2T, int tb, int overwrite,
+                                                              int64_t cap, BinQueue *__restrict__ queue,
+                                                              AccItem *__restrict__ items,
+                                                              float *__restrict__ gtable) {
+  __shared__ uint32_t wholes, first_whole;
+  const int lane = threadIdx.x & (kWave - 1), tpl_log2 = log2T - tb;
+  const uint32_t bin =
+      __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kPlanBlock / kWave) + threadIdx.x / kWave));
+  const bool live = bin < (uint32_t)nl << tpl_log2;
+  if (threadIdx.x == 0) wholes = 0u;
+  const uint32_t Sn = (uint32_t)count_of(S, S_dev), chunks = (Sn + kSortChunk - 1) / kSortChunk;
+  const uint2 *run = runs + (int64_t)bin * chunk_cap;
+  uint32_t total = 0;
+#pragma unroll 4
+  for (uint32_t c = lane; live && c < chunks; c += kWave) {
+    const uint2 q = run[c];
+    total += (q.x >> 16) + (q.y >> 16);
   }
+  total = (uint32_t)__builtin_amdgcn_readlane(wave_incl_scan((int)total), kWave - 1);
+  // half of what a resident workgroup would get of a level mix without empty
+  // tiles, so the largest items do not outlast the others
+  const uint32_t even = 4u * (uint32_t)nl * Sn / (2u * kAccMaxGrid);  // 8 L S < 2^32
+  const uint32_t target = even > kAccTarget ? even : kAccTarget;
+  // one global add per block: an add per tile is 15 us of adds to one address
+  const bool whole = total <= target && total != 0u;
   __syncthreads();
-  float m = 0.0f;
-  int f = 0;
-  for (int w = 0; w < kAccBlock / kWave; ++w) {
-    m = fmaxf(m, red[w]);
-    f |= redf[w];
-  }
+  uint32_t at = 0;
+  if (whole && lane == 0) at = atomicAdd(&wholes, 1u);
   __syncthreads();
-  *any = f != 0;
-  return m;
+  if (threadIdx.x == 0 && wholes != 0u) first_whole = atomicAdd(&queue->whole, wholes);
+  __syncthreads();
+  if (whole && lane == 0) items[cap - 1 - (int64_t)(first_whole + at)] = AccItem{bin, 0u, chunks, 0u};
+  if (whole || !live) return;
+  if (overwrite) {
+    const uint32_t lr = bin >> tpl_log2, tile = bin - (lr << tpl_log2);
+    float4 *dst = reinterpret_cast<float4 *>(
+        gtable + ((((int64_t)l0 + lr) << (log2T + 1)) + ((int64_t)tile << (tb + 1))));
+    for (int i = lane; i < 1 << (tb - 1); i += kWave) dst[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  }
+  if (total == 0u) return;
+  const uint32_t groups = total / target + 1u, per = total / groups + 1u;  // records
+  uint32_t before = 0, start = 0, group = 0;  // records before the step, the open item's first chunk and group
+  for (uint32_t cb = 0; cb < chunks; cb += kWave) {
+    const uint32_t c = cb + lane;
+    const uint2 q = c < chunks ? run[c] : make_uint2(0u, 0u);
+    const uint32_t n = (q.x >> 16) + (q.y >> 16), incl = (uint32_t)wave_incl_scan((int)n);
+    const uint32_t mine = c < chunks ? (before + incl - n) / per : 0xffffffffu;  // < groups
+    const uint32_t prev = lane == 0 ? group : (uint32_t)__shfl_up((int)mine, 1, kWave);
+    const bool opens = c < chunks && mine != prev;
+    const uint64_t m = __ballot(opens);
+    if (m != 0ull) {  // each closes the item before it
+      uint32_t at = 0;
+      if (lane == 0) at = atomicAdd(&queue->split, (uint32_t)__popcll(m));
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+      const uint64_t lower = m & ((1ull << lane) - 1ull);
+      const uint32_t from = lower ? cb + 63u - (uint32_t)__clzll((long long)lower) : start;
+      if (opens) items[at + (uint32_t)__popcll(lower)] = AccItem{bin, from, c, 1u};
+      start = cb + 63u - (uint32_t)__clzll((long long)m);
+      group = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)(start - cb));
+    }
+    before += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  }
+  if (lane == 0) items[atomicAdd(&queue->split, 1u)] = AccItem{bin, start, chunks, 1u};
 }
 
-// Four consecutive fixed-point sums back to FP32 (one rounding each).
-__device__ __forceinline__ float4 from_fixed4(const unsigned long long *a, int s) {
-  return make_float4((float)ldexp((double)(long long)a[0], -s), (float)ldexp((double)(long long)a[1], -s),
-                     (float)ldexp((double)(long long)a[2], -s), (float)ldexp((double)(long long)a[3], -s));
-}
-
-// v * 2^s rounded to an integer, as two's complement bits (|v| 2^s < 2^48)
-__device__ __forceinline__ unsigned long long to_fixed(float v, int s) {
-  return (unsigned long long)(long long)rint((double)ldexpf(v, s));
-}
-
-__global__ void __launch_bounds__(kAccBlock) bin_accum_kernel(const float3 *__restrict__ rec,
-                                                             const uint32_t *__restrict__ chunk_first,
-                                                             const uint4 *__restrict__ chunk_info, int nbins,
-                                                             uint32_t qmax, uint32_t rmax, int l0, int log2T, int tb,
-                                                             int overwrite, float *__restrict__ gtable) {
+// The block's waves share a window of 64 pieces, a piece being up to 64
+// consecutive records of a run; a batch is the pieces of up to kAccRuns runs
+// (chunks).  Four waves scan the runs' numbers of pieces into LDS, then each
+// lane of a wave looks up one piece of the window, and the wave reads its
+// eight from those lanes.
+// The next window's records, also those of the next item, are loaded before
+// this window's sums are converted and stored, and the runs of the batch
+// after it before that, so the loads' latency hides behind the conversion.
+// The items' sizes differ, so they come from a queue, the shared tiles' first.
+// Bound by the chain of a window (load, maximum, LDS adds, conversion), two
+// workgroups per CU by LDS.
+__global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__restrict__ queue,
+                                                                const AccItem *__restrict__ list, int64_t cap,
+                                                                const uint2 *__restrict__ runs,
+                                                                const char *__restrict__ rec, int64_t S,
+                                                                const int64_t *__restrict__ S_dev, int64_t chunk_cap,
+                                                                int l0, int log2T, int tb, int overwrite,
+                                                                float *__restrict__ gtable) {
   extern __shared__ unsigned long long acc[];  // 2 E fixed-point sums
-  __shared__ float red[kAccBlock / kWave];
-  __shared__ int redf[kAccBlock / kWave];
+  __shared__ float red[kAccWaves];
+  __shared__ int redf[kAccWaves];
+  __shared__ AccItem queued;  // the item after the next (bin kNoItem: none)
+  __shared__ uint32_t trun[kAccRuns];  // the batch's runs (first record, count << 16)
+  __shared__ int toff[kAccRuns];       // their first pieces, within the 64 runs of a wave
+  __shared__ int ttot[kRunWaves];      // pieces of each 64 runs; whether they have single records
+  __shared__ int tsing[kRunWaves];
+  const int tpl_log2 = log2T - tb;
   const int n2 = 1 << tb;  // entries of a tile (2 sums each)
   const int n4 = n2 / 2;   // float4 (2 entries) per tile
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int64_t Sn = count_of(S, S_dev);
+  const uint32_t nsplit = queue->split, nitems = nsplit + queue->whole;
+  if (blockIdx.x >= nitems) return;
+  auto item_at = [&](uint32_t i) {
+    return i < nsplit ? list[i] : i < nitems ? list[cap - 1 - (int64_t)(i - nsplit)] : AccItem{kNoItem, 0u, 0u, 0u};
+  };
+  auto uniform = [](const AccItem &I) {
+    return AccItem{(uint32_t)__builtin_amdgcn_readfirstlane((int)I.bin),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)I.c0),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)I.c1),
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)I.split)};
+  };
+  if (tid == 0) queued = item_at(atomicAdd(&queue->next, 1u));
   ulonglong2 *a2 = reinterpret_cast<ulonglong2 *>(acc);
-  const uint32_t Q = chunk_first[nbins] < qmax ? chunk_first[nbins] : qmax;
-  for (uint32_t q = blockIdx.x; q < Q; q += gridDim.x) {
-    const uint4 ci = chunk_info[q];  // bin, first record, end, chunks of the bin
-    const int b = (int)ci.x;
-    const uint32_t rb = ci.y, re = ci.z, nch = ci.w;
-    // a plan from this workspace always passes; the checks keep a misused
-    // one (IA355_TABLE_REUSE_PLAN without a plan) inside the buffers
-    if (ci.x >= (uint32_t)nbins || rb > re || re > rmax || re - rb > kAccChunk) continue;
-    float4 *dst = tile_ptr(gtable, b, l0, log2T, tb);
-    if (rb == re) {  // no update in this tile (then nch == 1)
-      if (overwrite)
-        for (int j = threadIdx.x; j < n4; j += kAccBlock) dst[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      continue;
+  for (int j = tid; j < n2; j += kAccBlock) a2[j] = make_ulonglong2(0ull, 0ull);
+  __syncthreads();
+  // run of chunk cb + 64 wid + lane, in the first kRunWaves waves
+  auto load_runs = [&](const AccItem &I, uint32_t cb) {
+    const uint32_t c = cb + wid * kWave + lane;
+    uint2 q = make_uint2(0u, 0u);
+    if (wid < kRunWaves && c < I.c1) q = runs[(int64_t)I.bin * chunk_cap + c];
+    return q;
+  };
+  AccItem I = uniform(item_at(blockIdx.x)), In = I;  // the item, that of the next batch
+  AccItem item_n = uniform(queued);                  // the next item
+  uint32_t cb = I.c0, cbn = 0;
+  int kind = 0;  // 0: pair records, 1: single records
+  uint2 ri = load_runs(I, cb), rin = make_uint2(0u, 0u);
+  int total = 0, next = 0;  // pieces of the batch; the next window's first
+  int sing = 0;             // the batch has single records as well
+  uint4 raw[kAccPer];
+  uint32_t in = 0;  // bit k: raw[k] holds a record
+  auto begin = [&]() {  // the tables of batch (cb, kind); a barrier follows
+    if (wid < kRunWaves) {
+      const uint32_t x = kind ? ri.y : ri.x;
+      const int n = (int)((x >> 16) + kWave - 1) / kWave;
+      const int incl = wave_incl_scan(n);
+      trun[wid * kWave + lane] = x;
+      toff[wid * kWave + lane] = incl - n;
+      const int sing = __any(ri.y >> 16) != 0;
+      if (lane == kWave - 1) {
+        ttot[wid] = incl;
+        tsing[wid] = sing;
+      }
     }
-    // this thread's records (at most kAccPer), read once; non-finite values
-    // stay out of the scale and the integer sums (added with atomics below)
-    float3 v[kAccPer];
+    next = 0;
+  };
+  auto fill = [&]() {  // this wave's pieces of the next window
+    in = 0u;
+    int base[kRunWaves];
+    total = sing = 0;
+#pragma unroll
+    for (int h = 0; h < kRunWaves; ++h) {
+      base[h] = total;
+      total += __builtin_amdgcn_readfirstlane(ttot[h]);
+      sing |= __builtin_amdgcn_readfirstlane(tsing[h]);
+    }
+    if (next < total) {
+      // lane l: piece next + l
+      int jl = next + lane, t0 = 0;
+      const bool live = jl < total;
+      int sub = 0;
+#pragma unroll
+      for (int h = 1; h < kRunWaves; ++h)
+        if (jl >= base[h]) {
+          t0 = h * kWave;
+          sub = base[h];
+        }
+      jl -= sub;
+      // the last run that starts at or before it (runs without records share
+      // the next one's first piece and come before it)
+      int c = t0;
+#pragma unroll
+      for (int st = kWave / 2; st > 0; st >>= 1)
+        if (toff[c + st] <= jl) c += st;
+      const uint32_t x = trun[c], i0 = (uint32_t)(jl - toff[c]) * kWave;
+      const int left = live ? (int)(x >> 16) - (int)i0 : 0;
+      int at = c * (kSortChunk * kSampleBytes);  // bytes from the batch's first chunk
+      if (kind == 0) {
+        at += 16 * (int)((x & 0xffffu) + i0);
+      } else {  // a chunk's single records lie downwards from its end
+        const int64_t ns = Sn - (int64_t)(cb + c) * kSortChunk;
+        at += (int)(ns < kSortChunk ? ns : kSortChunk) * kSampleBytes - 12 * (int)((x & 0xffffu) + i0 + 1u);
+      }
+      const char *region0 = rec + ((int64_t)(I.bin >> tpl_log2) * S + (int64_t)cb * kSortChunk) * kSampleBytes;
+      const int step = kind == 0 ? 16 : -12;
+#pragma unroll
+      for (int k = 0; k < kAccPer; ++k) {
+        const int n = __builtin_amdgcn_readlane(left, k * kAccWaves + wid);
+        const int o = __builtin_amdgcn_readlane(at, k * kAccWaves + wid);
+        // lanes past the piece load the region's first bytes, which stay
+        // unused, as do the last four of a single record's sixteen
+        raw[k] = load16(region0 + (lane < n ? o + lane * step : 0));
+        in |= lane < n ? 1u << k : 0u;
+      }
+    }
+    next += kAccPer * kAccWaves;
+  };
+  auto next_batch = [&]() {  // the batch after (I, cb, kind 1), its runs on their way
+    cbn = cb + kAccRuns;
+    In = I;
+    if (cbn >= I.c1) {
+      In.c0 = In.c1 = cbn = 0;
+      if (item_n.bin != kNoItem) {
+        In = item_n;
+        cbn = In.c0;
+        if (tid == 0) queued = item_at(atomicAdd(&queue->next, 1u));  // read after the next barrier
+      }
+    }
+    rin = load_runs(In, cbn);
+  };
+  begin();
+  __syncthreads();
+  fill();
+  next_batch();
+  float4 out[kAccWr];
+#pragma unroll
+  for (int q = 0; q < kAccWr; ++q) out[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  bool any = false;
+  for (;;) {
+    // the window's largest finite |value|, and whether it holds a NaN or an
+    // infinity (they stay out of the scale and the integer sums)
     float m = 0.0f;
     bool odd = false;
 #pragma unroll
-    for (int j = 0; j < kAccPer; ++j) {
-      const uint32_t r = rb + threadIdx.x + j * kAccBlock;
-      v[j] = r < re ? rec[r] : make_float3(0.0f, 0.0f, 0.0f);
-      const bool fx = isfinite(v[j].x), fy = isfinite(v[j].y);
-      m = fmaxf(m, fmaxf(fx ? fabsf(v[j].x) : 0.0f, fy ? fabsf(v[j].y) : 0.0f));
-      odd = odd || !fx || !fy;
-    }
-    for (int j = threadIdx.x; j < n2; j += kAccBlock) a2[j] = make_ulonglong2(0ull, 0ull);
-    // scale: |sum of the chunk's values| <= n max|v| < 2^(ex + 12) with
-    // max|v| < 2^ex and n <= 2^12 records, so 2^s with s = 47 - ex keeps
-    // every partial sum below 2^59
-    bool odd_tile;  // some value of the chunk is NaN or infinite
-    m = block_max(m, odd, red, redf, &odd_tile);  // its barriers also order the clear above
-    int ex = 0;
-    frexpf(m, &ex);  // m < 2^ex (m = 0: ex = 0)
-    const int sc = 47 - ex;
-#pragma unroll
-    for (int j = 0; j < kAccPer; ++j) {
-      if (rb + threadIdx.x + j * kAccBlock < re) {
-        const uint32_t e = __float_as_uint(v[j].z) & (uint32_t)(n2 - 1);  // < E for every record written here
-        if (isfinite(v[j].x)) atomicAdd(&acc[2 * e], to_fixed(v[j].x, sc));
-        if (isfinite(v[j].y)) atomicAdd(&acc[2 * e + 1], to_fixed(v[j].y, sc));
-      }
-    }
-    // NaN or infinite values (kept out of the integer sums) are added to a
-    // float copy of the tile in LDS, so they reach their own entries as FP32
-    // adds would; only chunks that hold such a value take this path
-    float *fv = reinterpret_cast<float *>(acc);
-    __syncthreads();  // the integer adds are complete
-    if (odd_tile) {
-      float4 tmp[kAccWr];
-#pragma unroll
-      for (int q = 0; q < kAccWr; ++q) {
-        const int j = threadIdx.x + q * kAccBlock;
-        if (j < n4) tmp[q] = from_fixed4(acc + 4 * j, sc);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kAccWr; ++q) {
-        const int j = threadIdx.x + q * kAccBlock;
-        if (j < n4) reinterpret_cast<float4 *>(fv)[j] = tmp[q];
-      }
-      __syncthreads();
-      // the records again (from cache): keeping them in registers across
-      // the write-out would cost occupancy on every chunk
-      for (uint32_t r = rb + threadIdx.x; r < re; r += kAccBlock) {
-        const float3 w = rec[r];
-        const uint32_t e = __float_as_uint(w.z) & (uint32_t)(n2 - 1);
-        if (!isfinite(w.x)) atomicAdd(&fv[2 * e], w.x);
-        if (!isfinite(w.y)) atomicAdd(&fv[2 * e + 1], w.y);
-      }
-      __syncthreads();
-    }
-    for (int j = threadIdx.x; j < n4; j += kAccBlock) {
-      float4 o = odd_tile ? reinterpret_cast<const float4 *>(fv)[j] : from_fixed4(acc + 4 * j, sc);
-      if (nch == 1u) {  // the only writer of this tile
-        if (!overwrite) {
-          const float4 p = dst[j];
-          o.x += p.x;
-          o.y += p.y;
-          o.z += p.z;
-          o.w += p.w;
-        }
-        dst[j] = o;
+    for (int k = 0; k < kAccPer; ++k) {
+      if (!((in >> k) & 1u)) continue;
+      const float4 v = values(raw[k], kind);
+      const float t = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
+      // finite unless a term is not (or their sum overflows: the slow path)
+      if (isfinite(fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w))) {
+        m = fmaxf(m, t);
       } else {
-        float *df = reinterpret_cast<float *>(dst + j);
-        if (o.x != 0.0f) atomicAdd(df, o.x);
-        if (o.y != 0.0f) atomicAdd(df + 1, o.y);
-        if (o.z != 0.0f) atomicAdd(df + 2, o.z);
-        if (o.w != 0.0f) atomicAdd(df + 3, o.w);
+        odd = true;
+        const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int h = 0; h < 4; ++h) m = isfinite(f[h]) ? fmaxf(m, fabsf(f[h])) : m;
       }
     }
-    __syncthreads();  // the sums are cleared for the next chunk
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
+    const int flags = (__any(odd) ? 1 : 0) | (__any(in != 0u) ? 2 : 0);
+    if (lane == 0) {
+      red[wid] = m;
+      redf[wid] = flags;
+    }
+    __syncthreads();  // also: the sums are clear
+    m = 0.0f;
+    int wf = 0;
+#pragma unroll
+    for (int w = 0; w < kAccWaves; ++w) {
+      m = fmaxf(m, red[w]);
+      wf |= redf[w];
+    }
+    wf = __builtin_amdgcn_readfirstlane(wf);
+    const bool odd_tile = (wf & 1) != 0, full = (wf & 2) != 0, again = next < total;
+    const AccItem item_q = uniform(queued);
+    const uint32_t in_now = in;
+    const int kind_now = kind;
+    // |value| < 2^ex: with 2^s, s = 47 - ex, an entry's sum over the
+    // window's 2^12 records stays below 2^59
+    int ex = 0;
+    frexpf(m, &ex);
+    const int sc = 47 - ex;
+    if (full) {
+      const double scale = ldexp(1.0, sc);
+#pragma unroll
+      for (int k = 0; k < kAccPer; ++k) {
+        if (!((in_now >> k) & 1u)) continue;
+        opaque(raw[k]);
+        const float4 v = values(raw[k], kind_now);
+        const uint32_t e = kind_now ? raw[k].z : raw[k].w;
+        const uint32_t e0 = e & (uint32_t)(n2 - 1), e1 = (e >> 16) & (uint32_t)(n2 - 1);
+        if (!odd_tile || isfinite(v.x)) atomicAdd(&acc[e0], to_fixed(v.x, scale));
+        if (!odd_tile || isfinite(v.y)) atomicAdd(&acc[n2 + e0], to_fixed(v.y, scale));
+        if (kind_now) continue;
+        if (!odd_tile || isfinite(v.z)) atomicAdd(&acc[e1], to_fixed(v.z, scale));
+        if (!odd_tile || isfinite(v.w)) atomicAdd(&acc[n2 + e1], to_fixed(v.w, scale));
+      }
+    }
+    // move on: the same batch, its single records, the next batch or item
+    const AccItem I_now = I;
+    bool last = false, stop = false;  // last window of the item; no item left
+    if (!again) {
+      if (kind == 0 && sing) {
+        kind = 1;
+      } else {
+        last = cb + kAccRuns >= I.c1;
+        stop = last && item_n.bin == kNoItem;
+        if (last) item_n = item_q;
+        I = In;
+        cb = cbn;
+        ri = rin;
+        kind = 0;
+      }
+      begin();
+    }
+    __syncthreads();  // the integer adds are complete, the tables written
+    if (!odd_tile) fill();
+    if (full) {
+      any = true;
+#pragma unroll
+      for (int q = 0; q < kAccWr; ++q) {
+        const int j = tid + q * kAccBlock;
+        if (j < n4) {  // the first features' sums, then (n2 on) the second features'
+          const ulonglong2 f = a2[j], g = a2[n4 + j];
+          out[q].x += from_fixed(f.x, sc);
+          out[q].y += from_fixed(g.x, sc);
+          out[q].z += from_fixed(f.y, sc);
+          out[q].w += from_fixed(g.y, sc);
+          a2[j] = make_ulonglong2(0ull, 0ull);
+          a2[n4 + j] = make_ulonglong2(0ull, 0ull);
+        }
+      }
+    }
+    if (odd_tile) {
+      // NaN and infinite values are added as FP32 values in the cleared tile,
+      // so they reach their own entries as FP32 adds would
+      float *fv = reinterpret_cast<float *>(acc);
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kAccPer; ++k) {
+        if (!((in_now >> k) & 1u)) continue;
+        const float4 v = values(raw[k], kind_now);
+        const uint32_t e = kind_now ? raw[k].z : raw[k].w;
+        const uint32_t e0 = e & (uint32_t)(n2 - 1), e1 = (e >> 16) & (uint32_t)(n2 - 1);
+        if (!isfinite(v.x)) atomicAdd(&fv[2 * e0], v.x);
+        if (!isfinite(v.y)) atomicAdd(&fv[2 * e0 + 1], v.y);
+        if (kind_now) continue;
+        if (!isfinite(v.z)) atomicAdd(&fv[2 * e1], v.z);
+        if (!isfinite(v.w)) atomicAdd(&fv[2 * e1 + 1], v.w);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kAccWr; ++q) {
+        const int j = tid + q * kAccBlock;
+        if (j < n4) {
+          const float4 f = reinterpret_cast<const float4 *>(fv)[j];
+          out[q].x += f.x;
+          out[q].y += f.y;
+          out[q].z += f.z;
+          out[q].w += f.w;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kAccWr; ++q) {
+        const int j = tid + q * kAccBlock;
+        if (j < n4) reinterpret_cast<float4 *>(fv)[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      }
+      fill();
+    }
+    if (last) {
+      float4 *dst =
+          reinterpret_cast<float4 *>(gtable + ((((int64_t)l0 << log2T) + ((int64_t)I_now.bin << tb)) << 1));
+      if (I_now.split) {
+        if (any)
+#pragma unroll
+          for (int q = 0; q < kAccWr; ++q) {
+            const int j = tid + q * kAccBlock;
+            if (j >= n4) continue;
+            float *df = reinterpret_cast<float *>(dst + j);
+            if (out[q].x != 0.0f) atomicAdd(df, out[q].x);
+            if (out[q].y != 0.0f) atomicAdd(df + 1, out[q].y);
+            if (out[q].z != 0.0f) atomicAdd(df + 2, out[q].z);
+            if (out[q].w != 0.0f) atomicAdd(df + 3, out[q].w);
+          }
+      } else if (overwrite || any) {  // the only writer of this tile
+#pragma unroll
+        for (int q = 0; q < kAccWr; ++q) {
+          const int j = tid + q * kAccBlock;
+          if (j >= n4) continue;
+          float4 o = out[q];
+          if (!overwrite) {
+            const float4 p = dst[j];
+            o.x += p.x;
+            o.y += p.y;
+            o.z += p.z;
+            o.w += p.w;
+          }
+          dst[j] = o;
+        }
+      }
+      if (stop) return;
+#pragma unroll
+      for (int q = 0; q < kAccWr; ++q) out[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      any = false;
+    }
+    if (!again && kind == 0) next_batch();
   }
 }
 
@@ -1013,7 +1183,7 @@ extern "C" int32_t ia355_hashgrid_encode_bwd(const float *grad_feat, const float
 extern "C" size_t ia355_hashgrid_table_grad_workspace_size(int64_t S, int32_t L, int32_t log2T) {
   BinGeom g;
   if (L <= 0 || L > 16 || !bin_geom(L, S, log2T, &g)) return 0;
-  return bin_ws(g, nullptr).bytes;
+  return bin_ws(L, S, g, nullptr).bytes;
 }
 
 extern "C" int32_t ia355_hashgrid_table_grad(const float *grad_feat, const float *xc, const int16_t *bone, int64_t S,
@@ -1034,7 +1204,7 @@ extern "C" int32_t ia355_hashgrid_table_grad(const float *grad_feat, const float
   if (make_levels(L, log2T, base_res, growth, &lv) || make_box(aabb, &box)) return IA355_ERR_INVALID_ARG;
   BinGeom full;
   if (!bin_geom(L, S, log2T, &full)) return IA355_ERR_INVALID_ARG;
-  if (!ws || ws_bytes < bin_ws(full, nullptr).bytes) return IA355_ERR_WORKSPACE;
+  if (!ws || ws_bytes < bin_ws(L, S, full, nullptr).bytes) return IA355_ERR_WORKSPACE;
   int ndense = 0;
   while (ndense < L && lv.dense[ndense] && lv.res[ndense] <= kAggMaxRes) ++ndense;
   const bool coarse = !(flags & IA355_TABLE_FINE) || (flags & IA355_TABLE_COARSE);
@@ -1048,25 +1218,21 @@ extern "C" int32_t ia355_hashgrid_table_grad(const float *grad_feat, const float
     const size_t level_floats = 2 * ((size_t)1 << log2T);
     return ia355_zero(grad_table + level_floats * l0, sizeof(float) * level_floats * (l1 - l0), stream);
   }
+  if (plan_only) return IA355_OK;  // nothing to prepare: the sort finds its own offsets
+  const int nl = l1 - l0;
   BinGeom g;
-  bin_geom(l1 - l0, S, log2T, &g);  // fewer levels than `full`: fits its workspace
-  const BinWs w = bin_ws(g, ws);
-  const size_t cnt_lds = sizeof(uint32_t) * (size_t)g.nbins;
-  if (!reuse) {  // passes 1-3 read only the positions, the bones and the count
-    bin_count_kernel<<<g.P, kBinBlock, cnt_lds, s>>>(xc, bone, S, S_dev, ld, l0, l1 - l0, log2T, g.tb, lv, box,
-                                                     w.hist);
-    bin_hist_scan_kernel<<<g.nchunk, 1024, 0, s>>>(w.hist, g.H, g.P, g.nbins, w.csum);
-    bin_plan_kernel<<<1, 1024, 0, s>>>(w.hist, w.csum, g.nchunk, g.nbins, g.P, w.chunk_first, w.chunk_info);
-    if (plan_only) return launch_status();
-  }
-  bin_scatter_kernel<<<g.P, kBinBlock, cnt_lds, s>>>(grad_feat, xc, bone, S, S_dev, ld, l0, l1 - l0, log2T, g.tb, lv,
-                                                     box, w.hist, w.csum, w.rec, (uint32_t)g.rmax);
-  if (overwrite)
-    bin_clear_split_kernel<<<g.nbins < 1024 ? g.nbins : 1024, 256, 0, s>>>(w.chunk_first, g.nbins, l0, log2T, g.tb,
-                                                                           grad_table);
-  const unsigned acc_grid = (unsigned)(g.qmax < kAccMaxGrid ? g.qmax : kAccMaxGrid);
-  bin_accum_kernel<<<acc_grid, kAccBlock, sizeof(unsigned long long) * 2 * ((size_t)1 << g.tb), s>>>(
-      w.rec, w.chunk_first, w.chunk_info, g.nbins, (uint32_t)g.qmax, (uint32_t)g.rmax, l0, log2T, g.tb, overwrite,
-      grad_table);
+  bin_geom(nl, S, log2T, &g);  // fewer levels than `full`: fits its workspace
+  const BinWs w = bin_ws(nl, S, g, ws);
+  const size_t cnt_lds = sizeof(uint32_t) * ((size_t)1 << g.tpl_log2);  // at most 64 KB
+  // the blocks loop over the chunks; with a device count the grid is bounded
+  int64_t per_level = g.chunks < 4096 ? g.chunks : 4096;
+  if (S_dev && per_level > 64) per_level = 64;
+  bin_sort_kernel<<<(unsigned)(nl * per_level), kSortBlock, cnt_lds, s>>>(grad_feat, xc, bone, S, S_dev, ld, l0, nl,
+                                                                          log2T, g.tb, lv, box, g.chunks, w.queue,
+                                                                          w.runs, w.rec);
+  bin_plan_kernel<<<(unsigned)ceil_div((int64_t)nl << g.tpl_log2, kPlanBlock / kWave), kPlanBlock, 0, s>>>(
+      w.runs, S, S_dev, g.chunks, l0, nl, log2T, g.tb, overwrite, w.cap, w.queue, w.items, grad_table);
+  bin_accum_kernel<<<kAccMaxGrid, kAccBlock, sizeof(unsigned long long) * 2 * ((size_t)1 << g.tb), s>>>(
+      w.queue, w.items, w.cap, w.runs, w.rec, S, S_dev, g.chunks, l0, log2T, g.tb, overwrite, grad_table);
   return launch_status();
 }

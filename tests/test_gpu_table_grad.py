@@ -304,3 +304,54 @@ def test_table_grad_binned_mixed_magnitudes(orc, small):
     below = shared & dense & (small < m_ent * 2.0 ** -48)  # every record of the entry is below m 2^-48
     if small < 1e-15:
         assert below.any() and (got[below] == 0).all() and (atom[below] != 0).all()
+
+
+@pytest.mark.parametrize("log2T,L,S,count,overwrite", [
+    (19, 10, 5003, None, True),    # pairs that a tile boundary separates, one of them NaN
+    (13, 10, 1281, 1280, False),   # one full sort chunk of two
+    (14, 2, 330001, None, True),   # more than 256 chunks, most records in one split tile
+    (14, 2, 330001, 163840, False),
+    (19, 10, 5003, 0, True)])
+def test_table_grad_binned_sort_chunks(orc, log2T, L, S, count, overwrite):
+    """Edges of the sort's chunks, the runs' batches and the work items.
+    The resolutions are powers of two and the positions multiples of 2^-20, so
+    cell fractions and weights are exact in FP32: a value is within
+    4 roundings, and an entry's sum within one more per window and work item
+    (at most 8 S / 4096 plus one per chunk), each 2^-24 of the sum of its
+    terms' magnitudes."""
+    K = _K()
+    rng = np.random.default_rng(7)
+    x = rng.integers(0, 1 << 20, size=(S, 3)).astype(np.float64) / (1 << 20)
+    x[::3, 0] = 0.5 - rng.integers(1, 1 << 7, size=len(x[::3])) / (1 << 20)  # cell 4095 of 8192, as of all halves
+    if S > 100000:  # a corner of the box: the first tile of both levels
+        x[S // 7:] /= 16.0
+    x = np.round(x * (1 << 20)) / (1 << 20)
+    gfeat = rng.normal(size=(S, 2 * L)).astype(np.float32)
+    bone = np.where(np.arange(S) % 13 == 4, -1, 0).astype(np.int16)
+    n = S if count is None else count
+    if n > 3:
+        gfeat[3, 2 * L - 1] = np.nan
+    start = 7.0 if overwrite else 0.0
+    gt = torch.full((L, 1 << log2T, 2), start, device=dev())
+    ws = torch.empty(K.hashgrid_table_grad_workspace_size(S, L, 1 << log2T), dtype=torch.uint8, device=dev())
+    gf = up(gfeat.reshape(S, L, 2).transpose(1, 0, 2).reshape(-1))
+    Sd = None if count is None else torch.tensor([count], dtype=torch.int64, device=dev())
+    K.hashgrid_table_grad(gf, soa(x, S), up(bone), S, S, 16.0, 2.0, AABB, gt, ws, K.OVERWRITE if overwrite else 0,
+                          S_dev=Sd)
+    torch.cuda.synchronize()
+    got = host(gt)
+    if n == 0:
+        assert (got == 0).all()
+        return
+    table, res = np.zeros((L, 1 << log2T, 2), np.float32), [16 << k for k in range(L)]
+    args = (x[:n], table, res, AABB_NP)
+    clean = np.nan_to_num(gfeat[:n])
+    ref, _ = orc.hash_encode_bwd(gfeat[:n], *args, valid=bone[:n])
+    fin, _ = orc.hash_encode_bwd(clean, *args, valid=bone[:n])
+    mag, _ = orc.hash_encode_bwd(np.abs(clean), *args, valid=bone[:n])
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
+    err = np.where(np.isnan(ref), 0.0, np.abs(np.nan_to_num(got) - fin))
+    adds = 4 + 8 * n // 4096 + (n + 1279) // 1280
+    tol = adds * 2.0 ** -24 * mag + 8 * n * 2.0 ** -47 * np.abs(clean).max()
+    assert (err <= tol).all(), f"worst {(err / tol).max():.2f} of the bound"
+    print(f"worst {(err[tol > 0] / tol[tol > 0]).max():.3f} of the bound ({adds} roundings)")
