@@ -474,37 +474,79 @@ __global__ void __launch_bounds__(kBwdBlock) mlp_bwd_f32(const float *__restrict
 
 // --------------------------------------------------------------- BF16 bwd
 // Same algebra as the FP32 backward, on BF16 MFMA 16x16x32 (FP32
-// accumulate).  A wave owns a 32-sample tile: two 16-sample sub-tiles run
-// the BF16 forward and the chained backward (gh1 = W2^T d2, gfeat = W1^T d1
-// with transposed weight fragments; the 4-wide head gh2 = W3^T d3 on FP32
-// MFMA), then the weight gradients take K = 32 samples per MFMA from
-// [neuron][sample] BF16 tiles in LDS.
-constexpr int LDB = 40;  // BF16 row stride of the sample tiles (32 + 8 pad)
+// accumulate).  Each of a workgroup's four waves takes 16 of its 64 samples
+// through the forward and the deltas; then the waves share the weight
+// gradients, wave w the rows of neurons 16w .. 16w + 15, with K = the 64
+// samples from [neuron][sample] tiles in LDS.  So a wave holds 28 accumulator
+// registers, not 112, and two fit a SIMD without moves to and from the
+// accumulation registers.  An MFMA with its operands exchanged gives the
+// transposed product from the same registers, out[sample 4g + i][neuron r] in
+// place of out[neuron 4g + i][sample r]: each layer is computed in both, the
+// first for the next layer, the second, four samples to a lane, for 8-byte
+// stores to those tiles.
+// 262,143 samples: 36 us.  A wave alone on a SIMD with every accumulator, 2-byte
+// stores to its own tiles and loads at their use took 75 us: 6 of preparing
+// weights, 7 us per 32 samples and 6 of adding the waves.
+constexpr int kBfBlock = 256, kBfWaves = kBfBlock / 64;
+constexpr int kBfSamples = 16 * kBfWaves;  // per block and step
+constexpr int LDB = kBfSamples + 8;        // row stride of the sample tiles
 constexpr int BR_X = 0, BR_H1 = 32, BR_H2 = 96, BR_D2 = 160, BR_D1 = 224, BR_D3 = 288, BR_ROWS = 292;
-constexpr int SCRB_BYTES = BR_ROWS * LDB * 2;
-constexpr int LDS_BF_BYTES = kBwdWaves * SCRB_BYTES;
-static_assert(LDS_BF_BYTES >= NPARAM * 4, "block partial reuses the scratch region");
-static_assert(LDS_BF_BYTES <= 65536, "one workgroup's LDS");
+// LDS copy of the parameters, rows padded so that the lanes (r, g) of a
+// fragment read distinct banks along rows and along columns
+constexpr int PW1 = 36, PW2 = 68, PW3 = 80;
+constexpr int PO_W1 = 0, PO_W2 = PO_W1 + NH * PW1, PO_W3 = PO_W2 + NH * PW2, PO_B1 = PO_W3 + NOUT * PW3,
+              PO_B2 = PO_B1 + NH, PO_B3 = PO_B2 + NH, PO_SIZE = PO_B3 + NOUT;
 
-struct FragBfT {
-  bf16x8 w2t[4][2];  // [mt][c]: W2[16(2c + j/4) + 4g + j%4][16mt + r]
-  bf16x8 w1t[2][2];  // [mt][c]: W1[16(2c + j/4) + 4g + j%4][16mt + r]
-  float w3t[4];      // [mt]: W3[g][16mt + r]
+struct BfBwdLds {
+  union {
+    float p[PO_SIZE];
+    __bf16 t[BR_ROWS * LDB];
+  };
+  // fragments 2 mt + c of W2's transpose, 8 + 2 mt + c of W1's, 12 + mt of W1
+  // (in registers all of them would not leave room for two waves on a SIMD)
+  bf16x8 w[16][64];
+  float b1[NH], b2[NH];
+  float bias[kBfWaves][9][16];
 };
 
-__device__ __forceinline__ void load_frag_bft(const float *P, int r, int g, FragBfT &f) {
+__device__ __forceinline__ void stage_padded(const float *__restrict__ P, float *p) {
+  const float4 *P4 = reinterpret_cast<const float4 *>(P);
+  constexpr int kPer = (NPARAM / 4 + kBfBlock - 1) / kBfBlock, kLast = NPARAM / 4 - 1;
+  float4 v[kPer];
+  // every load in flight before the first is used; threads past the end copy
+  // the last group again
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int k = 0; k < kPer; ++k) {
+    const int e = threadIdx.x + k * kBfBlock;
+    v[k] = P4[e < kLast ? e : kLast];
+  }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int k = 16 * (2 * c + j / 4) + 4 * g + (j % 4);
+  for (int k = 0; k < kPer; ++k) asm volatile("" : "+v"(v[k].x), "+v"(v[k].y), "+v"(v[k].z), "+v"(v[k].w));
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) f.w2t[mt][c][j] = (__bf16)P[OFF_W2 + k * NH + 16 * mt + r];
+  for (int k = 0; k < kPer; ++k) {
+    const int e = threadIdx.x + k * kBfBlock, i = 4 * (e < kLast ? e : kLast);
+    int o = PO_B3 + i - OFF_B3;
+    o = i < OFF_B3 ? PO_W3 + ((i - OFF_W3) / NH) * PW3 + (i - OFF_W3) % NH : o;
+    o = i < OFF_W3 ? PO_B2 + i - OFF_B2 : o;
+    o = i < OFF_B2 ? PO_W2 + ((i - OFF_W2) / NH) * PW2 + (i - OFF_W2) % NH : o;
+    o = i < OFF_W2 ? PO_B1 + i - OFF_B1 : o;
+    o = i < OFF_B1 ? PO_W1 + (i / NIN) * PW1 + i % NIN : o;
+    *reinterpret_cast<float4 *>(p + o) = v[k];
+  }
+}
+
+__device__ __forceinline__ f32x4 splat(float v) { return f32x4{v, v, v, v}; }
+
+// Eight parameters, four each from p and q, as BF16.
+__device__ __forceinline__ bf16x8 bf_halves(const float *p, const float *q) {
+  const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(q);
+  bf16x8 v;
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) f.w1t[mt][c][j] = (__bf16)P[OFF_W1 + k * NIN + 16 * mt + r];
-    }
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) f.w3t[mt] = (float)(__bf16)P[OFF_W3 + g * NH + 16 * mt + r];
+  for (int j = 0; j < 4; ++j) {
+    v[j] = (__bf16)a[j];
+    v[4 + j] = (__bf16)b[j];
+  }
+  return v;
 }
 
 __device__ __forceinline__ bf16x8 pack_raw(const f32x4 z[4], int c) {
@@ -514,203 +556,247 @@ __device__ __forceinline__ bf16x8 pack_raw(const f32x4 z[4], int c) {
   return b;
 }
 
-__device__ __forceinline__ bf16x8 lds_row8(const __bf16 *scr, int row, int col) {
-  return *reinterpret_cast<const bf16x8 *>(scr + row * LDB + col);
+// The inputs of a 16-sample half tile for lane (r, g): loaded for a valid
+// sample index in any case, so that nothing branches around the loads.
+struct BfIn {
+  uint32_t x[4];  // levels 4g .. 4g + 3 of sample r
+  float go;       // gradient of output g of sample r
+  int bone;
+};
+
+template <bool kBone>
+__device__ __forceinline__ void load_half(const uint32_t *feat, const float *go, const int16_t *bone, int64_t S,
+                                          int64_t ld, int64_t s, int g, BfIn &in) {
+  s = s < S ? s : S - 1;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) in.x[j] = feat[(int64_t)(4 * g + j) * ld + s];
+  in.go = go[s];
+  in.bone = kBone ? bone[s] : 0;
 }
 
-__global__ void __launch_bounds__(kBwdBlock) mlp_bwd_bf16(const float *__restrict__ gsig,
-                                                          const float *__restrict__ grgb,
-                                                          const __hip_bfloat16 *__restrict__ feat,
-                                                          const int16_t *__restrict__ bone, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
-                                                          const float *__restrict__ P, float *__restrict__ gfeat,
-                                                          float *__restrict__ partial) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
-  // the forward's fragments stay in LDS (read as each MFMA needs them); held
-  // in registers beside the weight-gradient accumulators they spill
-  __shared__ __attribute__((aligned(16))) FragLds sF;
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, wid = threadIdx.x >> 6;
-  __bf16 *scr = reinterpret_cast<__bf16 *>(ldsb + wid * SCRB_BYTES);
-  stage_frag_lds(P, sF);
-  // the parameters go to the scratch region until every wave holds its
-  // transposed fragments
-  float *sP = reinterpret_cast<float *>(ldsb);
-  stage_params(P, sP);
+// Values of four consecutive samples of a neuron, as BF16.
+__device__ __forceinline__ void store_row4(__bf16 *t, int row, int col, const f32x4 &v) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  bf16x4 b;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = (__bf16)v[i];
+  *reinterpret_cast<bf16x4 *>(t + row * LDB + col) = b;
+}
+
+__device__ __forceinline__ bf16x8 lds_row8(const __bf16 *t, int row, int col) {
+  return *reinterpret_cast<const bf16x8 *>(t + row * LDB + col);
+}
+
+template <bool kBone>
+__global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restrict__ gsig,
+                                                            const float *__restrict__ grgb,
+                                                            const __hip_bfloat16 *__restrict__ featb,
+                                                            const int16_t *__restrict__ bone, int64_t S,
+                                                            const int64_t *__restrict__ S_dev, int64_t ld,
+                                                            const float *__restrict__ P, float *__restrict__ gfeat,
+                                                            float *__restrict__ partial) {
+  __shared__ __attribute__((aligned(16))) BfBwdLds lds;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const uint32_t *feat = reinterpret_cast<const uint32_t *>(featb);
+  S = count_of(S, S_dev);
+  const int64_t step = (int64_t)gridDim.x * kBfSamples;
+  const float *go = g == 0 ? gsig : grgb + (g - 1) * ld;
+  int64_t s0 = (int64_t)blockIdx.x * kBfSamples + 16 * wid;
+  BfIn in = {};
+  if (S > 0) load_half<kBone>(feat, go, bone, S, ld, s0 + r, g, in);
+  stage_padded(P, lds.p);
   __syncthreads();
-  FragBfT ft;
-  load_frag_bft(sP, r, g, ft);
-  __syncthreads();
-  f32x4 aW1[4][2], aW2[4][4], aW3[4];
-  float ab1[4][4], ab2[4][4], ab3[4];
+  const float *p = lds.p;
+  bf16x8 w2[4][2], w3[2];
+  float w3t[4], b1t[4], b2t[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const float *q2 = p + PO_W2 + (16 * mt + r) * PW2 + 32 * c + 4 * g;
+      w2[mt][c] = bf_halves(q2, q2 + 16);
+    }
+    b1t[mt] = p[PO_B1 + 16 * mt + r];
+    b2t[mt] = p[PO_B2 + 16 * mt + r];
+    w3t[mt] = (float)(__bf16)p[PO_W3 + g * PW3 + 16 * mt + r];
+  }
+  // rows 4k of the last layer's operand are W3's, the others zero, so that lane
+  // (r, g) gets output g of sample r
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const float *q3 = p + PO_W3 + (r >> 2) * PW3 + 32 * c + 4 * g;
+    const bf16x8 v = bf_halves(q3, q3 + 16), zero = {};
+    w3[c] = (r & 3) == 0 ? v : zero;
+  }
+  const float b3 = p[PO_B3 + g];
+  // the fragments in LDS, a quarter by each wave:
+  // [16(2c + j/4) + 4g + j%4][16mt + r] of W2, W1; W1[16mt + r][8g + j]
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int q = kBfWaves * k + wid, mt = (q & 7) >> 1, c = q & 1;
+    const float *col = p + (k < 2 ? PO_W2 : PO_W1) + 16 * mt + r;
+    bf16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = (__bf16)col[(16 * (2 * c + j / 4) + 4 * g + (j % 4)) * (k < 2 ? PW2 : PW1)];
+    lds.w[q][lane] = v;
+  }
+  const float *q1 = p + PO_W1 + (16 * wid + r) * PW1 + 8 * g;
+  lds.w[12 + wid][lane] = bf_halves(q1, q1 + 4);
+  if (threadIdx.x < 2 * NH) (threadIdx.x < NH ? lds.b1 : lds.b2 - NH)[threadIdx.x] = p[PO_B1 + threadIdx.x];
+  __syncthreads();  // the tiles take the parameters' place
+  f32x4 aW1[2], aW2[4], aW3 = splat(0.0f);
+  float ab1[4], ab2[4], ab3 = 0.0f;
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
-    aW3[a] = f32x4{0, 0, 0, 0};
-    ab3[a] = 0.0f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      aW2[a][b] = f32x4{0, 0, 0, 0};
-      ab1[a][b] = 0.0f;
-      ab2[a][b] = 0.0f;
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) aW1[a][b] = f32x4{0, 0, 0, 0};
+    ab1[a] = ab2[a] = 0.0f;
+    aW2[a] = splat(0.0f);
+    if (a < 2) aW1[a] = splat(0.0f);
   }
-  S = count_of(S, S_dev);
-  const int64_t ntile = ceil_div(S, 32);
-  const int64_t wstride = (int64_t)gridDim.x * kBwdWaves;
-  for (int64_t tile = (int64_t)blockIdx.x * kBwdWaves + wid; tile < ntile; tile += wstride) {
+  const int col = 16 * wid + 4 * g;  // of the transposed products' samples
+  for (int64_t b0 = (int64_t)blockIdx.x * kBfSamples; b0 < S; b0 += step, s0 += step) {  // uniform in the block
+    const int64_t s = s0 + r;
+    const bool ok = s < S, use = ok && (!kBone || in.bone >= 0);
+    bf16x8 X;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int col = 16 * half + r;
-      const int64_t s = tile * 32 + col;
-      const bool ok = s < S;
-      const bf16x8 X = load_x_bf16(feat, ld, s, g, ok);
-      f32x4 z1[4], z2[4], o;
-      pin_in_loop();
-      fwd_bf_src(LdsW{sF, lane, g}, X, z1, z2, o);
-      float d3[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (g == 0 && ok && (!bone || bone[s] >= 0)) {
-        const float ov[4] = {o[0], o[1], o[2], o[3]};
-        float sg, c[3];
-        head(ov, &sg, c);
-        d3[0] = ov[0] < 80.0f ? gsig[s] * sg : 0.0f;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) d3[1 + k] = grgb[k * ld + s] * c[k] * (1.0f - c[k]);
-      }
-      // the 4-wide head runs on FP32 MFMA with BF16-valued operands (the
-      // forward's W3, the output delta as stored for the weight gradient)
-      float b3 = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float t = __shfl(d3[k], r, 64);
-        b3 = (g == k) ? (float)(__bf16)t : b3;
-      }
-      f32x4 d2[4], d1[4];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        f32x4 acc = mfma4(ft.w3t[mt], b3, f32x4{0, 0, 0, 0});
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[i] = z2[mt][i] < 0.0f ? 0.0f : acc[i];
-          ab2[mt][i] += acc[i];
-        }
-        d2[mt] = acc;
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) ab3[i] += (g == 0) ? d3[i] : 0.0f;
-      const bf16x8 d2a = pack_raw(d2, 0), d2b = pack_raw(d2, 1);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        f32x4 acc = mfma32(ft.w2t[mt][0], d2a, f32x4{0, 0, 0, 0});
-        acc = mfma32(ft.w2t[mt][1], d2b, acc);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          acc[i] = z1[mt][i] < 0.0f ? 0.0f : acc[i];
-          ab1[mt][i] += acc[i];
-        }
-        d1[mt] = acc;
-      }
-      if (gfeat) {
-        const bf16x8 d1a = pack_raw(d1, 0), d1b = pack_raw(d1, 1);
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          f32x4 acc = mfma32(ft.w1t[mt][0], d1a, f32x4{0, 0, 0, 0});
-          acc = mfma32(ft.w1t[mt][1], d1b, acc);
-          if (ok) {
-            float2 *gf = reinterpret_cast<float2 *>(gfeat);
-            gf[(int64_t)(8 * mt + 2 * g) * ld + s] = make_float2(acc[0], acc[1]);
-            gf[(int64_t)(8 * mt + 2 * g + 1) * ld + s] = make_float2(acc[2], acc[3]);
-          }
-        }
-      }
-      // [neuron][sample] tiles for the weight gradients
-#pragma unroll
-      for (int j = 0; j < 8; ++j) scr[(BR_X + 8 * g + j) * LDB + col] = X[j];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int n = 16 * t + 4 * g + i;
-          scr[(BR_H1 + n) * LDB + col] = (__bf16)relu(z1[t][i]);
-          scr[(BR_H2 + n) * LDB + col] = (__bf16)relu(z2[t][i]);
-          scr[(BR_D2 + n) * LDB + col] = (__bf16)d2[t][i];
-          scr[(BR_D1 + n) * LDB + col] = (__bf16)d1[t][i];
-        }
-      if (g == 0)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) scr[(BR_D3 + k) * LDB + col] = (__bf16)d3[k];
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t v = ok ? in.x[j] : 0u;
+      X[2 * j] = __builtin_bit_cast(__bf16, (uint16_t)(v & 0xffffu));
+      X[2 * j + 1] = __builtin_bit_cast(__bf16, (uint16_t)(v >> 16));
+      lds.t[(BR_X + 8 * g + 2 * j) * LDB + 16 * wid + r] = X[2 * j];
+      lds.t[(BR_X + 8 * g + 2 * j + 1) * LDB + 16 * wid + r] = X[2 * j + 1];
     }
-    wave_sync();
-    // weight gradients, K = the tile's 32 samples
-    const bf16x8 zero8 = {};
+    const float go_s = in.go;
+    // the next step's inputs (after the last: the last sample's again)
+    load_half<kBone>(feat, go, bone, S, ld, s + step, g, in);
+    // pre-activations and their transposes
+    f32x4 z1[4], y1[4], z2[4], y2[4];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const bf16x8 bh1 = lds_row8(scr, BR_H1 + 16 * nt + r, 8 * g);
-      const bf16x8 bh2 = lds_row8(scr, BR_H2 + 16 * nt + r, 8 * g);
-      const bf16x8 a3 = r < NOUT ? lds_row8(scr, BR_D3 + r, 8 * g) : zero8;
-      aW3[nt] = mfma32(a3, bh2, aW3[nt]);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) aW2[mt][nt] = mfma32(lds_row8(scr, BR_D2 + 16 * mt + r, 8 * g), bh1, aW2[mt][nt]);
+    for (int mt = 0; mt < 4; ++mt) {
+      const bf16x8 w1 = lds.w[12 + mt][lane];
+      z1[mt] = mfma32(w1, X, *reinterpret_cast<const f32x4 *>(lds.b1 + 16 * mt + 4 * g));
+      y1[mt] = mfma32(X, w1, splat(b1t[mt]));
     }
+    const bf16x8 h1a = pack_act(z1, 0), h1b = pack_act(z1, 1);
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const bf16x8 bx = lds_row8(scr, BR_X + 16 * nt + r, 8 * g);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) aW1[mt][nt] = mfma32(lds_row8(scr, BR_D1 + 16 * mt + r, 8 * g), bx, aW1[mt][nt]);
+    for (int mt = 0; mt < 4; ++mt) {
+      z2[mt] = mfma32(w2[mt][0], h1a, *reinterpret_cast<const f32x4 *>(lds.b2 + 16 * mt + 4 * g));
+      z2[mt] = mfma32(w2[mt][1], h1b, z2[mt]);
+      y2[mt] = mfma32(h1b, w2[mt][1], mfma32(h1a, w2[mt][0], splat(b2t[mt])));
     }
-    wave_sync();
-  }
+    f32x4 oa = {b3, 0.0f, 0.0f, 0.0f};
+    oa = mfma32(w3[0], pack_act(z2, 0), oa);
+    oa = mfma32(w3[1], pack_act(z2, 1), oa);
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int mt = 0; mt < 4; ++mt) {
+      f32x4 h1, h2;
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) {
-        ab1[a][b] += __shfl_xor(ab1[a][b], o, 16);
-        ab2[a][b] += __shfl_xor(ab2[a][b], o, 16);
+      for (int i = 0; i < 4; ++i) {
+        h1[i] = relu(y1[mt][i]);
+        h2[i] = relu(y2[mt][i]);
       }
+      store_row4(lds.t, BR_H1 + 16 * mt + r, col, h1);
+      store_row4(lds.t, BR_H2 + 16 * mt + r, col, h2);
+    }
+    // the gradient of output g of sample r
+    const float o = oa[0], e = expf(g == 0 ? fminf(o, 80.0f) : -o), c = __builtin_amdgcn_rcpf(1.0f + e);
+    float d3 = g == 0 ? (o < 80.0f ? go_s * e : 0.0f) : go_s * c * (1.0f - c);
+    d3 = use ? d3 : 0.0f;
+    ab3 += d3;
+    lds.t[(BR_D3 + g) * LDB + 16 * wid + r] = (__bf16)d3;
+    // the 4-wide head runs on FP32 MFMA with BF16-valued operands (the
+    // forward's W3, the output delta as stored for the weight gradient)
+    const float d3b = (float)(__bf16)d3;
+    f32x4 d2[4], e2[4], d1[4], e1[4];  // deltas and their transposes
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+    for (int mt = 0; mt < 4; ++mt) {
+      d2[mt] = mfma4(w3t[mt], d3b, splat(0.0f));
+      e2[mt] = mfma4(d3b, w3t[mt], splat(0.0f));
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) ab3[a] += __shfl_xor(ab3[a], o, 16);
-  __syncthreads();
-  float *bp = reinterpret_cast<float *>(ldsb);
-  for (int w = 0; w < kBwdWaves; ++w) {
-    if (wid == w) {
+      for (int i = 0; i < 4; ++i) {
+        d2[mt][i] = z2[mt][i] < 0.0f ? 0.0f : d2[mt][i];
+        e2[mt][i] = y2[mt][i] < 0.0f ? 0.0f : e2[mt][i];
+        ab2[mt] += e2[mt][i];
+      }
+      store_row4(lds.t, BR_D2 + 16 * mt + r, col, e2[mt]);
+    }
+    const bf16x8 d2a = pack_raw(d2, 0), d2b = pack_raw(d2, 1);
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt) {
+      const bf16x8 wa = lds.w[2 * mt][lane], wb = lds.w[2 * mt + 1][lane];
+      d1[mt] = mfma32(wb, d2b, mfma32(wa, d2a, splat(0.0f)));
+      e1[mt] = mfma32(d2b, wb, mfma32(d2a, wa, splat(0.0f)));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int m = 16 * mt + 4 * g + i;
+      for (int i = 0; i < 4; ++i) {
+        d1[mt][i] = z1[mt][i] < 0.0f ? 0.0f : d1[mt][i];
+        e1[mt][i] = y1[mt][i] < 0.0f ? 0.0f : e1[mt][i];
+        ab1[mt] += e1[mt][i];
+      }
+      store_row4(lds.t, BR_D1 + 16 * mt + r, col, e1[mt]);
+    }
+    if (gfeat) {
+      const bf16x8 d1a = pack_raw(d1, 0), d1b = pack_raw(d1, 1);
 #pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            const int e = OFF_W1 + m * NIN + 16 * nt + r;
-            bp[e] = (w ? bp[e] : 0.0f) + aW1[mt][nt][i];
-          }
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            const int e = OFF_W2 + m * NH + 16 * nt + r;
-            bp[e] = (w ? bp[e] : 0.0f) + aW2[mt][nt][i];
-          }
-          if (r == 0) {
-            bp[OFF_B1 + m] = (w ? bp[OFF_B1 + m] : 0.0f) + ab1[mt][i];
-            bp[OFF_B2 + m] = (w ? bp[OFF_B2 + m] : 0.0f) + ab2[mt][i];
-          }
-        }
-      if (g == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            const int e = OFF_W3 + i * NH + 16 * nt + r;
-            bp[e] = (w ? bp[e] : 0.0f) + aW3[nt][i];
-          }
-          if (r == 0) bp[OFF_B3 + i] = (w ? bp[OFF_B3 + i] : 0.0f) + ab3[i];
+      for (int mt = 0; mt < 2; ++mt) {
+        const f32x4 acc = mfma32(lds.w[9 + 2 * mt][lane], d1b, mfma32(lds.w[8 + 2 * mt][lane], d1a, splat(0.0f)));
+        if (ok) {
+          float2 *gf = reinterpret_cast<float2 *>(gfeat);
+          gf[(int64_t)(8 * mt + 2 * g) * ld + s] = make_float2(acc[0], acc[1]);
+          gf[(int64_t)(8 * mt + 2 * g + 1) * ld + s] = make_float2(acc[2], acc[3]);
         }
       }
     }
     __syncthreads();
+    // weight gradients of this wave's rows, K = the block's samples
+#pragma unroll
+    for (int k = 0; k < kBfSamples / 32; ++k) {
+      const int at = 32 * k + 8 * g;
+      const bf16x8 zero = {}, v3 = lds_row8(lds.t, BR_D3 + (r & 3), at);
+      aW3 = mfma32(r < NOUT ? v3 : zero, lds_row8(lds.t, BR_H2 + 16 * wid + r, at), aW3);
+      const bf16x8 v2 = lds_row8(lds.t, BR_D2 + 16 * wid + r, at), v1 = lds_row8(lds.t, BR_D1 + 16 * wid + r, at);
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt) aW2[nt] = mfma32(v2, lds_row8(lds.t, BR_H1 + 16 * nt + r, at), aW2[nt]);
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) aW1[nt] = mfma32(v1, lds_row8(lds.t, BR_X + 16 * nt + r, at), aW1[nt]);
+    }
+    __syncthreads();  // the tiles are written again
   }
-  for (int e = threadIdx.x; e < NPARAM; e += kBwdBlock) partial[(int64_t)blockIdx.x * NPARAM + e] = bp[e];
+  // the block's partial: the weights as they are, the biases over the waves in
+  // order (within a wave over the sample groups g, the last layer's over r)
+#pragma unroll
+  for (int k = 8; k > 0; k >>= 1) ab3 += __shfl_xor(ab3, k, 16);
+#pragma unroll
+  for (int k = 16; k < 64; k <<= 1)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      ab1[a] += __shfl_xor(ab1[a], k, 64);
+      ab2[a] += __shfl_xor(ab2[a], k, 64);
+    }
+  if (g == 0)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      lds.bias[wid][a][r] = ab1[a];
+      lds.bias[wid][4 + a][r] = ab2[a];
+    }
+  if (r == 0) lds.bias[wid][8][g] = ab3;
+  float *out = partial + (int64_t)blockIdx.x * NPARAM;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = 16 * wid + 4 * g + i;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) out[OFF_W2 + m * NH + 16 * nt + r] = aW2[nt][i];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) out[OFF_W1 + m * NIN + 16 * nt + r] = aW1[nt][i];
+    if (g == 0) out[OFF_W3 + i * NH + 16 * wid + r] = aW3[i];
+  }
+  __syncthreads();
+  const int a = threadIdx.x / 16, q = threadIdx.x % 16;
+  if (a < 8 || (a == 8 && q < NOUT)) {
+    float v = lds.bias[0][a][q];
+#pragma unroll
+    for (int w = 1; w < kBfWaves; ++w) v += lds.bias[w][a][q];
+    out[a == 8 ? OFF_B3 + q : (a < 4 ? OFF_B1 : OFF_B2) + 16 * (a % 4) + q] = v;
+  }
 }
 
 // Sum of the block partials per parameter: 64 parameters x 16 partial groups
@@ -749,6 +835,12 @@ int bwd_blocks(int64_t S) {
   int64_t b = ceil_div(ceil_div(S, 16), kBwdWaves);
   if (b > kMaxBwdBlocks) b = kMaxBwdBlocks;
   return b < 1 ? 1 : (int)b;
+}
+
+// two workgroups per CU; never more than bwd_blocks, which sizes the workspace
+int bf_bwd_blocks(int64_t S) {
+  const int64_t b = ceil_div(S, (int64_t)kBfSamples);
+  return b > kMaxBwdBlocks ? kMaxBwdBlocks : (int)b;
 }
 
 // as many blocks as stay resident (2 waves per SIMD by registers): each
@@ -813,13 +905,13 @@ extern "C" int32_t ia355_mlp_bwd(const float *grad_sigma, const float *grad_rgb,
   if (S == 0) return (flags & IA355_OVERWRITE) ? ia355_zero(grad_params, sizeof(float) * NPARAM, stream) : IA355_OK;
   if (!ws || ws_bytes < ia355_mlp_bwd_workspace_size(S)) return IA355_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
-  const int nb = bwd_blocks(S);
+  const int nb = dtype == IA355_F32 ? bwd_blocks(S) : bf_bwd_blocks(S);
   if (dtype == IA355_F32)
     mlp_bwd_f32<<<nb, kBwdBlock, LDS_FLOATS * sizeof(float), s>>>(grad_sigma, grad_rgb, (const float *)feat, bone, S,
                                                                   S_dev, ld, params, grad_feat, (float *)ws);
   else
-    mlp_bwd_bf16<<<nb, kBwdBlock, LDS_BF_BYTES, s>>>(grad_sigma, grad_rgb, (const __hip_bfloat16 *)feat, bone, S,
-                                                     S_dev, ld, params, grad_feat, (float *)ws);
+    (bone ? mlp_bwd_bf16<true> : mlp_bwd_bf16<false>)<<<nb, kBfBlock, 0, s>>>(
+        grad_sigma, grad_rgb, (const __hip_bfloat16 *)feat, bone, S, S_dev, ld, params, grad_feat, (float *)ws);
   reduce_partials<<<(unsigned)ceil_div(NPARAM, kRedP), kRedP * kRedG, 0, s>>>((const float *)ws, nb, grad_params,
                                                                                      (flags & IA355_OVERWRITE) != 0);
   return launch_status();
