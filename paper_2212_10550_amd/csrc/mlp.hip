@@ -215,316 +215,44 @@ __global__ void __launch_bounds__(kFwdBlock, 4) mlp_fwd_bf16(const __hip_bfloat1
   }
 }
 
-// --------------------------------------------------------------- FP32 bwd
-// Per 16-sample tile (one wave): recompute the forward, then
+// --------------------------------------------------------------- backward
+// Per sample: recompute the forward, then
 //   d3 = dL/do (exp / sigmoid heads), gh2 = W3^T d3, d2 = gh2 * [z2 >= 0],
 //   gh1 = W2^T d2, d1 = gh1 * [z1 >= 0], gfeat = W1^T d1,
 //   dW3 += d3 h2^T, dW2 += d2 h1^T, dW1 += d1 x^T, db += sum d.
-// The transposed products chain in registers like the forward; the weight
-// gradients (K = samples) read tiles transposed through a per-wave LDS
-// scratch.  Block partials are reduced in a fixed order.
-constexpr int kBwdWaves = 2;
-constexpr int kBwdBlock = 64 * kBwdWaves;
-constexpr int LDP = 17;  // padded sample stride of the scratch tiles
-constexpr int SCR_X = 0, SCR_H1 = SCR_X + 32 * LDP, SCR_H2 = SCR_H1 + 64 * LDP, SCR_D = SCR_H2 + 64 * LDP,
-              SCR_D3 = SCR_D + 64 * LDP, SCR_SIZE = SCR_D3 + 4 * LDP;
-// transposed-weight fragments in LDS, stored lane-contiguous: [mfma][lane]
-constexpr int FT3 = 0;                 // 4 mfma   : W3[g][16mt + r]
-constexpr int FT2 = FT3 + 4 * 64;      // 64 mfma  : W2[16t + 4g + i][16mt + r]   (mt, 4t+i)
-constexpr int FT1 = FT2 + 64 * 64;     // 32 mfma  : W1[16t + 4g + i][16mt + r]   (mt in 0..1, 4t+i)
-constexpr int FT_SIZE = FT1 + 32 * 64;
-constexpr int LDS_FLOATS = FT_SIZE + kBwdWaves * SCR_SIZE;
-static_assert(kBwdWaves * SCR_SIZE >= NPARAM, "parameters and block partial use the scratch region");
-static_assert((FT_SIZE * 4) % 16 == 0, "16-byte aligned scratch region");
-static_assert(LDS_FLOATS * 4 <= 65536, "one workgroup's LDS");
-
-__global__ void __launch_bounds__(kBwdBlock) mlp_bwd_f32(const float *__restrict__ gsig, const float *__restrict__ grgb,
-                                                         const float *__restrict__ feat,
-                                                         const int16_t *__restrict__ bone, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
-                                                         const float *__restrict__ P, float *__restrict__ gfeat,
-                                                         float *__restrict__ partial) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, wid = threadIdx.x >> 6;
-  float *ft = lds;
-  float *scr = lds + FT_SIZE + wid * SCR_SIZE;
-  // the parameters go to the scratch region, which the tiles use only after
-  // the fragments are built
-  float *sP = lds + FT_SIZE;
-  stage_params(P, sP);
-  __syncthreads();
-  // transposed fragments, from the LDS copy
-  for (int e = threadIdx.x; e < FT_SIZE; e += kBwdBlock) {
-    const int L = e & 63, rr = L & 15, gg = L >> 4;
-    float v;
-    if (e < FT2) {
-      const int mt = e >> 6;
-      v = sP[OFF_W3 + gg * NH + 16 * mt + rr];
-    } else if (e < FT1) {
-      const int q = (e - FT2) >> 6, mt = q >> 4, ti = q & 15, t = ti >> 2, i = ti & 3;
-      v = sP[OFF_W2 + (16 * t + 4 * gg + i) * NH + 16 * mt + rr];
-    } else {
-      const int q = (e - FT1) >> 6, mt = q >> 4, ti = q & 15, t = ti >> 2, i = ti & 3;
-      v = sP[OFF_W1 + (16 * t + 4 * gg + i) * NIN + 16 * mt + rr];
-    }
-    ft[e] = v;
-  }
-  Frag32 f;
-  load_frag32(sP, r, g, f);
-  __syncthreads();  // every wave holds its fragments before the scratch is reused
-  f32x4 aW1[4][2], aW2[4][4], aW3[4];
-  float ab1[4][4], ab2[4][4], ab3[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    aW3[a] = f32x4{0, 0, 0, 0};
-    ab3[a] = 0.0f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      aW2[a][b] = f32x4{0, 0, 0, 0};
-      ab1[a][b] = 0.0f;
-      ab2[a][b] = 0.0f;
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) aW1[a][b] = f32x4{0, 0, 0, 0};
-  }
-  S = count_of(S, S_dev);
-  const int64_t ntile = ceil_div(S, 16);
-  const int64_t wstride = (int64_t)gridDim.x * kBwdWaves;
-  for (int64_t tile = (int64_t)blockIdx.x * kBwdWaves + wid; tile < ntile; tile += wstride) {
-    const int64_t s = tile * 16 + r;
-    const bool ok = s < S;
-    float X[8];
-    load_x(feat, ld, s, g, ok, X);
-    f32x4 z1[4], z2[4], o;
-    fwd32(f, X, z1, z2, o);
-    // output-head gradient (lanes g == 0 hold sample r's four outputs)
-    float d3[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (g == 0 && ok && (!bone || bone[s] >= 0)) {
-      const float ov[4] = {o[0], o[1], o[2], o[3]};
-      float sg, c[3];
-      head(ov, &sg, c);
-      d3[0] = ov[0] < 80.0f ? gsig[s] * sg : 0.0f;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) d3[1 + k] = grgb[k * ld + s] * c[k] * (1.0f - c[k]);
-    }
-    // scratch: x, h1, h2, d3 tiles [feature/neuron][sample]
-#pragma unroll
-    for (int c = 0; c < 8; ++c) scr[SCR_X + (8 * g + c) * LDP + r] = X[c];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        scr[SCR_H1 + (16 * t + 4 * g + i) * LDP + r] = relu(z1[t][i]);
-        scr[SCR_H2 + (16 * t + 4 * g + i) * LDP + r] = relu(z2[t][i]);
-      }
-    if (g == 0)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) scr[SCR_D3 + k * LDP + r] = d3[k];
-    // B operand of gh2 = W3^T d3: d3[output g][sample r]
-    float b3 = 0.0f;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float t = __shfl(d3[k], r, 64);
-      b3 = (g == k) ? t : b3;
-    }
-    f32x4 d2[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      f32x4 acc = mfma4(ft[FT3 + mt * 64 + lane], b3, f32x4{0, 0, 0, 0});
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[i] = z2[mt][i] < 0.0f ? 0.0f : acc[i];
-        ab2[mt][i] += acc[i];
-      }
-      d2[mt] = acc;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ab3[i] += (g == 0) ? d3[i] : 0.0f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) scr[SCR_D + (16 * t + 4 * g + i) * LDP + r] = d2[t][i];
-    wave_sync();
-    // dW3 += d3 h2^T ; dW2 += d2 h1^T   (K = 16 samples, 4 steps)
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float a3 = r < NOUT ? scr[SCR_D3 + r * LDP + 4 * c + g] : 0.0f;
-      float bh2[4], bh1[4];
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        bh2[nt] = scr[SCR_H2 + (16 * nt + r) * LDP + 4 * c + g];
-        bh1[nt] = scr[SCR_H1 + (16 * nt + r) * LDP + 4 * c + g];
-      }
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) aW3[nt] = mfma4(a3, bh2[nt], aW3[nt]);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const float ad = scr[SCR_D + (16 * mt + r) * LDP + 4 * c + g];
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) aW2[mt][nt] = mfma4(ad, bh1[nt], aW2[mt][nt]);
-      }
-    }
-    wave_sync();
-    // gh1 = W2^T d2 ; d1
-    f32x4 d1[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc = mfma4(ft[FT2 + (mt * 16 + 4 * t + i) * 64 + lane], d2[t][i], acc);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[i] = z1[mt][i] < 0.0f ? 0.0f : acc[i];
-        ab1[mt][i] += acc[i];
-      }
-      d1[mt] = acc;
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) scr[SCR_D + (16 * t + 4 * g + i) * LDP + r] = d1[t][i];
-    // gfeat = W1^T d1 -> feature 16mt + 4g + i = level 8mt + 2g + i/2, f = i%2
-    if (gfeat) {
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt) {
-        f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) acc = mfma4(ft[FT1 + (mt * 16 + 4 * t + i) * 64 + lane], d1[t][i], acc);
-        if (ok) {
-          float2 *gf = reinterpret_cast<float2 *>(gfeat);
-          gf[(int64_t)(8 * mt + 2 * g) * ld + s] = make_float2(acc[0], acc[1]);
-          gf[(int64_t)(8 * mt + 2 * g + 1) * ld + s] = make_float2(acc[2], acc[3]);
-        }
-      }
-    }
-    wave_sync();
-    // dW1 += d1 x^T
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float bx[2];
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) bx[nt] = scr[SCR_X + (16 * nt + r) * LDP + 4 * c + g];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const float ad = scr[SCR_D + (16 * mt + r) * LDP + 4 * c + g];
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) aW1[mt][nt] = mfma4(ad, bx[nt], aW1[mt][nt]);
-      }
-    }
-    wave_sync();
-  }
-  // bias partials: sum over the 16 sample lanes r
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) {
-        ab1[a][b] += __shfl_xor(ab1[a][b], o, 16);
-        ab2[a][b] += __shfl_xor(ab2[a][b], o, 16);
-      }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) ab3[a] += __shfl_xor(ab3[a], o, 16);
-  // block partial in the (now free) scratch region, waves added in order
-  __syncthreads();
-  float *bp = lds + FT_SIZE;
-  for (int w = 0; w < kBwdWaves; ++w) {
-    if (wid == w) {
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int m = 16 * mt + 4 * g + i;
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            const int e = OFF_W1 + m * NIN + 16 * nt + r;
-            bp[e] = (w ? bp[e] : 0.0f) + aW1[mt][nt][i];
-          }
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            const int e = OFF_W2 + m * NH + 16 * nt + r;
-            bp[e] = (w ? bp[e] : 0.0f) + aW2[mt][nt][i];
-          }
-          if (r == 0) {
-            bp[OFF_B1 + m] = (w ? bp[OFF_B1 + m] : 0.0f) + ab1[mt][i];
-            bp[OFF_B2 + m] = (w ? bp[OFF_B2 + m] : 0.0f) + ab2[mt][i];
-          }
-        }
-      if (g == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-          for (int nt = 0; nt < 4; ++nt) {
-            const int e = OFF_W3 + i * NH + 16 * nt + r;
-            bp[e] = (w ? bp[e] : 0.0f) + aW3[nt][i];
-          }
-          if (r == 0) bp[OFF_B3 + i] = (w ? bp[OFF_B3 + i] : 0.0f) + ab3[i];
-        }
-      }
-    }
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < NPARAM; e += kBwdBlock) partial[(int64_t)blockIdx.x * NPARAM + e] = bp[e];
-}
-
-// --------------------------------------------------------------- BF16 bwd
-// Same algebra as the FP32 backward, on BF16 MFMA 16x16x32 (FP32
-// accumulate).  Each of a workgroup's four waves takes 16 of its 64 samples
-// through the forward and the deltas; then the waves share the weight
-// gradients, wave w the rows of neurons 16w .. 16w + 15, with K = the 64
-// samples from [neuron][sample] tiles in LDS.  So a wave holds 28 accumulator
-// registers, not 112, and two fit a SIMD without moves to and from the
-// accumulation registers.  An MFMA with its operands exchanged gives the
-// transposed product from the same registers, out[sample 4g + i][neuron r] in
-// place of out[neuron 4g + i][sample r]: each layer is computed in both, the
-// first for the next layer, the second, four samples to a lane, for 8-byte
-// stores to those tiles.
-// 262,143 samples: 36 us.  A wave alone on a SIMD with every accumulator, 2-byte
-// stores to its own tiles and loads at their use took 75 us: 6 of preparing
-// weights, 7 us per 32 samples and 6 of adding the waves.
-constexpr int kBfBlock = 256, kBfWaves = kBfBlock / 64;
-constexpr int kBfSamples = 16 * kBfWaves;  // per block and step
-constexpr int LDB = kBfSamples + 8;        // row stride of the sample tiles
+// The transposed products chain in registers like the forward.  Each of a
+// workgroup's four waves takes 16 of its 64 samples through the forward and
+// the deltas; then the waves share the weight gradients, wave w the rows of
+// neurons 16w .. 16w + 15, with K = the 64 samples from [neuron][sample] tiles
+// in LDS.  So a wave holds 28 accumulator registers, not 112, and works
+// without moves to and from the accumulation registers.  The next step's
+// inputs are in flight during a step.  Block partials are reduced in a fixed
+// order.
+constexpr int kBwdBlock = 256, kBwdWaves = kBwdBlock / 64;
+constexpr int kBwdSamples = 16 * kBwdWaves;  // per block and step
+// rows of the sample tiles
 constexpr int BR_X = 0, BR_H1 = 32, BR_H2 = 96, BR_D2 = 160, BR_D1 = 224, BR_D3 = 288, BR_ROWS = 292;
 // LDS copy of the parameters, rows padded so that the lanes (r, g) of a
 // fragment read distinct banks along rows and along columns
 constexpr int PW1 = 36, PW2 = 68, PW3 = 80;
 constexpr int PO_W1 = 0, PO_W2 = PO_W1 + NH * PW1, PO_W3 = PO_W2 + NH * PW2, PO_B1 = PO_W3 + NOUT * PW3,
               PO_B2 = PO_B1 + NH, PO_B3 = PO_B2 + NH, PO_SIZE = PO_B3 + NOUT;
-
-struct BfBwdLds {
-  union {
-    float p[PO_SIZE];
-    __bf16 t[BR_ROWS * LDB];
-  };
-  // fragments 2 mt + c of W2's transpose, 8 + 2 mt + c of W1's, 12 + mt of W1
-  // (in registers all of them would not leave room for two waves on a SIMD)
-  bf16x8 w[16][64];
-  float b1[NH], b2[NH];
-  float bias[kBfWaves][9][16];
-};
-
 __device__ __forceinline__ void stage_padded(const float *__restrict__ P, float *p) {
   const float4 *P4 = reinterpret_cast<const float4 *>(P);
-  constexpr int kPer = (NPARAM / 4 + kBfBlock - 1) / kBfBlock, kLast = NPARAM / 4 - 1;
+  constexpr int kPer = (NPARAM / 4 + kBwdBlock - 1) / kBwdBlock, kLast = NPARAM / 4 - 1;
   float4 v[kPer];
   // every load in flight before the first is used; threads past the end copy
   // the last group again
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int e = threadIdx.x + k * kBfBlock;
+    const int e = threadIdx.x + k * kBwdBlock;
     v[k] = P4[e < kLast ? e : kLast];
   }
 #pragma unroll
   for (int k = 0; k < kPer; ++k) asm volatile("" : "+v"(v[k].x), "+v"(v[k].y), "+v"(v[k].z), "+v"(v[k].w));
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int e = threadIdx.x + k * kBfBlock, i = 4 * (e < kLast ? e : kLast);
+    const int e = threadIdx.x + k * kBwdBlock, i = 4 * (e < kLast ? e : kLast);
     int o = PO_B3 + i - OFF_B3;
     o = i < OFF_B3 ? PO_W3 + ((i - OFF_W3) / NH) * PW3 + (i - OFF_W3) % NH : o;
     o = i < OFF_W3 ? PO_B2 + i - OFF_B2 : o;
@@ -536,6 +264,275 @@ __device__ __forceinline__ void stage_padded(const float *__restrict__ P, float 
 }
 
 __device__ __forceinline__ f32x4 splat(float v) { return f32x4{v, v, v, v}; }
+
+// --------------------------------------------------------------- FP32 bwd
+// Bound by the FP32 matrix rate: 324 MFMAs of 32 cycles for 16 samples.
+// 36,503 samples: 28 us.  Two waves a block with every accumulator, waiting
+// for each tile's loads, took 48 us: 8 of preparing weights, 9.7 us per 16
+// samples and 8 of adding the waves.
+constexpr int LDF = kBwdSamples + 4;  // row stride of the sample tiles
+struct F32BwdLds {
+  union {
+    float p[PO_SIZE];
+    float t[BR_ROWS * LDF];
+  };
+  // fragments of four k-steps: 4 mt + t of W2's transpose, 16 + 4 mt + t of
+  // W1's, 24 + t of W3
+  f32x4 w[28][64];
+  float b1[NH], b2[NH];
+};
+static_assert(sizeof(F32BwdLds) <= 160 * 1024, "one workgroup's LDS");
+
+// The inputs of a 16-sample tile for lane (r, g): loaded for a valid sample
+// index in any case, so that nothing branches around the loads.
+struct F32In {
+  float2 x[4];  // levels 4g .. 4g + 3 of sample r
+  float go;     // gradient of output g of sample r
+  int bone;
+};
+
+template <bool kBone>
+__device__ __forceinline__ void load_in(const float2 *feat, const float *go, const int16_t *bone, int64_t S,
+                                        int64_t ld, int64_t s, int g, F32In &in) {
+  s = s < S ? s : S - 1;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) in.x[j] = feat[(int64_t)(4 * g + j) * ld + s];
+  in.go = go[s];
+  in.bone = kBone ? bone[s] : 0;
+}
+
+// acc + the products of four k-steps.
+__device__ __forceinline__ f32x4 mfma4x4(const f32x4 &a, const f32x4 &b, f32x4 acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc = mfma4(a[i], b[i], acc);
+  return acc;
+}
+
+__device__ __forceinline__ f32x4 relu4(const f32x4 &z) {
+  return f32x4{relu(z[0]), relu(z[1]), relu(z[2]), relu(z[3])};
+}
+
+template <bool kBone>
+__global__ void __launch_bounds__(kBwdBlock, 2) mlp_bwd_f32(const float *__restrict__ gsig,
+                                                            const float *__restrict__ grgb,
+                                                            const float *__restrict__ feat,
+                                                            const int16_t *__restrict__ bone, int64_t S,
+                                                            const int64_t *__restrict__ S_dev, int64_t ld,
+                                                            const float *__restrict__ P, float *__restrict__ gfeat,
+                                                            float *__restrict__ partial) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char f32_lds[];
+  F32BwdLds &lds = *reinterpret_cast<F32BwdLds *>(f32_lds);
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const float2 *feat2 = reinterpret_cast<const float2 *>(feat);
+  S = count_of(S, S_dev);
+  const int64_t step = (int64_t)gridDim.x * kBwdSamples;
+  const float *go = g == 0 ? gsig : grgb + (g - 1) * ld;
+  int64_t s0 = (int64_t)blockIdx.x * kBwdSamples + 16 * wid;
+  F32In in = {};
+  if (S > 0) load_in<kBone>(feat2, go, bone, S, ld, s0 + r, g, in);
+  stage_padded(P, lds.p);
+  __syncthreads();
+  const float *p = lds.p;
+  f32x4 w1[4][2], w2[4][4];
+  float w3t[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) w1[mt][c] = *reinterpret_cast<const f32x4 *>(p + PO_W1 + (16 * mt + r) * PW1 + 8 * g + 4 * c);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w2[mt][t] = *reinterpret_cast<const f32x4 *>(p + PO_W2 + (16 * mt + r) * PW2 + 16 * t + 4 * g);
+    w3t[mt] = p[PO_W3 + g * PW3 + 16 * mt + r];
+  }
+  const float b3 = p[PO_B3 + g];
+  // the fragments in LDS, a quarter by each wave: [16t + 4g + i][16mt + r] of
+  // W2, W1; W3[r / 4][16t + 4g + i] in the rows r = 0, 4, .. and zero in the
+  // others, so that lane (r, g) gets output g of sample r
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    const int q = kBwdWaves * k + wid, mt = (q & 15) >> 2, t = q & 3;
+    f32x4 v;
+    if (k < 6) {
+      const float *col = p + (k < 4 ? PO_W2 : PO_W1) + 16 * mt + r;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = col[(16 * t + 4 * g + i) * (k < 4 ? PW2 : PW1)];
+    } else {
+      v = *reinterpret_cast<const f32x4 *>(p + PO_W3 + (r >> 2) * PW3 + 16 * t + 4 * g);
+      v = (r & 3) == 0 ? v : splat(0.0f);
+    }
+    lds.w[q][lane] = v;
+  }
+  if (threadIdx.x < 2 * NH) (threadIdx.x < NH ? lds.b1 : lds.b2 - NH)[threadIdx.x] = p[PO_B1 + threadIdx.x];
+  __syncthreads();  // the tiles take the parameters' place
+  f32x4 aW1[2], aW2[4], aW3 = splat(0.0f);
+  float ab1 = 0.0f, ab2 = 0.0f, ab3 = 0.0f;  // of neuron 16 wid + r, output r
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    aW2[a] = splat(0.0f);
+    if (a < 2) aW1[a] = splat(0.0f);
+  }
+  float *tc = lds.t + 16 * wid + r;  // this lane's sample in row 0
+  for (int64_t c0 = (int64_t)blockIdx.x * kBwdSamples; c0 < S; c0 += step, s0 += step) {  // uniform in the block
+    const int64_t s = s0 + r;
+    const bool ok = s < S, use = ok && (!kBone || in.bone >= 0);
+    f32x4 X[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      X[j / 2][2 * (j % 2)] = ok ? in.x[j].x : 0.0f;
+      X[j / 2][2 * (j % 2) + 1] = ok ? in.x[j].y : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) tc[(BR_X + 8 * g + k) * LDF] = X[k / 4][k % 4];
+    const float go_s = in.go;
+    // the next step's inputs (after the last: the last sample's again)
+    load_in<kBone>(feat2, go, bone, S, ld, s + step, g, in);
+    f32x4 z1[4], z2[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      z1[mt] = *reinterpret_cast<const f32x4 *>(lds.b1 + 16 * mt + 4 * g);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) z1[mt] = mfma4x4(w1[mt][c], X[c], z1[mt]);
+    }
+    f32x4 h[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      h[t] = relu4(z1[t]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tc[(BR_H1 + 16 * t + 4 * g + i) * LDF] = h[t][i];
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      z2[mt] = *reinterpret_cast<const f32x4 *>(lds.b2 + 16 * mt + 4 * g);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) z2[mt] = mfma4x4(w2[mt][t], h[t], z2[mt]);
+    }
+    f32x4 oa = {b3, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      h[t] = relu4(z2[t]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tc[(BR_H2 + 16 * t + 4 * g + i) * LDF] = h[t][i];
+      oa = mfma4x4(lds.w[24 + t][lane], h[t], oa);
+    }
+    // the gradient of output g of sample r
+    const float o = oa[0], e = expf(g == 0 ? fminf(o, 80.0f) : -o), c = __builtin_amdgcn_rcpf(1.0f + e);
+    float d3 = g == 0 ? (o < 80.0f ? go_s * e : 0.0f) : go_s * c * (1.0f - c);
+    d3 = use ? d3 : 0.0f;
+    tc[(BR_D3 + g) * LDF] = d3;
+    f32x4 d2[4], d1[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      d2[mt] = mfma4(w3t[mt], d3, splat(0.0f));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d2[mt][i] = z2[mt][i] < 0.0f ? 0.0f : d2[mt][i];
+        tc[(BR_D2 + 16 * mt + 4 * g + i) * LDF] = d2[mt][i];
+      }
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      d1[mt] = splat(0.0f);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) d1[mt] = mfma4x4(lds.w[4 * mt + t][lane], d2[t], d1[mt]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d1[mt][i] = z1[mt][i] < 0.0f ? 0.0f : d1[mt][i];
+        tc[(BR_D1 + 16 * mt + 4 * g + i) * LDF] = d1[mt][i];
+      }
+    }
+    // gfeat = W1^T d1 -> feature 16mt + 4g + i = level 8mt + 2g + i/2, f = i%2
+    if (gfeat) {
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        f32x4 acc = splat(0.0f);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc = mfma4x4(lds.w[16 + 4 * mt + t][lane], d1[t], acc);
+        if (ok) {
+          float2 *gf = reinterpret_cast<float2 *>(gfeat);
+          gf[(int64_t)(8 * mt + 2 * g) * ld + s] = make_float2(acc[0], acc[1]);
+          gf[(int64_t)(8 * mt + 2 * g + 1) * ld + s] = make_float2(acc[2], acc[3]);
+        }
+      }
+    }
+    __syncthreads();
+    // weight gradients of this wave's rows, K = the block's samples (slot g of
+    // step i: sample 16k + 4g + i), each 32 samples summed from zero so that
+    // the chains of roundings stay short
+#pragma unroll
+    for (int k2 = 0; k2 < kBwdSamples / 32; ++k2) {
+      const float *tr = lds.t + r * LDF + 32 * k2 + 4 * g;
+      auto rows = [&](int row, int k) { return *reinterpret_cast<const f32x4 *>(tr + row * LDF + 16 * k); };
+      f32x4 v1[2], v2[2], v3[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        v1[k] = rows(BR_D1 + 16 * wid, k);
+        v2[k] = rows(BR_D2 + 16 * wid, k);
+        v3[k] = *reinterpret_cast<const f32x4 *>(lds.t + (BR_D3 + (r & 3)) * LDF + 32 * k2 + 4 * g + 16 * k);
+        v3[k] = r < NOUT ? v3[k] : splat(0.0f);
+      }
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt)
+        aW2[nt] += mfma4x4(v2[1], rows(BR_H1 + 16 * nt, 1), mfma4x4(v2[0], rows(BR_H1 + 16 * nt, 0), splat(0.0f)));
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+        aW1[nt] += mfma4x4(v1[1], rows(BR_X + 16 * nt, 1), mfma4x4(v1[0], rows(BR_X + 16 * nt, 0), splat(0.0f)));
+      aW3 += mfma4x4(v3[1], rows(BR_H2 + 16 * wid, 1), mfma4x4(v3[0], rows(BR_H2 + 16 * wid, 0), splat(0.0f)));
+      auto sum8 = [](const f32x4 v[2]) {
+        return ((v[0][0] + v[0][1]) + (v[0][2] + v[0][3])) + ((v[1][0] + v[1][1]) + (v[1][2] + v[1][3]));
+      };
+      ab1 += sum8(v1);
+      ab2 += sum8(v2);
+      ab3 += sum8(v3);
+    }
+    __syncthreads();  // the tiles are written again
+  }
+  // the block's partial
+#pragma unroll
+  for (int k = 16; k < 64; k <<= 1) {
+    ab1 += __shfl_xor(ab1, k, 64);
+    ab2 += __shfl_xor(ab2, k, 64);
+    ab3 += __shfl_xor(ab3, k, 64);
+  }
+  float *out = partial + (int64_t)blockIdx.x * NPARAM;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = 16 * wid + 4 * g + i;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) out[OFF_W2 + m * NH + 16 * nt + r] = aW2[nt][i];
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) out[OFF_W1 + m * NIN + 16 * nt + r] = aW1[nt][i];
+    if (g == 0) out[OFF_W3 + i * NH + 16 * wid + r] = aW3[i];
+  }
+  if (g == 0) {
+    out[OFF_B1 + 16 * wid + r] = ab1;
+    out[OFF_B2 + 16 * wid + r] = ab2;
+    if (wid == 0 && r < NOUT) out[OFF_B3 + r] = ab3;
+  }
+}
+
+// --------------------------------------------------------------- BF16 bwd
+// On BF16 MFMA 16x16x32 (FP32 accumulate), two waves to a SIMD.  An MFMA with
+// its operands exchanged gives the
+// transposed product from the same registers, out[sample 4g + i][neuron r] in
+// place of out[neuron 4g + i][sample r]: each layer is computed in both, the
+// first for the next layer, the second, four samples to a lane, for 8-byte
+// stores to those tiles.
+// 262,143 samples: 36 us.  A wave alone on a SIMD with every accumulator, 2-byte
+// stores to its own tiles and loads at their use took 75 us: 6 of preparing
+// weights, 7 us per 32 samples and 6 of adding the waves.
+constexpr int LDB = kBwdSamples + 8;        // row stride of the sample tiles
+
+struct BfBwdLds {
+  union {
+    float p[PO_SIZE];
+    __bf16 t[BR_ROWS * LDB];
+  };
+  // fragments 2 mt + c of W2's transpose, 8 + 2 mt + c of W1's, 12 + mt of W1
+  // (in registers all of them would not leave room for two waves on a SIMD)
+  bf16x8 w[16][64];
+  float b1[NH], b2[NH];
+  float bias[kBwdWaves][9][16];
+};
 
 // Eight parameters, four each from p and q, as BF16.
 __device__ __forceinline__ bf16x8 bf_halves(const float *p, const float *q) {
@@ -588,7 +585,7 @@ __device__ __forceinline__ bf16x8 lds_row8(const __bf16 *t, int row, int col) {
 }
 
 template <bool kBone>
-__global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restrict__ gsig,
+__global__ void __launch_bounds__(kBwdBlock, 2) mlp_bwd_bf16(const float *__restrict__ gsig,
                                                             const float *__restrict__ grgb,
                                                             const __hip_bfloat16 *__restrict__ featb,
                                                             const int16_t *__restrict__ bone, int64_t S,
@@ -600,9 +597,9 @@ __global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restr
   const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const uint32_t *feat = reinterpret_cast<const uint32_t *>(featb);
   S = count_of(S, S_dev);
-  const int64_t step = (int64_t)gridDim.x * kBfSamples;
+  const int64_t step = (int64_t)gridDim.x * kBwdSamples;
   const float *go = g == 0 ? gsig : grgb + (g - 1) * ld;
-  int64_t s0 = (int64_t)blockIdx.x * kBfSamples + 16 * wid;
+  int64_t s0 = (int64_t)blockIdx.x * kBwdSamples + 16 * wid;
   BfIn in = {};
   if (S > 0) load_half<kBone>(feat, go, bone, S, ld, s0 + r, g, in);
   stage_padded(P, lds.p);
@@ -634,7 +631,7 @@ __global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restr
   // [16(2c + j/4) + 4g + j%4][16mt + r] of W2, W1; W1[16mt + r][8g + j]
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const int q = kBfWaves * k + wid, mt = (q & 7) >> 1, c = q & 1;
+    const int q = kBwdWaves * k + wid, mt = (q & 7) >> 1, c = q & 1;
     const float *col = p + (k < 2 ? PO_W2 : PO_W1) + 16 * mt + r;
     bf16x8 v;
 #pragma unroll
@@ -654,7 +651,7 @@ __global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restr
     if (a < 2) aW1[a] = splat(0.0f);
   }
   const int col = 16 * wid + 4 * g;  // of the transposed products' samples
-  for (int64_t b0 = (int64_t)blockIdx.x * kBfSamples; b0 < S; b0 += step, s0 += step) {  // uniform in the block
+  for (int64_t b0 = (int64_t)blockIdx.x * kBwdSamples; b0 < S; b0 += step, s0 += step) {  // uniform in the block
     const int64_t s = s0 + r;
     const bool ok = s < S, use = ok && (!kBone || in.bone >= 0);
     bf16x8 X;
@@ -747,18 +744,24 @@ __global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restr
       }
     }
     __syncthreads();
-    // weight gradients of this wave's rows, K = the block's samples
+    // weight gradients of this wave's rows, K = the block's samples, summed from
+    // zero so that the chains of roundings stay short
+    auto rows = [&](int row, int k) { return lds_row8(lds.t, row + r, 32 * k + 8 * g); };
+    const bf16x8 v1[2] = {rows(BR_D1 + 16 * wid, 0), rows(BR_D1 + 16 * wid, 1)};
+    const bf16x8 v2[2] = {rows(BR_D2 + 16 * wid, 0), rows(BR_D2 + 16 * wid, 1)};
+    bf16x8 v3[2];
 #pragma unroll
-    for (int k = 0; k < kBfSamples / 32; ++k) {
-      const int at = 32 * k + 8 * g;
-      const bf16x8 zero = {}, v3 = lds_row8(lds.t, BR_D3 + (r & 3), at);
-      aW3 = mfma32(r < NOUT ? v3 : zero, lds_row8(lds.t, BR_H2 + 16 * wid + r, at), aW3);
-      const bf16x8 v2 = lds_row8(lds.t, BR_D2 + 16 * wid + r, at), v1 = lds_row8(lds.t, BR_D1 + 16 * wid + r, at);
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) aW2[nt] = mfma32(v2, lds_row8(lds.t, BR_H1 + 16 * nt + r, at), aW2[nt]);
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) aW1[nt] = mfma32(v1, lds_row8(lds.t, BR_X + 16 * nt + r, at), aW1[nt]);
+    for (int k = 0; k < 2; ++k) {
+      const bf16x8 zero = {}, v = lds_row8(lds.t, BR_D3 + (r & 3), 32 * k + 8 * g);
+      v3[k] = r < NOUT ? v : zero;
     }
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+      aW2[nt] += mfma32(v2[1], rows(BR_H1 + 16 * nt, 1), mfma32(v2[0], rows(BR_H1 + 16 * nt, 0), splat(0.0f)));
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+      aW1[nt] += mfma32(v1[1], rows(BR_X + 16 * nt, 1), mfma32(v1[0], rows(BR_X + 16 * nt, 0), splat(0.0f)));
+    aW3 += mfma32(v3[1], rows(BR_H2 + 16 * wid, 1), mfma32(v3[0], rows(BR_H2 + 16 * wid, 0), splat(0.0f)));
     __syncthreads();  // the tiles are written again
   }
   // the block's partial: the weights as they are, the biases over the waves in
@@ -794,7 +797,7 @@ __global__ void __launch_bounds__(kBfBlock, 2) mlp_bwd_bf16(const float *__restr
   if (a < 8 || (a == 8 && q < NOUT)) {
     float v = lds.bias[0][a][q];
 #pragma unroll
-    for (int w = 1; w < kBfWaves; ++w) v += lds.bias[w][a][q];
+    for (int w = 1; w < kBwdWaves; ++w) v += lds.bias[w][a][q];
     out[a == 8 ? OFF_B3 + q : (a < 4 ? OFF_B1 : OFF_B2) + 16 * (a % 4) + q] = v;
   }
 }
@@ -829,18 +832,10 @@ __global__ void __launch_bounds__(kRedP *kRedG) reduce_partials(const float *__r
   }
 }
 
-constexpr int kMaxBwdBlocks = 512;
-
-int bwd_blocks(int64_t S) {
-  int64_t b = ceil_div(ceil_div(S, 16), kBwdWaves);
-  if (b > kMaxBwdBlocks) b = kMaxBwdBlocks;
-  return b < 1 ? 1 : (int)b;
-}
-
-// two workgroups per CU; never more than bwd_blocks, which sizes the workspace
-int bf_bwd_blocks(int64_t S) {
-  const int64_t b = ceil_div(S, (int64_t)kBfSamples);
-  return b > kMaxBwdBlocks ? kMaxBwdBlocks : (int)b;
+// workgroups a CU holds by LDS: one for FP32, two for BF16
+int bwd_blocks(int64_t S, int per_cu) {
+  const int64_t b = ceil_div(S, (int64_t)kBwdSamples), most = 256 * per_cu;
+  return b > most ? (int)most : (b < 1 ? 1 : (int)b);
 }
 
 // as many blocks as stay resident (2 waves per SIMD by registers): each
@@ -887,7 +882,7 @@ extern "C" int32_t ia355_mlp_fwd(const void *feat, int32_t feat_dtype, const int
 }
 
 extern "C" size_t ia355_mlp_bwd_workspace_size(int64_t S) {
-  return align256(sizeof(float) * (size_t)NPARAM * bwd_blocks(S));
+  return align256(sizeof(float) * (size_t)NPARAM * bwd_blocks(S, 2));
 }
 
 extern "C" int32_t ia355_mlp_bwd(const float *grad_sigma, const float *grad_rgb, const void *feat, int32_t feat_dtype,
@@ -905,12 +900,16 @@ extern "C" int32_t ia355_mlp_bwd(const float *grad_sigma, const float *grad_rgb,
   if (S == 0) return (flags & IA355_OVERWRITE) ? ia355_zero(grad_params, sizeof(float) * NPARAM, stream) : IA355_OK;
   if (!ws || ws_bytes < ia355_mlp_bwd_workspace_size(S)) return IA355_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
-  const int nb = dtype == IA355_F32 ? bwd_blocks(S) : bf_bwd_blocks(S);
-  if (dtype == IA355_F32)
-    mlp_bwd_f32<<<nb, kBwdBlock, LDS_FLOATS * sizeof(float), s>>>(grad_sigma, grad_rgb, (const float *)feat, bone, S,
-                                                                  S_dev, ld, params, grad_feat, (float *)ws);
-  else
-    (bone ? mlp_bwd_bf16<true> : mlp_bwd_bf16<false>)<<<nb, kBfBlock, 0, s>>>(
+  const int nb = bwd_blocks(S, dtype == IA355_F32 ? 1 : 2);
+  if (dtype == IA355_F32) {
+    auto fn = bone ? mlp_bwd_f32<true> : mlp_bwd_f32<false>;
+    if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(F32BwdLds)) !=
+        hipSuccess)
+      return IA355_ERR_HIP;
+    fn<<<nb, kBwdBlock, sizeof(F32BwdLds), s>>>(grad_sigma, grad_rgb, (const float *)feat, bone, S, S_dev, ld, params,
+                                                grad_feat, (float *)ws);
+  } else
+    (bone ? mlp_bwd_bf16<true> : mlp_bwd_bf16<false>)<<<nb, kBwdBlock, 0, s>>>(
         grad_sigma, grad_rgb, (const __hip_bfloat16 *)feat, bone, S, S_dev, ld, params, grad_feat, (float *)ws);
   reduce_partials<<<(unsigned)ceil_div(NPARAM, kRedP), kRedP * kRedG, 0, s>>>((const float *)ws, nb, grad_params,
                                                                                      (flags & IA355_OVERWRITE) != 0);
