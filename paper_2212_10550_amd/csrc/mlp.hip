@@ -23,194 +23,272 @@ using namespace ia355::mlpd;
 
 namespace {
 
-// --------------------------------------------------------------- FP32 fwd
-// Loads the 8 features of lane group g for sample s (levels 4g..4g+3).
-__device__ __forceinline__ void load_x(const float *feat, int64_t fst, int64_t s, int g, bool ok, float X[8]) {
+constexpr int kMlpBlock = 256;
+
+// LDS copy of the parameters, rows padded so that the lanes (r, g) of a
+// fragment read distinct banks along rows and along columns
+constexpr int PW1 = 36, PW2 = 68, PW3 = 80;
+constexpr int PO_W1 = 0, PO_W2 = PO_W1 + NH * PW1, PO_W3 = PO_W2 + NH * PW2, PO_B1 = PO_W3 + NOUT * PW3,
+              PO_B2 = PO_B1 + NH, PO_B3 = PO_B2 + NH, PO_SIZE = PO_B3 + NOUT;
+__device__ __forceinline__ void stage_padded(const float *__restrict__ P, float *p) {
+  const float4 *P4 = reinterpret_cast<const float4 *>(P);
+  constexpr int kPer = (NPARAM / 4 + kMlpBlock - 1) / kMlpBlock, kLast = NPARAM / 4 - 1;
+  float4 v[kPer];
+  // every load in flight before the first is used; threads past the end copy
+  // the last group again
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    float2 v = make_float2(0.0f, 0.0f);
-    if (ok) v = reinterpret_cast<const float2 *>(feat)[(int64_t)(4 * g + j) * fst + s];
-    X[2 * j] = v.x;
-    X[2 * j + 1] = v.y;
+  for (int k = 0; k < kPer; ++k) {
+    const int e = threadIdx.x + k * kMlpBlock;
+    v[k] = P4[e < kLast ? e : kLast];
+  }
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) asm volatile("" : "+v"(v[k].x), "+v"(v[k].y), "+v"(v[k].z), "+v"(v[k].w));
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int e = threadIdx.x + k * kMlpBlock, i = 4 * (e < kLast ? e : kLast);
+    int o = PO_B3 + i - OFF_B3;
+    o = i < OFF_B3 ? PO_W3 + ((i - OFF_W3) / NH) * PW3 + (i - OFF_W3) % NH : o;
+    o = i < OFF_W3 ? PO_B2 + i - OFF_B2 : o;
+    o = i < OFF_B2 ? PO_W2 + ((i - OFF_W2) / NH) * PW2 + (i - OFF_W2) % NH : o;
+    o = i < OFF_W2 ? PO_B1 + i - OFF_B1 : o;
+    o = i < OFF_B1 ? PO_W1 + (i / NIN) * PW1 + i % NIN : o;
+    *reinterpret_cast<float4 *>(p + o) = v[k];
   }
 }
 
-struct Frag32 {
-  float w1[4][8];   // [mt][c]  = W1[16mt + r][8g + c]
-  float w2[4][16];  // [mt][4t+i] = W2[16mt + r][16t + 4g + i]
-  float w3[16];     // [4t+i]   = W3[r][16t + 4g + i] (r < 4)
-  float b1[4][4], b2[4][4], b3[4];  // [mt][i] = b[16mt + 4g + i]
+__device__ __forceinline__ f32x4 splat(float v) { return f32x4{v, v, v, v}; }
+
+// acc + the products of four k-steps.
+__device__ __forceinline__ f32x4 mfma4x4(const f32x4 &a, const f32x4 &b, f32x4 acc) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) acc = mfma4(a[i], b[i], acc);
+  return acc;
+}
+
+__device__ __forceinline__ f32x4 relu4(const f32x4 &z) {
+  return f32x4{relu(z[0]), relu(z[1]), relu(z[2]), relu(z[3])};
+}
+
+// The activated output of lane (r, g), output g of sample r, given as its
+// pre-activation o: the density exp(o) (clamped at exp(80)) or a colour
+// sigmoid(o), as head() computes them.
+__device__ __forceinline__ float head_lane(int g, float o) {
+  const float e = expf(g == 0 ? fminf(o, 80.0f) : -o);
+  return g == 0 ? e : __builtin_amdgcn_rcpf(1.0f + e);
+}
+
+// --------------------------------------------------------------- forward
+// A wave takes 16 samples at a time, the inputs of the next kFwdPre tiles in
+// flight (a tile's MFMA chain is far shorter than a load's latency).  The last
+// layer's operand has W3's rows at 0, 4, 8 and 12 and zeros between, so lane
+// (r, g) ends with output g of sample r: one exponential and one store a lane.
+constexpr int kFwdPre = 2;
+
+// The inputs of a 16-sample tile for lane (r, g): loaded for a valid sample
+// index in any case, so that nothing branches around the loads.
+struct F32X {
+  float2 x[4];  // levels 4g .. 4g + 3 of sample r
+  int16_t bone;
 };
 
-__device__ __forceinline__ void load_frag32(const float *P, int r, int g, Frag32 &f) {
+template <bool kBone>
+__device__ __forceinline__ void load_x(const float2 *feat, const int16_t *bone, int64_t S, int64_t ld,
+                                       int64_t s, int g, F32X &in) {
+  s = s < S ? s : S - 1;
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) f.w1[mt][c] = P[OFF_W1 + (16 * mt + r) * NIN + 8 * g + c];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) f.w2[mt][4 * t + i] = P[OFF_W2 + (16 * mt + r) * NH + 16 * t + 4 * g + i];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f.b1[mt][i] = P[OFF_B1 + 16 * mt + 4 * g + i];
-      f.b2[mt][i] = P[OFF_B2 + 16 * mt + 4 * g + i];
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f.w3[4 * t + i] = r < NOUT ? P[OFF_W3 + r * NH + 16 * t + 4 * g + i] : 0.0f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) f.b3[i] = (4 * g + i) < NOUT ? P[OFF_B3 + 4 * g + i] : 0.0f;
+  for (int j = 0; j < 4; ++j) in.x[j] = feat[(int64_t)(4 * g + j) * ld + s];
+  in.bone = kBone ? bone[s] : (int16_t)0;
 }
 
-// Forward of one tile; z1/z2 are pre-activations, o the 4 outputs (valid in
-// lanes g == 0).
-__device__ __forceinline__ void fwd32(const Frag32 &f, const float X[8], f32x4 z1[4], f32x4 z2[4], f32x4 &o) {
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    f32x4 acc = {f.b1[mt][0], f.b1[mt][1], f.b1[mt][2], f.b1[mt][3]};
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc = mfma4(f.w1[mt][c], X[c], acc);
-    z1[mt] = acc;
-  }
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    f32x4 acc = {f.b2[mt][0], f.b2[mt][1], f.b2[mt][2], f.b2[mt][3]};
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc = mfma4(f.w2[mt][4 * t + i], relu(z1[t][i]), acc);
-    z2[mt] = acc;
-  }
-  f32x4 acc = {f.b3[0], f.b3[1], f.b3[2], f.b3[3]};
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc = mfma4(f.w3[4 * t + i], relu(z2[t][i]), acc);
-  o = acc;
-}
-
-constexpr int kFwdBlock = 256;
-constexpr int kFwdPre = 2;    // tiles whose features are in flight per wave (BF16)
-constexpr int kFwdPre32 = 2;  // the same for FP32 features (eight registers a tile)
-
-__global__ void __launch_bounds__(kFwdBlock) mlp_fwd_f32(const float *__restrict__ feat,
-                                                         const int16_t *__restrict__ bone, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
-                                                         const float *__restrict__ P, float *__restrict__ sigma,
-                                                         float *__restrict__ rgb) {
-  __shared__ __attribute__((aligned(16))) float sP[NPARAM];
+// FP32: the two hidden layers' weights in registers (two waves per SIMD).
+// 36,503 samples: 11 us, 262,144: 36.  With fragments gathered one
+// conflicting LDS word at a time and sixteen lanes computing the four outputs
+// of their samples: 12.5 and 41.6 us.
+template <bool kBone>
+__global__ void __launch_bounds__(kMlpBlock, 2) mlp_fwd_f32(const float *__restrict__ feat,
+                                                            const int16_t *__restrict__ bone, int64_t S,
+                                                            const int64_t *__restrict__ S_dev, int64_t ld,
+                                                            const float *__restrict__ P, float *__restrict__ sigma,
+                                                            float *__restrict__ rgb) {
+  __shared__ __attribute__((aligned(16))) float p[PO_SIZE];
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   S = count_of(S, S_dev);
-  const int64_t ntile = ceil_div(S, 16);
-  const int64_t wstride = (int64_t)gridDim.x * (kFwdBlock / 64);
-  if ((int64_t)blockIdx.x * (kFwdBlock / 64) >= ntile) return;  // the whole block (before the barrier)
-  stage_params(P, sP);
+  const int64_t ntile = ceil_div(S, 16), wstride = (int64_t)gridDim.x * (kMlpBlock / 64);
+  int64_t tile = (int64_t)blockIdx.x * (kMlpBlock / 64) + wid;
+  if ((int64_t)blockIdx.x * (kMlpBlock / 64) >= ntile) return;  // the whole block (before the barrier)
+  const float2 *feat2 = reinterpret_cast<const float2 *>(feat);
+  F32X in[kFwdPre];
+#pragma unroll
+  for (int u = 0; u < kFwdPre; ++u) load_x<kBone>(feat2, bone, S, ld, (tile + u * wstride) * 16 + r, g, in[u]);
+  stage_padded(P, p);
   __syncthreads();
-  // a wave without a tile skips the fragment loads (no barriers after this)
-  if ((int64_t)blockIdx.x * (kFwdBlock / 64) + (threadIdx.x >> 6) >= ntile) return;
-  Frag32 f;
-  load_frag32(sP, r, g, f);
-  // the features and bone of the next kFwdPre32 tiles of this wave are in
-  // flight while a tile computes (a tile's MFMA chain is far shorter than
-  // a load's latency)
-  const int64_t tile0 = (int64_t)blockIdx.x * (kFwdBlock / 64) + (threadIdx.x >> 6);
-  float Xq[kFwdPre32][8];
-  int Bq[kFwdPre32];
+  f32x4 w1[4][2], w2[4][4], w3[4];
 #pragma unroll
-  for (int u = 0; u < kFwdPre32; ++u) {
-    const int64_t su = (tile0 + u * wstride) * 16 + r;
-    const bool okn = tile0 + u * wstride < ntile && su < S;
-    load_x(feat, ld, su, g, okn, Xq[u]);
-    Bq[u] = okn && bone && g == 0 ? bone[su] : 0;
+  for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) w1[mt][c] = *reinterpret_cast<const f32x4 *>(p + PO_W1 + (16 * mt + r) * PW1 + 8 * g + 4 * c);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w2[mt][t] = *reinterpret_cast<const f32x4 *>(p + PO_W2 + (16 * mt + r) * PW2 + 16 * t + 4 * g);
+    const f32x4 v = *reinterpret_cast<const f32x4 *>(p + PO_W3 + (r >> 2) * PW3 + 16 * mt + 4 * g);
+    w3[mt] = (r & 3) == 0 ? v : splat(0.0f);
   }
-  for (int64_t tile = tile0; tile < ntile; tile += kFwdPre32 * wstride) {
-#pragma unroll
-    for (int u = 0; u < kFwdPre32; ++u) {
-      const int64_t tu = tile + u * wstride;
-      if (tu >= ntile) break;
-      const int64_t s = tu * 16 + r;
-      const bool ok = s < S;
-      float X[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) X[c] = Xq[u][c];
-      const int bn = Bq[u];
-      const int64_t tn = tu + kFwdPre32 * wstride, sn = tn * 16 + r;
-      const bool okn = tn < ntile && sn < S;
-      load_x(feat, ld, sn, g, okn, Xq[u]);
-      Bq[u] = okn && bone && g == 0 ? bone[sn] : 0;
-      f32x4 z1[4], z2[4], o;
-      fwd32(f, X, z1, z2, o);
-      if (g == 0 && ok) {
-        float sg = 0.0f, c[3] = {0.0f, 0.0f, 0.0f};
-        if (!bone || bn >= 0) {
-          const float ov[4] = {o[0], o[1], o[2], o[3]};
-          head(ov, &sg, c);
-        }
-        sigma[s] = sg;
-        rgb[s] = c[0];
-        rgb[ld + s] = c[1];
-        rgb[2 * ld + s] = c[2];
-      }
-    }
-  }
-}
-
-__global__ void __launch_bounds__(kFwdBlock, 4) mlp_fwd_bf16(const __hip_bfloat16 *__restrict__ feat,
-                                                          const int16_t *__restrict__ bone, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
-                                                          const float *__restrict__ P, float *__restrict__ sigma,
-                                                          float *__restrict__ rgb) {
-  __shared__ __attribute__((aligned(16))) FragLds sF;
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  S = count_of(S, S_dev);
-  const int64_t ntile = ceil_div(S, 16);
-  const int64_t wstride = (int64_t)gridDim.x * (kFwdBlock / 64);
-  if ((int64_t)blockIdx.x * (kFwdBlock / 64) >= ntile) return;  // the whole block (before the barrier)
-  stage_frag_lds(P, sF);
-  __syncthreads();
-  if ((int64_t)blockIdx.x * (kFwdBlock / 64) + (threadIdx.x >> 6) >= ntile) return;
-  // the fragments stay in LDS and are read as each MFMA needs them (held in
-  // registers they cost 90 registers a lane, two waves per SIMD)
-  // the features and bone of the next kFwdPre tiles of this wave are in
-  // flight while a tile computes
-  const int64_t tile0 = (int64_t)blockIdx.x * (kFwdBlock / 64) + (threadIdx.x >> 6);
-  bf16x8 Xq[kFwdPre];
-  int Bq[kFwdPre];
-#pragma unroll
-  for (int u = 0; u < kFwdPre; ++u) {
-    const int64_t su = (tile0 + u * wstride) * 16 + r;
-    const bool okn = tile0 + u * wstride < ntile && su < S;
-    Xq[u] = load_x_bf16(feat, ld, su, g, okn);
-    Bq[u] = okn && bone && g == 0 ? bone[su] : 0;
-  }
-  for (int64_t tile = tile0; tile < ntile; tile += kFwdPre * wstride) {
+  const float b3 = p[PO_B3 + g];
+  float *out = g == 0 ? sigma : rgb + (g - 1) * ld;
+  for (; tile < ntile; tile += kFwdPre * wstride) {
 #pragma unroll
     for (int u = 0; u < kFwdPre; ++u) {
-      const int64_t tu = tile + u * wstride;
-      if (tu >= ntile) break;
-      const int64_t s = tu * 16 + r;
+      if (tile + u * wstride >= ntile) break;
+      const int64_t s = (tile + u * wstride) * 16 + r;
       const bool ok = s < S;
-      const bf16x8 X = Xq[u];
-      const int bn = Bq[u];
-      const int64_t tn = tu + kFwdPre * wstride, sn = tn * 16 + r;
-      const bool okn = tn < ntile && sn < S;
-      Xq[u] = load_x_bf16(feat, ld, sn, g, okn);
-      Bq[u] = okn && bone && g == 0 ? bone[sn] : 0;
-      f32x4 z1[4], z2[4], o;
-      pin_in_loop();
-      fwd_bf_src(LdsW{sF, lane, g}, X, z1, z2, o);
-      if (g == 0 && ok) {
-        float sg = 0.0f, c[3] = {0.0f, 0.0f, 0.0f};
-        if (!bone || bn >= 0) {
-          const float ov[4] = {o[0], o[1], o[2], o[3]};
-          head(ov, &sg, c);
-        }
-        sigma[s] = sg;
-        rgb[s] = c[0];
-        rgb[ld + s] = c[1];
-        rgb[2 * ld + s] = c[2];
+      f32x4 X[2];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        X[j / 2][2 * (j % 2)] = in[u].x[j].x;
+        X[j / 2][2 * (j % 2) + 1] = in[u].x[j].y;
       }
+      const bool use = !kBone || in[u].bone >= 0;
+      f32x4 z[4], h[4];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        z[mt] = *reinterpret_cast<const f32x4 *>(p + PO_B1 + 16 * mt + 4 * g);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) z[mt] = mfma4x4(w1[mt][c], X[c], z[mt]);
+        h[mt] = relu4(z[mt]);
+      }
+      // only now, into the registers that the first layer has read
+      __builtin_amdgcn_sched_barrier(0);
+      load_x<kBone>(feat2, bone, S, ld, s + kFwdPre * wstride * 16, g, in[u]);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        z[mt] = *reinterpret_cast<const f32x4 *>(p + PO_B2 + 16 * mt + 4 * g);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z[mt] = mfma4x4(w2[mt][t], h[t], z[mt]);
+      }
+      f32x4 o = {b3, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o = mfma4x4(w3[t], relu4(z[t]), o);
+      const float v = head_lane(g, o[0]);
+      if (ok) out[s] = use ? v : 0.0f;
+    }
+  }
+}
+
+// BF16: the weights in LDS, read as each MFMA needs them (held in registers
+// they cost 90 a lane, two waves per SIMD).  1,000,003 samples: 27 us;
+// with branches around the loads, serial waits in the weights' staging and
+// sixteen lanes computing the four outputs of their samples 35 us.
+struct BfX {
+  uint32_t x[4];  // levels 4g .. 4g + 3 of sample r
+  int16_t bone;
+};
+
+template <bool kBone>
+__device__ __forceinline__ void load_x(const uint32_t *feat, const int16_t *bone, int64_t S, int64_t ld, int64_t s,
+                                       int g, BfX &in) {
+  s = s < S ? s : S - 1;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) in.x[j] = feat[(int64_t)(4 * g + j) * ld + s];
+  in.bone = kBone ? bone[s] : (int16_t)0;
+}
+
+// A whole block fills the store from the parameters in global memory (16-byte
+// aligned), each fragment two 16-byte loads of consecutive parameters,
+// converted as frag_value converts them; W3's rows go to 0, 4, 8 and 12.
+// Every load is in flight before the first is used.
+__device__ __forceinline__ void stage_frag_spread(const float *__restrict__ P, FragLds &s) {
+  constexpr int kPer = (14 * 64 + kMlpBlock - 1) / kMlpBlock;
+  float4 v[kPer][2];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int e = threadIdx.x + k * kMlpBlock, q = e < 14 * 64 ? e >> 6 : 13, r = e & 15, g = (e >> 4) & 3;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      v[k][h] = *reinterpret_cast<const float4 *>(P + frag_half_at(q, q < 12 ? r : r >> 2, g, h));
+  }
+  const int b = threadIdx.x < 2 * NH ? (threadIdx.x < NH ? OFF_B1 : OFF_B2 - NH) + threadIdx.x
+                                     : OFF_B3 + (threadIdx.x & (NOUT - 1));
+  float bias = P[b];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      asm volatile("" : "+v"(v[k][h].x), "+v"(v[k][h].y), "+v"(v[k][h].z), "+v"(v[k][h].w));
+  asm volatile("" : "+v"(bias));
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int e = threadIdx.x + k * kMlpBlock, q = e >> 6;
+    if (e >= 14 * 64) break;
+    bf16x8 f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      f[4 * h] = (__bf16)v[k][h].x;
+      f[4 * h + 1] = (__bf16)v[k][h].y;
+      f[4 * h + 2] = (__bf16)v[k][h].z;
+      f[4 * h + 3] = (__bf16)v[k][h].w;
+    }
+    const bf16x8 zero = {};
+    s.mw[q][e & 63] = q < 12 || (e & 3) == 0 ? f : zero;
+  }
+  if (threadIdx.x < 2 * NH)
+    (threadIdx.x < NH ? s.b1 : s.b2 - NH)[threadIdx.x] = bias;
+  else if (threadIdx.x < 2 * NH + NOUT)
+    s.b3[threadIdx.x - 2 * NH] = bias;
+}
+
+template <bool kBone>
+__global__ void __launch_bounds__(kMlpBlock, 4) mlp_fwd_bf16(const __hip_bfloat16 *__restrict__ featb,
+                                                            const int16_t *__restrict__ bone, int64_t S,
+                                                            const int64_t *__restrict__ S_dev, int64_t ld,
+                                                            const float *__restrict__ P, float *__restrict__ sigma,
+                                                            float *__restrict__ rgb) {
+  __shared__ __attribute__((aligned(16))) FragLds sF;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  S = count_of(S, S_dev);
+  const int64_t ntile = ceil_div(S, 16), wstride = (int64_t)gridDim.x * (kMlpBlock / 64);
+  int64_t tile = (int64_t)blockIdx.x * (kMlpBlock / 64) + wid;
+  if ((int64_t)blockIdx.x * (kMlpBlock / 64) >= ntile) return;  // the whole block (before the barrier)
+  const uint32_t *feat = reinterpret_cast<const uint32_t *>(featb);
+  BfX in[kFwdPre];
+#pragma unroll
+  for (int u = 0; u < kFwdPre; ++u) load_x<kBone>(feat, bone, S, ld, (tile + u * wstride) * 16 + r, g, in[u]);
+  stage_frag_spread(P, sF);
+  __syncthreads();
+  const LdsW w{sF, lane, g};
+  const float b3 = sF.b3[g];
+  float *out = g == 0 ? sigma : rgb + (g - 1) * ld;
+  for (; tile < ntile; tile += kFwdPre * wstride) {
+#pragma unroll
+    for (int u = 0; u < kFwdPre; ++u) {
+      if (tile + u * wstride >= ntile) break;
+      const int64_t s = (tile + u * wstride) * 16 + r;
+      const bool ok = s < S;
+      bf16x8 X;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        X[2 * j] = __builtin_bit_cast(__bf16, (uint16_t)(in[u].x[j] & 0xffffu));
+        X[2 * j + 1] = __builtin_bit_cast(__bf16, (uint16_t)(in[u].x[j] >> 16));
+      }
+      const bool use = !kBone || in[u].bone >= 0;
+      pin_in_loop();
+      f32x4 z[4];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) z[mt] = mfma32(w.w1(mt), X, w.b1(mt));
+      // only now, into the registers that the first layer has read
+      __builtin_amdgcn_sched_barrier(0);
+      load_x<kBone>(feat, bone, S, ld, s + kFwdPre * wstride * 16, g, in[u]);
+      const bf16x8 h1a = pack_act(z, 0), h1b = pack_act(z, 1);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        z[mt] = mfma32(w.w2(mt, 0), h1a, w.b2(mt));
+        z[mt] = mfma32(w.w2(mt, 1), h1b, z[mt]);
+      }
+      f32x4 o = {b3, 0.0f, 0.0f, 0.0f};
+      o = mfma32(w.w3(0), pack_act(z, 0), o);
+      o = mfma32(w.w3(1), pack_act(z, 1), o);
+      const float v = head_lane(g, o[0]);
+      if (ok) out[s] = use ? v : 0.0f;
     }
   }
 }
@@ -228,43 +306,10 @@ __global__ void __launch_bounds__(kFwdBlock, 4) mlp_fwd_bf16(const __hip_bfloat1
 // without moves to and from the accumulation registers.  The next step's
 // inputs are in flight during a step.  Block partials are reduced in a fixed
 // order.
-constexpr int kBwdBlock = 256, kBwdWaves = kBwdBlock / 64;
+constexpr int kBwdBlock = kMlpBlock, kBwdWaves = kBwdBlock / 64;
 constexpr int kBwdSamples = 16 * kBwdWaves;  // per block and step
 // rows of the sample tiles
 constexpr int BR_X = 0, BR_H1 = 32, BR_H2 = 96, BR_D2 = 160, BR_D1 = 224, BR_D3 = 288, BR_ROWS = 292;
-// LDS copy of the parameters, rows padded so that the lanes (r, g) of a
-// fragment read distinct banks along rows and along columns
-constexpr int PW1 = 36, PW2 = 68, PW3 = 80;
-constexpr int PO_W1 = 0, PO_W2 = PO_W1 + NH * PW1, PO_W3 = PO_W2 + NH * PW2, PO_B1 = PO_W3 + NOUT * PW3,
-              PO_B2 = PO_B1 + NH, PO_B3 = PO_B2 + NH, PO_SIZE = PO_B3 + NOUT;
-__device__ __forceinline__ void stage_padded(const float *__restrict__ P, float *p) {
-  const float4 *P4 = reinterpret_cast<const float4 *>(P);
-  constexpr int kPer = (NPARAM / 4 + kBwdBlock - 1) / kBwdBlock, kLast = NPARAM / 4 - 1;
-  float4 v[kPer];
-  // every load in flight before the first is used; threads past the end copy
-  // the last group again
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int e = threadIdx.x + k * kBwdBlock;
-    v[k] = P4[e < kLast ? e : kLast];
-  }
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) asm volatile("" : "+v"(v[k].x), "+v"(v[k].y), "+v"(v[k].z), "+v"(v[k].w));
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int e = threadIdx.x + k * kBwdBlock, i = 4 * (e < kLast ? e : kLast);
-    int o = PO_B3 + i - OFF_B3;
-    o = i < OFF_B3 ? PO_W3 + ((i - OFF_W3) / NH) * PW3 + (i - OFF_W3) % NH : o;
-    o = i < OFF_W3 ? PO_B2 + i - OFF_B2 : o;
-    o = i < OFF_B2 ? PO_W2 + ((i - OFF_W2) / NH) * PW2 + (i - OFF_W2) % NH : o;
-    o = i < OFF_W2 ? PO_B1 + i - OFF_B1 : o;
-    o = i < OFF_B1 ? PO_W1 + (i / NIN) * PW1 + i % NIN : o;
-    *reinterpret_cast<float4 *>(p + o) = v[k];
-  }
-}
-
-__device__ __forceinline__ f32x4 splat(float v) { return f32x4{v, v, v, v}; }
-
 // --------------------------------------------------------------- FP32 bwd
 // Bound by the FP32 matrix rate: 324 MFMAs of 32 cycles for 16 samples.
 // 36,503 samples: 28 us.  Two waves a block with every accumulator, waiting
@@ -283,33 +328,16 @@ struct F32BwdLds {
 };
 static_assert(sizeof(F32BwdLds) <= 160 * 1024, "one workgroup's LDS");
 
-// The inputs of a 16-sample tile for lane (r, g): loaded for a valid sample
-// index in any case, so that nothing branches around the loads.
 struct F32In {
-  float2 x[4];  // levels 4g .. 4g + 3 of sample r
-  float go;     // gradient of output g of sample r
-  int bone;
+  F32X x;
+  float go;  // gradient of output g of sample r
 };
 
 template <bool kBone>
 __device__ __forceinline__ void load_in(const float2 *feat, const float *go, const int16_t *bone, int64_t S,
                                         int64_t ld, int64_t s, int g, F32In &in) {
-  s = s < S ? s : S - 1;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) in.x[j] = feat[(int64_t)(4 * g + j) * ld + s];
-  in.go = go[s];
-  in.bone = kBone ? bone[s] : 0;
-}
-
-// acc + the products of four k-steps.
-__device__ __forceinline__ f32x4 mfma4x4(const f32x4 &a, const f32x4 &b, f32x4 acc) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc = mfma4(a[i], b[i], acc);
-  return acc;
-}
-
-__device__ __forceinline__ f32x4 relu4(const f32x4 &z) {
-  return f32x4{relu(z[0]), relu(z[1]), relu(z[2]), relu(z[3])};
+  load_x<kBone>(feat, bone, S, ld, s, g, in.x);
+  in.go = go[s < S ? s : S - 1];
 }
 
 template <bool kBone>
@@ -374,12 +402,12 @@ __global__ void __launch_bounds__(kBwdBlock, 2) mlp_bwd_f32(const float *__restr
   float *tc = lds.t + 16 * wid + r;  // this lane's sample in row 0
   for (int64_t c0 = (int64_t)blockIdx.x * kBwdSamples; c0 < S; c0 += step, s0 += step) {  // uniform in the block
     const int64_t s = s0 + r;
-    const bool ok = s < S, use = ok && (!kBone || in.bone >= 0);
+    const bool ok = s < S, use = ok && (!kBone || in.x.bone >= 0);
     f32x4 X[2];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      X[j / 2][2 * (j % 2)] = ok ? in.x[j].x : 0.0f;
-      X[j / 2][2 * (j % 2) + 1] = ok ? in.x[j].y : 0.0f;
+      X[j / 2][2 * (j % 2)] = ok ? in.x.x[j].x : 0.0f;
+      X[j / 2][2 * (j % 2) + 1] = ok ? in.x.x[j].y : 0.0f;
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) tc[(BR_X + 8 * g + k) * LDF] = X[k / 4][k % 4];
@@ -553,22 +581,16 @@ __device__ __forceinline__ bf16x8 pack_raw(const f32x4 z[4], int c) {
   return b;
 }
 
-// The inputs of a 16-sample half tile for lane (r, g): loaded for a valid
-// sample index in any case, so that nothing branches around the loads.
 struct BfIn {
-  uint32_t x[4];  // levels 4g .. 4g + 3 of sample r
-  float go;       // gradient of output g of sample r
-  int bone;
+  BfX x;
+  float go;  // gradient of output g of sample r
 };
 
 template <bool kBone>
 __device__ __forceinline__ void load_half(const uint32_t *feat, const float *go, const int16_t *bone, int64_t S,
                                           int64_t ld, int64_t s, int g, BfIn &in) {
-  s = s < S ? s : S - 1;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) in.x[j] = feat[(int64_t)(4 * g + j) * ld + s];
-  in.go = go[s];
-  in.bone = kBone ? bone[s] : 0;
+  load_x<kBone>(feat, bone, S, ld, s, g, in.x);
+  in.go = go[s < S ? s : S - 1];
 }
 
 // Values of four consecutive samples of a neuron, as BF16.
@@ -653,11 +675,11 @@ __global__ void __launch_bounds__(kBwdBlock, 2) mlp_bwd_bf16(const float *__rest
   const int col = 16 * wid + 4 * g;  // of the transposed products' samples
   for (int64_t b0 = (int64_t)blockIdx.x * kBwdSamples; b0 < S; b0 += step, s0 += step) {  // uniform in the block
     const int64_t s = s0 + r;
-    const bool ok = s < S, use = ok && (!kBone || in.bone >= 0);
+    const bool ok = s < S, use = ok && (!kBone || in.x.bone >= 0);
     bf16x8 X;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint32_t v = ok ? in.x[j] : 0u;
+      const uint32_t v = ok ? in.x.x[j] : 0u;
       X[2 * j] = __builtin_bit_cast(__bf16, (uint16_t)(v & 0xffffu));
       X[2 * j + 1] = __builtin_bit_cast(__bf16, (uint16_t)(v >> 16));
       lds.t[(BR_X + 8 * g + 2 * j) * LDB + 16 * wid + r] = X[2 * j];
@@ -838,11 +860,11 @@ int bwd_blocks(int64_t S, int per_cu) {
   return b > most ? (int)most : (b < 1 ? 1 : (int)b);
 }
 
-// as many blocks as stay resident (2 waves per SIMD by registers): each
-// wave then loops over its tiles with the next tile's loads in flight
-// workgroups per CU the forward kernels keep resident: two for FP32 (256
-// registers a lane), four for BF16 (fragments in LDS, 100 registers)
-unsigned fwd_blocks(int64_t S, int per_cu) { return grid_for(ceil_div(S, 16) * 64, kFwdBlock, 256 * per_cu); }
+// as many workgroups as stay resident, each wave looping over its tiles with
+// the next tiles' loads in flight: two per CU for FP32 (180 registers a lane),
+// four for BF16 (seven, which its 72 registers would allow, took 13.2 us for
+// 262,143 samples against 12.0)
+unsigned fwd_blocks(int64_t S, int per_cu) { return grid_for(ceil_div(S, 16) * 64, kMlpBlock, 256 * per_cu); }
 
 }  // namespace
 
@@ -874,10 +896,11 @@ extern "C" int32_t ia355_mlp_fwd(const void *feat, int32_t feat_dtype, const int
   if (S == 0) return IA355_OK;
   hipStream_t s = as_stream(stream);
   if (dtype == IA355_F32)
-    mlp_fwd_f32<<<fwd_blocks(S, 2), kFwdBlock, 0, s>>>((const float *)feat, bone, S, S_dev, ld, params, sigma, rgb);
+    (bone ? mlp_fwd_f32<true> : mlp_fwd_f32<false>)<<<fwd_blocks(S, 2), kMlpBlock, 0, s>>>(
+        (const float *)feat, bone, S, S_dev, ld, params, sigma, rgb);
   else
-    mlp_fwd_bf16<<<fwd_blocks(S, 4), kFwdBlock, 0, s>>>((const __hip_bfloat16 *)feat, bone, S, S_dev, ld, params, sigma,
-                                                     rgb);
+    (bone ? mlp_fwd_bf16<true> : mlp_fwd_bf16<false>)<<<fwd_blocks(S, 4), kMlpBlock, 0, s>>>(
+        (const __hip_bfloat16 *)feat, bone, S, S_dev, ld, params, sigma, rgb);
   return launch_status();
 }
 

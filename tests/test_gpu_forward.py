@@ -351,6 +351,40 @@ def test_mlp_fwd_bf16(orc):
     assert e_c.mean() < 1e-3 and e_s.mean() < 2e-3
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("S,cap", [(1, 1), (65, 80), (131100, 131107), (0, 70)])
+def test_mlp_fwd_ragged(orc, S, cap, dtype):
+    """Ragged ends of the 16-sample tiles and of the waves' rounds, with
+    padding rows, invalid samples and a device count below the capacity.
+    Features, weights and biases are small multiples of powers of two, so the
+    hidden layers are exact and both sides store the same activations; the
+    outputs differ by the FP32 sums of 65 terms (each rounding at most 2^-24
+    of the terms' magnitudes) and a few roundings of the exponential."""
+    from tests import bounds
+    K = _K()
+    rng = np.random.default_rng(S + 9)
+    ld = cap + 3
+    feat = np.full((cap, 32), np.nan, np.float32)  # past the count: not to be used
+    feat[:S] = rng.integers(-8, 9, (S, 32)) / 8
+    params = np.concatenate([rng.integers(-4, 5, k) / q for k, q in
+                             [(2048, 16), (64, 8), (4096, 64), (64, 8), (256, 16), (4, 8)]]).astype(np.float32)
+    bone = np.where(rng.uniform(size=cap) < 0.2, -1, 1).astype(np.int16)
+    b16 = dtype == "bf16"
+    sigma, rgb = torch.full((ld,), 9.0, device=dev()), torch.full((3, ld), 9.0, device=dev())
+    Sd = None if cap == S else torch.tensor([S], dtype=torch.int64, device=dev())
+    K.mlp_fwd(feat_dev(feat, ld, torch.bfloat16 if b16 else torch.float32), up(bone), cap, ld, up(params),
+              K.BF16 if b16 else K.F32, sigma, rgb, S_dev=Sd)
+    torch.cuda.synchronize()
+    assert (host(sigma)[S:] == 9.0).all() and (host(rgb)[:, S:] == 9.0).all()
+    if S == 0:
+        return
+    s_ref, c_ref = orc.mlp_fwd(feat[:S], params, valid=bone[:S], bf16=b16)
+    om = 70 * 2.0 ** -24 * bounds.mlp_fwd_magnitude(np.abs(feat[:S]), params)
+    es, ec = np.abs(host(sigma)[:S] - s_ref), np.abs(host(rgb)[:, :S].T - c_ref)
+    assert (es <= s_ref * (om[:, 0] + 2.0 ** -21)).all()
+    assert (ec <= om[:, 1:] / 4 + 2.0 ** -22).all()
+
+
 def test_volrender_fwd(orc):
     K = _K()
     w = synth.train_step()
