@@ -174,10 +174,14 @@ __global__ void __launch_bounds__(kMlpBlock, 2) mlp_fwd_f32(const float *__restr
   }
 }
 
-// BF16: the weights in LDS, read as each MFMA needs them (held in registers
-// they cost 90 a lane, two waves per SIMD).  1,000,003 samples: 27 us;
-// with branches around the loads, serial waits in the weights' staging and
-// sixteen lanes computing the four outputs of their samples 35 us.
+// BF16: the weights in LDS, read as the MFMAs need them (held in registers
+// they cost 90 a lane, two waves per SIMD), each read serving kBfTiles tiles:
+// with one, the 22 16-byte reads of a tile took two thirds of the time.
+// 1,000,003 samples: 24 us (one tile a read: 27); with branches around the
+// loads, serial waits in the weights' staging and sixteen lanes computing the
+// four outputs of their samples 35 us.
+constexpr int kBfTiles = 2;
+
 struct BfX {
   uint32_t x[4];  // levels 4g .. 4g + 3 of sample r
   int16_t bone;
@@ -246,49 +250,66 @@ __global__ void __launch_bounds__(kMlpBlock, 4) mlp_fwd_bf16(const __hip_bfloat1
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   S = count_of(S, S_dev);
-  const int64_t ntile = ceil_div(S, 16), wstride = (int64_t)gridDim.x * (kMlpBlock / 64);
-  int64_t tile = (int64_t)blockIdx.x * (kMlpBlock / 64) + wid;
-  if ((int64_t)blockIdx.x * (kMlpBlock / 64) >= ntile) return;  // the whole block (before the barrier)
+  const int64_t nstep = ceil_div(S, 16 * kBfTiles), wstride = (int64_t)gridDim.x * (kMlpBlock / 64);
+  int64_t st = (int64_t)blockIdx.x * (kMlpBlock / 64) + wid;
+  if ((int64_t)blockIdx.x * (kMlpBlock / 64) >= nstep) return;  // the whole block (before the barrier)
   const uint32_t *feat = reinterpret_cast<const uint32_t *>(featb);
-  BfX in[kFwdPre];
+  BfX in[kBfTiles];
 #pragma unroll
-  for (int u = 0; u < kFwdPre; ++u) load_x<kBone>(feat, bone, S, ld, (tile + u * wstride) * 16 + r, g, in[u]);
+  for (int u = 0; u < kBfTiles; ++u) load_x<kBone>(feat, bone, S, ld, (st * kBfTiles + u) * 16 + r, g, in[u]);
   stage_frag_spread(P, sF);
   __syncthreads();
   const LdsW w{sF, lane, g};
   const float b3 = sF.b3[g];
   float *out = g == 0 ? sigma : rgb + (g - 1) * ld;
-  for (; tile < ntile; tile += kFwdPre * wstride) {
+  for (; st < nstep; st += wstride) {
+    bf16x8 X[kBfTiles], ha[kBfTiles], hb[kBfTiles];
+    bool use[kBfTiles];
 #pragma unroll
-    for (int u = 0; u < kFwdPre; ++u) {
-      if (tile + u * wstride >= ntile) break;
-      const int64_t s = (tile + u * wstride) * 16 + r;
-      const bool ok = s < S;
-      bf16x8 X;
+    for (int u = 0; u < kBfTiles; ++u) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        X[2 * j] = __builtin_bit_cast(__bf16, (uint16_t)(in[u].x[j] & 0xffffu));
-        X[2 * j + 1] = __builtin_bit_cast(__bf16, (uint16_t)(in[u].x[j] >> 16));
+        X[u][2 * j] = __builtin_bit_cast(__bf16, (uint16_t)(in[u].x[j] & 0xffffu));
+        X[u][2 * j + 1] = __builtin_bit_cast(__bf16, (uint16_t)(in[u].x[j] >> 16));
       }
-      const bool use = !kBone || in[u].bone >= 0;
-      pin_in_loop();
-      f32x4 z[4];
+      use[u] = !kBone || in[u].bone >= 0;
+    }
+    pin_in_loop();
+    f32x4 z[kBfTiles][4], o[kBfTiles];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) z[mt] = mfma32(w.w1(mt), X, w.b1(mt));
-      // only now, into the registers that the first layer has read
-      __builtin_amdgcn_sched_barrier(0);
-      load_x<kBone>(feat, bone, S, ld, s + kFwdPre * wstride * 16, g, in[u]);
-      const bf16x8 h1a = pack_act(z, 0), h1b = pack_act(z, 1);
+    for (int mt = 0; mt < 4; ++mt) {
+      const bf16x8 a = w.w1(mt);
+      const f32x4 b = w.b1(mt);
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        z[mt] = mfma32(w.w2(mt, 0), h1a, w.b2(mt));
-        z[mt] = mfma32(w.w2(mt, 1), h1b, z[mt]);
-      }
-      f32x4 o = {b3, 0.0f, 0.0f, 0.0f};
-      o = mfma32(w.w3(0), pack_act(z, 0), o);
-      o = mfma32(w.w3(1), pack_act(z, 1), o);
-      const float v = head_lane(g, o[0]);
-      if (ok) out[s] = use ? v : 0.0f;
+      for (int u = 0; u < kBfTiles; ++u) z[u][mt] = mfma32(a, X[u], b);
+    }
+    // only now, into the registers that the first layer has read
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < kBfTiles; ++u) {
+      load_x<kBone>(feat, bone, S, ld, ((st + wstride) * kBfTiles + u) * 16 + r, g, in[u]);
+      ha[u] = pack_act(z[u], 0);
+      hb[u] = pack_act(z[u], 1);
+      o[u] = f32x4{b3, 0.0f, 0.0f, 0.0f};
+    }
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      const bf16x8 a0 = w.w2(mt, 0), a1 = w.w2(mt, 1);
+      const f32x4 b = w.b2(mt);
+#pragma unroll
+      for (int u = 0; u < kBfTiles; ++u) z[u][mt] = mfma32(a1, hb[u], mfma32(a0, ha[u], b));
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const bf16x8 a = w.w3(c);
+#pragma unroll
+      for (int u = 0; u < kBfTiles; ++u) o[u] = mfma32(a, pack_act(z[u], c), o[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kBfTiles; ++u) {
+      const int64_t s = (st * kBfTiles + u) * 16 + r;
+      const float v = head_lane(g, o[u][0]);
+      if (s < S) out[s] = use[u] ? v : 0.0f;
     }
   }
 }
@@ -899,7 +920,7 @@ extern "C" int32_t ia355_mlp_fwd(const void *feat, int32_t feat_dtype, const int
     (bone ? mlp_fwd_f32<true> : mlp_fwd_f32<false>)<<<fwd_blocks(S, 2), kMlpBlock, 0, s>>>(
         (const float *)feat, bone, S, S_dev, ld, params, sigma, rgb);
   else
-    (bone ? mlp_fwd_bf16<true> : mlp_fwd_bf16<false>)<<<fwd_blocks(S, 4), kMlpBlock, 0, s>>>(
+    (bone ? mlp_fwd_bf16<true> : mlp_fwd_bf16<false>)<<<fwd_blocks(ceil_div(S, kBfTiles), 4), kMlpBlock, 0, s>>>(
         (const __hip_bfloat16 *)feat, bone, S, S_dev, ld, params, sigma, rgb);
   return launch_status();
 }
