@@ -61,6 +61,7 @@ __device__ __forceinline__ void fold_pose(const float *P, const Layout &l, const
   const int np = 6 * nb;
   float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
   int i = q;
+#pragma unroll 3
   for (; i + 12 < np; i += 16) {
     a0 += wrow[i] * pose[i];
     a1 += wrow[i + 4] * pose[i + 4];
@@ -150,6 +151,42 @@ __device__ __forceinline__ bf16x8 frag_bf(const float *P, const Layout &l, int q
   return v;
 }
 
+// The argmax bone (ties: the lowest) and the three offsets of a tile from its
+// outputs o (lane r + 16 g holds outputs 16 mt + 4 g + i of sample r), in every
+// lane of sample r: bones are the outputs below nb, offsets the three after.
+// Selects, not branches: the wave runs both sides of nearly every comparison.
+__device__ __forceinline__ void pick(const f32x4 o[2], int nb, int g, int *bone, float off_out[3]) {
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int idx = 16 * mt + 4 * g + i;
+      const float v = o[mt][i];
+      const bool take = (idx < nb) & ((v > best) | ((v == best) & (idx < bi)));
+      best = take ? v : best;
+      bi = take ? idx : bi;
+    }
+#pragma unroll
+  for (int m = 16; m < 64; m <<= 1) {
+    const float v2 = __shfl_xor(best, m, 64);
+    const int i2 = __shfl_xor(bi, m, 64);
+    const bool take = (v2 > best) | ((v2 == best) & (i2 < bi));
+    best = take ? v2 : best;
+    bi = take ? i2 : bi;
+  }
+  *bone = bi;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int k = nb + a, sel = 4 * (k >> 4) + (k & 3);  // uniform
+    float v = o[0][0];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) v = sel == q ? o[q / 4][q % 4] : v;
+    off_out[a] = 0.0f + __shfl(v, (int)(threadIdx.x & 15) + 16 * ((k >> 2) & 3), 64);
+  }
+}
+
 // Layers 2-3 and the argmax of one 16-sample tile from the layer-1
 // activations h1 (lane r + 16 g holds neurons 16t + 4g + i of sample r),
 // with the weight fragments from a source: w.w2f(mt, k) / w.w3f(mt, k)
@@ -205,39 +242,12 @@ __device__ __forceinline__ void tile_tail(const float h1[4][4], const WSrc &w, i
       o[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w3b(mt, 1), hb, acc, 0, 0, 0);
     }
   }
-  // argmax over the bone logits (output index 16 mt + 4 g + i < nb), ties to
-  // the lowest index; offsets are outputs nb, nb + 1, nb + 2
-  float best = -INFINITY, off[3] = {0.0f, 0.0f, 0.0f};
-  int bi = 0x7fffffff;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = 16 * mt + 4 * g + i;
-      const float v = o[mt][i];
-      if (idx < nb && (v > best || (v == best && idx < bi))) {
-        best = v;
-        bi = idx;
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-        if (idx == nb + a) off[a] = v;
-    }
-#pragma unroll
-  for (int m = 16; m < 64; m <<= 1) {
-    const float v2 = __shfl_xor(best, m, 64);
-    const int i2 = __shfl_xor(bi, m, 64);
-    if (v2 > best || (v2 == best && i2 < bi)) {
-      best = v2;
-      bi = i2;
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) off[a] += __shfl_xor(off[a], m, 64);
-  }
-  *bone = bi;
-  off_out[0] = off[0];
-  off_out[1] = off[1];
-  off_out[2] = off[2];
+  pick(o, nb, g, bone, off_out);
+}
+
+// Layer 1's neuron with constant c and x weights w at point x.
+__device__ __forceinline__ float neuron1(const float x[3], float c, const float *w) {
+  return relu(c + w[0] * x[0] + w[1] * x[1] + w[2] * x[2]);
 }
 
 // Layer 1 on the VALU: lane r + 16 g holds neurons 16t + 4g + i of sample
@@ -248,7 +258,7 @@ __device__ __forceinline__ void layer1(const float x[3], const float *c1, const 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int n = 16 * t + 4 * g + i;
-      h1[t][i] = relu(c1[n] + w1x[3 * n] * x[0] + w1x[3 * n + 1] * x[1] + w1x[3 * n + 2] * x[2]);
+      h1[t][i] = neuron1(x, c1[n], w1x + 3 * n);
     }
 }
 
@@ -284,30 +294,46 @@ struct LdsFragW {
   __device__ __forceinline__ f32x4 b3(int mt) const { return *reinterpret_cast<const f32x4 *>(rb3 + 16 * mt + 4 * g); }
 };
 
-// The block fills an LdsFragW's arrays from the parameters P (global
-// memory), one fragment per thread at a time.
+// A block of 256 threads fills an LdsFragW's arrays from the parameters P
+// (global memory), three fragments a thread.
 __device__ __forceinline__ void stage_frag_lds(const float *__restrict__ P, const Layout &l, bf16x8 (*rw)[kWave],
                                                float *rb2, float *rb3) {
+  constexpr int kPer = 3;
   // a fragment's elements j = 0..3 and 4..7 are consecutive parameters at
-  // 16-byte aligned offsets: two 16-byte loads when P is 16-byte aligned
-  const bool al = ((uintptr_t)P & 15) == 0;
-  for (int e = threadIdx.x; e < 12 * kWave; e += blockDim.x) {
-    const int q = e / kWave, ln = e % kWave, r = ln & 15, g = ln >> 4;
-    if (al) {
-      bf16x8 v;
+  // 16-byte aligned offsets: two 16-byte loads when P is 16-byte aligned, all
+  // in flight before the first is used
+  if (((uintptr_t)P & 15) == 0) {
+    float4 v[kPer][2];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
+        const int e = threadIdx.x + 256 * k, q = e / kWave, r = e & 15, g = (e >> 4) & 3;
         const int i = q < 8 ? w2b_at(l, q / 2, q % 2, 4 * h, r, g) : w3b_at(l, (q - 8) / 2, q % 2, 4 * h, r, g);
-        const float4 p4 = i >= 0 ? *reinterpret_cast<const float4 *>(P + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        v[4 * h] = (__bf16)p4.x;
-        v[4 * h + 1] = (__bf16)p4.y;
-        v[4 * h + 2] = (__bf16)p4.z;
-        v[4 * h + 3] = (__bf16)p4.w;
+        v[k][h] = *reinterpret_cast<const float4 *>(P + (i >= 0 ? i : 0));
       }
-      rw[q][ln] = v;
-    } else {
-      rw[q][ln] = frag_bf(P, l, q, r, g);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        asm volatile("" : "+v"(v[k][h].x), "+v"(v[k][h].y), "+v"(v[k][h].z), "+v"(v[k][h].w));
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int e = threadIdx.x + 256 * k, q = e / kWave, r = e & 15;
+      const bool row = q < 8 || 16 * ((q - 8) / 2) + r < l.nout;  // else a padded row
+      bf16x8 f;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        f[4 * h] = (__bf16)(row ? v[k][h].x : 0.0f);
+        f[4 * h + 1] = (__bf16)(row ? v[k][h].y : 0.0f);
+        f[4 * h + 2] = (__bf16)(row ? v[k][h].z : 0.0f);
+        f[4 * h + 3] = (__bf16)(row ? v[k][h].w : 0.0f);
+      }
+      rw[q][e % kWave] = f;
     }
+  } else {
+    for (int e = threadIdx.x; e < 12 * kWave; e += 256)
+      rw[e / kWave][e % kWave] = frag_bf(P, l, e / kWave, e & 15, (e >> 4) & 3);
   }
   for (int i = threadIdx.x; i < H; i += blockDim.x) rb2[i] = P[l.offb2 + i];
   for (int i = threadIdx.x; i < kMaxOut; i += blockDim.x) rb3[i] = i < l.nout ? P[l.offb3 + i] : 0.0f;

@@ -48,6 +48,44 @@ def test_rootinit_fwd(orc, dtype):
         assert np.abs(gx - rx0)[agree].mean() < 1e-2
 
 
+@pytest.mark.parametrize("nb", [1, 13, 14, 29])
+def test_rootinit_bones_and_ragged(orc, nb):
+    """Bone counts whose offsets lie in one or both output tiles, up to the
+    most; the FP32 form against the oracle (the bars of the test above), and
+    the BF16 form on ragged counts bit-equal to the first samples of a longer
+    call (samples are independent), writing nothing past the count."""
+    K = _K()
+    rng = np.random.default_rng(nb)
+    w = synth.train_step()
+    S = 700
+    xp = rng.uniform(0.2, 0.8, (S, 3)).astype(np.float32)
+    B = np.ascontiguousarray(np.resize(w.B, (nb, 3, 4))).astype(np.float32)
+    pose = rng.normal(0, 0.3, (nb, 6)).astype(np.float32)
+    nin, nout = 3 + 6 * nb, nb + 3
+    params = np.concatenate([rng.normal(0, 1 / np.sqrt(a), a * b).tolist() + rng.normal(0, 0.1, b).tolist()
+                             for a, b in [(nin, 64), (64, 64), (64, nout)]]).astype(np.float32)
+
+    def run(n, dtype, cap=None):
+        cap = n if cap is None else cap
+        bone = torch.full((S,), -7, dtype=torch.int16, device=dev())
+        x0 = torch.full((3, S), -7.0, device=dev())
+        Sd = None if cap == n else torch.tensor([n], dtype=torch.int64, device=dev())
+        K.rootinit_fwd(soa(xp), cap, S, up(pose.reshape(-1)), up(params), up(B), dtype, bone, x0, S_dev=Sd)
+        torch.cuda.synchronize()
+        return host(bone).astype(int), host(x0)
+
+    gb, gx = run(S, K.F32)
+    rb, rx0 = orc.rootinit_fwd(xp, pose, params, B)
+    agree = gb == rb
+    assert agree.mean() > 0.99
+    assert_mixed(gx.T[agree], rx0[agree], 1e-5, "x0")
+    fb, fx = run(S, K.BF16)
+    for n, cap in [(1, None), (15, None), (63, None), (64, None), (65, None), (321, None), (130, S), (0, S)]:
+        b, x = run(n, K.BF16, cap)
+        assert np.array_equal(b[:n], fb[:n]) and np.array_equal(x[:, :n], fx[:, :n]), n
+        assert (b[n:] == -7).all() and (x[:, n:] == -7.0).all(), n
+
+
 def test_rootinit_bf16_unaligned_params():
     """BF16 initialiser with its parameter block at an address that is not a
     multiple of 16 bytes (the fragments are then gathered one value at a
