@@ -243,7 +243,7 @@ __global__ void __launch_bounds__(kSolveBlock) fallback_kernel(
 //         (y_b = B_b x*_h), v = J^{-T} dL/dx*; dL/dx' = v.
 //  ift_q: accumulates the per-vertex moment
 //         Q_v = sum_s tri_v(x*_s) v_s x*_h,s^T   (3 x 4 per vertex)
-//         with FP32 atomics laid out for few cache lines per instruction
+//         over the samples of a cell, then with FP32 atomics
 //         (12 floats per corner instead of the 24-bone products).  Both
 //         parameter gradients are contractions of Q:
 //           dL/dW[v][b] = -sum_ij B_b[i][j] Q_v[i][j]
@@ -254,7 +254,6 @@ __global__ void __launch_bounds__(kSolveBlock) fallback_kernel(
 // ------------------------------------------------------------------------
 constexpr int kBwdBlock = 256;
 constexpr int kMaxBonesBwd = 32;  // skinning weights of one sample kept in registers
-constexpr int kOwnBlock = 256;
 
 __device__ __forceinline__ void ift_v_one(const float *__restrict__ gxc, const float *__restrict__ xc_soa,
                                           const int16_t *__restrict__ bone, int64_t n, int64_t S, int64_t ld,
@@ -349,75 +348,103 @@ __global__ void __launch_bounds__(kBwdBlock) ift_v_kernel(const float *__restric
 }
 
 
-// Q_v += tri_v(x*) v x*_h^T: 64 lanes per sample, lane = 8 * corner + slot,
-// slots j and j + 8 (< 12) of the corner's 12 floats.  A corner's 12 floats
-// are 48 contiguous bytes and x-neighbouring corners are adjacent vertices,
-// so each wave instruction touches about four cache lines (FP32 atomics to
-// random lines are limited by L2 requests, not by floats).  A wave takes
-// kQRun consecutive samples in turn (samples of a ray follow each other, and
-// neighbouring samples often share a skinning-grid cell): contributions are
-// summed in registers while the cell stays the same and added to Q when it
-// changes, which saves the atomics of the repeats.
-constexpr int kQRun = 8;
+// Q_v += tri_v(x*) v x*_h^T, summed over the samples of a cell first: FP32
+// atomics to Q take the time (they are limited by requests, not by floats),
+// and samples of a ray or of neighbouring pixels share cells.  A workgroup
+// groups kQSet samples by cell in LDS (a hash table gives each cell a slot and
+// each sample a rank in it, a scan the places), then a wave takes a cell at a
+// time: 64 lanes, lane = 8 corner + slot, slots j and j + 8 (< 12) of the
+// corner's 12 floats, over the cell's samples, and two atomic instructions.  A
+// corner's 12 floats are 48 contiguous bytes and x-neighbouring corners are
+// adjacent vertices, so each touches about four cache lines.
+// 36,503 samples on a surface, 19 cells in 64: 17 us (sets of 256, 58 cells:
+// 16); in the captured step of 8,192 random rays, 51 cells in 64, the step
+// takes 306 us (sets of 256: 309).  Eight consecutive samples a wave, summed
+// while their cell stayed the same, took 46 us and a step of 310.
+constexpr int kQSet = 64;
+constexpr int kQTable = 128;
+constexpr int kQBlock = 256;
+static_assert(kQSet % kWave == 0 && kQTable == 2 * kQSet, "the first kQSet threads take a sample and two slots each");
 
-__global__ void __launch_bounds__(kOwnBlock) ift_q_kernel(const float *__restrict__ xc_soa,
+__global__ void __launch_bounds__(kQBlock) ift_q_kernel(const float *__restrict__ xc_soa,
                                                         const int16_t *__restrict__ bone, const float *__restrict__ vbuf,
                                                         int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
                                                         Grid gr, float *__restrict__ Q) {
+  __shared__ int key[kQTable], count[kQTable], place[kQTable];
+  __shared__ int cell_slot[kQSet], wsum[2][kQSet / kWave];
+  __shared__ __attribute__((aligned(16))) float rec[kQSet][12];  // x_h, v, the cell fractions, padding
   const int64_t Sn = count_of(S, S_dev);
-  const int lane = (int)(threadIdx.x & 63), k = lane >> 3, j = lane & 7;
-  constexpr int kWaves = kOwnBlock / 64;
-  const int64_t nruns = ceil_div(Sn, (int64_t)kQRun);
-  for (int64_t run = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6); run < nruns;
-       run += (int64_t)gridDim.x * kWaves) {
-    // lane i < kQRun loads sample n0 + i; the samples are then taken in turn
-    const int64_t n0 = run * kQRun;
-    int lb = -1;
-    float lx[3] = {0.0f, 0.0f, 0.0f}, lv[3] = {0.0f, 0.0f, 0.0f};
-    if (lane < kQRun && n0 + lane < Sn) {
-      const int64_t n = n0 + lane;
-      lb = bone[n];
-      lx[0] = xc_soa[n];
-      lx[1] = xc_soa[ld + n];
-      lx[2] = xc_soa[2 * ld + n];
-      lv[0] = vbuf[n];
-      lv[1] = vbuf[S + n];
-      lv[2] = vbuf[2 * S + n];
+  const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int k = lane >> 3, j = lane & 7;
+  uint32_t corner = 0;  // of corner k's moment, in floats
+#pragma unroll
+  for (int c = 1; c < 8; ++c) corner = k == c ? gr.dc[c] / 4u : corner;
+  for (int64_t n0 = (int64_t)blockIdx.x * kQSet; n0 < Sn; n0 += (int64_t)gridDim.x * kQSet) {
+    const int64_t m = n0 + tid, n = m < Sn ? m : Sn - 1;
+    const bool use = tid < kQSet && m < Sn && bone[n] >= 0;
+    const float x[3] = {xc_soa[n], xc_soa[ld + n], xc_soa[2 * ld + n]};
+    const float v[3] = {vbuf[n], vbuf[S + n], vbuf[2 * S + n]};
+    for (int h = tid; h < kQTable; h += kQBlock) {
+      key[h] = -1;
+      count[h] = 0;
     }
-    int64_t cur = -1, cur_vtx = 0;
-    float a0 = 0.0f, a1 = 0.0f;
-    for (int i = 0; i < kQRun; ++i) {
-      if (__shfl(lb, i, kWave) < 0) continue;  // wave-uniform: invalid or past the count
-      const float x[3] = {__shfl(lx[0], i, kWave), __shfl(lx[1], i, kWave), __shfl(lx[2], i, kWave)};
-      const float v[3] = {__shfl(lv[0], i, kWave), __shfl(lv[1], i, kWave), __shfl(lv[2], i, kWave)};
-      const Cell c = locate(gr, x);
-      const int64_t base = ((int64_t)c.i0[2] * gr.D[1] + c.i0[1]) * gr.D[0] + c.i0[0];
-      const int64_t vtx = ((int64_t)(c.i0[2] + ((k >> 2) & 1)) * gr.D[1] + (c.i0[1] + ((k >> 1) & 1))) * gr.D[0] +
-                          (c.i0[0] + (k & 1));
-      const float tw = tri_weight(c.f, k);
-      const float xh[4] = {x[0], x[1], x[2], 1.0f};
-      const float c0 = tw * v[j >> 2] * xh[j & 3];
-      const float c1 = j < 4 ? tw * v[2] * xh[j] : 0.0f;
-      if (base != cur) {  // wave-uniform
-        if (cur >= 0) {
-          float *q = Q + 12 * cur_vtx;
-          atomicAdd(q + j, a0);
-          if (j < 4) atomicAdd(q + 8 + j, a1);
-        }
-        cur = base;
-        cur_vtx = vtx;
-        a0 = c0;
-        a1 = c1;
-      } else {
-        a0 += c0;
-        a1 += c1;
+    __syncthreads();
+    const Cell c = locate(gr, x);
+    const int cell = (c.i0[2] * gr.D[1] + c.i0[1]) * gr.D[0] + c.i0[0];
+    int slot = (int)(((uint32_t)cell * 2654435761u) >> 25), rank = 0;
+    if (use) {
+      for (;;) {  // at most kQSet of the slots are taken
+        const int was = atomicCAS(&key[slot], -1, cell);
+        if (was == -1 || was == cell) break;
+        slot = (slot + 1) & (kQTable - 1);
       }
+      rank = atomicAdd(&count[slot], 1);
     }
-    if (cur >= 0) {
-      float *q = Q + 12 * cur_vtx;
+    __syncthreads();
+    // samples and cells before each slot (two slots a thread)
+    const bool two = tid < kQSet;
+    const int ca = two ? count[2 * tid] : 0, cb = two ? count[2 * tid + 1] : 0, sl = (ca != 0) + (cb != 0);
+    const int incl = wave_incl_scan(ca + cb), sincl = wave_incl_scan(sl);
+    if (two && lane == kWave - 1) {
+      wsum[0][wid] = incl;
+      wsum[1][wid] = sincl;
+    }
+    __syncthreads();
+    int before = incl - ca - cb, cells = sincl - sl, ncell = 0;
+#pragma unroll
+    for (int w = 0; w < kQSet / kWave; ++w) {
+      before += w < wid ? wsum[0][w] : 0;
+      cells += w < wid ? wsum[1][w] : 0;
+      ncell += wsum[1][w];
+    }
+    if (two) {
+      place[2 * tid] = before;
+      place[2 * tid + 1] = before + ca;
+    }
+    if (ca != 0) cell_slot[cells++] = 2 * tid;
+    if (cb != 0) cell_slot[cells] = 2 * tid + 1;
+    __syncthreads();
+    if (use) {
+      float4 *d = reinterpret_cast<float4 *>(rec[place[slot] + rank]);
+      d[0] = make_float4(x[0], x[1], x[2], 1.0f);
+      d[1] = make_float4(v[0], v[1], v[2], c.f[0]);
+      d[2] = make_float4(c.f[1], c.f[2], 0.0f, 0.0f);
+    }
+    __syncthreads();
+    for (int e = wid; e < ncell; e += kQBlock / kWave) {
+      const int h = cell_slot[e], first = place[h], last = first + count[h];
+      float a0 = 0.0f, a1 = 0.0f;
+      for (int s = first; s < last; ++s) {
+        const float *p = rec[s];
+        const float tw = tri_weight(p + 7, k);
+        a0 += tw * p[4 + (j >> 2)] * p[j & 3];
+        a1 += tw * p[6] * p[j & 3];
+      }
+      float *q = Q + 12 * (int64_t)key[h] + corner;
       atomicAdd(q + j, a0);
       if (j < 4) atomicAdd(q + 8 + j, a1);
     }
+    __syncthreads();  // the tables are cleared for the next set
   }
 }
 
@@ -761,9 +788,8 @@ extern "C" int32_t ia355_snarf_deform_bwd(const float *grad_xc, const float *xc,
       if (st != IA355_OK) return st;
     }
     if (S > 0)
-      ift_q_kernel<<<stride_grid(ceil_div(ceil_div(S, kQRun) * 64, kOwnBlock), S_dev != nullptr, 8192), kOwnBlock, 0,
-                     s>>>(
-          xc, bone, vbuf, S, S_dev, ld, g, Q);
+      ift_q_kernel<<<stride_grid(ceil_div(S, (int64_t)kQSet), S_dev != nullptr), kQBlock, 0, s>>>(xc, bone, vbuf, S,
+                                                                                                   S_dev, ld, g, Q);
     ift_contract_kernel<<<(unsigned)nblk, kConThreads, 0, s>>>(Q, B, nb, W, nvert, grad_W, grad_B ? partB : nullptr,
                                                                overwrite);
     if (grad_B)

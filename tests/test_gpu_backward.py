@@ -237,6 +237,35 @@ def test_deform_bwd(orc):
           f"grad_W {e3:.2e} of its bound, norm-wise {e5:.2e}")
 
 
+@pytest.mark.parametrize("S,count,span", [(1, None, 0.4), (63, None, 0.0), (65, 64, 0.004), (300, None, 0.03),
+                                          (300, 129, 0.4), (70, 0, 0.4)])
+def test_deform_bwd_cells(orc, S, count, span):
+    """The grouping of samples by cell: ragged sets of 64, all samples in one
+    cell, in a few, in as many as samples, invalid ones, a device count below
+    the capacity.  The bars of the test above."""
+    K = _K()
+    w = synth.train_step()
+    rng = np.random.default_rng(S + int(1000 * span))
+    xc = (np.array([0.504, 0.504, 0.504]) + rng.uniform(-span, span, (S, 3)) * [1, 1, 0.5]).astype(np.float32)
+    u = rng.normal(size=(S, 3)).astype(np.float32)
+    bone = np.where(np.arange(S) % 13 == 4, -1, 2).astype(np.int16)
+    n = S if count is None else count
+    Dz, Dy, Dx, nb = w.W.shape
+    gxp, gB, gW = (torch.full(sh, 5.0, device=dev()) for sh in ((3, S), w.B.shape, w.W.shape))
+    ws = torch.empty(K.deform_bwd_workspace_size(S, Dx, Dy, Dz, nb), dtype=torch.uint8, device=dev())
+    K.snarf_deform_bwd(soa(u), soa(xc), up(bone), S, S, up(w.B), up(w.W), w.skin_aabb, gxp, gB, gW, ws,
+                       flags=K.OVERWRITE, S_dev=None if count is None else torch.tensor([count], device=dev()))
+    torch.cuda.synchronize()
+    if n == 0:
+        assert (host(gB) == 0).all() and (host(gW) == 0).all()
+        return
+    rxp, rB, rW = orc.deform_bwd(u[:n], xc[:n], bone[:n], w.B, w.W, w.skin_aabb)
+    mag_B, mag_W, cnt_W = bounds.deform_grad_magnitude(rxp, xc[:n], bone[:n], w.B, w.W, w.skin_aabb)
+    ef = bounds.cell_fraction_error((Dx, Dy, Dz))
+    bounds.check_bound(host(gW), rW, GTOL * mag_W + ef * cnt_W + 1e-10 * GTOL * mag_W.max(), "grad_W")
+    bounds.check_scaled(host(gB), rB, mag_B, GTOL, "grad_B (of its magnitude sum)")
+
+
 def test_train_step_subset(orc):
     """A whole training step (forward, L2 loss, every backward) on 1/8 of the
     training rays: loss, colours and every gradient against the oracle.
