@@ -128,7 +128,10 @@ def lib():
 
 
 def _stream():
-    return _vp(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle, as torch.cuda.current_stream() gives it
+    (2.9 us a call, of seven in a field's forward and backward) but read
+    directly (0.2)."""
+    return _vp(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _p(t, dtype=None, name="tensor"):
