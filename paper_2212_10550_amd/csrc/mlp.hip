@@ -505,34 +505,39 @@ __global__ void __launch_bounds__(kBwdBlock, 2) mlp_bwd_f32(const float *__restr
     }
     __syncthreads();
     // weight gradients of this wave's rows, K = the block's samples (slot g of
-    // step i: sample 16k + 4g + i), each 32 samples summed from zero so that
-    // the chains of roundings stay short
+    // step i: sample 16k + 4g + i), each 32 samples summed from zero, then the
+    // two sums, so that the chains of roundings stay short
+    const float *tr = lds.t + r * LDF + 4 * g;
+    auto rows = [&](int row, int k) { return *reinterpret_cast<const f32x4 *>(tr + row * LDF + 16 * k); };
+    auto products = [&](const f32x4 v[4], int row) {
+      const f32x4 a = mfma4x4(v[1], rows(row, 1), mfma4x4(v[0], rows(row, 0), splat(0.0f)));
+      return a + mfma4x4(v[3], rows(row, 3), mfma4x4(v[2], rows(row, 2), splat(0.0f)));
+    };
+    auto sum = [](const f32x4 v[4]) {
+      float s[4];
 #pragma unroll
-    for (int k2 = 0; k2 < kBwdSamples / 32; ++k2) {
-      const float *tr = lds.t + r * LDF + 32 * k2 + 4 * g;
-      auto rows = [&](int row, int k) { return *reinterpret_cast<const f32x4 *>(tr + row * LDF + 16 * k); };
-      f32x4 v1[2], v2[2], v3[2];
+      for (int k = 0; k < 4; ++k) s[k] = (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
+      return (s[0] + s[1]) + (s[2] + s[3]);
+    };
+    static_assert(kBwdSamples == 64, "four sets of 16 samples");
+    f32x4 v[4];
 #pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        v1[k] = rows(BR_D1 + 16 * wid, k);
-        v2[k] = rows(BR_D2 + 16 * wid, k);
-        v3[k] = *reinterpret_cast<const f32x4 *>(lds.t + (BR_D3 + (r & 3)) * LDF + 32 * k2 + 4 * g + 16 * k);
-        v3[k] = r < NOUT ? v3[k] : splat(0.0f);
-      }
+    for (int k = 0; k < 4; ++k) v[k] = rows(BR_D2 + 16 * wid, k);
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        aW2[nt] += mfma4x4(v2[1], rows(BR_H1 + 16 * nt, 1), mfma4x4(v2[0], rows(BR_H1 + 16 * nt, 0), splat(0.0f)));
+    for (int nt = 0; nt < 4; ++nt) aW2[nt] += products(v, BR_H1 + 16 * nt);
+    ab2 += sum(v);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-        aW1[nt] += mfma4x4(v1[1], rows(BR_X + 16 * nt, 1), mfma4x4(v1[0], rows(BR_X + 16 * nt, 0), splat(0.0f)));
-      aW3 += mfma4x4(v3[1], rows(BR_H2 + 16 * wid, 1), mfma4x4(v3[0], rows(BR_H2 + 16 * wid, 0), splat(0.0f)));
-      auto sum8 = [](const f32x4 v[2]) {
-        return ((v[0][0] + v[0][1]) + (v[0][2] + v[0][3])) + ((v[1][0] + v[1][1]) + (v[1][2] + v[1][3]));
-      };
-      ab1 += sum8(v1);
-      ab2 += sum8(v2);
-      ab3 += sum8(v3);
+    for (int k = 0; k < 4; ++k) v[k] = rows(BR_D1 + 16 * wid, k);
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) aW1[nt] += products(v, BR_X + 16 * nt);
+    ab1 += sum(v);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = *reinterpret_cast<const f32x4 *>(lds.t + (BR_D3 + (r & 3)) * LDF + 4 * g + 16 * k);
+      v[k] = r < NOUT ? v[k] : splat(0.0f);
     }
+    aW3 += products(v, BR_H2 + 16 * wid);
+    ab3 += sum(v);
     __syncthreads();  // the tiles are written again
   }
   // the block's partial
