@@ -180,12 +180,16 @@ __global__ void __launch_bounds__(kSolveBlock) guided_kernel(
     int max_iter, float tol_stop, float tol_valid, float *__restrict__ xc_soa, int16_t *__restrict__ bone_out,
     float *__restrict__ resid_out, int16_t *__restrict__ steps_out, int32_t *__restrict__ queue,
     int32_t *__restrict__ qlen, int16_t *__restrict__ gsteps) {
+  __shared__ CellLds cells[kSolveBlock / kWave];
   const int64_t Sn = count_of(S, S_dev);
-  for (int64_t n = (int64_t)blockIdx.x * kSolveBlock + threadIdx.x; n < Sn; n += (int64_t)gridDim.x * kSolveBlock) {
+  // every lane of a block runs the same iterations (the cells are loaded by all)
+  for (int64_t n0 = (int64_t)blockIdx.x * kSolveBlock; n0 < Sn; n0 += (int64_t)gridDim.x * kSolveBlock) {
+    const int64_t m = n0 + threadIdx.x, n = m < Sn ? m : Sn - 1;
     const float xp[3] = {xp_soa[n], xp_soa[ld + n], xp_soa[2 * ld + n]};
     float x[3] = {x0_soa[n], x0_soa[ld + n], x0_soa[2 * ld + n]};
-    HeldCorners cs(A, gr);
+    SharedCorners cs(A, gr, cells[threadIdx.x / kWave]);
     const InitResult q = broyden_from(cs, gr, x, true, xp, max_iter, tol_stop);
+    if (m >= Sn) continue;
     gsteps[n] = (int16_t)q.steps;
     if (q.ok && q.r < tol_valid && in_hbox(q.x, hbox)) {
       xc_soa[n] = q.x[0];

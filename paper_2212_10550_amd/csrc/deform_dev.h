@@ -116,16 +116,27 @@ __device__ __forceinline__ uint32_t cell_base(const Grid &g, const Cell &c) {
 
 // Sources of a cell's eight corner transforms for the residuals below: start()
 // and at() name the cell (byte offset of its base vertex), corner() gives the
-// three rows of corner k.  Both sources give the same floats.
+// three rows of corner k.  at() changes the cell of the lanes with `need`; it is
+// called by the whole wave.  Every source gives the same floats.
 //  * HeldCorners keeps the last cell's 96 floats in registers and gathers
-//    only when the cell changes.  The staged kernels use it: their time went
-//    to the texture path (24 gathers of 16 bytes per residual), and Broyden's
+//    only when the cell changes.  The staged multi-init kernels use it: their
+//    time went to the texture path (24 gathers of 16 bytes per residual), and Broyden's
 //    steps shrink so fast that only the start, the first step and a fifth of
 //    the second steps reach a new cell of a 64 x 64 x 32 grid.  It costs 60
 //    to 70 registers (guided solve 91 -> 160, three waves per SIMD; multi-init
 //    solve 121 -> 176, two) and pays all the same: guided solve of 875,600
 //    samples 133 -> 76 us, multi-init solve of 36,503 samples 83 -> 72 us, of
 //    a 64^3 lattice 477 -> 398 us.
+//  * SharedCorners adds to it: the cells that a wave's lanes lack are loaded
+//    once each into LDS (24 lanes load a cell's 384 bytes directly) and read
+//    from there into the lanes' registers.  The guided solve uses it, whose 64
+//    neighbouring samples lie in few cells: 875,600 samples 75 -> 46 us, of a
+//    frame 78 -> 67.  After kCellSlots distinct cells the lanes left gather
+//    their own, so samples in random order lose no more than the first cells'
+//    search (whole guided pass 123 -> 124 us; with 24 slots 132, and 88 for
+//    either in order).  The multi-init solve starts in a different cell in
+//    nearly every lane and is bound by its arithmetic once the later cells are
+//    shared: 73 -> 77 us for 36,503 samples.
 //  * GatherCorners reads them from the blended grid each time: the persistent
 //    renderer, whose other stages leave no registers to hold a cell.
 struct GatherCorners {
@@ -134,7 +145,7 @@ struct GatherCorners {
   uint32_t base;
   __device__ __forceinline__ GatherCorners(const float *A_, const Grid &g) : A(A_), dc(g.dc), base(0) {}
   __device__ __forceinline__ void start(uint32_t b) { base = b; }
-  __device__ __forceinline__ void at(uint32_t b) { base = b; }
+  __device__ __forceinline__ void at(uint32_t b, bool need) { base = need ? b : base; }
   __device__ __forceinline__ void corner(int k, float4 r[3]) const {
     const float4 *p = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(A) + (base + dc[k]));
     r[0] = p[0];
@@ -159,13 +170,62 @@ struct HeldCorners {
       v[k][2] = p[2];
     }
   }
-  __device__ __forceinline__ void at(uint32_t b) {
-    if (b != base) start(b);
+  __device__ __forceinline__ void at(uint32_t b, bool need) {
+    if (need && b != base) start(b);
   }
   __device__ __forceinline__ void corner(int k, float4 r[3]) const {
     r[0] = v[k][0];
     r[1] = v[k][1];
     r[2] = v[k][2];
+  }
+};
+
+constexpr int kCellSlots = 12;   // distinct cells of a wave loaded through LDS at a time
+constexpr int kCellBytes = 400;  // 8 x 48, and 16 to spread the slots over the banks
+struct CellLds {
+  __attribute__((aligned(16))) unsigned char slot[kCellSlots][kCellBytes];
+};
+
+struct SharedCorners : HeldCorners {
+  CellLds &lds;   // of this wave
+  uint32_t part;  // byte offset from a cell's base vertex of the 16 bytes that this lane loads (of 24 lanes)
+  __device__ __forceinline__ SharedCorners(const float *A_, const Grid &g, CellLds &l) : HeldCorners(A_, g), lds(l) {
+    const int ln = threadIdx.x & (kWave - 1), k = ln < 24 ? ln / 3 : 0;
+    part = 16u * (uint32_t)(ln % 3);
+#pragma unroll
+    for (int c = 1; c < 8; ++c) part += k == c ? g.dc[c] : 0u;
+  }
+  __device__ __forceinline__ void start(uint32_t b) {
+    base = 0xffffffffu;
+    at(b, true);
+  }
+  __device__ __forceinline__ void at(uint32_t b, bool need) {
+    const int ln = threadIdx.x & (kWave - 1);
+    uint64_t rem = __ballot(need && b != base);
+    if (rem == 0ull) return;
+    int slot = -1;
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the slots' last readers are done
+    for (int s = 0; s < kCellSlots && rem != 0ull; ++s) {
+      const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)b, __ffsll((unsigned long long)rem) - 1);
+      const bool same = need && b == sb;
+      slot = same ? s : slot;
+      rem &= ~__ballot(same);
+      if (ln < 24)
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *)(reinterpret_cast<const char *>(A) + (sb + part)),
+            (__attribute__((address_space(3))) void *)(lds.slot[s]), 16, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    asm volatile("" ::: "memory");
+    if (slot >= 0) {
+      base = b;
+      const float4 *q = reinterpret_cast<const float4 *>(lds.slot[slot]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[k][i] = q[3 * k + i];
+    }
+    if (rem != 0ull && need) HeldCorners::at(b, true);
   }
 };
 
@@ -197,10 +257,9 @@ __device__ __forceinline__ void fma4(float t, const float4 &r, float4 &m) {
 // g = (sum_c tri_c A_c) x_h - x': the 12 blended channels are interpolated
 // first, then applied to x_h once.
 template <class Corners>
-__device__ __forceinline__ void residual(Corners &cs, const Grid &gr, const float x[3], const float xp[3], float g[3]) {
+__device__ __forceinline__ void residual(const Corners &cs, const Cell &c, const float x[3], const float xp[3],
+                                         float g[3]) {
 #pragma clang fp contract(off)
-  const Cell c = locate(gr, x);
-  cs.at(cell_base(gr, c));
   float t[8];
   tri_weights(c.f, t);
   float4 m0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), m1 = m0, m2 = m0;
@@ -298,17 +357,26 @@ __device__ __forceinline__ InitResult broyden_from(Corners &cs, const Grid &gr, 
   residual_jac(cs, gr, x, xp, g, J);
   const float detJ = inv3(J, H);
   bool ok = bone_ok && fabsf(detJ) >= 1e-12f;
-  int k = 0;
+  int steps = 0;
   const float tol2 = tol_stop * tol_stop;
-  if (ok) {
-    for (; k < max_iter; ++k) {
-      if (dot3(g[0], g[0], g[1], g[1], g[2], g[2]) < tol2) break;
-      float dx[3], xn[3], gn[3], dg[3], Hdg[3], dxH[3];
+  // the lanes iterate together (at() may need them all); run: not done yet
+  bool run = ok;
+  for (int k = 0; k < max_iter; ++k) {
+    run = run && !(dot3(g[0], g[0], g[1], g[1], g[2], g[2]) < tol2);
+    if (!__any(run)) break;
+    float dx[3], xn[3];
+    Cell c;
+    if (run) {
 #pragma unroll
       for (int a = 0; a < 3; ++a) dx[a] = -dot3(H[a][0], g[0], H[a][1], g[1], H[a][2], g[2]);
 #pragma unroll
       for (int a = 0; a < 3; ++a) xn[a] = x[a] + dx[a];
-      residual(cs, gr, xn, xp, gn);
+      c = locate(gr, xn);
+    }
+    cs.at(run ? cell_base(gr, c) : 0u, run);
+    if (run) {
+      float gn[3], dg[3], Hdg[3], dxH[3];
+      residual(cs, c, xn, xp, gn);
 #pragma unroll
       for (int a = 0; a < 3; ++a) dg[a] = gn[a] - g[a];
 #pragma unroll
@@ -321,23 +389,23 @@ __device__ __forceinline__ InitResult broyden_from(Corners &cs, const Grid &gr, 
         x[a] = xn[a];
         g[a] = gn[a];
       }
+      ++steps;
       if (fabsf(den) < 1e-30f) {
-        ok = false;
-        ++k;
-        break;
+        ok = run = false;
+      } else {
+        const float iden = __builtin_amdgcn_rcpf(den);  // 1 ulp: H is an approximation of J^-1 anyway
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int b = 0; b < 3; ++b) H[a][b] = fmaf((dx[a] - Hdg[a]) * dxH[b], iden, H[a][b]);
       }
-      const float iden = __builtin_amdgcn_rcpf(den);  // 1 ulp: H is an approximation of J^-1 anyway
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) H[a][b] = fmaf((dx[a] - Hdg[a]) * dxH[b], iden, H[a][b]);
     }
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) res.x[a] = x[a];
   res.r = norm3(g);
   res.ok = ok;
-  res.steps = k;
+  res.steps = steps;
   return res;
 }
 
@@ -370,22 +438,24 @@ __device__ __forceinline__ Choice multi_init(Corners &cs, const Grid &gr, const 
                                              int max_iter, float tol_stop, float tol_valid) {
   float best_r = INFINITY, best_x[3] = {0.0f, 0.0f, 0.0f}, x0[3] = {0.0f, 0.0f, 0.0f};
   int best = 0x7fffffff, steps = 0;
-  if (act) {
-    for (int i = j; i < nb; i += kG) {
-      const InitResult q = broyden(cs, gr, sBinv + 12 * i, sBok[i], xp, max_iter, tol_stop);
-      steps += q.steps;
-      if (i == 0) {
-        x0[0] = q.x[0];
-        x0[1] = q.x[1];
-        x0[2] = q.x[2];
-      }
-      if (q.ok && q.r < tol_valid && in_hbox(q.x, hbox) && q.r < best_r) {
-        best_r = q.r;
-        best = i;
-        best_x[0] = q.x[0];
-        best_x[1] = q.x[1];
-        best_x[2] = q.x[2];
-      }
+  // (the same number of inits for every lane: at() may need them all)
+  for (int i0 = 0; i0 < nb; i0 += kG) {
+    const bool mine = act && i0 + j < nb;
+    const int i = mine ? i0 + j : 0;
+    const InitResult q = broyden(cs, gr, sBinv + 12 * i, mine && sBok[i], xp, max_iter, tol_stop);
+    if (!mine) continue;
+    steps += q.steps;
+    if (i == 0) {
+      x0[0] = q.x[0];
+      x0[1] = q.x[1];
+      x0[2] = q.x[2];
+    }
+    if (q.ok && q.r < tol_valid && in_hbox(q.x, hbox) && q.r < best_r) {
+      best_r = q.r;
+      best = i;
+      best_x[0] = q.x[0];
+      best_x[1] = q.x[1];
+      best_x[2] = q.x[2];
     }
   }
 #pragma unroll

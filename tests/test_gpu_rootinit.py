@@ -155,6 +155,43 @@ def test_deform_guided(orc):
     print(f"guided: fallback gpu {int(nfb.item())} oracle {ofb.sum()} of {S}")
 
 
+@pytest.mark.parametrize("S,count", [(1, None), (63, None), (65, None), (1000, None), (300, 129), (70, 0)])
+def test_deform_guided_order(S, count):
+    """Samples in an order where a wave's lie in few cells (they are then
+    loaded once and shared) and in one where they do not: the same bits for
+    every sample, on ragged counts and under a device count."""
+    K = _K()
+    w = synth.train_step()
+    rng = np.random.default_rng(S)
+    skel = synth.make_skeleton(0)
+    base = synth.sample_posed_points(skel, w.B.astype(np.float64), max(S // 50, 1), 11)
+    xp = (np.repeat(base, 50 + S % 50 + 1, axis=0)[:S] + rng.uniform(-0.004, 0.004, (S, 3))).astype(np.float32)
+    x0 = (xp + rng.normal(0, 0.02, (S, 3))).astype(np.float32)
+    guide = rng.integers(0, 24, S).astype(np.int16)
+    Dz, Dy, Dx, nb = w.W.shape
+    n = S if count is None else count
+
+    def run(order):
+        xc = torch.full((3, S), -7.0, device=dev())
+        bone = torch.full((S,), -7, dtype=torch.int16, device=dev())
+        steps = torch.full((S,), -7, dtype=torch.int16, device=dev())
+        nfb = torch.zeros(1, dtype=torch.int32, device=dev())
+        ws = torch.empty(K.deform_guided_workspace_size(S, Dx, Dy, Dz), dtype=torch.uint8, device=dev())
+        K.snarf_deform_guided(soa(xp[order]), S, S, soa(x0[order]), up(guide[order]), up(w.B), up(w.W), w.skin_aabb,
+                              w.hash_aabb, 10, 1e-6, 1e-5, xc, bone, None, steps, nfb, ws,
+                              S_dev=None if count is None else torch.tensor([count], device=dev()))
+        torch.cuda.synchronize()
+        return host(xc), host(bone), host(steps), int(nfb.item())
+
+    order = np.arange(S)
+    a = run(order)
+    perm = np.concatenate([rng.permutation(n), np.arange(n, S)]).astype(int)
+    b = run(perm)
+    assert (a[0][:, n:] == -7.0).all() and (a[1][n:] == -7).all()
+    assert np.array_equal(a[0][:, perm], b[0]) and np.array_equal(a[1][perm], b[1])
+    assert np.array_equal(a[2][perm], b[2]) and a[3] == b[3]
+
+
 def test_learned_init_end_to_end():
     """Fit a small initialiser on solver roots of 16 poses, then guided
     solves on held-out poses: every accepted root is a valid root, and most
