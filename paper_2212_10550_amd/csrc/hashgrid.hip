@@ -888,7 +888,7 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
   begin();
   __syncthreads();
   fill();
-  next_batch();
+  if (next >= total && !sing) next_batch();
   float4 out[kAccWr];
 #pragma unroll
   for (int q = 0; q < kAccWr; ++q) out[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -1062,7 +1062,9 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
       for (int q = 0; q < kAccWr; ++q) out[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       any = false;
     }
-    if (!again && kind == 0) next_batch();
+    // once a batch, when its last window is on its way: an item taken earlier
+    // would wait longer behind this one
+    if (next >= total && (kind != 0 || !sing)) next_batch();
   }
 }
 
