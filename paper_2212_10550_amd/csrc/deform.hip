@@ -12,7 +12,12 @@
 //    Broyden solves in FP32 registers and pick the lowest residual with
 //    shuffles; bone inverses are staged in LDS once per block; the blended
 //    grid is read through the vector L1/L2 with float4 gathers, a cell's
-//    eight corners once for as long as the iterate stays in it.
+//    eight corners once for as long as the iterate stays in it.  The inits of a
+//    sample meet after the first step, so from then on a wave loads each of
+//    its cells once (SharedLater).  Bound by instruction issue (about 1,700
+//    vector instructions for 64 inits of 4.3 residuals on average), at three
+//    waves per SIMD: 36,503 samples 64 us, a 64^3 lattice 360 us; gathering
+//    every lane's cells, 176 registers and two waves, 73 and 413.
 #include <mutex>
 
 #include "common.h"
@@ -36,13 +41,15 @@ __global__ void __launch_bounds__(kBlendBlock) blend_kernel(const float *__restr
   blend_block(W, B, nb, nvert, A, blockIdx.x, sB, sW);
 }
 
-__global__ void __launch_bounds__(kSolveBlock) solve_kernel(
+__global__ void __launch_bounds__(kSolveBlock, 3) solve_kernel(
     const float *__restrict__ xp_soa, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
     const float *__restrict__ B, int nb, const float *__restrict__ A, Grid gr, Box hbox, int max_iter, float tol_stop,
     float tol_valid, float *__restrict__ xc_soa, int16_t *__restrict__ bone_out, float *__restrict__ resid_out,
     int16_t *__restrict__ steps_out) {
   __shared__ float sBinv[kMaxBones * 12];
   __shared__ int sBok[kMaxBones];
+  __shared__ float keep[6 * kSolveBlock];
+  __shared__ CellLds cells[kSolveBlock / kWave];
   stage_bone_inverses(B, nb, sBinv, sBok);
   __syncthreads();
   const int64_t Sn = count_of(S, S_dev);
@@ -59,8 +66,8 @@ __global__ void __launch_bounds__(kSolveBlock) solve_kernel(
       xp[1] = xp_soa[ld + n];
       xp[2] = xp_soa[2 * ld + n];
     }
-    HeldCorners cs(A, gr);
-    const Choice c = multi_init<kGroup>(cs, gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
+    SharedLater cs(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]);
+    const Choice c = multi_init<kGroup>(cs, LdsKeep(keep), gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
     if (act && j == 0) write_choice(c, n, ld, 0, xc_soa, bone_out, resid_out, steps_out);
   }
 }
@@ -187,7 +194,7 @@ __global__ void __launch_bounds__(kSolveBlock) guided_kernel(
     const int64_t m = n0 + threadIdx.x, n = m < Sn ? m : Sn - 1;
     const float xp[3] = {xp_soa[n], xp_soa[ld + n], xp_soa[2 * ld + n]};
     float x[3] = {x0_soa[n], x0_soa[ld + n], x0_soa[2 * ld + n]};
-    SharedCorners cs(A, gr, cells[threadIdx.x / kWave]);
+    SharedCorners cs(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]);
     const InitResult q = broyden_from(cs, gr, x, true, xp, max_iter, tol_stop);
     if (m >= Sn) continue;
     gsteps[n] = (int16_t)q.steps;
@@ -236,7 +243,7 @@ __global__ void __launch_bounds__(kSolveBlock) fallback_kernel(
       xp[2] = xp_soa[2 * ld + n];
     }
     HeldCorners cs(A, gr);
-    const Choice c = multi_init<kFbGroup>(cs, gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
+    const Choice c = multi_init<kFbGroup>(cs, RegKeep(), gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
     if (act && j == 0) write_choice(c, n, ld, gsteps[n], xc_soa, bone_out, resid_out, steps_out);
   }
 }

@@ -129,14 +129,15 @@ __device__ __forceinline__ uint32_t cell_base(const Grid &g, const Cell &c) {
 //    a 64^3 lattice 477 -> 398 us.
 //  * SharedCorners adds to it: the cells that a wave's lanes lack are loaded
 //    once each into LDS (24 lanes load a cell's 384 bytes directly) and read
-//    from there into the lanes' registers.  The guided solve uses it, whose 64
-//    neighbouring samples lie in few cells: 875,600 samples 75 -> 46 us, of a
-//    frame 78 -> 67.  After kCellSlots distinct cells the lanes left gather
-//    their own, so samples in random order lose no more than the first cells'
-//    search (whole guided pass 123 -> 124 us; with 24 slots 132, and 88 for
-//    either in order).  The multi-init solve starts in a different cell in
-//    nearly every lane and is bound by its arithmetic once the later cells are
-//    shared: 73 -> 77 us for 36,503 samples.
+//    from there into the lanes' registers.  After kCellSlots distinct cells
+//    the lanes left gather their own.  The guided solve uses it, whose 64
+//    neighbouring samples lie in few cells: 875,600 samples 75 -> 43 us, of a
+//    frame 78 -> 65; in random order a whole guided pass takes 124 us as it
+//    did before (24 slots: 132).
+//  * SharedLater gathers the start cells, which differ in nearly every lane of
+//    the multi-init solve, and shares the later ones: 14 cells a wave at the
+//    first step and 6 at the second (24 slots in place of 12: 36,503 samples
+//    67 us against 64, eight: 65).
 //  * GatherCorners reads them from the blended grid each time: the persistent
 //    renderer, whose other stages leave no registers to hold a cell.
 struct GatherCorners {
@@ -201,20 +202,21 @@ struct SharedCorners : HeldCorners {
   }
   __device__ __forceinline__ void at(uint32_t b, bool need) {
     const int ln = threadIdx.x & (kWave - 1);
-    uint64_t rem = __ballot(need && b != base);
+    uint64_t rem = __builtin_amdgcn_ballot_w64(need && b != base);
     if (rem == 0ull) return;
     int slot = -1;
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the slots' last readers are done
-    for (int s = 0; s < kCellSlots && rem != 0ull; ++s) {
-      const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)b, __ffsll((unsigned long long)rem) - 1);
-      const bool same = need && b == sb;
+    int s = 0;
+    do {
+      const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)b, __builtin_ctzll(rem));
+      const bool same = b == sb;  // a lane without need may join: its copy stays that of its cell
       slot = same ? s : slot;
-      rem &= ~__ballot(same);
+      rem &= ~__builtin_amdgcn_ballot_w64(same);
       if (ln < 24)
         __builtin_amdgcn_global_load_lds(
             (const __attribute__((address_space(1))) void *)(reinterpret_cast<const char *>(A) + (sb + part)),
             (__attribute__((address_space(3))) void *)(lds.slot[s]), 16, 0, 0);
-    }
+    } while (++s < kCellSlots && rem != 0ull);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     asm volatile("" ::: "memory");
     if (slot >= 0) {
@@ -225,8 +227,13 @@ struct SharedCorners : HeldCorners {
 #pragma unroll
         for (int i = 0; i < 3; ++i) v[k][i] = q[3 * k + i];
     }
-    if (rem != 0ull && need) HeldCorners::at(b, true);
+    if (rem != 0ull) HeldCorners::at(b, need);
   }
+};
+
+struct SharedLater : SharedCorners {
+  using SharedCorners::SharedCorners;
+  __device__ __forceinline__ void start(uint32_t b) { HeldCorners::start(b); }
 };
 
 // Trilinear weights of the eight corners (k = cx + 2 cy + 4 cz).
@@ -432,11 +439,28 @@ struct Choice {
   int bone, steps;
 };
 
-template <int kG, class Corners>
-__device__ __forceinline__ Choice multi_init(Corners &cs, const Grid &gr, const float *sBinv,
+// Where a lane keeps its best root and init 0's last iterate between inits:
+// registers, or LDS (seldom touched; the multi-init solve has none to spare).
+struct RegKeep {
+  float v[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  __device__ __forceinline__ void set(int k, float x) { v[k] = x; }
+  __device__ __forceinline__ float get(int k) const { return v[k]; }
+};
+struct LdsKeep {
+  float *p;  // [6][kSolveBlock], at this thread's column
+  __device__ __forceinline__ explicit LdsKeep(float *base) : p(base + threadIdx.x) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) p[k * kSolveBlock] = 0.0f;
+  }
+  __device__ __forceinline__ void set(int k, float x) { p[k * kSolveBlock] = x; }
+  __device__ __forceinline__ float get(int k) const { return p[k * kSolveBlock]; }
+};
+
+template <int kG, class Corners, class Keep>
+__device__ __forceinline__ Choice multi_init(Corners &cs, Keep kept, const Grid &gr, const float *sBinv,
                                              const int *sBok, int nb, const float xp[3], bool act, int j, Box hbox,
                                              int max_iter, float tol_stop, float tol_valid) {
-  float best_r = INFINITY, best_x[3] = {0.0f, 0.0f, 0.0f}, x0[3] = {0.0f, 0.0f, 0.0f};
+  float best_r = INFINITY;
   int best = 0x7fffffff, steps = 0;
   // (the same number of inits for every lane: at() may need them all)
   for (int i0 = 0; i0 < nb; i0 += kG) {
@@ -445,18 +469,21 @@ __device__ __forceinline__ Choice multi_init(Corners &cs, const Grid &gr, const 
     const InitResult q = broyden(cs, gr, sBinv + 12 * i, mine && sBok[i], xp, max_iter, tol_stop);
     if (!mine) continue;
     steps += q.steps;
-    if (i == 0) {
-      x0[0] = q.x[0];
-      x0[1] = q.x[1];
-      x0[2] = q.x[2];
-    }
+    if (i == 0)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) kept.set(3 + a, q.x[a]);
     if (q.ok && q.r < tol_valid && in_hbox(q.x, hbox) && q.r < best_r) {
       best_r = q.r;
       best = i;
-      best_x[0] = q.x[0];
-      best_x[1] = q.x[1];
-      best_x[2] = q.x[2];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) kept.set(a, q.x[a]);
     }
+  }
+  float best_x[3], x0[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    best_x[a] = kept.get(a);
+    x0[a] = kept.get(3 + a);
   }
 #pragma unroll
   for (int o = kG / 2; o > 0; o >>= 1) {

@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(kDgBlock) table_grad_dense_kernel(const float 
 // The traffic is the records (64 bytes per sample and level, written once and
 // read once) and one pass over the table slice.
 // 16 levels of 2^19 entries, field gradients (traced: sort, plan,
-// accumulate): 18 + 10 + 45 us for 36,503 samples, 81 + 13 + 149 us for
+// accumulate): 18 + 10 + 41 us for 36,503 samples, 81 + 14 + 145 us for
 // 262,143.  Counting, scanning and placing 12-byte single records across all
 // workgroups took six passes, 85 and 422 us: four of them only to agree on
 // offsets, and every 4096 records flushed a tile with global atomics.  A fixed

@@ -155,8 +155,9 @@ def test_deform_guided(orc):
     print(f"guided: fallback gpu {int(nfb.item())} oracle {ofb.sum()} of {S}")
 
 
+@pytest.mark.parametrize("guided", [True, False])
 @pytest.mark.parametrize("S,count", [(1, None), (63, None), (65, None), (1000, None), (300, 129), (70, 0)])
-def test_deform_guided_order(S, count):
+def test_deform_order(S, count, guided):
     """Samples in an order where a wave's lie in few cells (they are then
     loaded once and shared) and in one where they do not: the same bits for
     every sample, on ragged counts and under a device count."""
@@ -177,9 +178,13 @@ def test_deform_guided_order(S, count):
         steps = torch.full((S,), -7, dtype=torch.int16, device=dev())
         nfb = torch.zeros(1, dtype=torch.int32, device=dev())
         ws = torch.empty(K.deform_guided_workspace_size(S, Dx, Dy, Dz), dtype=torch.uint8, device=dev())
-        K.snarf_deform_guided(soa(xp[order]), S, S, soa(x0[order]), up(guide[order]), up(w.B), up(w.W), w.skin_aabb,
-                              w.hash_aabb, 10, 1e-6, 1e-5, xc, bone, None, steps, nfb, ws,
-                              S_dev=None if count is None else torch.tensor([count], device=dev()))
+        Sd = None if count is None else torch.tensor([count], device=dev())
+        if guided:
+            K.snarf_deform_guided(soa(xp[order]), S, S, soa(x0[order]), up(guide[order]), up(w.B), up(w.W),
+                                  w.skin_aabb, w.hash_aabb, 10, 1e-6, 1e-5, xc, bone, None, steps, nfb, ws, S_dev=Sd)
+        else:
+            K.snarf_deform(soa(xp[order]), S, S, up(w.B), up(w.W), w.skin_aabb, w.hash_aabb, 10, 1e-6, 1e-5, xc, bone,
+                           None, steps, ws, S_dev=Sd)
         torch.cuda.synchronize()
         return host(xc), host(bone), host(steps), int(nfb.item())
 
