@@ -576,11 +576,12 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
       const CellPos p = level_pos(x[j], box, N);
       int t0[4], t1[4];
       bool pair[4];
-      uint32_t r[4];
+      uint32_t r[4], idx[8];
+      cell_indices(p, N, dense, Tmask, idx);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        t0[k] = (int)(corner_index(p, 2 * k, N, dense, Tmask) >> tb);
-        t1[k] = (int)(corner_index(p, 2 * k + 1, N, dense, Tmask) >> tb);
+        t0[k] = (int)(idx[2 * k] >> tb);
+        t1[k] = (int)(idx[2 * k + 1] >> tb);
         pair[k] = act[j] && t0[k] == t1[k];
       }
       wave_reserve4(cnt, t0, pair, dense, r);
@@ -621,9 +622,11 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
           gfeat)[(int64_t)level * ld + c * kSortChunk + sample0 + j * sstep];
       const CellPos p = level_pos(x[j], box, N);
       const float w0 = 1.0f - p.f[0], w1 = p.f[0];
+      uint32_t idx[8];
+      cell_indices(p, N, dense, Tmask, idx);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const uint32_t i0 = corner_index(p, 2 * k, N, dense, Tmask), i1 = corner_index(p, 2 * k + 1, N, dense, Tmask);
+        const uint32_t i0 = idx[2 * k], i1 = idx[2 * k + 1];
         const float wyz = ((k & 1) ? p.f[1] : 1.0f - p.f[1]) * ((k & 2) ? p.f[2] : 1.0f - p.f[2]);
         const float a = wyz * g.x, b = wyz * g.y;
         const uint32_t t0 = i0 >> tb, t1 = i1 >> tb, e0 = i0 & emask, e1 = i1 & emask;
