@@ -47,8 +47,25 @@ __device__ __forceinline__ int xcd_level(int x, int g, int t, int L) {
   return l < L ? l : -1;
 }
 
-// Block b works for XCD b % 8 on the levels xcd_level gives its slots t <
-// kLv in level group g = slot % ngroup (slot = b / 8), on chunks of
+// The XCD whose levels a block serves.  FP16 table: the pairs move on by one
+// XCD seven times a call -- the slots in use, which run about in order, are
+// eight phases, and in phase p XCD x serves what xcd_level gives for
+// (x + p) % 8.  The pairs are not equally dear (of 16 levels from 16 up by
+// 1.38 with 2^19 entries, eleven are hashed: some pairs have two scattered levels), and the call
+// lasted as long as the dearest: 1,000,003 points 125.5 -> 113.3 us.  An FP32
+// level of 2^19 entries fills an XCD's 4 MB L2, and fetching eight of them
+// costs what the balance gives (0.4 to 1 % slower over training steps and
+// grid updates): it stays.  The FP16 position gradient gains alike (262,143
+// points: encode 36 -> 33 us, gradient 41 -> 38 us).
+template <typename TT>
+__device__ __forceinline__ int served_xcd(int slot, int64_t nslot, int64_t chunks) {
+  const uint32_t used = (uint32_t)(chunks < nslot ? chunks : nslot);  // nslot < 2^28
+  if (sizeof(TT) != 2 || (uint32_t)slot >= used) return blockIdx.x % kXcd;
+  return (blockIdx.x + (uint32_t)slot * kXcd / used) % kXcd;
+}
+
+// Block b works on XCD b % 8 on the levels xcd_level gives served_xcd's slots
+// t < kLv in level group g = slot % ngroup (slot = b / 8), on chunks of
 // 256 kSp samples slot / ngroup, + nslot, + 2 nslot ...  A lane takes kSp
 // samples of a chunk (256 apart) and reads each sample's position and bone
 // once for its kLv levels; all their corner gathers are in flight together.
@@ -57,16 +74,16 @@ __global__ void __launch_bounds__(kFwdBlock) encode_kernel(const float *__restri
                                                            int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
                                                            const TT *__restrict__ table, int L, int log2T, Levels lv,
                                                            Box box, FT *__restrict__ feat, int ngroup) {
-  const int xcd = blockIdx.x % kXcd;
   const int slot = blockIdx.x / kXcd;
+  const int64_t Sn = count_of(S, S_dev);
+  const int64_t nslot = gridDim.x / (kXcd * ngroup);
+  constexpr int64_t kSpan = (int64_t)kFwdBlock * kSp;
+  const int xcd = served_xcd<TT>(slot / ngroup, nslot, ceil_div(Sn, kSpan));
   int lev[kLv];
 #pragma unroll
   for (int t = 0; t < kLv; ++t) lev[t] = xcd_level<kLv>(xcd, slot % ngroup, t, L);
   if (lev[0] < 0) return;
-  const int64_t Sn = count_of(S, S_dev);
-  const int64_t nslot = gridDim.x / (kXcd * ngroup);
   const uint32_t T = 1u << log2T;
-  constexpr int64_t kSpan = (int64_t)kFwdBlock * kSp;
   for (int64_t chunk = slot / ngroup; chunk * kSpan < Sn; chunk += nslot) {
     int64_t n[kSp];
     float x[kSp][3];
@@ -149,7 +166,7 @@ void launch_encode(const EncodeArgs &a, int lv_lane, int sp_lane, unsigned g, hi
 
 // Position gradient dL/dx = sum_l sum_c (grad w_c) (theta_c . dL/dfeat_l),
 // in two kernels.  The first has the forward's mapping (block b on XCD
-// b % 8, the levels xcd_level gives, one lane per sample): every sample of a
+// b % 8, the levels xcd_level gives served_xcd's, one lane per sample): every sample of a
 // level is served by one XCD's L2, so cells shared by samples are fetched
 // once rather than once per XCD; it writes each level's contribution to a
 // workspace part [L][3][S].  The second sums the levels in a fixed order.
@@ -162,14 +179,14 @@ __global__ void __launch_bounds__(kBwdBlock) xgrad_level_kernel(
     const int64_t *__restrict__ S_dev, int64_t ld, const TT *__restrict__ table, int L, int log2T, Levels lv, Box box,
     float *__restrict__ part, int ngroup) {
   // the encode's mapping: kLv levels (b % 8) + 8 (kLv g + t) per lane
-  const int xcd = blockIdx.x % kXcd;
   const int slot = blockIdx.x / kXcd;
+  const int64_t Sn = count_of(S, S_dev);
+  const int64_t nslot = gridDim.x / (kXcd * ngroup);
+  const int xcd = served_xcd<TT>(slot / ngroup, nslot, ceil_div(Sn, (int64_t)kBwdBlock));
   int lev[kLv];
 #pragma unroll
   for (int t = 0; t < kLv; ++t) lev[t] = xcd_level<kLv>(xcd, slot % ngroup, t, L);
   if (lev[0] < 0) return;
-  const int64_t Sn = count_of(S, S_dev);
-  const int64_t nslot = gridDim.x / (kXcd * ngroup);
   const uint32_t T = 1u << log2T;
   for (int64_t chunk = slot / ngroup; chunk * kBwdBlock < Sn; chunk += nslot) {
     const int64_t n = chunk * kBwdBlock + threadIdx.x;

@@ -277,6 +277,30 @@ def test_hash_encode_two_samples_per_lane(orc):
     print(f"hash two samples per lane: max err {err:.2e}")
 
 
+@pytest.mark.parametrize("S,L,cap", [(1, 16, 1), (257, 16, 257), (7 * 256, 12, 7 * 256), (8 * 256 + 1, 16, 8 * 256 + 1),
+                                     (11 * 256 + 5, 20, 11 * 256 + 5), (5 * 256 + 3, 16, 1 << 15), (0, 16, 4096)])
+def test_hash_encode_fp16_level_turns(orc, S, L, cap):
+    """FP16 table: the level pairs change XCD with the chunk slot.  Fewer than
+    eight chunks, eight and more, two level groups, and a device-side count of
+    fewer chunks than the capacity has slots: every level of every sample is
+    written once (the oracle's values), nothing past the count."""
+    K = _K()
+    x = synth.random_points(max(S, 1), 35)[:S]
+    xs = torch.zeros((3, cap), device=dev())
+    if S:
+        xs[:, :S] = up(x.T, torch.float32)
+    table = synth.make_hash_table(L, 1 << 14, 2, seed=11, scale=0.5).astype(np.float16)
+    feat = torch.full((L, cap, 2), 5.0, device=dev())
+    count = torch.tensor([S], dtype=torch.int64, device=dev()) if cap > S else None
+    K.hashgrid_encode(xs, None, cap, cap, up(table), 16.0, 1.38, (0, 0, 0, 1, 1, 1), feat, S_dev=count)
+    torch.cuda.synchronize()
+    assert bool((feat[:, S:, :] == 5.0).all())
+    if S:
+        got = host(feat[:, :S, :]).transpose(1, 0, 2).reshape(S, 2 * L)
+        ref = orc.hash_encode(x, table, orc.resolutions(L), np.array([0, 0, 0, 1, 1, 1.0]))
+        assert_mixed(got, ref, TOL, f"hash level turns S={S} L={L}")
+
+
 def test_hash_encode_bf16_features(orc):
     K = _K()
     S = 2049
