@@ -41,6 +41,17 @@ __global__ void __launch_bounds__(kBlendBlock) blend_kernel(const float *__restr
   blend_block(W, B, nb, nvert, A, blockIdx.x, sB, sW);
 }
 
+// kG lanes per sample: eight (three inits each of 24, one after the other), or
+// 32 for calls of at most kWideSamples samples (capacity), whose time is a
+// lane's chain of inits and not the chip's rate: 200 samples 31.5 -> 12.1 us,
+// 4096 32.6 -> 17.6, 8192 32.7 -> 26.2, 16,384 45.7 -> 42.6, but 24,576 56.5
+// -> 58.0.  Same bits: each init's arithmetic is its own, and the lowest
+// residual (first init among equals) and the sum of steps do not depend on
+// the lanes that hold them.
+constexpr int kWideGroup = 32;
+constexpr int64_t kWideSamples = 16384;
+
+template <int kG>
 __global__ void __launch_bounds__(kSolveBlock, 3) solve_kernel(
     const float *__restrict__ xp_soa, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
     const float *__restrict__ B, int nb, const float *__restrict__ A, Grid gr, Box hbox, int max_iter, float tol_stop,
@@ -53,12 +64,12 @@ __global__ void __launch_bounds__(kSolveBlock, 3) solve_kernel(
   stage_bone_inverses(B, nb, sBinv, sBok);
   __syncthreads();
   const int64_t Sn = count_of(S, S_dev);
-  const int j = threadIdx.x % kGroup;
-  constexpr int kPerBlock = kSolveBlock / kGroup;
+  const int j = threadIdx.x % kG;
+  constexpr int kPerBlock = kSolveBlock / kG;
   // every lane of a block runs the same iterations, so the groups' shuffles
-  // always see all eight lanes
+  // always see all their lanes
   for (int64_t n0 = (int64_t)blockIdx.x * kPerBlock; n0 < Sn; n0 += (int64_t)gridDim.x * kPerBlock) {
-    const int64_t n = n0 + threadIdx.x / kGroup;
+    const int64_t n = n0 + threadIdx.x / kG;
     const bool act = n < Sn;
     float xp[3] = {0.0f, 0.0f, 0.0f};
     if (act) {
@@ -67,7 +78,8 @@ __global__ void __launch_bounds__(kSolveBlock, 3) solve_kernel(
       xp[2] = xp_soa[2 * ld + n];
     }
     SharedLater cs(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]);
-    const Choice c = multi_init<kGroup>(cs, LdsKeep(keep), gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
+    const Choice c = multi_init<kG>(cs, LdsKeep(keep), gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop,
+                                     tol_valid);
     if (act && j == 0) write_choice(c, n, ld, 0, xc_soa, bone_out, resid_out, steps_out);
   }
 }
@@ -590,7 +602,10 @@ int32_t deform_launch(const float *xp, int64_t S, const int64_t *S_dev, int64_t 
     hb.lo[a] = hash_aabb[a];
     hb.hi[a] = hash_aabb[3 + a];
   }
-  solve_kernel<<<stride_grid(ceil_div(S * kGroup, kSolveBlock), S_dev != nullptr), kSolveBlock, 0, s>>>(
+  const bool wide = S <= kWideSamples;
+  const int lanes = wide ? kWideGroup : kGroup;
+  auto *kernel = wide ? solve_kernel<kWideGroup> : solve_kernel<kGroup>;
+  kernel<<<stride_grid(ceil_div(S * lanes, kSolveBlock), S_dev != nullptr), kSolveBlock, 0, s>>>(
       xp, S, S_dev, ld, B, nb, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps);
   return launch_status();
 }

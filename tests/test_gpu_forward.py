@@ -211,6 +211,37 @@ def test_deform_train_pose_ragged(orc):
     _deform_check(orc, w, xp, "train pose")
 
 
+@pytest.mark.parametrize("S,count", [(1, None), (8, None), (9, None), (4099, None), (16384, None), (300, 129),
+                                     (16384, 7), (16385, 16384)])
+def test_deform_lanes_per_sample(S, count):
+    """Calls of at most 16,384 samples take 32 lanes a sample, larger ones
+    eight: the same bits for every sample in either, on ragged counts, under a
+    device count and at the border; nothing past the count."""
+    K = _K()
+    w = synth.train_step()
+    big = 16385 + 64
+    Dz, Dy, Dx, _ = w.W.shape
+    xp = synth.sample_posed_points(synth.make_skeleton(0), w.B.astype(np.float64), big, 13).astype(np.float32)
+    xp[5] = [9.0, 9.0, 9.0]  # no root
+
+    def run(n, cnt):
+        xc = torch.full((3, n), -7.0, device=dev())
+        bone = torch.full((n,), -7, dtype=torch.int16, device=dev())
+        resid = torch.full((n,), -7.0, device=dev())
+        steps = torch.full((n,), -7, dtype=torch.int16, device=dev())
+        ws = torch.empty(K.deform_workspace_size(Dx, Dy, Dz), dtype=torch.uint8, device=dev())
+        Sd = None if cnt is None else torch.tensor([cnt], device=dev())
+        K.snarf_deform(soa(xp[:n]), n, n, up(w.B), up(w.W), w.skin_aabb, w.hash_aabb, 10, 1e-6, 1e-5, xc, bone, resid,
+                       steps, ws, S_dev=Sd)
+        torch.cuda.synchronize()
+        return host(xc), host(bone), host(resid), host(steps)
+
+    n = S if count is None else count
+    for got, ref in zip(run(S, count), run(big, None)):
+        assert got[..., :n].tobytes() == ref[..., :n].tobytes()
+        assert (got[..., n:] == -7).all()
+
+
 @pytest.mark.parametrize("log2T,scale,tdt", [(14, 1e-4, "f32"), (19, 1e-4, "f32"), (19, 0.5, "f32"),
                                              (19, 0.5, "f16")])
 def test_hash_encode(orc, log2T, scale, tdt):
