@@ -30,14 +30,16 @@ namespace {
 
 constexpr int kFwdBlock = 256;
 constexpr int64_t kTwoSampleMin = (int64_t)1 << 22;  // samples (or capacity) from which a lane takes two
-// Most chunk slots with a device-side count.  Blocks of one chunk, taken in
-// order, keep what runs at a time to neighbouring samples and to one or two
-// phases of served_xcd; blocks that loop drift apart.  Past the count a slot's
-// eight blocks cost 4 ns.  FP16, 875,600 samples of a 2.3 million capacity: a frame
-// 317.3 us with 1024 slots, 311.7 with 2048, 307.9 with 4096, 325.0 with
-// 8192; four poses 1253, 1222, 1197, 1164.  FP32 steps gain nothing (325.1 us
-// with 1024, 325.7 with 4096).
-constexpr int64_t kDevSlotsF16 = 4096, kDevSlotsF32 = 1024;
+// Chunk slots with a device-side count: 1024, and with an FP16 table a quarter
+// of what the capacity holds if that is more, at most 4096.  Blocks of one
+// chunk, taken in order, keep what runs at a time to neighbouring samples and
+// to one or two phases of served_xcd; blocks that loop drift apart.  Past the
+// count a slot's eight blocks cost 4 ns.  1024, 2048 and 4096 slots, FP16:
+// frames of 540 x 540 (9112 chunks of capacity) with 0.88 M samples 305, 300
+// and 296 us, with 0.44 M 193, 192 and 200; of 300 x 300 (2813) 123, 125 and
+// 129; a training step (4096, 143 in use) 247, 247 and 255.  FP32 steps gain
+// nothing (325.1 us with 1024, 325.7 with 4096).
+constexpr int64_t kDevSlots = 1024, kDevSlotsMost = 4096;
 
 // Level of a lane's slot t in level group g on XCD x, or -1 (no level).  With
 // two levels per lane and at most 16 levels, XCD x serves level x and level
@@ -1118,12 +1120,14 @@ extern "C" int32_t ia355_hashgrid_encode(const float *xc, const int16_t *bone, i
   // two samples per lane as well for frame-sized calls (more gathers in
   // flight per lane; at training-step sizes the halved lane count costs more)
   const int sp_lane = lv_lane == 2 && S >= kTwoSampleMin ? 2 : 1;
-  // chunk slots per (XCD, level group); with a device count at most so
-  // many per group, the blocks loop over the rest (blocks past the count exit at
-  // once)
+  // chunk slots per (XCD, level group); with a device count the blocks loop
+  // over what is left (blocks past the count exit at once)
   int64_t nslot = ceil_div(S, (int64_t)kFwdBlock * sp_lane);
-  const int64_t most = table_dtype == IA355_F16 ? kDevSlotsF16 : kDevSlotsF32;
-  if (S_dev && nslot > most) nslot = most;
+  if (S_dev) {
+    const int64_t quarter = table_dtype == IA355_F16 ? nslot / 4 : 0;
+    const int64_t most = quarter < kDevSlots ? kDevSlots : quarter < kDevSlotsMost ? quarter : kDevSlotsMost;
+    if (nslot > most) nslot = most;
+  }
   const int64_t blocks = nslot * ngroup * kXcd;
   if (blocks > 0x7fffffffLL) return IA355_ERR_INVALID_ARG;
   hipStream_t s = as_stream(stream);
