@@ -78,14 +78,14 @@ RENDER_FWD_BYTES_PER_SAMPLE, RENDER_BWD_BYTES_PER_SAMPLE, RENDER_BYTES_PER_RAY =
 # kernels of each stage (names as rocprofv3 reports them)
 STAGE_KERNELS = {
     "march": ["march_count", "march_scan", "march_fill"],
-    "deform": ["blend_kernel", "solve_kernel", "guided_kernel", "fallback_kernel", "rootinit_kernel"],
+    "deform": ["blend_kernel", "solve_kernel", "guided_kernel", "fallback_kernel", "rootinit_f32",
+               "rootinit_bf16"],
     "hash_fwd": ["encode_kernel"],
     "mlp_fwd": ["mlp_fwd_f32", "mlp_fwd_bf16"],
     "render_fwd": ["render_fwd"],
     "loss+render_bwd": ["l2_loss_kernel", "render_bwd"],
     "mlp_bwd": ["mlp_bwd_f32", "mlp_bwd_bf16", "reduce_partials"],
-    "hash_bwd_table": ["bin_count_kernel", "bin_hist_scan_kernel", "bin_plan_kernel", "bin_scatter_kernel",
-                       "bin_clear_split_kernel", "bin_accum_kernel"],
+    "hash_bwd_table": ["bin_sort_kernel", "bin_plan_kernel", "bin_accum_kernel"],
     "hash_bwd_x": ["xgrad_level_kernel", "xgrad_sum_kernel"],
     "deform_bwd": ["ift_v_kernel", "ift_q_kernel", "ift_contract_kernel", "ift_b_kernel"],
 }
