@@ -123,7 +123,8 @@ int32_t ia355_occ_pack(const uint8_t *occ, int32_t G, uint32_t *bits, ia355_stre
  * kept count to *n_required and returns IA355_ERR_CAPACITY when it exceeds
  * cap (the outputs then hold the first cap samples), IA355_OK otherwise.
  * ws: ia355_march_workspace_size(R, max_steps) bytes (per-block totals,
- * and each ray's keep masks, 8 bytes per 64 steps, and entry distance). */
+ * and each ray's keep masks, 8 bytes per 64 steps, and entry distance); it
+ * never falls as R or max_steps grows, so the largest call's serves all. */
 size_t ia355_march_workspace_size(int64_t R, int32_t max_steps);
 int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d, int64_t R,
                             const uint32_t *occ_bits, int32_t G, const float *aabb,

@@ -373,7 +373,11 @@ __global__ void __launch_bounds__(kBlock) march_fill_many(const float *__restric
 }  // namespace
 
 // Workspace: block totals, chunk totals, keep masks [R][ceil(max_steps/64)]
-// and entry distances [R], each slice 256-byte aligned.
+// and entry distances [R], each slice 256-byte aligned.  Its size never falls
+// as R or max_steps grows: a workspace for the largest call of a pool serves
+// the smaller ones.  Block totals: one for four rays up to 65,535 rays (the
+// kernels of few rays need that below kManyRays; callers count on the rest),
+// from there on no fewer, and at least one for 16 rays (kBlock would do).
 struct MarchWs {
   int64_t *block_sum, *chunk_sum;
   uint64_t *masks;
@@ -382,8 +386,9 @@ struct MarchWs {
 };
 
 static MarchWs march_ws(void *base, int64_t R, int32_t max_steps) {
-  const int64_t Rp = R > 0 ? R : 1;
-  const int64_t nblk = ceil_div(Rp, many_rays(Rp, max_steps) && Rp >= 65536 ? 16 : kWavesPerBlock);  // at least the block totals
+  const int64_t Rp = R > 0 ? R : 1, few = Rp < 65536 ? Rp : 65535;
+  const int64_t per_wave = ceil_div(max_steps <= kManySteps ? few : Rp, kWavesPerBlock), rest = ceil_div(Rp, 16);
+  const int64_t nblk = per_wave > rest ? per_wave : rest;
   const int64_t nw = ceil_div(max_steps > 0 ? max_steps : 1, kWave);
   char *p = (char *)base;
   MarchWs w;

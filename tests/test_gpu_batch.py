@@ -85,6 +85,18 @@ def test_batch_matches_single_pose(small_batch, n_streams):
     print(f"batch ({n_streams} streams): samples {[p.S for p in br.poses]}")
 
 
+def test_batch_pool_serves_smaller_poses():
+    """Two poses of 65,536 and 62,500 rays (256^2, 250^2) in one stream: the
+    slot's march workspace, sized for the larger, serves both."""
+    from paper_2212_10550_amd.batch import BatchRenderer
+    w = synth.batch_pose(4)
+    ws = [synth.ray_subset(w, np.linspace(0, w.R - 1, n).astype(int)) for n in (256 * 256, 250 * 250)]
+    params = _params()
+    br = BatchRenderer(ws, params, n_streams=1)
+    br.capture()
+    _check_replays(br, _single_refs(ws, params, br.poses), "two poses, one slot")
+
+
 # schedules: rays per tile (ragged last tiles, 64 = one lane per ray),
 # samples per segment (256: a 64-ray tile splits into several segments),
 # waves per workgroup, workgroups per CU (every kernel instantiation)

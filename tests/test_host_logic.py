@@ -23,6 +23,19 @@ def test_march_workspace_covers_masks_and_scan():
     assert K.march_workspace_size(-1, 128) == 0 and K.march_workspace_size(10, -1) == 0
 
 
+def test_march_workspace_never_falls():
+    """A workspace sized for the largest call of a pool (the batch renderer's
+    slots) holds every smaller one."""
+    rays = sorted([0, 1, 5, 4096, 62500, 70001, 1 << 21, 1 << 24] +
+                  [b + d for b in (32768, 65536, 131072, 524288) for d in (-17, -1, 0, 1, 300)])
+    steps = (0, 1, 64, 65, 128, 1 << 22, (1 << 22) + 1)
+    size = [[K.march_workspace_size(R, n) for n in steps] for R in rays]
+    for i in range(len(rays)):
+        for j in range(len(steps)):
+            assert i == 0 or size[i][j] >= size[i - 1][j], (rays[i - 1], rays[i], steps[j])
+            assert j == 0 or size[i][j] >= size[i][j - 1], (rays[i], steps[j - 1], steps[j])
+
+
 def test_backward_and_regulariser_workspaces():
     assert K.hashgrid_encode_bwd_workspace_size(36503, 16) >= 4 * 3 * 16 * 36503
     assert K.hashgrid_encode_bwd_workspace_size(-1, 16) == 0
