@@ -756,7 +756,8 @@ __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__res
     const uint2 q = c < chunks ? run[c] : make_uint2(0u, 0u);
     const uint32_t n = (q.x >> 16) + (q.y >> 16), incl = (uint32_t)wave_incl_scan((int)n);
     const uint32_t mine = c < chunks ? (before + incl - n) / per : 0xffffffffu;  // < groups
-    const uint32_t prev = lane == 0 ? group : (uint32_t)__shfl_up((int)mine, 1, kWave);
+    const uint32_t below = (uint32_t)__shfl_up((int)mine, 1, kWave);  // by every lane: an inactive one gives nothing
+    const uint32_t prev = lane == 0 ? group : below;
     const bool opens = c < chunks && mine != prev;
     const uint64_t m = __ballot(opens);
     if (m != 0ull) {  // each closes the item before it

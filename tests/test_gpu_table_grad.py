@@ -355,3 +355,23 @@ def test_table_grad_binned_sort_chunks(orc, log2T, L, S, count, overwrite):
     tol = adds * 2.0 ** -24 * mag + 8 * n * 2.0 ** -47 * np.abs(clean).max()
     assert (err <= tol).all(), f"worst {(err / tol).max():.2f} of the bound"
     print(f"worst {(err[tol > 0] / tol[tol > 0]).max():.3f} of the bound ({adds} roundings)")
+
+
+def test_table_grad_binned_work_items():
+    """The plan's list has room for tiles + records / 8192 items: a tile of n
+    records must not take more than n / 8192 + 1 of them, also where the
+    chunks of a shared tile span many steps of the planning wave (the counts
+    are the second and third word of the workspace)."""
+    K = _K()
+    log2T, L, S = 14, 2, 330001
+    rng = np.random.default_rng(9)
+    x = rng.random((S, 3)) / 16.0  # the first tile of level 0, a few cells of level 1
+    gf = up(rng.normal(size=2 * L * S).astype(np.float32))
+    gt = torch.empty(L, 1 << log2T, 2, device=dev())
+    ws = torch.empty(K.hashgrid_table_grad_workspace_size(S, L, 1 << log2T), dtype=torch.uint8, device=dev())
+    K.hashgrid_table_grad(gf, soa(x.astype(np.float32), S), None, S, S, 16.0, 2.0, AABB, gt, ws, K.OVERWRITE)
+    torch.cuda.synchronize()
+    _, split, whole = host(ws[:12].view(torch.int32)).tolist()
+    # level 0: one tile with every record (pairs of corners); level 1: its records lie in at most four tiles
+    most = (4 * S // 8192 + 1) + (4 * S // 8192 + 4)
+    assert 0 < split and split + whole <= most, (split, whole, most)
