@@ -362,20 +362,22 @@ int32_t ia355_hashgrid_encode_bwd(const float *grad_feat, const float *xc, const
  * without global atomics on almost every entry: the corner updates are
  * binned by (level, table tile of 4096 entries), written once as 16-byte
  * records of the two corners that neighbour in x (12-byte ones where a tile
- * boundary separates them) and summed per tile in LDS as exact 64-bit fixed point (a power-of-two scale per group of at
- * most 4096 records, chosen from its largest |value| m), then converted back
- * and written with plain stores.  Accuracy is absolute, relative to m: each
- * record is rounded to a quantum below m 2^-46, so an entry's error is at
- * most its record count times m 2^-47 plus one FP32 rounding of the entry
- * (values below m 2^-48 contribute zero).  A tile with many more records than
- * others (more than 8192, and than half of what an even spread would give a
- * workgroup) is summed by several workgroups that add their nonzero entries
- * with FP32 atomics.  Every tile of the selected levels is written, so
- * IA355_OVERWRITE needs no separate clear.  A tile summed by one workgroup
- * does not depend on the order of its records; split tiles may vary in the
- * last bit from run to run.  NaN and infinite values are kept out of the
- * fixed-point sums and added to their entries as FP32 values, so they
- * propagate as with ia355_hashgrid_encode_bwd.
+ * boundary separates them) and summed per tile in LDS as exact 64-bit fixed
+ * point with one power-of-two scale, chosen from the largest |value| m (of a
+ * corner's update), then converted back once and written with plain stores.
+ * Accuracy is absolute, relative to m: each value is rounded to a quantum of
+ * at most m 2^-46, so an entry's error is at most its update count times
+ * m 2^-47 plus one FP32 rounding of the entry (values below m 2^-49 contribute
+ * zero), besides the FP32 roundings that form each value.  A tile with more
+ * records than 4096 and than half of what an even spread would give a
+ * workgroup (16,384 at most) is summed by several workgroups, each with its
+ * own m, that add their nonzero entries with FP32 atomics, one rounding each.
+ * Every tile of the selected levels is written, so IA355_OVERWRITE needs no
+ * separate clear.  A tile summed by one workgroup does not depend on the order
+ * of its records, nor of the samples; shared tiles may vary in the last bit
+ * from run to run.  NaN and infinite values are kept out of the fixed-point
+ * sums and set their entries to what FP32 adds would give, so they propagate
+ * as with ia355_hashgrid_encode_bwd.
  *   grad_table: [L][T][F] FP32, 16-byte aligned, T = 2^log2T.
  *   ws: ia355_hashgrid_table_grad_workspace_size(S, L, log2T) bytes
  *       (S is the capacity when S_dev is given); about 96 bytes per sample

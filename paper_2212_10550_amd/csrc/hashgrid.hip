@@ -387,9 +387,9 @@ __global__ void __launch_bounds__(kDgBlock) table_grad_dense_kernel(const float 
 //  1. sort: a workgroup takes one level and kSortChunk samples, counts its
 //     updates per tile in LDS (keeping each update's rank in a register),
 //     scans the counts and writes its updates in tile order into the chunk's
-//     own part of the workspace, and each tile's run into the run table.  A
-//     chunk's part is sized for its samples, so no pass has to agree on
-//     offsets across workgroups.
+//     own part of the workspace, and each tile's run, with the largest exponent
+//     of its values, into the run table.  A chunk's part is sized for its
+//     samples, so no pass has to agree on offsets across workgroups.
 //  2. plan: from the run table, a work item for each tile with records, or
 //     several, by chunks, for one with many (coarse levels, whose samples
 //     crowd on the subject).
@@ -403,25 +403,29 @@ __global__ void __launch_bounds__(kDgBlock) table_grad_dense_kernel(const float 
 // separates are 12-byte records at the end of the chunk's part; a sample's
 // eight updates take at most 96 bytes either way.
 // The LDS sums are 64-bit fixed point, added exactly: LDS float atomic adds run at
-// about a sixteenth of the rate of integer ones on gfx950, so each window of
-// at most 4096 records scales its values by a power of two 2^s chosen from its
-// largest |value| m (no overflow), adds them as integers and converts each
-// entry back once.  Each record is rounded to the quantum 2^-s < m 2^-46, so
-// an entry's error is at most (its records) x m 2^-47 plus one FP32 rounding
-// per window: an absolute bound relative to the window's largest value.  An
-// entry near m is as accurate as FP32 adds leave it or better; one far
-// below m (under about m 2^-24) is less accurate than FP32 adds, and a
-// record below m 2^-48 rounds to zero.  Integer addition is associative, so
-// a tile summed by one workgroup does not depend on the order of its records.
+// about a sixteenth of the rate of integer ones on gfx950, so each work item
+// scales its values by a power of two 2^s chosen from its largest |value| m
+// (no overflow), adds them as integers and converts each entry back once.
+// Each value is rounded to the quantum 2^-s <= m 2^-46, so an entry's error is
+// at most (its values) x m 2^-47 plus one FP32 rounding, and one more per
+// addition to the table where items share the tile: an absolute bound relative
+// to the item's largest value.  An entry near m is as accurate as FP32 adds
+// leave it or better; one far below m (under about m 2^-24) is less accurate
+// than FP32 adds, and a value below m 2^-49 rounds to zero.  Integer addition
+// is associative, so a tile summed by one workgroup (any with 4096 updates or
+// fewer) does not depend on the order of its records.
 // The traffic is the records (64 bytes per sample and level, written once and
 // read once) and one pass over the table slice.
 // 16 levels of 2^19 entries, field gradients (traced: sort, plan,
-// accumulate): 18 + 10 + 41 us for 36,503 samples, 81 + 14 + 145 us for
-// 262,143.  Counting, scanning and placing 12-byte single records across all
-// workgroups took six passes, 85 and 422 us: four of them only to agree on
-// offsets, and every 4096 records flushed a tile with global atomics.  A fixed
-// share of a level's tiles per item in place of the plan left the accumulate
-// pass 62 and 243 us (the largest items ran on alone for half of it).
+// accumulate): 19 + 10 + 31 us for 36,503 samples, 100 + 13 + 115 us for
+// 262,143.  With a scale, a conversion and a clear of the tile for each window
+// of at most 4096 records, whose maximum the workgroup found first: 18 + 10 +
+// 41 and 81 + 14 + 145 us.  Counting, scanning and placing 12-byte single
+// records across all workgroups took six passes, 85 and 422 us: four of them
+// only to agree on offsets, and every 4096 records flushed a tile with global
+// atomics.  A fixed share of a level's tiles per item in place of the plan left
+// the accumulate pass 62 and 243 us (the largest items ran on alone for half
+// of it).
 constexpr int kSortBlock = 320;
 constexpr int kSortPer = 4;                        // samples per thread
 constexpr int kSortChunk = kSortBlock * kSortPer;  // at 128 tiles a hashed level's runs average 40 pairs
@@ -433,13 +437,23 @@ constexpr int kAccWaves = kAccBlock / kWave;
 constexpr int kAccPer = 8;         // records per thread and window
 constexpr int kRunWaves = 4;       // waves that load a batch's runs, one per lane
 constexpr int kAccRuns = kRunWaves * kWave;
-constexpr uint32_t kAccTarget = 8192;  // records of a work item at least, where a tile has more
+// Records of a work item at least, where a tile has more: a pair record is two
+// updates, and shorter items cost more additions to the table (8192: 37 us for
+// 36,503 samples in place of 31, as the shared tiles' items outlast the others).
+constexpr uint32_t kAccTarget = 4096;
+constexpr uint32_t kAccMost = 16384;  // and at most, but for its last chunk's
+// Records an item, on average, below which no item goes by queue: an add to
+// one address takes 10 ns, and a workgroup waits for its turn (36,503 samples,
+// 1580 records an item: 37 us by place, 41 with the last rounds by queue;
+// 262,143 samples, 9500 records: 128 and 117).
+constexpr uint32_t kAccBrief = 4096;
 constexpr int kPlanBlock = 1024;
 constexpr uint32_t kNoItem = 0xffffffffu;
 constexpr int kAccWr = (1 << (kTileLog2Max - 1)) / kAccBlock;  // float4 of a tile per thread
+constexpr int kAccSums = 2 << kTileLog2Max;
 constexpr int kAccMaxGrid = 512;   // two workgroups per CU by LDS
-static_assert(8 * kSortChunk < 65536, "16-bit run places");
-static_assert(kAccPer * kAccBlock <= (1 << 12), "fixed-point head room");
+static_assert(4 * kSortChunk < 1 << 13 && 8 * kSortChunk < 1 << 14, "run places");
+static_assert((int64_t)(kAccMost + 8 * kSortChunk) << 48 > 0, "fixed-point head room");
 
 struct BinGeom {
   int tb;        // log2 entries per tile
@@ -456,14 +470,25 @@ inline bool bin_geom(int nl, int64_t S, int log2T, BinGeom *g) {
   return (int64_t)nl * S * 8 < 0xffffffffLL;
 }
 
-// runs[level][tile][chunk]: x the first pair record and their number << 16, y
-// the same for single records; rec: chunk c of level lr has the bytes from
-// (lr S + c kSortChunk) 96, pair records upwards from its start, single
-// records downwards from its end.
+// runs[level][tile][chunk], see pack_run; rec: chunk c of level lr has the
+// bytes from (lr S + c kSortChunk) 96, pair records upwards from its start,
+// single records downwards from its end.
 struct BinQueue {
-  uint32_t next;          // the accumulate pass's next work item
+  uint32_t next;          // items that the accumulate pass took from the queue
   uint32_t split, whole;  // work items of tiles that several share, of whole tiles
 };
+
+// A run: its first pair record and their number, the same of its single
+// records, the largest exponent field of its finite values, and whether its
+// chunk holds a NaN or an infinity on this level.
+__device__ __forceinline__ uint2 pack_run(uint32_t p0, uint32_t pn, uint32_t s0, uint32_t sn, uint32_t ex,
+                                          uint32_t odd) {
+  return make_uint2(p0 | pn << 13 | (ex & 63u) << 26, s0 | sn << 14 | (ex >> 6) << 28 | odd << 30);
+}
+__device__ __forceinline__ uint32_t run_pairs(const uint2 &q) { return (q.x >> 13) & 0x1fffu; }
+__device__ __forceinline__ uint32_t run_singles(const uint2 &q) { return (q.y >> 14) & 0x3fffu; }
+__device__ __forceinline__ uint32_t run_exponent(const uint2 &q) { return q.x >> 26 | ((q.y >> 28) & 3u) << 6; }
+__device__ __forceinline__ bool run_odd(const uint2 &q) { return (q.y >> 30) != 0u; }
 
 // A work item of the accumulate pass: a range of chunks of a tile.
 struct AccItem {
@@ -517,16 +542,16 @@ __device__ __forceinline__ uint32_t block_scan_u32(uint32_t v, uint32_t *wsum, u
   return base + incl - v;
 }
 
-// Adds 1 to the LDS counter c[bin[k]] for each lane with act[k], k < 4, and
+// Adds 1 to the LDS counter c[bin[k]].x for each lane with act[k], k < 4, and
 // gives the counter's value before the lane's own add.  few: the wave's bins
 // are likely one or two (dense levels: neighbouring samples); the lanes that
 // share the first lane's bin then make one add of their number, instead of
 // that many serialised on one LDS address.
-__device__ __forceinline__ void wave_reserve4(uint32_t *c, const int bin[4], const bool act[4], bool few,
+__device__ __forceinline__ void wave_reserve4(uint2 *c, const int bin[4], const bool act[4], bool few,
                                               uint32_t rank[4]) {
   if (!few) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) rank[k] = act[k] ? atomicAdd(&c[bin[k]], 1u) : 0u;
+    for (int k = 0; k < 4; ++k) rank[k] = act[k] ? atomicAdd(&c[bin[k]].x, 1u) : 0u;
     return;
   }
   const int lane = threadIdx.x & (kWave - 1);
@@ -541,7 +566,7 @@ __device__ __forceinline__ void wave_reserve4(uint32_t *c, const int bin[4], con
     same[k] = __ballot(act[k] && bin[k] == b0);
     const bool lead = lane == first[k] && same[k] != 0ull, alone = act[k] && bin[k] != b0;
     base[k] = own[k] = 0u;
-    if (lead || alone) own[k] = atomicAdd(&c[bin[k]], lead ? (uint32_t)__popcll(same[k]) : 1u);
+    if (lead || alone) own[k] = atomicAdd(&c[bin[k]].x, lead ? (uint32_t)__popcll(same[k]) : 1u);
   }
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -561,14 +586,34 @@ __device__ __forceinline__ SingleRec *single_at(char *end, uint32_t i) {
   return reinterpret_cast<SingleRec *>(end) - 1 - i;
 }
 
+// Zeroes a tile with `threads` threads.
+__device__ __forceinline__ void clear_tile(float *gtable, uint32_t bin, int l0, int log2T, int tb, int thread,
+                                           int threads) {
+  float4 *dst = reinterpret_cast<float4 *>(gtable + ((((int64_t)l0 << log2T) + ((int64_t)bin << tb)) << 1));
+  for (int i = thread; i < 1 << (tb - 1); i += threads) dst[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+// The larger exponent field of a and b, of the finite ones; a NaN or an
+// infinity sets odd.  By the bits as integers, where fmaxf would hide a NaN.
+__device__ __forceinline__ uint32_t top_exponent(float a, float b, int &odd) {
+  const uint32_t ea = (__float_as_uint(a) >> 23) & 255u, eb = (__float_as_uint(b) >> 23) & 255u;
+  uint32_t ex = max(ea, eb);
+  if (ex == 255u) {
+    odd = 1;
+    ex = max(ea == 255u ? 0u : ea, eb == 255u ? 0u : eb);
+  }
+  return ex;
+}
+
 __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
     const float *__restrict__ gfeat, const float *__restrict__ xc, const int16_t *__restrict__ bone, int64_t S,
     const int64_t *__restrict__ S_dev, int64_t ld, int l0, int nl, int log2T, int tb, Levels lv, Box box,
     int64_t chunk_cap, BinQueue *__restrict__ queue, uint2 *__restrict__ runs, char *__restrict__ rec) {
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    *queue = BinQueue{kAccMaxGrid, 0u, 0u};  // the accumulate pass's first items go by block
-  extern __shared__ uint32_t cnt[];  // per tile: pair records, single records << 16
+  if (blockIdx.x == 0 && threadIdx.x == 0) *queue = BinQueue{0u, 0u, 0u};
+  // per tile: pair records, single records << 16; the largest exponent field
+  extern __shared__ uint2 cnt[];
   __shared__ uint32_t wsum[kSortBlock / kWave];
+  __shared__ int odd;  // the chunk holds a NaN or an infinity
   const int tpl_log2 = log2T - tb, tiles = 1 << tpl_log2;
   const int lr = blockIdx.x % nl, level = l0 + lr;
   const int N = lv.res[level];
@@ -584,7 +629,8 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
                             : (int)threadIdx.x;
   const int sstep = dense ? 1 : kSortBlock;
   for (int64_t c = blockIdx.x / nl; c < chunks; c += gridDim.x / nl) {
-    for (int i = threadIdx.x; i < tiles; i += kSortBlock) cnt[i] = 0u;
+    for (int i = threadIdx.x; i < tiles; i += kSortBlock) cnt[i] = make_uint2(0u, 0u);
+    if (threadIdx.x == 0) odd = 0;
     float x[kSortPer][3];
     bool act[kSortPer];
 #pragma unroll
@@ -615,24 +661,20 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         if (act[j] && !pair[k]) {
-          atomicAdd(&cnt[t0[k]], 1u << 16);
-          atomicAdd(&cnt[t1[k]], 1u << 16);
+          atomicAdd(&cnt[t0[k]].x, 1u << 16);
+          atomicAdd(&cnt[t1[k]].x, 1u << 16);
         }
       rank[j] = make_uint2((r[0] & 0xffffu) | r[1] << 16, (r[2] & 0xffffu) | r[3] << 16);
     }
     __syncthreads();
-    // counts -> offsets, in place and into the run table
+    // counts -> offsets, in place
     uint32_t carry = 0;
     for (int b0 = 0; b0 < tiles; b0 += kSortBlock) {
       const int i = b0 + threadIdx.x;
-      const uint32_t v = i < tiles ? cnt[i] : 0u;
+      const uint32_t v = i < tiles ? cnt[i].x : 0u;
       uint32_t total;
       const uint32_t off = carry + block_scan_u32<kSortBlock>(v, wsum, &total);  // the halves do not overflow
-      if (i < tiles) {
-        cnt[i] = off;
-        runs[(((int64_t)lr << tpl_log2) + i) * chunk_cap + c] =
-            make_uint2((off & 0xffffu) | v << 16, (off >> 16) | (v & 0xffff0000u));
-      }
+      if (i < tiles) cnt[i].x = off;
       carry += total;
     }
     __syncthreads();
@@ -657,37 +699,56 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
         const float wyz = ((k & 1) ? p.f[1] : 1.0f - p.f[1]) * ((k & 2) ? p.f[2] : 1.0f - p.f[2]);
         const float a = wyz * g.x, b = wyz * g.y;
         const uint32_t t0 = i0 >> tb, t1 = i1 >> tb, e0 = i0 & emask, e1 = i1 & emask;
+        // few of a tile's values raise its largest exponent: a read and a
+        // compare for most
         if (t0 == t1) {
           const uint32_t r = ((k & 2 ? rank[j].y : rank[j].x) >> (k & 1 ? 16 : 0)) & 0xffffu;
-          pairs[(cnt[t0] & 0xffffu) + r] =
+          const uint2 q = cnt[t0];
+          const uint32_t ex = top_exponent(a, b, odd);  // of the values: this one or the one below
+          if (ex > q.y) atomicMax(&cnt[t0].y, ex);
+          pairs[(q.x & 0xffffu) + r] =
               make_uint4(__float_as_uint(a), __float_as_uint(b), __float_as_uint(w1), e0 | e1 << 16);
         } else {  // the singles' next places are counted in the high halves
-          *single_at(end, atomicAdd(&cnt[t0], 1u << 16) >> 16) = SingleRec{w0 * a, w0 * b, e0};
-          *single_at(end, atomicAdd(&cnt[t1], 1u << 16) >> 16) = SingleRec{w1 * a, w1 * b, e1};
+          const SingleRec s0{w0 * a, w0 * b, e0}, s1{w1 * a, w1 * b, e1};
+          atomicMax(&cnt[t0].y, top_exponent(s0.a, s0.b, odd));
+          atomicMax(&cnt[t1].y, top_exponent(s1.a, s1.b, odd));
+          *single_at(end, atomicAdd(&cnt[t0].x, 1u << 16) >> 16) = s0;
+          *single_at(end, atomicAdd(&cnt[t1].x, 1u << 16) >> 16) = s1;
         }
       }
+    }
+    __syncthreads();
+    // the run table; a tile's single records end where the next one's begin
+    for (int i = threadIdx.x; i < tiles; i += kSortBlock) {
+      const uint32_t p0 = cnt[i].x & 0xffffu, p1 = (i + 1 < tiles ? cnt[i + 1].x : carry) & 0xffffu;
+      const uint32_t s0 = i ? cnt[i - 1].x >> 16 : 0u, s1 = cnt[i].x >> 16;
+      runs[(((int64_t)lr << tpl_log2) + i) * chunk_cap + c] =
+          pack_run(p0, p1 - p0, s0, s1 - s0, cnt[i].y, (uint32_t)odd);
     }
     __syncthreads();  // the counters are cleared for the next chunk
   }
 }
 
-// v 2^s rounded to an integer (ties to even), as two's complement bits
-// (|v| 2^s < 2^50): the sum with 1.5 2^52 has it in its low bits.
+// v scale rounded to an integer (ties to even), as two's complement bits
+// (|v| scale < 2^50): the sum with 1.5 2^52 has it in its low bits.
 __device__ __forceinline__ unsigned long long to_fixed(float v, double scale) {
   const double magic = 6755399441055744.0;
   return (unsigned long long)(__double_as_longlong(fma((double)v, scale, magic)) - __double_as_longlong(magic));
 }
 
-// A fixed-point sum back to FP32 (one rounding).
-__device__ __forceinline__ float from_fixed(unsigned long long a, int s) {
-  return (float)ldexp((double)(long long)a, -s);
-}
+// A fixed-point sum back to FP32 (one rounding); inv: 1 / scale.
+__device__ __forceinline__ float from_fixed(unsigned long long a, double inv) { return (float)((double)(long long)a * inv); }
 
 // Sixteen bytes at a multiple of four.
 __device__ __forceinline__ uint4 load16(const char *p) {
   typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
   const u4 v = *reinterpret_cast<const u4 *>(p);
   return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// A store whose line is not needed in the cache again.
+__device__ __forceinline__ void store_once(float4 *p, const float4 &v) {
+  __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p));
 }
 
 // The two features of a record's first and second entry (raw: a, b, x
@@ -697,10 +758,6 @@ __device__ __forceinline__ float4 values(const uint4 &raw, int kind) {
   return make_float4((1.0f - x) * a, (1.0f - x) * b, x * a, x * b);
 }
 
-// Keeps the compiler from carrying what it computed of raw before (the values
-// are cheaper to find again than to hold).
-__device__ __forceinline__ void opaque(uint4 &raw) { asm volatile("" : "+v"(raw.x), "+v"(raw.y), "+v"(raw.z), "+v"(raw.w)); }
-
 // The work items of the accumulate pass, a wave per tile.  A tile without
 // records is cleared here when overwriting, and one with more than `target`
 // is split at the chunks where about as many are reached; its workgroups add
@@ -709,10 +766,10 @@ __device__ __forceinline__ void opaque(uint4 &raw) { asm volatile("" : "+v"(raw.
 // run table once or twice (0.5 MB for 36,503 samples, 3.4 MB for 262,143).
 __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__restrict__ runs, int64_t S,
                                                               const int64_t *__restrict__ S_dev, int64_t chunk_cap,
-                                                              int l0, int nl, int log2T, int tb, int overwrite,
-                                                              int64_t cap, BinQueue *__restrict__ queue,
+                                                              int l0, int nl, int log2T, int tb, int64_t cap,
+                                                              BinQueue *__restrict__ queue,
                                                               AccItem *__restrict__ items,
-                                                              float *__restrict__ gtable) {
+                                                              float *__restrict__ clear) {
   __shared__ uint32_t wholes, first_whole;
   const int lane = threadIdx.x & (kWave - 1), tpl_log2 = log2T - tb;
   const uint32_t bin =
@@ -725,13 +782,13 @@ __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__res
 #pragma unroll 4
   for (uint32_t c = lane; live && c < chunks; c += kWave) {
     const uint2 q = run[c];
-    total += (q.x >> 16) + (q.y >> 16);
+    total += run_pairs(q) + run_singles(q);
   }
   total = (uint32_t)__builtin_amdgcn_readlane(wave_incl_scan((int)total), kWave - 1);
   // half of what a resident workgroup would get of a level mix without empty
   // tiles, so the largest items do not outlast the others
   const uint32_t even = 4u * (uint32_t)nl * Sn / (2u * kAccMaxGrid);  // 8 L S < 2^32
-  const uint32_t target = even > kAccTarget ? even : kAccTarget;
+  const uint32_t target = even < kAccTarget ? kAccTarget : even < kAccMost ? even : kAccMost;
   // one global add per block: an add per tile is 15 us of adds to one address
   const bool whole = total <= target && total != 0u;
   __syncthreads();
@@ -742,19 +799,14 @@ __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__res
   __syncthreads();
   if (whole && lane == 0) items[cap - 1 - (int64_t)(first_whole + at)] = AccItem{bin, 0u, chunks, 0u};
   if (whole || !live) return;
-  if (overwrite) {
-    const uint32_t lr = bin >> tpl_log2, tile = bin - (lr << tpl_log2);
-    float4 *dst = reinterpret_cast<float4 *>(
-        gtable + ((((int64_t)l0 + lr) << (log2T + 1)) + ((int64_t)tile << (tb + 1))));
-    for (int i = lane; i < 1 << (tb - 1); i += kWave) dst[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  }
+  if (clear) clear_tile(clear, bin, l0, log2T, tb, lane, kWave);
   if (total == 0u) return;
   const uint32_t groups = total / target + 1u, per = total / groups + 1u;  // records
   uint32_t before = 0, start = 0, group = 0;  // records before the step, the open item's first chunk and group
   for (uint32_t cb = 0; cb < chunks; cb += kWave) {
     const uint32_t c = cb + lane;
     const uint2 q = c < chunks ? run[c] : make_uint2(0u, 0u);
-    const uint32_t n = (q.x >> 16) + (q.y >> 16), incl = (uint32_t)wave_incl_scan((int)n);
+    const uint32_t n = run_pairs(q) + run_singles(q), incl = (uint32_t)wave_incl_scan((int)n);
     const uint32_t mine = c < chunks ? (before + incl - n) / per : 0xffffffffu;  // < groups
     const uint32_t below = (uint32_t)__shfl_up((int)mine, 1, kWave);  // by every lane: an inactive one gives nothing
     const uint32_t prev = lane == 0 ? group : below;
@@ -775,41 +827,70 @@ __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__res
   if (lane == 0) items[atomicAdd(&queue->split, 1u)] = AccItem{bin, start, chunks, 1u};
 }
 
+// The largest of the wave's values below 2^8.
+__device__ __forceinline__ uint32_t wave_max8(uint32_t v) {
+  uint32_t r = 0u;
+  bool in = true;
+#pragma unroll
+  for (int b = 7; b >= 0; --b) {
+    const bool one = in && ((v >> b) & 1u) != 0u;
+    if (__any(one)) {
+      r |= 1u << b;
+      in = one;
+    }
+  }
+  return r;
+}
+
 // The block's waves share a window of 64 pieces, a piece being up to 64
 // consecutive records of a run; a batch is the pieces of up to kAccRuns runs
 // (chunks).  Four waves scan the runs' numbers of pieces into LDS, then each
 // lane of a wave looks up one piece of the window, and the wave reads its
 // eight from those lanes.
-// The next window's records, also those of the next item, are loaded before
-// this window's sums are converted and stored, and the runs of the batch
-// after it before that, so the loads' latency hides behind the conversion.
-// The items' sizes differ, so they come from a queue, the shared tiles' first.
-// Bound by the chain of a window (load, maximum, LDS adds, conversion), two
-// workgroups per CU by LDS.
+// An item's windows are added one after the other without a barrier, all with
+// the item's scale; its sums are converted and stored once.  The next item's
+// first records and the runs of the batch after it are loaded before that, so
+// their latency hides behind it.  A NaN or an infinity (only where the item
+// says so) stays out of the sums and sets a bit of its entry.
+// A workgroup takes every gridDim.x-th item, the shared tiles' first, and where
+// items are long the last two rounds' from a queue, as their sizes differ.
+// Bound by the chain of an item (its runs, their places, its records, the LDS
+// adds, the conversion), two workgroups per CU by LDS.
 __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__restrict__ queue,
                                                                 const AccItem *__restrict__ list, int64_t cap,
                                                                 const uint2 *__restrict__ runs,
                                                                 const char *__restrict__ rec, int64_t S,
                                                                 const int64_t *__restrict__ S_dev, int64_t chunk_cap,
-                                                                int l0, int log2T, int tb, int overwrite,
+                                                                int l0, int nl, int log2T, int tb, int overwrite,
                                                                 float *__restrict__ gtable) {
-  extern __shared__ unsigned long long acc[];  // 2 E fixed-point sums
-  __shared__ float red[kAccWaves];
-  __shared__ int redf[kAccWaves];
+  extern __shared__ unsigned long long acc[];  // 2 E fixed-point sums: first features, second features
+  __shared__ uint32_t special[3][kAccSums / 32];  // of each sum: an infinity, a negative one, a NaN came in
   __shared__ AccItem queued;  // the item after the next (bin kNoItem: none)
   __shared__ uint32_t trun[kAccRuns];  // the batch's runs (first record, count << 16)
   __shared__ int toff[kAccRuns];       // their first pieces, within the 64 runs of a wave
   __shared__ int ttot[kRunWaves];      // pieces of each 64 runs; whether they have single records
   __shared__ int tsing[kRunWaves];
+  __shared__ uint32_t tex[kRunWaves];  // of the item: largest exponent field, kOdd
+  constexpr uint32_t kOdd = 1u << 8;
   const int tpl_log2 = log2T - tb;
   const int n2 = 1 << tb;  // entries of a tile (2 sums each)
   const int n4 = n2 / 2;   // float4 (2 entries) per tile
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int64_t Sn = count_of(S, S_dev);
   const uint32_t nsplit = queue->split, nitems = nsplit + queue->whole;
+  ulonglong2 *a2 = reinterpret_cast<ulonglong2 *>(acc);  // cleared while the counts are on their way
+  for (int j = tid; j < n2; j += kAccBlock) a2[j] = make_ulonglong2(0ull, 0ull);
+  for (int j = tid; j < kAccSums / 32; j += kAccBlock) special[0][j] = special[1][j] = special[2][j] = 0u;
   if (blockIdx.x >= nitems) return;
   auto item_at = [&](uint32_t i) {
     return i < nsplit ? list[i] : i < nitems ? list[cap - 1 - (int64_t)(i - nsplit)] : AccItem{kNoItem, 0u, 0u, 0u};
+  };
+  // the items taken by place; the others by queue
+  const uint32_t rounds = nitems / gridDim.x;
+  const bool brief = 4u * (uint32_t)nl * (uint32_t)Sn / kAccBrief < nitems;
+  const uint32_t fixed = (rounds > 2u ? rounds - 1u : 1u) * gridDim.x;
+  auto index_after = [&](uint32_t i) {
+    return i + gridDim.x < fixed || brief ? i + gridDim.x : fixed + atomicAdd(&queue->next, 1u);
   };
   auto uniform = [](const AccItem &I) {
     return AccItem{(uint32_t)__builtin_amdgcn_readfirstlane((int)I.bin),
@@ -817,9 +898,8 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
                    (uint32_t)__builtin_amdgcn_readfirstlane((int)I.c1),
                    (uint32_t)__builtin_amdgcn_readfirstlane((int)I.split)};
   };
-  if (tid == 0) queued = item_at(atomicAdd(&queue->next, 1u));
-  ulonglong2 *a2 = reinterpret_cast<ulonglong2 *>(acc);
-  for (int j = tid; j < n2; j += kAccBlock) a2[j] = make_ulonglong2(0ull, 0ull);
+  uint32_t taken = blockIdx.x;  // in thread 0: index of the item that was queued last
+  if (tid == 0) queued = item_at(taken = index_after(taken));
   __syncthreads();
   // run of chunk cb + 64 wid + lane, in the first kRunWaves waves
   auto load_runs = [&](const AccItem &I, uint32_t cb) {
@@ -837,14 +917,25 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
   int sing = 0;             // the batch has single records as well
   uint4 raw[kAccPer];
   uint32_t in = 0;  // bit k: raw[k] holds a record
-  auto begin = [&]() {  // the tables of batch (cb, kind); a barrier follows
+  auto begin = [&](bool first) {  // the tables of batch (cb, kind), the first of the item; a barrier follows
     if (wid < kRunWaves) {
-      const uint32_t x = kind ? ri.y : ri.x;
-      const int n = (int)((x >> 16) + kWave - 1) / kWave;
+      if (first) {
+        uint32_t ex = run_exponent(ri);
+        bool odd = run_odd(ri);
+        for (uint32_t c = cb + kAccRuns + wid * kWave + lane; c < I.c1; c += kAccRuns) {
+          const uint2 q = runs[(int64_t)I.bin * chunk_cap + c];
+          ex = max(ex, run_exponent(q));
+          odd |= run_odd(q);
+        }
+        ex = wave_max8(ex) | (__any(odd) ? kOdd : 0u);
+        if (lane == 0) tex[wid] = ex;
+      }
+      const uint32_t count = kind ? run_singles(ri) : run_pairs(ri), first = kind ? ri.y & 0x3fffu : ri.x & 0x1fffu;
+      const int n = (int)(count + kWave - 1) / kWave;
       const int incl = wave_incl_scan(n);
-      trun[wid * kWave + lane] = x;
+      trun[wid * kWave + lane] = first | count << 16;
       toff[wid * kWave + lane] = incl - n;
-      const int sing = __any(ri.y >> 16) != 0;
+      const int sing = __any(run_singles(ri)) != 0;
       if (lane == kWave - 1) {
         ttot[wid] = incl;
         tsing[wid] = sing;
@@ -911,187 +1002,122 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
       if (item_n.bin != kNoItem) {
         In = item_n;
         cbn = In.c0;
-        if (tid == 0) queued = item_at(atomicAdd(&queue->next, 1u));  // read after the next barrier
+        if (tid == 0) queued = item_at(taken = index_after(taken));  // read after the next barrier
       }
     }
     rin = load_runs(In, cbn);
   };
-  begin();
+  uint32_t how = 0;  // the item's largest exponent field, kOdd
+  auto item_how = [&]() {
+    uint32_t ex = 0, odd = 0;
+#pragma unroll
+    for (int h = 0; h < kRunWaves; ++h) {
+      const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane((int)tex[h]);
+      ex = max(ex, t & 0xffu);
+      odd |= t & kOdd;
+    }
+    return ex | odd;
+  };
+  begin(true);
   __syncthreads();
+  how = item_how();
   fill();
   if (next >= total && !sing) next_batch();
-  float4 out[kAccWr];
-#pragma unroll
-  for (int q = 0; q < kAccWr; ++q) out[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  bool any = false;
   for (;;) {
-    // the window's largest finite |value|, and whether it holds a NaN or an
-    // infinity (they stay out of the scale and the integer sums)
-    float m = 0.0f;
-    bool odd = false;
+    // |value| < 2^(exponent - 126): with 2^s, s = 174 - exponent, a value is
+    // below 2^48 and a sum of the item's below 2^63
+    const int sc = 174 - (int)(how & 0xffu);
+    const double scale = __longlong_as_double((long long)(1023 + sc) << 52);
+    const bool odd = (how & kOdd) != 0;
+    auto add = [&](uint32_t i, float f) {
+      if (odd && !isfinite(f))
+        atomicOr(&special[isnan(f) ? 2 : f < 0.0f ? 1 : 0][i >> 5], 1u << (i & 31u));
+      else
+        atomicAdd(&acc[i], to_fixed(f, scale));
+    };
 #pragma unroll
     for (int k = 0; k < kAccPer; ++k) {
       if (!((in >> k) & 1u)) continue;
       const float4 v = values(raw[k], kind);
-      const float t = fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
-      // finite unless a term is not (or their sum overflows: the slow path)
-      if (isfinite(fabsf(v.x) + fabsf(v.y) + fabsf(v.z) + fabsf(v.w))) {
-        m = fmaxf(m, t);
-      } else {
-        odd = true;
-        const float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int h = 0; h < 4; ++h) m = isfinite(f[h]) ? fmaxf(m, fabsf(f[h])) : m;
-      }
+      const uint32_t e = kind ? raw[k].z : raw[k].w;
+      const uint32_t e0 = e & (uint32_t)(n2 - 1), e1 = (e >> 16) & (uint32_t)(n2 - 1);
+      add(e0, v.x);
+      add(n2 + e0, v.y);
+      if (kind) continue;
+      add(e1, v.z);
+      add(n2 + e1, v.w);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
-    const int flags = (__any(odd) ? 1 : 0) | (__any(in != 0u) ? 2 : 0);
-    if (lane == 0) {
-      red[wid] = m;
-      redf[wid] = flags;
-    }
-    __syncthreads();  // also: the sums are clear
-    m = 0.0f;
-    int wf = 0;
-#pragma unroll
-    for (int w = 0; w < kAccWaves; ++w) {
-      m = fmaxf(m, red[w]);
-      wf |= redf[w];
-    }
-    wf = __builtin_amdgcn_readfirstlane(wf);
-    const bool odd_tile = (wf & 1) != 0, full = (wf & 2) != 0, again = next < total;
-    const AccItem item_q = uniform(queued);
-    const uint32_t in_now = in;
-    const int kind_now = kind;
-    // |value| < 2^ex: with 2^s, s = 47 - ex, an entry's sum over the
-    // window's 2^12 records stays below 2^59
-    int ex = 0;
-    frexpf(m, &ex);
-    const int sc = 47 - ex;
-    if (full) {
-      const double scale = ldexp(1.0, sc);
-#pragma unroll
-      for (int k = 0; k < kAccPer; ++k) {
-        if (!((in_now >> k) & 1u)) continue;
-        opaque(raw[k]);
-        const float4 v = values(raw[k], kind_now);
-        const uint32_t e = kind_now ? raw[k].z : raw[k].w;
-        const uint32_t e0 = e & (uint32_t)(n2 - 1), e1 = (e >> 16) & (uint32_t)(n2 - 1);
-        if (!odd_tile || isfinite(v.x)) atomicAdd(&acc[e0], to_fixed(v.x, scale));
-        if (!odd_tile || isfinite(v.y)) atomicAdd(&acc[n2 + e0], to_fixed(v.y, scale));
-        if (kind_now) continue;
-        if (!odd_tile || isfinite(v.z)) atomicAdd(&acc[e1], to_fixed(v.z, scale));
-        if (!odd_tile || isfinite(v.w)) atomicAdd(&acc[n2 + e1], to_fixed(v.w, scale));
-      }
-    }
-    // move on: the same batch, its single records, the next batch or item
-    const AccItem I_now = I;
-    bool last = false, stop = false;  // last window of the item; no item left
-    if (!again) {
+    if (next < total) {
+      fill();
+    } else {
+      // move on: the batch's single records, the next batch or item
+      const AccItem I_now = I;
+      bool last = false, stop = false;  // last window of the item; no item left
+      __syncthreads();                  // the adds are complete, the tables and the queued item free to change
       if (kind == 0 && sing) {
         kind = 1;
       } else {
         last = cb + kAccRuns >= I.c1;
         stop = last && item_n.bin == kNoItem;
-        if (last) item_n = item_q;
+        if (last) item_n = uniform(queued);
         I = In;
         cb = cbn;
         ri = rin;
         kind = 0;
       }
-      begin();
-    }
-    __syncthreads();  // the integer adds are complete, the tables written
-    if (!odd_tile) fill();
-    if (full) {
-      any = true;
-#pragma unroll
-      for (int q = 0; q < kAccWr; ++q) {
-        const int j = tid + q * kAccBlock;
-        if (j < n4) {  // the first features' sums, then (n2 on) the second features'
-          const ulonglong2 f = a2[j], g = a2[n4 + j];
-          out[q].x += from_fixed(f.x, sc);
-          out[q].y += from_fixed(g.x, sc);
-          out[q].z += from_fixed(f.y, sc);
-          out[q].w += from_fixed(g.y, sc);
-          a2[j] = make_ulonglong2(0ull, 0ull);
-          a2[n4 + j] = make_ulonglong2(0ull, 0ull);
-        }
+      if (!stop) begin(last);
+      __syncthreads();  // the tables are written
+      if (!stop) {
+        if (last) how = item_how();
+        fill();
       }
-    }
-    if (odd_tile) {
-      // NaN and infinite values are added as FP32 values in the cleared tile,
-      // so they reach their own entries as FP32 adds would
-      float *fv = reinterpret_cast<float *>(acc);
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < kAccPer; ++k) {
-        if (!((in_now >> k) & 1u)) continue;
-        const float4 v = values(raw[k], kind_now);
-        const uint32_t e = kind_now ? raw[k].z : raw[k].w;
-        const uint32_t e0 = e & (uint32_t)(n2 - 1), e1 = (e >> 16) & (uint32_t)(n2 - 1);
-        if (!isfinite(v.x)) atomicAdd(&fv[2 * e0], v.x);
-        if (!isfinite(v.y)) atomicAdd(&fv[2 * e0 + 1], v.y);
-        if (kind_now) continue;
-        if (!isfinite(v.z)) atomicAdd(&fv[2 * e1], v.z);
-        if (!isfinite(v.w)) atomicAdd(&fv[2 * e1 + 1], v.w);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kAccWr; ++q) {
-        const int j = tid + q * kAccBlock;
-        if (j < n4) {
-          const float4 f = reinterpret_cast<const float4 *>(fv)[j];
-          out[q].x += f.x;
-          out[q].y += f.y;
-          out[q].z += f.z;
-          out[q].w += f.w;
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kAccWr; ++q) {
-        const int j = tid + q * kAccBlock;
-        if (j < n4) reinterpret_cast<float4 *>(fv)[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      }
-      fill();
-    }
-    if (last) {
-      float4 *dst =
-          reinterpret_cast<float4 *>(gtable + ((((int64_t)l0 << log2T) + ((int64_t)I_now.bin << tb)) << 1));
-      if (I_now.split) {
-        if (any)
-#pragma unroll
-          for (int q = 0; q < kAccWr; ++q) {
-            const int j = tid + q * kAccBlock;
-            if (j >= n4) continue;
-            float *df = reinterpret_cast<float *>(dst + j);
-            if (out[q].x != 0.0f) atomicAdd(df, out[q].x);
-            if (out[q].y != 0.0f) atomicAdd(df + 1, out[q].y);
-            if (out[q].z != 0.0f) atomicAdd(df + 2, out[q].z);
-            if (out[q].w != 0.0f) atomicAdd(df + 3, out[q].w);
-          }
-      } else if (overwrite || any) {  // the only writer of this tile
+      if (last) {
+        const double inv = __longlong_as_double((long long)(1023 - sc) << 52);
+        float4 *dst =
+            reinterpret_cast<float4 *>(gtable + ((((int64_t)l0 << log2T) + ((int64_t)I_now.bin << tb)) << 1));
 #pragma unroll
         for (int q = 0; q < kAccWr; ++q) {
           const int j = tid + q * kAccBlock;
           if (j >= n4) continue;
-          float4 o = out[q];
-          if (!overwrite) {
-            const float4 p = dst[j];
-            o.x += p.x;
-            o.y += p.y;
-            o.z += p.z;
-            o.w += p.w;
+          const ulonglong2 f = a2[j], g = a2[n4 + j];
+          a2[j] = make_ulonglong2(0ull, 0ull);
+          a2[n4 + j] = make_ulonglong2(0ull, 0ull);
+          float4 o = make_float4(from_fixed(f.x, inv), from_fixed(g.x, inv), from_fixed(f.y, inv), from_fixed(g.y, inv));
+          if (odd) {
+            auto mend = [&](uint32_t i, float &v) {
+              const uint32_t w = i >> 5, b = 1u << (i & 31u);
+              const bool pos = (special[0][w] & b) != 0, neg = (special[1][w] & b) != 0, nan = (special[2][w] & b) != 0;
+              v = nan || (pos && neg) ? NAN : pos ? INFINITY : neg ? -INFINITY : v;
+            };
+            mend(2 * j, o.x);
+            mend(n2 + 2 * j, o.y);
+            mend(2 * j + 1, o.z);
+            mend(n2 + 2 * j + 1, o.w);
           }
-          dst[j] = o;
+          if (I_now.split) {
+            float *df = reinterpret_cast<float *>(dst + j);
+            if (o.x != 0.0f) atomicAdd(df, o.x);
+            if (o.y != 0.0f) atomicAdd(df + 1, o.y);
+            if (o.z != 0.0f) atomicAdd(df + 2, o.z);
+            if (o.w != 0.0f) atomicAdd(df + 3, o.w);
+          } else {  // the only writer of this tile
+            if (!overwrite) {
+              const float4 p = dst[j];
+              o.x += p.x;
+              o.y += p.y;
+              o.z += p.z;
+              o.w += p.w;
+            }
+            store_once(dst + j, o);
+          }
         }
+        if (stop) return;
+        if (odd) {
+          __syncthreads();  // the bits are read
+          for (int j = tid; j < kAccSums / 32; j += kAccBlock) special[0][j] = special[1][j] = special[2][j] = 0u;
+        }
+        __syncthreads();  // the sums are clear
       }
-      if (stop) return;
-#pragma unroll
-      for (int q = 0; q < kAccWr; ++q) out[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      any = false;
     }
     // once a batch, when its last window is on its way: an item taken earlier
     // would wait longer behind this one
@@ -1260,16 +1286,19 @@ extern "C" int32_t ia355_hashgrid_table_grad(const float *grad_feat, const float
   BinGeom g;
   bin_geom(nl, S, log2T, &g);  // fewer levels than `full`: fits its workspace
   const BinWs w = bin_ws(nl, S, g, ws);
-  const size_t cnt_lds = sizeof(uint32_t) * ((size_t)1 << g.tpl_log2);  // at most 64 KB
+  const size_t cnt_lds = sizeof(uint2) * ((size_t)1 << g.tpl_log2), most_lds = sizeof(uint2) * kMaxBins;  // 128 KB
   // the blocks loop over the chunks; with a device count the grid is bounded
   int64_t per_level = g.chunks < 4096 ? g.chunks : 4096;
   if (S_dev && per_level > 64) per_level = 64;
+  if (cnt_lds > 48 * 1024 && hipFuncSetAttribute((const void *)bin_sort_kernel,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)most_lds) != hipSuccess)
+    return IA355_ERR_HIP;
   bin_sort_kernel<<<(unsigned)(nl * per_level), kSortBlock, cnt_lds, s>>>(grad_feat, xc, bone, S, S_dev, ld, l0, nl,
                                                                           log2T, g.tb, lv, box, g.chunks, w.queue,
                                                                           w.runs, w.rec);
   bin_plan_kernel<<<(unsigned)ceil_div((int64_t)nl << g.tpl_log2, kPlanBlock / kWave), kPlanBlock, 0, s>>>(
-      w.runs, S, S_dev, g.chunks, l0, nl, log2T, g.tb, overwrite, w.cap, w.queue, w.items, grad_table);
+      w.runs, S, S_dev, g.chunks, l0, nl, log2T, g.tb, w.cap, w.queue, w.items, overwrite ? grad_table : nullptr);
   bin_accum_kernel<<<kAccMaxGrid, kAccBlock, sizeof(unsigned long long) * 2 * ((size_t)1 << g.tb), s>>>(
-      w.queue, w.items, w.cap, w.runs, w.rec, S, S_dev, g.chunks, l0, log2T, g.tb, overwrite, grad_table);
+      w.queue, w.items, w.cap, w.runs, w.rec, S, S_dev, g.chunks, l0, nl, log2T, g.tb, overwrite, grad_table);
   return launch_status();
 }

@@ -358,8 +358,8 @@ def test_table_grad_binned_sort_chunks(orc, log2T, L, S, count, overwrite):
 
 
 def test_table_grad_binned_work_items():
-    """The plan's list has room for tiles + records / 8192 items: a tile of n
-    records must not take more than n / 8192 + 1 of them, also where the
+    """The plan's list has room for tiles + updates / 4096 items: a tile of n
+    records must not take more than n / 4096 + 1 of them, also where the
     chunks of a shared tile span many steps of the planning wave (the counts
     are the second and third word of the workspace)."""
     K = _K()
@@ -373,5 +373,75 @@ def test_table_grad_binned_work_items():
     torch.cuda.synchronize()
     _, split, whole = host(ws[:12].view(torch.int32)).tolist()
     # level 0: one tile with every record (pairs of corners); level 1: its records lie in at most four tiles
-    most = (4 * S // 8192 + 1) + (4 * S // 8192 + 4)
+    most = (4 * S // 4096 + 1) + (4 * S // 4096 + 4)
     assert 0 < split and split + whole <= most, (split, whole, most)
+
+
+@pytest.mark.parametrize("many,overwrite,odd", [(False, True, False), (False, False, False), (False, True, True),
+                                                (True, True, False), (True, False, True)])
+def test_table_grad_binned_exact_whole_tiles(orc, many, overwrite, odd):
+    """A tile summed by one workgroup is the exact sum of its records, rounded
+    to FP32 once, in whatever order the samples come, in one call or in two:
+    positions, weights and gradients are such that every record and every sum
+    is exact in 64 bits (the oracle's), with gradients of 2^23 among gradients
+    of 1; either runs of more than 64 records and pairs that a tile boundary
+    separates, or short runs from many chunks.  Infinities change only their
+    own entries."""
+    K = _K()
+    rng = np.random.default_rng(3)
+    if many:
+        log2T, L, S, base = 19, 1, 90000, 128
+        x = rng.integers(0, 512, size=(S, 3)) / 512.0
+        x[1::100] = [9.25 / 128, 8.5 / 128, 20.75 / 128]  # one cell, in every chunk
+    else:
+        log2T, L, S, base = 16, 3, 2400, 32
+        x = rng.integers(0, 256, size=(S, 3)) / 256.0
+        x[::9] = [3.25 / 32, 25.5 / 32, 3.75 / 32]   # entries 4095 | 4096 of level 0
+        x[1::9] = [9.25 / 32, 8.5 / 32, 20.75 / 32]  # one cell: long runs
+        x[2::9] = [2.25 / 32, 25.5 / 32, 3.75 / 32]  # entries 4094 and 4095, 4127 and 4128, ...
+        x[3::9] = [4.25 / 32, 25.5 / 32, 3.75 / 32]  # entries 4096 and 4097, ...
+    g = rng.integers(-8, 9, size=(S, 2 * L)).astype(np.float32)
+    g[::7] *= 2.0 ** 20
+    if odd:
+        g[8, 0], g[1600, 1] = np.inf, -np.inf
+    res, zero = [base << k for k in range(L)], np.zeros((L, 1 << log2T, 2))
+    with np.errstate(invalid="ignore"):
+        marked, _ = orc.hash_encode_bwd(g, x, zero, res, AABB_NP)
+    clean = np.where(np.isfinite(g), g, 0.0)
+    ref, _ = orc.hash_encode_bwd(clean, x, zero, res, AABB_NP)
+    fin = np.isfinite(marked)
+    assert fin.all() != odd
+    start = 0.0 if overwrite else 0.5
+    want = np.float32(start) + ref.astype(np.float32)
+    ws = torch.empty(K.hashgrid_table_grad_workspace_size(S, L, 1 << log2T), dtype=torch.uint8, device=dev())
+    flag = K.OVERWRITE if overwrite else 0
+    for order, phases in ((np.arange(S), 1), (np.arange(S), 2), (rng.permutation(S), 1)):
+        gt = torch.full((L, 1 << log2T, 2), 7.0 if overwrite else start, device=dev())
+        gf = up(g[order].reshape(S, L, 2).transpose(1, 0, 2).reshape(-1))
+        args = (soa(x[order].astype(np.float32), S), None, S, S, float(base), 2.0, AABB, gt, ws)
+        if phases == 2:
+            K.hashgrid_table_grad(None, *args, K.TABLE_PLAN)
+            assert bool((gt == (7.0 if overwrite else start)).all())
+        K.hashgrid_table_grad(gf, *args, flag | (K.TABLE_REUSE_PLAN if phases == 2 else 0))
+        torch.cuda.synchronize()
+        got = host(gt)
+        np.testing.assert_array_equal(got[fin], want[fin])
+        assert np.array_equal(np.isnan(got), np.isnan(marked))
+        assert np.array_equal(got[np.isinf(marked)], marked[np.isinf(marked)].astype(np.float32))
+
+
+def test_table_grad_binned_most_tiles():
+    """One level of 2^26 entries, 16,384 tiles (128 KB of counters in the
+    sort): exact small sums, so equal to the atomic path's."""
+    K = _K()
+    S, T = 3001, 1 << 26
+    rng = np.random.default_rng(5)
+    x = soa((rng.integers(0, 1024, size=(S, 3)) / 1024.0).astype(np.float32), S)
+    gf = up(rng.integers(-8, 9, size=2 * S).astype(np.float32))
+    got = torch.full((1, T, 2), 7.0, device=dev())
+    ws = torch.empty(K.hashgrid_table_grad_workspace_size(S, 1, T), dtype=torch.uint8, device=dev())
+    K.hashgrid_table_grad(gf, x, None, S, S, 512.0, 2.0, AABB, got, ws, K.OVERWRITE)
+    ref = torch.zeros_like(got)
+    K.hashgrid_encode_bwd(gf, x, None, S, S, torch.zeros(1, T, 2, device=dev()), 512.0, 2.0, AABB, ref, None)
+    torch.cuda.synchronize()
+    assert torch.equal(got, ref) and int((ref != 0).sum()) > 2 * S
