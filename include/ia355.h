@@ -367,10 +367,10 @@ int32_t ia355_hashgrid_encode_bwd(const float *grad_feat, const float *xc, const
  * corner's update), then converted back once and written with plain stores.
  * Accuracy is absolute, relative to m: each value is rounded to a quantum of
  * at most m 2^-46, so an entry's error is at most its update count times
- * m 2^-47 plus one FP32 rounding of the entry (values below m 2^-49 contribute
+ * m 2^-47 plus one FP32 rounding of the entry (values below m 2^-48 contribute
  * zero), besides the FP32 roundings that form each value.  A tile with more
- * records than 4096 and than half of what an even spread would give a
- * workgroup (16,384 at most) is summed by several workgroups, each with its
+ * records than 8192 and than half of what an even spread would give a
+ * workgroup, or than 32,768, is summed by several workgroups, each with its
  * own m, that add their nonzero entries with FP32 atomics, one rounding each.
  * Every tile of the selected levels is written, so IA355_OVERWRITE needs no
  * separate clear.  A tile summed by one workgroup does not depend on the order

@@ -411,16 +411,16 @@ __global__ void __launch_bounds__(kDgBlock) table_grad_dense_kernel(const float 
 // addition to the table where items share the tile: an absolute bound relative
 // to the item's largest value.  An entry near m is as accurate as FP32 adds
 // leave it or better; one far below m (under about m 2^-24) is less accurate
-// than FP32 adds, and a value below m 2^-49 rounds to zero.  Integer addition
-// is associative, so a tile summed by one workgroup (any with 4096 updates or
+// than FP32 adds, and a value below m 2^-48 rounds to zero.  Integer addition
+// is associative, so a tile summed by one workgroup (any with 8192 records or
 // fewer) does not depend on the order of its records.
 // The traffic is the records (64 bytes per sample and level, written once and
 // read once) and one pass over the table slice.
 // 16 levels of 2^19 entries, field gradients (traced: sort, plan,
-// accumulate): 19 + 10 + 31 us for 36,503 samples, 100 + 13 + 115 us for
+// accumulate): 19 + 9 + 36 us for 36,503 samples, 100 + 13 + 115 us for
 // 262,143.  With a scale, a conversion and a clear of the tile for each window
-// of at most 4096 records, whose maximum the workgroup found first: 18 + 10 +
-// 41 and 81 + 14 + 145 us.  Counting, scanning and placing 12-byte single
+// of at most 4096 records, whose maximum the workgroup found first: 17 + 10 +
+// 43 and 101 + 15 + 146 us.  Counting, scanning and placing 12-byte single
 // records across all workgroups took six passes, 85 and 422 us: four of them
 // only to agree on offsets, and every 4096 records flushed a tile with global
 // atomics.  A fixed share of a level's tiles per item in place of the plan left
@@ -437,23 +437,18 @@ constexpr int kAccWaves = kAccBlock / kWave;
 constexpr int kAccPer = 8;         // records per thread and window
 constexpr int kRunWaves = 4;       // waves that load a batch's runs, one per lane
 constexpr int kAccRuns = kRunWaves * kWave;
-// Records of a work item at least, where a tile has more: a pair record is two
-// updates, and shorter items cost more additions to the table (8192: 37 us for
-// 36,503 samples in place of 31, as the shared tiles' items outlast the others).
-constexpr uint32_t kAccTarget = 4096;
-constexpr uint32_t kAccMost = 16384;  // and at most, but for its last chunk's
-// Records an item, on average, below which no item goes by queue: an add to
-// one address takes 10 ns, and a workgroup waits for its turn (36,503 samples,
-// 1580 records an item: 37 us by place, 41 with the last rounds by queue;
-// 262,143 samples, 9500 records: 128 and 117).
-constexpr uint32_t kAccBrief = 4096;
+// Records of a work item at least, where a tile has more (each item of a shared
+// tile costs an addition per entry it holds: with 4096, 36,503 random points in
+// tables of 2^12 to 2^17 took 10 to 28 us more of 50 to 90, on a surface and
+// 2^19 entries 3 us less of 65), and at most, but for its last chunk's.
+constexpr uint32_t kAccTarget = 8192, kAccMost = 32768;
 constexpr int kPlanBlock = 1024;
 constexpr uint32_t kNoItem = 0xffffffffu;
 constexpr int kAccWr = (1 << (kTileLog2Max - 1)) / kAccBlock;  // float4 of a tile per thread
 constexpr int kAccSums = 2 << kTileLog2Max;
 constexpr int kAccMaxGrid = 512;   // two workgroups per CU by LDS
 static_assert(4 * kSortChunk < 1 << 13 && 8 * kSortChunk < 1 << 14, "run places");
-static_assert((int64_t)(kAccMost + 8 * kSortChunk) << 48 > 0, "fixed-point head room");
+static_assert(kAccMost + 8 * kSortChunk < 1 << 16, "fixed-point head room");
 
 struct BinGeom {
   int tb;        // log2 entries per tile
@@ -586,24 +581,24 @@ __device__ __forceinline__ SingleRec *single_at(char *end, uint32_t i) {
   return reinterpret_cast<SingleRec *>(end) - 1 - i;
 }
 
+// A store whose line is not needed in the cache again.
+__device__ __forceinline__ void store_once(float4 *p, const float4 &v) {
+  __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p));
+}
+
 // Zeroes a tile with `threads` threads.
 __device__ __forceinline__ void clear_tile(float *gtable, uint32_t bin, int l0, int log2T, int tb, int thread,
                                            int threads) {
   float4 *dst = reinterpret_cast<float4 *>(gtable + ((((int64_t)l0 << log2T) + ((int64_t)bin << tb)) << 1));
-  for (int i = thread; i < 1 << (tb - 1); i += threads) dst[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int i = thread; i < 1 << (tb - 1); i += threads) store_once(dst + i, make_float4(0.0f, 0.0f, 0.0f, 0.0f));
 }
 
-// The larger exponent field of a and b, of the finite ones; a NaN or an
-// infinity sets odd.  By the bits as integers, where fmaxf would hide a NaN.
-__device__ __forceinline__ uint32_t top_exponent(float a, float b, int &odd) {
-  const uint32_t ea = (__float_as_uint(a) >> 23) & 255u, eb = (__float_as_uint(b) >> 23) & 255u;
-  uint32_t ex = max(ea, eb);
-  if (ex == 255u) {
-    odd = 1;
-    ex = max(ea == 255u ? 0u : ea, eb == 255u ? 0u : eb);
-  }
-  return ex;
+// |v|, or zero for a NaN or an infinity.
+__device__ __forceinline__ float finite_abs(float v) {
+  const float a = fabsf(v);
+  return a < INFINITY ? a : 0.0f;
 }
+__device__ __forceinline__ uint32_t exponent_of(float nonnegative) { return __float_as_uint(nonnegative) >> 23; }
 
 __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
     const float *__restrict__ gfeat, const float *__restrict__ xc, const int16_t *__restrict__ bone, int64_t S,
@@ -689,8 +684,10 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
       asm volatile("" : "+v"(x[j][0]), "+v"(x[j][1]), "+v"(x[j][2]));
       const float2 g = reinterpret_cast<const float2 *>(
           gfeat)[(int64_t)level * ld + c * kSortChunk + sample0 + j * sstep];
+      const float top = fmaxf(finite_abs(g.x), finite_abs(g.y));
+      if (!(fabsf(g.x) + fabsf(g.y) < INFINITY)) odd = 1;
       const CellPos p = level_pos(x[j], box, N);
-      const float w0 = 1.0f - p.f[0], w1 = p.f[0];
+      const float w0 = 1.0f - p.f[0], w1 = p.f[0], wx = fmaxf(w0, w1);
       uint32_t idx[8];
       cell_indices(p, N, dense, Tmask, idx);
 #pragma unroll
@@ -704,16 +701,15 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
         if (t0 == t1) {
           const uint32_t r = ((k & 2 ? rank[j].y : rank[j].x) >> (k & 1 ? 16 : 0)) & 0xffffu;
           const uint2 q = cnt[t0];
-          const uint32_t ex = top_exponent(a, b, odd);  // of the values: this one or the one below
+          const uint32_t ex = exponent_of(wx * (wyz * top));  // the largest value's (rounding is monotonic)
           if (ex > q.y) atomicMax(&cnt[t0].y, ex);
           pairs[(q.x & 0xffffu) + r] =
               make_uint4(__float_as_uint(a), __float_as_uint(b), __float_as_uint(w1), e0 | e1 << 16);
         } else {  // the singles' next places are counted in the high halves
-          const SingleRec s0{w0 * a, w0 * b, e0}, s1{w1 * a, w1 * b, e1};
-          atomicMax(&cnt[t0].y, top_exponent(s0.a, s0.b, odd));
-          atomicMax(&cnt[t1].y, top_exponent(s1.a, s1.b, odd));
-          *single_at(end, atomicAdd(&cnt[t0].x, 1u << 16) >> 16) = s0;
-          *single_at(end, atomicAdd(&cnt[t1].x, 1u << 16) >> 16) = s1;
+          atomicMax(&cnt[t0].y, exponent_of(w0 * (wyz * top)));
+          atomicMax(&cnt[t1].y, exponent_of(w1 * (wyz * top)));
+          *single_at(end, atomicAdd(&cnt[t0].x, 1u << 16) >> 16) = SingleRec{w0 * a, w0 * b, e0};
+          *single_at(end, atomicAdd(&cnt[t1].x, 1u << 16) >> 16) = SingleRec{w1 * a, w1 * b, e1};
         }
       }
     }
@@ -744,11 +740,6 @@ __device__ __forceinline__ uint4 load16(const char *p) {
   typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
   const u4 v = *reinterpret_cast<const u4 *>(p);
   return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// A store whose line is not needed in the cache again.
-__device__ __forceinline__ void store_once(float4 *p, const float4 &v) {
-  __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4 *>(p));
 }
 
 // The two features of a record's first and second entry (raw: a, b, x
@@ -852,9 +843,8 @@ __device__ __forceinline__ uint32_t wave_max8(uint32_t v) {
 // first records and the runs of the batch after it are loaded before that, so
 // their latency hides behind it.  A NaN or an infinity (only where the item
 // says so) stays out of the sums and sets a bit of its entry.
-// A workgroup takes every gridDim.x-th item, the shared tiles' first, and where
-// items are long the last two rounds' from a queue, as their sizes differ.
-// Bound by the chain of an item (its runs, their places, its records, the LDS
+// A workgroup takes items by place and then from a queue, the shared tiles'
+// first, which are the longest.  Bound by the chain of an item (its runs, their places, its records, the LDS
 // adds, the conversion), two workgroups per CU by LDS.
 __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__restrict__ queue,
                                                                 const AccItem *__restrict__ list, int64_t cap,
@@ -885,12 +875,14 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
   auto item_at = [&](uint32_t i) {
     return i < nsplit ? list[i] : i < nitems ? list[cap - 1 - (int64_t)(i - nsplit)] : AccItem{kNoItem, 0u, 0u, 0u};
   };
-  // the items taken by place; the others by queue
-  const uint32_t rounds = nitems / gridDim.x;
-  const bool brief = 4u * (uint32_t)nl * (uint32_t)Sn / kAccBrief < nitems;
-  const uint32_t fixed = (rounds > 2u ? rounds - 1u : 1u) * gridDim.x;
+  // Items before `fixed` are taken by place, the last rounds' from a queue: an
+  // add to one address takes 10 ns, and a workgroup waits for its turn, but the
+  // items differ (36,503 samples, three rounds: 37 us, with two of them by
+  // queue 41; 262,143, three long ones: 117, all by place 128; 16,384 short
+  // ones 100, all by queue 118).
+  const uint32_t rounds = nitems / gridDim.x, fixed = (rounds > 3u ? rounds - 1u : 2u) * gridDim.x;
   auto index_after = [&](uint32_t i) {
-    return i + gridDim.x < fixed || brief ? i + gridDim.x : fixed + atomicAdd(&queue->next, 1u);
+    return i + gridDim.x < fixed ? i + gridDim.x : fixed + atomicAdd(&queue->next, 1u);
   };
   auto uniform = [](const AccItem &I) {
     return AccItem{(uint32_t)__builtin_amdgcn_readfirstlane((int)I.bin),
@@ -1024,9 +1016,9 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
   fill();
   if (next >= total && !sing) next_batch();
   for (;;) {
-    // |value| < 2^(exponent - 126): with 2^s, s = 174 - exponent, a value is
-    // below 2^48 and a sum of the item's below 2^63
-    const int sc = 174 - (int)(how & 0xffu);
+    // |value| < 2^(exponent - 126): with 2^s, s = 173 - exponent, a value is
+    // below 2^47 and a sum of the item's below 2^63
+    const int sc = 173 - (int)(how & 0xffu);
     const double scale = __longlong_as_double((long long)(1023 + sc) << 52);
     const bool odd = (how & kOdd) != 0;
     auto add = [&](uint32_t i, float f) {

@@ -358,8 +358,8 @@ def test_table_grad_binned_sort_chunks(orc, log2T, L, S, count, overwrite):
 
 
 def test_table_grad_binned_work_items():
-    """The plan's list has room for tiles + updates / 4096 items: a tile of n
-    records must not take more than n / 4096 + 1 of them, also where the
+    """The plan's list has room for tiles + updates / 8192 items: a tile of n
+    records must not take more than n / 8192 + 1 of them, also where the
     chunks of a shared tile span many steps of the planning wave (the counts
     are the second and third word of the workspace)."""
     K = _K()
@@ -373,7 +373,7 @@ def test_table_grad_binned_work_items():
     torch.cuda.synchronize()
     _, split, whole = host(ws[:12].view(torch.int32)).tolist()
     # level 0: one tile with every record (pairs of corners); level 1: its records lie in at most four tiles
-    most = (4 * S // 4096 + 1) + (4 * S // 4096 + 4)
+    most = (4 * S // 8192 + 1) + (4 * S // 8192 + 4)
     assert 0 < split and split + whole <= most, (split, whole, most)
 
 
