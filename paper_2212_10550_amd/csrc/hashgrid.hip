@@ -396,6 +396,8 @@ __global__ void __launch_bounds__(kDgBlock) table_grad_dense_kernel(const float 
 //  3. accumulate: a workgroup takes an item at a time, sums its runs into an
 //     LDS copy of the tile and writes it with plain vector stores, or adds its
 //     nonzero entries with global atomics where several share the tile.
+// The work items depend on the positions alone, so a first call may make them
+// before the gradients are known; the second then sorts and accumulates.
 // The two x-neighbouring corners of a cell are adjacent entries or differ in
 // their low index bits (the x prime is 1), so they nearly always fall in one
 // tile and travel as one 16-byte record: the two features' (w_y w_z) dL/dfeat,
@@ -496,6 +498,7 @@ struct BinWs {
   BinQueue *queue;
   AccItem *items;  // shared tiles' from the start on, whole tiles' from the end down
   int64_t cap;     // of items: a tile of n records has at most n / kAccTarget + 1
+  uint8_t *shared;  // per tile: no whole item, so an overwrite clears it before the accumulate pass
   uint2 *runs;
   char *rec;
   size_t bytes;
@@ -510,6 +513,8 @@ inline BinWs bin_ws(int nl, int64_t S, const BinGeom &g, void *base) {
   w.items = (AccItem *)(p + o);
   w.cap = ((int64_t)nl << g.tpl_log2) + (int64_t)nl * S * 8 / kAccTarget;
   o += align256(sizeof(AccItem) * (size_t)w.cap);
+  w.shared = (uint8_t *)(p + o);
+  o += align256((size_t)nl << g.tpl_log2);
   w.rec = p + o;
   o += align256((size_t)kSampleBytes * (size_t)nl * (size_t)(S > 0 ? S : 1));
   w.runs = (uint2 *)(p + o);  // after the records: a single record is loaded with the four bytes behind it
@@ -600,11 +605,22 @@ __device__ __forceinline__ float finite_abs(float v) {
 }
 __device__ __forceinline__ uint32_t exponent_of(float nonnegative) { return __float_as_uint(nonnegative) >> 23; }
 
+// The passes of a call: all of them, those that need only the positions (the
+// counts and the work items), or the others.
+enum BinPhase { kBinAll, kBinPlan, kBinRest };
+
+template <BinPhase kPhase>
 __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
     const float *__restrict__ gfeat, const float *__restrict__ xc, const int16_t *__restrict__ bone, int64_t S,
     const int64_t *__restrict__ S_dev, int64_t ld, int l0, int nl, int log2T, int tb, Levels lv, Box box,
-    int64_t chunk_cap, BinQueue *__restrict__ queue, uint2 *__restrict__ runs, char *__restrict__ rec) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *queue = BinQueue{0u, 0u, 0u};
+    int64_t chunk_cap, BinQueue *__restrict__ queue, uint2 *__restrict__ runs, char *__restrict__ rec,
+    const uint8_t *__restrict__ shared, float *__restrict__ gtable) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (kPhase == kBinRest)
+      queue->next = 0u;
+    else
+      *queue = BinQueue{0u, 0u, 0u};
+  }
   // per tile: pair records, single records << 16; the largest exponent field
   extern __shared__ uint2 cnt[];
   __shared__ uint32_t wsum[kSortBlock / kWave];
@@ -662,6 +678,13 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
       rank[j] = make_uint2((r[0] & 0xffffu) | r[1] << 16, (r[2] & 0xffffu) | r[3] << 16);
     }
     __syncthreads();
+    if (kPhase == kBinPlan) {
+      for (int i = threadIdx.x; i < tiles; i += kSortBlock)
+        runs[(((int64_t)lr << tpl_log2) + i) * chunk_cap + c] =
+            pack_run(0u, cnt[i].x & 0xffffu, 0u, cnt[i].x >> 16, 0u, 0u);
+      __syncthreads();  // the counters are cleared for the next chunk
+      continue;
+    }
     // counts -> offsets, in place
     uint32_t carry = 0;
     for (int b0 = 0; b0 < tiles; b0 += kSortBlock) {
@@ -723,6 +746,9 @@ __global__ void __launch_bounds__(kSortBlock, 6) bin_sort_kernel(
     }
     __syncthreads();  // the counters are cleared for the next chunk
   }
+  if (kPhase == kBinRest && gtable)  // overwriting: what the plan pass clears otherwise
+    for (uint32_t bin = blockIdx.x; bin < (uint32_t)nl << (log2T - tb); bin += gridDim.x)
+      if (shared[bin]) clear_tile(gtable, bin, l0, log2T, tb, threadIdx.x, kSortBlock);
 }
 
 // v scale rounded to an integer (ties to even), as two's complement bits
@@ -760,6 +786,7 @@ __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__res
                                                               int l0, int nl, int log2T, int tb, int64_t cap,
                                                               BinQueue *__restrict__ queue,
                                                               AccItem *__restrict__ items,
+                                                              uint8_t *__restrict__ shared,
                                                               float *__restrict__ clear) {
   __shared__ uint32_t wholes, first_whole;
   const int lane = threadIdx.x & (kWave - 1), tpl_log2 = log2T - tb;
@@ -782,6 +809,7 @@ __global__ void __launch_bounds__(kPlanBlock) bin_plan_kernel(const uint2 *__res
   const uint32_t target = even < kAccTarget ? kAccTarget : even < kAccMost ? even : kAccMost;
   // one global add per block: an add per tile is 15 us of adds to one address
   const bool whole = total <= target && total != 0u;
+  if (live && lane == 0) shared[bin] = !whole;
   __syncthreads();
   uint32_t at = 0;
   if (whole && lane == 0) at = atomicAdd(&wholes, 1u);
@@ -867,13 +895,18 @@ __global__ void __launch_bounds__(kAccBlock, 4) bin_accum_kernel(BinQueue *__res
   const int n4 = n2 / 2;   // float4 (2 entries) per tile
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int64_t Sn = count_of(S, S_dev);
+  const uint32_t chunks = (uint32_t)ceil_div(Sn, (int64_t)kSortChunk);
   const uint32_t nsplit = queue->split, nitems = nsplit + queue->whole;
   ulonglong2 *a2 = reinterpret_cast<ulonglong2 *>(acc);  // cleared while the counts are on their way
   for (int j = tid; j < n2; j += kAccBlock) a2[j] = make_ulonglong2(0ull, 0ull);
   for (int j = tid; j < kAccSums / 32; j += kAccBlock) special[0][j] = special[1][j] = special[2][j] = 0u;
-  if (blockIdx.x >= nitems) return;
+  // a plan of these positions always passes the checks here and in item_at;
+  // they keep a missing one (IA355_TABLE_REUSE_PLAN alone) inside the buffers
+  if (blockIdx.x >= nitems || nitems < nsplit || nitems > cap) return;
   auto item_at = [&](uint32_t i) {
-    return i < nsplit ? list[i] : i < nitems ? list[cap - 1 - (int64_t)(i - nsplit)] : AccItem{kNoItem, 0u, 0u, 0u};
+    AccItem I = i < nsplit ? list[i] : i < nitems ? list[cap - 1 - (int64_t)(i - nsplit)] : AccItem{kNoItem, 0u, 0u, 0u};
+    if (i < nitems && (I.bin >= (uint32_t)nl << tpl_log2 || I.c0 > I.c1 || I.c1 > chunks)) I = AccItem{0u, 0u, 0u, 1u};
+    return I;
   };
   // Items before `fixed` are taken by place, the last rounds' from a queue: an
   // add to one address takes 10 ns, and a workgroup waits for its turn, but the
@@ -1273,7 +1306,6 @@ extern "C" int32_t ia355_hashgrid_table_grad(const float *grad_feat, const float
     const size_t level_floats = 2 * ((size_t)1 << log2T);
     return ia355_zero(grad_table + level_floats * l0, sizeof(float) * level_floats * (l1 - l0), stream);
   }
-  if (plan_only) return IA355_OK;  // nothing to prepare: the sort finds its own offsets
   const int nl = l1 - l0;
   BinGeom g;
   bin_geom(nl, S, log2T, &g);  // fewer levels than `full`: fits its workspace
@@ -1282,15 +1314,19 @@ extern "C" int32_t ia355_hashgrid_table_grad(const float *grad_feat, const float
   // the blocks loop over the chunks; with a device count the grid is bounded
   int64_t per_level = g.chunks < 4096 ? g.chunks : 4096;
   if (S_dev && per_level > 64) per_level = 64;
-  if (cnt_lds > 48 * 1024 && hipFuncSetAttribute((const void *)bin_sort_kernel,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)most_lds) != hipSuccess)
+  auto *sort = plan_only ? bin_sort_kernel<kBinPlan> : reuse ? bin_sort_kernel<kBinRest> : bin_sort_kernel<kBinAll>;
+  if (cnt_lds > 48 * 1024 &&
+      hipFuncSetAttribute((const void *)sort, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most_lds) != hipSuccess)
     return IA355_ERR_HIP;
-  bin_sort_kernel<<<(unsigned)(nl * per_level), kSortBlock, cnt_lds, s>>>(grad_feat, xc, bone, S, S_dev, ld, l0, nl,
-                                                                          log2T, g.tb, lv, box, g.chunks, w.queue,
-                                                                          w.runs, w.rec);
-  bin_plan_kernel<<<(unsigned)ceil_div((int64_t)nl << g.tpl_log2, kPlanBlock / kWave), kPlanBlock, 0, s>>>(
-      w.runs, S, S_dev, g.chunks, l0, nl, log2T, g.tb, w.cap, w.queue, w.items, overwrite ? grad_table : nullptr);
-  bin_accum_kernel<<<kAccMaxGrid, kAccBlock, sizeof(unsigned long long) * 2 * ((size_t)1 << g.tb), s>>>(
-      w.queue, w.items, w.cap, w.runs, w.rec, S, S_dev, g.chunks, l0, nl, log2T, g.tb, overwrite, grad_table);
+  sort<<<(unsigned)(nl * per_level), kSortBlock, cnt_lds, s>>>(grad_feat, xc, bone, S, S_dev, ld, l0, nl, log2T, g.tb,
+                                                               lv, box, g.chunks, w.queue, w.runs, w.rec, w.shared,
+                                                               overwrite ? grad_table : nullptr);
+  if (!reuse)
+    bin_plan_kernel<<<(unsigned)ceil_div((int64_t)nl << g.tpl_log2, kPlanBlock / kWave), kPlanBlock, 0, s>>>(
+        w.runs, S, S_dev, g.chunks, l0, nl, log2T, g.tb, w.cap, w.queue, w.items, w.shared,
+        overwrite && !plan_only ? grad_table : nullptr);
+  if (!plan_only)
+    bin_accum_kernel<<<kAccMaxGrid, kAccBlock, sizeof(unsigned long long) * 2 * ((size_t)1 << g.tb), s>>>(
+        w.queue, w.items, w.cap, w.runs, w.rec, S, S_dev, g.chunks, l0, nl, log2T, g.tb, overwrite, grad_table);
   return launch_status();
 }

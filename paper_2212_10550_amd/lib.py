@@ -22,8 +22,8 @@ CAPACITY = 6  # IA355_ERR_CAPACITY
 MLP_WIDTHS = (32, 64, 64, 4)  # the decoder shape the library implements
 TABLE_COARSE = 2  # hash-table gradient: only the coarse dense levels
 TABLE_FINE = 4  # hash-table gradient: only the other levels
-TABLE_PLAN = 8  # binned table gradient: argument checks only (no pass depends on the positions alone)
-TABLE_REUSE_PLAN = 16  # binned table gradient: the whole call, after one with TABLE_PLAN
+TABLE_PLAN = 8  # binned table gradient: only the passes that depend on the positions alone
+TABLE_REUSE_PLAN = 16  # binned table gradient: the rest, on a plan made before
 _DT = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 
 _vp = ctypes.c_void_p
@@ -419,8 +419,8 @@ def hashgrid_table_grad_workspace_size(S, L, T):
 def hashgrid_table_grad(grad_feat, xc, bone, S, ld, base_res, growth, aabb, grad_table, ws, flags=0, S_dev=None):
     """Table gradient without global atomics (binned); grad_table [L, T, 2]
     FP32; ws: hashgrid_table_grad_workspace_size(S, L, T) bytes.  With
-    TABLE_PLAN the arguments are only checked (grad_feat may be None);
-    TABLE_REUSE_PLAN then does the work on the same positions."""
+    TABLE_PLAN only the position-dependent passes run (grad_feat may be
+    None); TABLE_REUSE_PLAN then runs the rest on the same positions."""
     L, T, F = grad_table.shape
     _check(lib().ia355_hashgrid_table_grad(
         _p(grad_feat, torch.float32, "grad_feat"), _p(xc, torch.float32, "xc"), _p(bone, torch.int16, "bone"), S,

@@ -227,8 +227,8 @@ class Pipeline:
 
     def _table_grad(self, S, Sd, overwrite=True, group=0, phase=0):
         """Table gradient of the level group (K.TABLE_COARSE, K.TABLE_FINE,
-        or 0 for every level).  phase: 0, or in binned mode
-        K.TABLE_PLAN (checks only) or K.TABLE_REUSE_PLAN (the whole call)."""
+        or 0 for every level).  Binned mode: phase K.TABLE_PLAN runs only the
+        position-dependent passes, K.TABLE_REUSE_PLAN the rest."""
         w = self.w
         if self.table_grad_mode == "binned":
             if self.ws_tgrad is None:

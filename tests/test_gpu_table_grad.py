@@ -420,7 +420,9 @@ def test_table_grad_binned_exact_whole_tiles(orc, many, overwrite, odd):
         gf = up(g[order].reshape(S, L, 2).transpose(1, 0, 2).reshape(-1))
         args = (soa(x[order].astype(np.float32), S), None, S, S, float(base), 2.0, AABB, gt, ws)
         if phases == 2:
+            ws.zero_()
             K.hashgrid_table_grad(None, *args, K.TABLE_PLAN)
+            assert int(ws[4:12].view(torch.int32).sum()) > 0  # the work items are there already
             assert bool((gt == (7.0 if overwrite else start)).all())
         K.hashgrid_table_grad(gf, *args, flag | (K.TABLE_REUSE_PLAN if phases == 2 else 0))
         torch.cuda.synchronize()
