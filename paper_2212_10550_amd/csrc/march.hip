@@ -53,6 +53,12 @@ constexpr int64_t kManyRays = 32768;
 constexpr int kManySteps = 1 << 22;  // step indices plus a half are exact in single
 
 inline bool many_rays(int64_t R, int max_steps) { return R >= kManyRays && max_steps <= kManySteps; }
+// Waves that share 64 rays in the fill of many rays: enough for 16,384 in all
+// (a wave's slots come one after the other), at most 16.
+inline unsigned fill_parts(int64_t R) {
+  const int64_t n = ((int64_t)1 << 20) / R;
+  return (unsigned)(n < 1 ? 1 : n > 16 ? 16 : n);
+}
 inline int rays_per_block(int64_t R, int max_steps) { return many_rays(R, max_steps) ? kBlock : kWavesPerBlock; }
 
 template <bool kPow2Ext>
@@ -293,10 +299,10 @@ __global__ void __launch_bounds__(kBlock) march_fill(const float *__restrict__ r
   }
 }
 
-// Many rays: each wave writes the samples of its 64 rays, 64 slots at a time.
-// The rays' first slots and inputs are in LDS; a lane finds its ray by binary
-// search and its step as the q-th set bit of the ray's masks (global memory,
-// read in the cache line of the neighbouring lanes' rays).
+// Many rays: gridDim.y waves write the samples of 64 rays, 64 slots at a time
+// each.  The rays' first slots and inputs are in LDS; a lane finds its ray by
+// binary search and its step as the q-th set bit of the ray's masks (global
+// memory, read in the cache line of the neighbouring lanes' rays).
 __global__ void __launch_bounds__(kBlock) march_fill_many(const float *__restrict__ ro, const float *__restrict__ rd,
                                                           int64_t R, const uint64_t *__restrict__ masks, int nw,
                                                           const float *__restrict__ ray_tn,
@@ -314,16 +320,16 @@ __global__ void __launch_bounds__(kBlock) march_fill_many(const float *__restric
   if (r0 >= R) return;  // no barrier below: a wave works alone
   const int64_t r = r0 + lane;
   const int cnt = r < R ? ray_cnt[r] : 0;
+  int above = 0;  // of the block's rays before the wave's (the offsets in ray_off change meanwhile)
+#pragma unroll
+  for (int i = 1; i < kWavesPerBlock; ++i) above += i <= wid ? ray_cnt[r - i * kWave < R ? r - i * kWave : R - 1] : 0;
   const int incl = wave_incl_scan(cnt);
-  const int n = __builtin_amdgcn_readfirstlane(__shfl(incl, kWave - 1, kWave));
-  const int64_t base = block_off[blockIdx.x] + chunk_off[blockIdx.x / kScanChunk];
-  int64_t off = 0;
-  if (r < R) {
-    off = ray_off[r] + base;
-    ray_off[r] = off;
-  }
-  if (n == 0) return;
-  const int64_t at0 = __shfl(off, 0, kWave);  // r0 < R: lane 0 holds the wave's first slot
+  const int n = __builtin_amdgcn_readlane(incl, kWave - 1);
+  const int64_t at0 = block_off[blockIdx.x] + chunk_off[blockIdx.x / kScanChunk] +
+                      __builtin_amdgcn_readlane(wave_incl_scan(above), kWave - 1);
+  if (r < R && blockIdx.y == 0) ray_off[r] = at0 + incl - cnt;
+  const int j0 = (int)blockIdx.y * kWave, step = (int)gridDim.y * kWave;
+  if (j0 >= n) return;
   {
     float o[3], d[3];
     const int64_t q = r < R ? r : R - 1;
@@ -340,7 +346,7 @@ __global__ void __launch_bounds__(kBlock) march_fill_many(const float *__restric
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  for (int j = lane; j < n; j += kWave) {
+  for (int j = j0 + lane; j < n; j += step) {
     const int64_t at = at0 + j;
     if (at >= cap) break;
     // the last ray whose first slot is at or before j (rays without samples
@@ -457,7 +463,7 @@ extern "C" int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d,
   if (nchunk != 1) march_scan_top<<<1, 1024, 0, s>>>(chunk_sum, nchunk, ray_off, R, n_samples);
   if (R > 0 && cap > 0) {
     if (many)
-      march_fill_many<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
+      march_fill_many<<<dim3((unsigned)nblk, fill_parts(R)), kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
                                                         ray_off, ray_cnt, ray_dt, xs, ts, ray_id, cap);
     else
       march_fill<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
