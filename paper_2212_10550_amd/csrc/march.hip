@@ -209,25 +209,28 @@ __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t *wsum
   return base + incl - v;
 }
 
-// Chunk c of the per-block totals, kScanPer per thread: exclusive scan in
-// place (offsets within the chunk) and the chunk's total.
+// Chunk c of the per-block totals, kPer per thread: exclusive scan in place
+// (offsets within the chunk) and the chunk's total.  kScanPer a thread where
+// there are several chunks; a single one takes as few as hold it (a thread's
+// totals are loaded and stored 8 bytes at a time, kPer apart).
 constexpr int kScanPer = 8;  // one chunk holds 2 M rays at 256 a block
 constexpr int64_t kScanChunk = 1024 * kScanPer;
 
+template <int kPer>
 __global__ void __launch_bounds__(1024) march_scan_chunk(int64_t *block_sum, int64_t nblk, int64_t *chunk_sum,
                                                          int64_t *ray_off, int64_t R, int64_t *n_samples) {
   __shared__ int64_t wsum[1024 / kWave];
-  const int64_t i0 = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanPer;
-  int64_t v[kScanPer], run = 0;
+  const int64_t i0 = (int64_t)blockIdx.x * 1024 * kPer + (int64_t)threadIdx.x * kPer;
+  int64_t v[kPer], run = 0;
 #pragma unroll
-  for (int j = 0; j < kScanPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     v[j] = i0 + j < nblk ? block_sum[i0 + j] : 0;
     run += v[j];
   }
   int64_t total;
   int64_t off = block_exclusive_scan(run, wsum, &total);
 #pragma unroll
-  for (int j = 0; j < kScanPer; ++j) {
+  for (int j = 0; j < kPer; ++j) {
     if (i0 + j < nblk) block_sum[i0 + j] = off;
     off += v[j];
   }
@@ -458,7 +461,8 @@ extern "C" int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d,
       march_count<false><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
                                                            max_steps, ray_off, ray_cnt, ray_dt, block_sum, mw.masks,
                                                            nw, mw.tn);
-    march_scan_chunk<<<(unsigned)nchunk, 1024, 0, s>>>(block_sum, nblk, chunk_sum, ray_off, R, n_samples);
+    auto *scan = nblk <= 1024 ? march_scan_chunk<1> : nblk <= 4096 ? march_scan_chunk<4> : march_scan_chunk<kScanPer>;
+    scan<<<(unsigned)nchunk, 1024, 0, s>>>(block_sum, nblk, chunk_sum, ray_off, R, n_samples);
   }
   if (nchunk != 1) march_scan_top<<<1, 1024, 0, s>>>(chunk_sum, nchunk, ray_off, R, n_samples);
   if (R > 0 && cap > 0) {
