@@ -36,30 +36,38 @@ namespace {
 
 // Two mappings, by the ray count.  Few rays (a training step's thousands): one
 // ray per wave, four waves per workgroup, lane l takes steps l, l + 64, ...,
-// so that there are enough waves.  From kManyRays on: one ray per lane, 256
-// per workgroup.  An image's neighbouring rays walk neighbouring cells, so the
-// 64 loads of a step touch a few lines, no lane is spent on steps past the
-// box (a 128-step ray crosses a unit box in 74 steps at most), the ray clip
-// with its six divisions is done once per ray instead of once per lane, and
-// the fill's waves are full although a ray keeps only 3 samples on average.
+// so that there are enough waves.  Many: one ray per lane, 256 per workgroup.
+// An image's neighbouring rays walk neighbouring cells, so the 64 loads of a
+// step touch a few lines, no lane is spent on steps past the box (a 128-step
+// ray crosses a unit box in 74 steps at most), the ray clip with its six
+// divisions is done once per ray instead of once per lane, and the fill's waves
+// are full although a ray keeps only 3 samples on average.
 // 1080^2 rays, 128^3 grid, 10 % occupied: count 358 -> 56 us, fill 194 -> 29
-// us against four rays per wave.  The line lies where the two cross (whole
-// march, us, wave / lane per ray): 8192 rays 12 / 23, 16384 rays 17 / 23,
-// 32768 rays 28 / 24, 65536 rays 39 / 26, the same for images, random pixels
-// and rays in random directions.
+// us against four rays per wave.  The line lies where the two cross: a lane's
+// chain of steps takes as long for one ray as for thousands, a wave per ray as
+// much as there are rays.  Whole march, us, wave / lane per ray, up to 128
+// steps: 16,384 rays 17-19 / 16-23, 20,480 21-23 / 16-23, 32,767 29-32 / 19-24
+// (an image with and without a grid, a general box, random directions); of 600
+// steps: 32,767 rays 54 / 80, 65,536 95 / 83.
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlock = kWavesPerBlock * kWave;
-constexpr int64_t kManyRays = 32768;
+constexpr int64_t kManyRays = 20480, kAnyManyRays = 65536;
 constexpr int kManySteps = 1 << 22;  // step indices plus a half are exact in single
 
-inline bool many_rays(int64_t R, int max_steps) { return R >= kManyRays && max_steps <= kManySteps; }
+// likely: the steps of a ray of unit direction along the box's diagonal
+inline bool many_rays(int64_t R, int max_steps, const float *aabb, float dt, int n_per_ray) {
+  const double ex = (double)aabb[3] - aabb[0], ey = (double)aabb[4] - aabb[1], ez = (double)aabb[5] - aabb[2];
+  const double likely = n_per_ray > 0 ? (double)n_per_ray : sqrt(ex * ex + ey * ey + ez * ez) / (double)dt;
+  const double steps = likely < (double)max_steps ? likely : (double)max_steps;
+  const double line = (double)kManyRays + (steps > 128.0 ? 32.0 * (steps - 128.0) : 0.0);
+  return max_steps <= kManySteps && ((double)R >= line || R >= kAnyManyRays);
+}
 // Waves that share 64 rays in the fill of many rays: enough for 16,384 in all
 // (a wave's slots come one after the other), at most 16.
 inline unsigned fill_parts(int64_t R) {
   const int64_t n = ((int64_t)1 << 20) / R;
   return (unsigned)(n < 1 ? 1 : n > 16 ? 16 : n);
 }
-inline int rays_per_block(int64_t R, int max_steps) { return many_rays(R, max_steps) ? kBlock : kWavesPerBlock; }
 
 template <bool kPow2Ext>
 __global__ void __launch_bounds__(kBlock) march_count(const float *ro, const float *rd, int64_t R,
@@ -115,6 +123,10 @@ __global__ void __launch_bounds__(kBlock) march_count(const float *ro, const flo
 // One lane per ray.  kStepsAhead steps' occupancy bytes (8 cells along x) are
 // loaded together.  Bound by instruction issue: about 40 per step and wave.
 constexpr int kStepsAhead = 8;
+// From this number of rays left on, a wave takes them one after the other, a
+// step per lane: 64 steps cost it some 60 instructions a ray, against 2500 for
+// all (65,536 rays of differing lengths, up to 1024 steps: 98 us -> 26).
+constexpr int kFewLive = 24;
 
 template <BoxKind kBox, bool kSkip>
 __global__ void __launch_bounds__(kBlock) march_count_many(const float *__restrict__ ro, const float *__restrict__ rd,
@@ -168,6 +180,33 @@ __global__ void __launch_bounds__(kBlock) march_count_many(const float *__restri
       }
     cnt += __popc(m[0]) + __popc(m[1]);
     if (r < R) masks[r * nw + w] = (uint64_t)m[0] | (uint64_t)m[1] << 32;
+    // the rays that go on; the fill reads no word past a ray's last kept step
+    uint64_t on = w + 1 < nw ? __ballot(step_t(s, (w + 1) * kWave) < tf) : 0ull;
+    if (on == 0ull) break;
+    // few rays go on, and one of them for more groups of steps than there are
+    // such rays: one after the other, a step per lane
+    const int few = __popcll(on);
+    if (few > kFewLive || !__any(step_t(s, (w + 1) * kWave + kStepsAhead * few) < tf)) continue;
+    for (; on != 0ull; on &= on - 1ull) {
+      const int u = __builtin_ctzll(on);
+      auto of = [&](float v) { return __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(v), u)); };
+      const float uo[3] = {of(o[0]), of(o[1]), of(o[2])}, ud[3] = {of(d[0]), of(d[1]), of(d[2])};
+      const float un = of(s.tn), uf = of(tf), udt = of(s.dt);
+      int kept = 0;
+      for (int q = w + 1; q < nw; ++q) {
+        const int k = q * kWave + lane;
+        const float t = un + ((float)k + 0.5f) * udt;
+        uint32_t cell[3];
+        sample_cell<kBox>(uo, ud, t, box, G, cell);
+        const uint32_t v = kSkip ? bits[occ_byte(cell[0], cell[1], cell[2], sy, sz)] : 0xffu;
+        const uint64_t keep = __ballot(k < max_steps && t < uf && ((v >> (cell[0] & 7u)) & 1u));
+        if (lane == u) masks[r * nw + q] = keep;
+        kept += __popcll(keep);
+        if (__ballot(t < uf) != ~0ull) break;
+      }
+      cnt += lane == u ? kept : 0;
+    }
+    break;
   }
   const int incl = wave_incl_scan(cnt);
   if (lane == kWave - 1) wsum[wid] = incl;
@@ -384,9 +423,8 @@ __global__ void __launch_bounds__(kBlock) march_fill_many(const float *__restric
 // Workspace: block totals, chunk totals, keep masks [R][ceil(max_steps/64)]
 // and entry distances [R], each slice 256-byte aligned.  Its size never falls
 // as R or max_steps grows: a workspace for the largest call of a pool serves
-// the smaller ones.  Block totals: one for four rays up to 65,535 rays (the
-// kernels of few rays need that below kManyRays; callers count on the rest),
-// from there on no fewer, and at least one for 16 rays (kBlock would do).
+// the smaller ones.  Block totals: one for four rays below kAnyManyRays, from
+// there on no fewer, and at least one for 16 rays (one for kBlock would do).
 struct MarchWs {
   int64_t *block_sum, *chunk_sum;
   uint64_t *masks;
@@ -395,7 +433,7 @@ struct MarchWs {
 };
 
 static MarchWs march_ws(void *base, int64_t R, int32_t max_steps) {
-  const int64_t Rp = R > 0 ? R : 1, few = Rp < 65536 ? Rp : 65535;
+  const int64_t Rp = R > 0 ? R : 1, few = Rp < kAnyManyRays ? Rp : kAnyManyRays - 1;
   const int64_t per_wave = ceil_div(max_steps <= kManySteps ? few : Rp, kWavesPerBlock), rest = ceil_div(Rp, 16);
   const int64_t nblk = per_wave > rest ? per_wave : rest;
   const int64_t nw = ceil_div(max_steps > 0 ? max_steps : 1, kWave);
@@ -436,12 +474,12 @@ extern "C" int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d,
   bool pow2;
   if (!make_box(aabb, &box, &pow2)) return IA355_ERR_INVALID_ARG;
   hipStream_t s = as_stream(stream);
-  const int64_t nblk = ceil_div(R, rays_per_block(R, max_steps));
+  const bool many = many_rays(R, max_steps, aabb, dt, n_per_ray);
+  const int64_t nblk = ceil_div(R, many ? kBlock : kWavesPerBlock);
   const int64_t nchunk = ceil_div(nblk, kScanChunk);
   const int nw = (int)ceil_div(max_steps, kWave);
   const MarchWs mw = march_ws(ws, R, max_steps);
   int64_t *block_sum = mw.block_sum, *chunk_sum = mw.chunk_sum;
-  const bool many = many_rays(R, max_steps);
   if (R > 0) {
     if (many) {
       const bool zero = box.lo[0] == 0.0f && box.lo[1] == 0.0f && box.lo[2] == 0.0f;

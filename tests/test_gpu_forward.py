@@ -125,6 +125,16 @@ def test_march_many_rays_bit_exact(orc, R, steps, box, grid, share):
     np.testing.assert_array_equal(host(ts), m["ts"][:cap])
 
 
+@pytest.mark.parametrize("R,steps,box,grid", [(20479, 128, "unit", 37), (20480, 128, "unit", 37),
+                                              (49151, 1024, "pow2", 64), (49153, 1024, "general", 64),
+                                              (65536, 4000, "unit", 0)])
+def test_march_line_and_long_rays_bit_exact(orc, R, steps, box, grid):
+    """Both sides of the line between the mappings, which rises with the
+    steps; and long rays of differing lengths, of which a wave takes the last
+    ones one after the other."""
+    test_march_many_rays_bit_exact(orc, R, steps, box, grid, 0.05 if steps > 2000 else 1.0)
+
+
 def test_march_empty_and_capacity(orc):
     w = synth.train_step()
     w0 = synth.ray_subset(w, np.arange(64))
