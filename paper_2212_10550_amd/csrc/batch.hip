@@ -533,8 +533,8 @@ __global__ void __launch_bounds__(kW * kWave, kMinGroups * kW / 4) render_kernel
           float xp[3] = {0.0f, 0.0f, 0.0f};
           if (qa) sample_xp(wm, ra, rb, sb + sj, xp);
           dfm::GatherCorners cs(A, pl.gr);
-          const dfm::Choice cc = dfm::multi_init<32>(cs, dfm::RegKeep(), pl.gr, pd.binv, pd.bok, nb, xp, qa, lane & 31, pl.hbox,
-                                                     pl.max_iter, pl.tol_stop, pl.tol_valid);
+          const dfm::Choice cc = dfm::multi_init(cs, dfm::RegKeep(), pl.gr, pd.binv, pd.bok, nb, xp, qa, 32, lane & 31,
+                                                 pl.hbox, pl.max_iter, pl.tol_stop, pl.tol_valid);
           const int sr = r < 2 ? 32 * r : 0;
           const float xs[3] = {__shfl(cc.x[0], sr, kWave), __shfl(cc.x[1], sr, kWave), __shfl(cc.x[2], sr, kWave)};
           const bool qs = __shfl((int)qa, sr, kWave) != 0 && r < 2;

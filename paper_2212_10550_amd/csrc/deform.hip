@@ -42,34 +42,44 @@ __global__ void __launch_bounds__(kBlendBlock) blend_kernel(const float *__restr
 }
 
 // kG lanes per sample: eight (three inits each of 24, one after the other), or
-// 32 for calls of at most kWideSamples samples (capacity), whose time is a
-// lane's chain of inits and not the chip's rate: 200 samples 31.5 -> 12.1 us,
-// 4096 32.6 -> 17.6, 8192 32.7 -> 26.2, 16,384 45.7 -> 42.6, but 24,576 56.5
-// -> 58.0.  Same bits: each init's arithmetic is its own, and the lowest
-// residual (first init among equals) and the sum of steps do not depend on
-// the lanes that hold them.
-constexpr int kWideGroup = 32;
-constexpr int64_t kWideSamples = 16384;
+// 32 for few samples, whose time is a lane's chain of inits and not the chip's
+// rate: 24 bones, 200 samples 31.5 -> 12.1 us, 4096 32.6 -> 17.6, 8192 32.7 ->
+// 26.2, 16,384 45.7 -> 42.6, but 24,576 56.5 -> 58.0; 12 bones (two inits a
+// lane) 4096 samples 22 -> 18, but 8192 20 -> 23; 8 bones (one) 200 samples 16
+// -> 14, but 4096 15 -> 16.  Two for at most two bones (262,143 samples of one:
+// 53 -> 22).  By the device-side count where there is one.  Same bits: each
+// init's arithmetic is its own, and the lowest residual (first init among
+// equals) and the sum of steps do not depend on the lanes that hold them.
+constexpr int kWideGroup = 32, kNarrowGroup = 2;
+inline int64_t wide_samples(int nb) {
+  return nb > 2 * kGroup ? 16384 : nb > kGroup ? 6144 : nb > kGroup / 2 ? 2048 : 0;
+}
+// Eight lanes hold the corners each for itself where two rounds of inits for
+// few samples leave the chip idle (no loop over a wave's cells; 8 bones, 8192
+// samples 16.0 -> 15.2 us, 12 bones 23.3 -> 20.2, but 36,503 48 -> 53).
+inline bool few_inits(int64_t S, int nb) { return S <= 16384 && nb <= 2 * kGroup; }
 
-template <int kG>
-__global__ void __launch_bounds__(kSolveBlock, 3) solve_kernel(
+// lanes: per sample; 32 up to `wide` samples.  kHeld: each lane holds the
+// corners for itself (two waves per SIMD).
+template <bool kHeld>
+__global__ void __launch_bounds__(kSolveBlock, kHeld ? 2 : 3) solve_kernel(
     const float *__restrict__ xp_soa, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
     const float *__restrict__ B, int nb, const float *__restrict__ A, Grid gr, Box hbox, int max_iter, float tol_stop,
     float tol_valid, float *__restrict__ xc_soa, int16_t *__restrict__ bone_out, float *__restrict__ resid_out,
-    int16_t *__restrict__ steps_out) {
+    int16_t *__restrict__ steps_out, int lanes, int64_t wide) {
   __shared__ float sBinv[kMaxBones * 12];
   __shared__ int sBok[kMaxBones];
   __shared__ float keep[6 * kSolveBlock];
-  __shared__ CellLds cells[kSolveBlock / kWave];
+  __shared__ CellLds cells[kHeld ? 1 : kSolveBlock / kWave];
   stage_bone_inverses(B, nb, sBinv, sBok);
   __syncthreads();
   const int64_t Sn = count_of(S, S_dev);
-  const int j = threadIdx.x % kG;
-  constexpr int kPerBlock = kSolveBlock / kG;
+  if (Sn <= wide) lanes = kWideGroup;
+  const int j = threadIdx.x & (lanes - 1), mine = (int)threadIdx.x / lanes, per_block = kSolveBlock / lanes;
   // every lane of a block runs the same iterations, so the groups' shuffles
   // always see all their lanes
-  for (int64_t n0 = (int64_t)blockIdx.x * kPerBlock; n0 < Sn; n0 += (int64_t)gridDim.x * kPerBlock) {
-    const int64_t n = n0 + threadIdx.x / kG;
+  for (int64_t n0 = (int64_t)blockIdx.x * per_block; n0 < Sn; n0 += (int64_t)gridDim.x * per_block) {
+    const int64_t n = n0 + mine;
     const bool act = n < Sn;
     float xp[3] = {0.0f, 0.0f, 0.0f};
     if (act) {
@@ -77,9 +87,14 @@ __global__ void __launch_bounds__(kSolveBlock, 3) solve_kernel(
       xp[1] = xp_soa[ld + n];
       xp[2] = xp_soa[2 * ld + n];
     }
-    SharedLater cs(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]);
-    const Choice c = multi_init<kG>(cs, LdsKeep(keep), gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop,
-                                     tol_valid);
+    auto solve = [&](auto &&cs) {
+      return multi_init(cs, LdsKeep(keep), gr, sBinv, sBok, nb, xp, act, lanes, j, hbox, max_iter, tol_stop, tol_valid);
+    };
+    Choice c;
+    if constexpr (kHeld)
+      c = solve(HeldCorners(A, gr));
+    else
+      c = solve(SharedLater(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]));
     if (act && j == 0) write_choice(c, n, ld, 0, xc_soa, bone_out, resid_out, steps_out);
   }
 }
@@ -255,7 +270,8 @@ __global__ void __launch_bounds__(kSolveBlock) fallback_kernel(
       xp[2] = xp_soa[2 * ld + n];
     }
     HeldCorners cs(A, gr);
-    const Choice c = multi_init<kFbGroup>(cs, RegKeep(), gr, sBinv, sBok, nb, xp, act, j, hbox, max_iter, tol_stop, tol_valid);
+    const Choice c = multi_init(cs, RegKeep(), gr, sBinv, sBok, nb, xp, act, kFbGroup, j, hbox, max_iter, tol_stop,
+                                tol_valid);
     if (act && j == 0) write_choice(c, n, ld, gsteps[n], xc_soa, bone_out, resid_out, steps_out);
   }
 }
@@ -602,11 +618,12 @@ int32_t deform_launch(const float *xp, int64_t S, const int64_t *S_dev, int64_t 
     hb.lo[a] = hash_aabb[a];
     hb.hi[a] = hash_aabb[3 + a];
   }
-  const bool wide = S <= kWideSamples;
-  const int lanes = wide ? kWideGroup : kGroup;
-  auto *kernel = wide ? solve_kernel<kWideGroup> : solve_kernel<kGroup>;
-  kernel<<<stride_grid(ceil_div(S * lanes, kSolveBlock), S_dev != nullptr), kSolveBlock, 0, s>>>(
-      xp, S, S_dev, ld, B, nb, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps);
+  const int64_t wide = wide_samples(nb);
+  const int lanes = nb <= kNarrowGroup ? kNarrowGroup : kGroup;
+  auto *kernel = S > wide && few_inits(S, nb) ? solve_kernel<true> : solve_kernel<false>;
+  kernel<<<stride_grid(ceil_div(S * (S <= wide ? kWideGroup : lanes), kSolveBlock), S_dev != nullptr), kSolveBlock, 0,
+           s>>>(xp, S, S_dev, ld, B, nb, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps, lanes,
+                wide);
   return launch_status();
 }
 

@@ -431,9 +431,10 @@ __device__ __forceinline__ bool in_hbox(const float x[3], const Box &b) {
          x[2] <= b.hi[2];
 }
 
-// Multi-init solve of one sample by a group of kGroup lanes (j = lane in
-// group): lowest valid residual, ties to the lowest bone.  Every lane of the
-// group returns the group's result; steps are summed over the inits.
+// Multi-init solve of one sample by a group of `lanes` lanes (a power of two,
+// uniform; j = lane in group): lowest valid residual, ties to the lowest bone.
+// Every lane of the group returns the group's result; steps are summed over the
+// inits.
 struct Choice {
   float x[3], r, x0[3];
   int bone, steps;
@@ -456,14 +457,14 @@ struct LdsKeep {
   __device__ __forceinline__ float get(int k) const { return p[k * kSolveBlock]; }
 };
 
-template <int kG, class Corners, class Keep>
+template <class Corners, class Keep>
 __device__ __forceinline__ Choice multi_init(Corners &cs, Keep kept, const Grid &gr, const float *sBinv,
-                                             const int *sBok, int nb, const float xp[3], bool act, int j, Box hbox,
-                                             int max_iter, float tol_stop, float tol_valid) {
+                                             const int *sBok, int nb, const float xp[3], bool act, int lanes, int j,
+                                             Box hbox, int max_iter, float tol_stop, float tol_valid) {
   float best_r = INFINITY;
   int best = 0x7fffffff, steps = 0;
   // (the same number of inits for every lane: at() may need them all)
-  for (int i0 = 0; i0 < nb; i0 += kG) {
+  for (int i0 = 0; i0 < nb; i0 += lanes) {
     const bool mine = act && i0 + j < nb;
     const int i = mine ? i0 + j : 0;
     const InitResult q = broyden(cs, gr, sBinv + 12 * i, mine && sBok[i], xp, max_iter, tol_stop);
@@ -485,14 +486,13 @@ __device__ __forceinline__ Choice multi_init(Corners &cs, Keep kept, const Grid 
     best_x[a] = kept.get(a);
     x0[a] = kept.get(3 + a);
   }
-#pragma unroll
-  for (int o = kG / 2; o > 0; o >>= 1) {
-    const float r2 = __shfl_xor(best_r, o, kG);
-    const int b2 = __shfl_xor(best, o, kG);
-    const float x20 = __shfl_xor(best_x[0], o, kG);
-    const float x21 = __shfl_xor(best_x[1], o, kG);
-    const float x22 = __shfl_xor(best_x[2], o, kG);
-    steps += __shfl_xor(steps, o, kG);
+  for (int o = lanes / 2; o > 0; o >>= 1) {
+    const float r2 = __shfl_xor(best_r, o, kWave);
+    const int b2 = __shfl_xor(best, o, kWave);
+    const float x20 = __shfl_xor(best_x[0], o, kWave);
+    const float x21 = __shfl_xor(best_x[1], o, kWave);
+    const float x22 = __shfl_xor(best_x[2], o, kWave);
+    steps += __shfl_xor(steps, o, kWave);
     if (r2 < best_r || (r2 == best_r && b2 < best)) {
       best_r = r2;
       best = b2;

@@ -252,6 +252,40 @@ def test_deform_lanes_per_sample(S, count):
         assert (got[..., n:] == -7).all()
 
 
+@pytest.mark.parametrize("nb", [1, 2, 3, 5, 8, 9, 16, 17, 24])
+def test_deform_lanes_by_bones_and_count(nb):
+    """The lanes per sample and the source of the corners go by the number of
+    bones and of samples, on the device where the count is there: the same
+    bits in all of them, nothing past the count."""
+    K = _K()
+    w = synth.train_step()
+    big = 20000
+    Dz, Dy, Dx, _ = w.W.shape
+    W = np.ascontiguousarray(w.W[..., :nb] + np.float32(1e-3))
+    W = (W / W.sum(-1, keepdims=True)).astype(np.float32)
+    B = np.ascontiguousarray(w.B[:nb])
+    xp = synth.sample_posed_points(synth.make_skeleton(0), w.B.astype(np.float64), big, 17).astype(np.float32)
+    xp[5] = [9.0, 9.0, 9.0]  # no root
+    ws = torch.empty(K.deform_workspace_size(Dx, Dy, Dz), dtype=torch.uint8, device=dev())
+
+    def run(cap, cnt):
+        xc = torch.full((3, cap), -7.0, device=dev())
+        bone, steps = (torch.full((cap,), -7, dtype=torch.int16, device=dev()) for _ in range(2))
+        Sd = None if cnt is None else torch.tensor([cnt], device=dev())
+        K.snarf_deform(soa(xp[:cap]), cap, cap, up(B), up(W), w.skin_aabb, w.hash_aabb, 10, 1e-6, 1e-5, xc, bone, None,
+                       steps, ws, S_dev=Sd)
+        torch.cuda.synchronize()
+        return host(xc), host(bone), host(steps)
+
+    ref = run(big, None)
+    assert (ref[1] >= 0).any()
+    for cap, cnt in ((100, None), (2049, None), (6145, None), (16384, None), (big, 100), (big, 6145), (big, 16385)):
+        n = cap if cnt is None else cnt
+        for got, r in zip(run(cap, cnt), ref):
+            assert got[..., :n].tobytes() == r[..., :n].tobytes(), (cap, cnt)
+            assert (got[..., n:] == -7).all(), (cap, cnt)
+
+
 @pytest.mark.parametrize("log2T,scale,tdt", [(14, 1e-4, "f32"), (19, 1e-4, "f32"), (19, 0.5, "f32"),
                                              (19, 0.5, "f16")])
 def test_hash_encode(orc, log2T, scale, tdt):
