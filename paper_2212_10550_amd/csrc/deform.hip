@@ -397,12 +397,14 @@ __global__ void __launch_bounds__(kBwdBlock) ift_v_kernel(const float *__restric
 // corner's 12 floats are 48 contiguous bytes and x-neighbouring corners are
 // adjacent vertices, so each touches about four cache lines.
 // 36,503 samples on a surface, 19 cells in 64: 17 us (sets of 256, 58 cells:
-// 16); in the captured step of 8,192 random rays, 51 cells in 64, the step
-// takes 306 us (sets of 256: 309).  Eight consecutive samples a wave, summed
-// while their cell stayed the same, took 46 us and a step of 310.
+// 16); in the captured step of 8,192 random rays, 51 cells in 64, the kernel
+// takes 31 us.  Eight consecutive samples a wave, summed while their cell stayed
+// the same, took 46 us and in the step 32.  64 samples: 5.2 us (9.0 with a
+// chain of LDS reads for each cell).
 constexpr int kQSet = 64;
 constexpr int kQTable = 128;
 constexpr int kQBlock = 256;
+static_assert(kQSet <= kQBlock, "a wave's cells in its lanes");
 static_assert(kQSet % kWave == 0 && kQTable == 2 * kQSet, "the first kQSet threads take a sample and two slots each");
 
 __global__ void __launch_bounds__(kQBlock) ift_q_kernel(const float *__restrict__ xc_soa,
@@ -470,8 +472,16 @@ __global__ void __launch_bounds__(kQBlock) ift_q_kernel(const float *__restrict_
       d[2] = make_float4(c.f[1], c.f[2], 0.0f, 0.0f);
     }
     __syncthreads();
-    for (int e = wid; e < ncell; e += kQBlock / kWave) {
-      const int h = cell_slot[e], first = place[h], last = first + count[h];
+    // the wave's cells, one per lane, so that the loop finds them in registers
+    int first_l = 0, count_l = 0, base_l = 0;
+    if (wid + (kQBlock / kWave) * lane < ncell) {
+      const int h = cell_slot[wid + (kQBlock / kWave) * lane];
+      first_l = place[h];
+      count_l = count[h];
+      base_l = 12 * key[h];
+    }
+    for (int e = wid, i = 0; e < ncell; e += kQBlock / kWave, ++i) {
+      const int first = __builtin_amdgcn_readlane(first_l, i), last = first + __builtin_amdgcn_readlane(count_l, i);
       float a0 = 0.0f, a1 = 0.0f;
       for (int s = first; s < last; ++s) {
         const float *p = rec[s];
@@ -479,7 +489,7 @@ __global__ void __launch_bounds__(kQBlock) ift_q_kernel(const float *__restrict_
         a0 += tw * p[4 + (j >> 2)] * p[j & 3];
         a1 += tw * p[6] * p[j & 3];
       }
-      float *q = Q + 12 * (int64_t)key[h] + corner;
+      float *q = Q + (uint32_t)__builtin_amdgcn_readlane(base_l, i) + corner;
       atomicAdd(q + j, a0);
       if (j < 4) atomicAdd(q + 8 + j, a1);
     }
@@ -821,7 +831,11 @@ extern "C" int32_t ia355_snarf_deform_bwd(const float *grad_xc, const float *xc,
     const int w_vec4 = (nb % 4 == 0) && ((reinterpret_cast<uintptr_t>(W) & 15) == 0);
     // Q (12 floats per vertex, 256-byte aligned in the workspace) is cleared
     // by this kernel when the parameter gradients are wanted
-    ift_v_kernel<<<stride_grid(ceil_div(S, kBwdBlock), S_dev != nullptr), kBwdBlock, 0, s>>>(
+    // (enough workgroups for that where the samples are few: 64 samples 60 -> 9 us)
+    int64_t blocks = ceil_div(S, (int64_t)kBwdBlock), clear = params ? ceil_div(3 * nvert, 4 * kBwdBlock) : 0;
+    clear = clear < 1024 ? clear : 1024;
+    blocks = blocks > clear ? blocks : clear;
+    ift_v_kernel<<<stride_grid(blocks, S_dev != nullptr), kBwdBlock, 0, s>>>(
         grad_xc, xc, bone, S, S_dev, ld, B, nb, W, g, w_vec4, grad_xp, vbuf, params ? (float4 *)Q : nullptr,
         params ? 3 * nvert : 0);
   }
