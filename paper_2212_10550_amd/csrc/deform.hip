@@ -208,21 +208,31 @@ __global__ void __launch_bounds__(256) select_max_kernel(int K, int64_t S, const
   }
 }
 
+// kHeld: each lane holds the corners for itself, where there are few samples
+// and the loop over a wave's cells is a chain of its own: 64 samples 17.0 ->
+// 14.9 us, 36,503 19.3 -> 18.5, 65,536 19.3 -> 18.7, but 131,072 20.3 -> 24.0.
+constexpr int64_t kHeldSamples = 65536;
+
+template <bool kHeld>
 __global__ void __launch_bounds__(kSolveBlock) guided_kernel(
     const float *__restrict__ xp_soa, const float *__restrict__ x0_soa, const int16_t *__restrict__ guide,
     int64_t S, const int64_t *__restrict__ S_dev, int64_t ld, const float *__restrict__ A, Grid gr, Box hbox,
     int max_iter, float tol_stop, float tol_valid, float *__restrict__ xc_soa, int16_t *__restrict__ bone_out,
     float *__restrict__ resid_out, int16_t *__restrict__ steps_out, int32_t *__restrict__ queue,
     int32_t *__restrict__ qlen, int16_t *__restrict__ gsteps) {
-  __shared__ CellLds cells[kSolveBlock / kWave];
+  __shared__ CellLds cells[kHeld ? 1 : kSolveBlock / kWave];
   const int64_t Sn = count_of(S, S_dev);
   // every lane of a block runs the same iterations (the cells are loaded by all)
   for (int64_t n0 = (int64_t)blockIdx.x * kSolveBlock; n0 < Sn; n0 += (int64_t)gridDim.x * kSolveBlock) {
     const int64_t m = n0 + threadIdx.x, n = m < Sn ? m : Sn - 1;
     const float xp[3] = {xp_soa[n], xp_soa[ld + n], xp_soa[2 * ld + n]};
     float x[3] = {x0_soa[n], x0_soa[ld + n], x0_soa[2 * ld + n]};
-    SharedCorners cs(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]);
-    const InitResult q = broyden_from(cs, gr, x, true, xp, max_iter, tol_stop);
+    auto solve = [&](auto &&cs) { return broyden_from(cs, gr, x, true, xp, max_iter, tol_stop); };
+    InitResult q;
+    if constexpr (kHeld)
+      q = solve(HeldCorners(A, gr));
+    else
+      q = solve(SharedCorners(A, gr, cells[__builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave)]));
     if (m >= Sn) continue;
     gsteps[n] = (int16_t)q.steps;
     if (q.ok && q.r < tol_valid && in_hbox(q.x, hbox)) {
@@ -785,7 +795,8 @@ extern "C" int32_t ia355_snarf_deform_guided(const float *xp, int64_t S, const i
     const bool dev = S_dev != nullptr;
     // up to one sample per lane at frame sizes (more waves in flight to
     // hide the gathers' latency)
-    guided_kernel<<<stride_grid(ceil_div(S, kSolveBlock), dev, 8192), kSolveBlock, 0, s>>>(
+    auto *guided = S <= kHeldSamples ? guided_kernel<true> : guided_kernel<false>;
+    guided<<<stride_grid(ceil_div(S, kSolveBlock), dev, 8192), kSolveBlock, 0, s>>>(
         xp, x0, guide_bone, S, S_dev, ld, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps, queue,
         qlen, gsteps);
     // bounded with a host count too (the queue is short): 109,000 empty

@@ -197,6 +197,36 @@ def test_deform_order(S, count, guided):
     assert np.array_equal(a[2][perm], b[2]) and a[3] == b[3]
 
 
+@pytest.mark.parametrize("count", [None, 40, 30000])
+def test_guided_either_side_of_the_line(count):
+    """65,536 samples and one more: each is the largest or the smallest call
+    of a kernel of its own, and a sample's bits are the same in both."""
+    K = _K()
+    w = synth.train_step()
+    rng = np.random.default_rng(5)
+    line = 65536
+    S = line + 1
+    base = synth.sample_posed_points(synth.make_skeleton(0), w.B.astype(np.float64), 4096, 12)
+    xp = (np.repeat(base, 17, axis=0)[:S] + rng.uniform(-0.004, 0.004, (S, 3))).astype(np.float32)
+    x0 = (xp + rng.normal(0, 0.02, (S, 3))).astype(np.float32)
+    guide = rng.integers(0, 24, S).astype(np.int16)
+    Dz, Dy, Dx, nb = w.W.shape
+    out = []
+    for n in (line, S):
+        xc = torch.full((3, n), -7.0, device=dev())
+        bone = torch.full((n,), -7, dtype=torch.int16, device=dev())
+        steps = torch.full((n,), -7, dtype=torch.int16, device=dev())
+        nfb = torch.zeros(1, dtype=torch.int32, device=dev())
+        ws = torch.empty(K.deform_guided_workspace_size(n, Dx, Dy, Dz), dtype=torch.uint8, device=dev())
+        K.snarf_deform_guided(soa(xp[:n]), n, n, soa(x0[:n]), up(guide[:n]), up(w.B), up(w.W), w.skin_aabb,
+                              w.hash_aabb, 10, 1e-6, 1e-5, xc, bone, None, steps, nfb, ws,
+                              S_dev=None if count is None else torch.tensor([count], device=dev()))
+        out.append([host(xc)[:, :line], host(bone)[:line], host(steps)[:line]])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    assert (out[0][1] >= 0).any()
+
+
 def test_learned_init_end_to_end():
     """Fit a small initialiser on solver roots of 16 poses, then guided
     solves on held-out poses: every accepted root is a valid root, and most
