@@ -78,13 +78,19 @@ __global__ void __launch_bounds__(kBlock, 1) rootinit_f32(const float *__restric
 
 // BF16: the parameters are read from global memory once per block (the pose
 // fold, layer 1's x weights, the layer 2-3 fragments into a 12 KB LDS store
-// read as the MFMAs need them).  A wave takes 64 samples a step, one per lane
-// for the points, the start points and the stores, and in pairs of 16-sample
-// tiles for the layers, so that each LDS read of weights serves two.
+// read as the MFMAs need them).  A wave takes 64 samples a step, or 32 in a
+// call (or a device count) too small to give every SIMD a wave of 64 and then
+// some: one per lane for the points, the start points and the stores, and in
+// pairs of 16-sample tiles for the layers, so that each LDS read of weights
+// serves two.
 // 875,600 samples: 34 us.  A tile at a time (34 16-byte LDS reads each,
 // branches in the argmax, sixteen lanes at the start points, staging that
 // waited for every load) took 43 us.
+// The line between the steps: 64 samples 7.8 -> 6.7 us with 32 a step, 16,384
+// 8.3 -> 7.2, 32,768 8.4 -> 7.3, a count of 5000 under a capacity of 200,000
+// 8.3 -> 7.2; 65,536 8.7 either way.
 constexpr int kPair = 2;
+constexpr int64_t kOnePairSamples = 32768;
 
 __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restrict__ xp_soa, int64_t S,
                                                            const int64_t *__restrict__ S_dev, int64_t ld,
@@ -93,7 +99,8 @@ __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restri
                                                            int16_t *__restrict__ bone_out, float *__restrict__ x0_soa) {
   const rid::Layout l = rid::layout(nb);
   S = count_of(S, S_dev);
-  const int64_t nstep = ceil_div(S, 64), wstride = (int64_t)gridDim.x * (kBlock / 64);
+  const int pairs = S <= kOnePairSamples ? 1 : 2, kStep = 16 * kPair * pairs;
+  const int64_t nstep = ceil_div(S, (int64_t)kStep), wstride = (int64_t)gridDim.x * (kBlock / 64);
   if ((int64_t)blockIdx.x * (kBlock / 64) >= nstep) return;  // as above
   __shared__ __attribute__((aligned(16))) float c1[H];       // W1[:, 3:] pose + b1
   __shared__ __attribute__((aligned(16))) float w1x[H * 3];  // W1[:, :3]
@@ -109,7 +116,7 @@ __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restri
 #pragma unroll
     for (int a = 0; a < 3; ++a) xn[a] = xp_soa[a * ld + s];
   };
-  load(st * 64 + lane);
+  load(st * kStep + (lane & kStep - 1));
   rid::stage_frag_lds(P, l, sRw, sRb2, sRb3);
   rid::fold_pose(P, l, pose, nb, c1);
   for (int e = threadIdx.x; e < H * 3; e += kBlock) w1x[e] = P[l.offW1 + (e / 3) * l.nin + (e % 3)];
@@ -118,14 +125,13 @@ __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restri
 
   const rid::LdsFragW w{sRw, sRb2, sRb3, lane, g};
   for (; st < nstep; st += wstride) {
-    const int64_t s = st * 64 + lane;
+    const int64_t s = st * kStep + (lane & kStep - 1);
     float x[3], off[3] = {0.0f, 0.0f, 0.0f};
     int bi = 0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) x[a] = xn[a];
-    load(s + wstride * 64);
-#pragma unroll
-    for (int p = 0; p < 4 / kPair; ++p) {
+    load(s + wstride * kStep);
+    for (int p = 0; p < pairs; ++p) {
       // the weights' reads stay in the loop (hoisted, they would hold every
       // fragment in registers)
       asm volatile("" ::: "memory");
@@ -190,7 +196,7 @@ __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restri
     const int k = bi < nb ? bi : 0;
     float x0[3];
     rid::start_point(sBinv + 12 * k, x, off, x0);
-    if (s < S) {
+    if (s < S && lane < kStep) {
       bone_out[s] = (int16_t)k;
 #pragma unroll
       for (int a = 0; a < 3; ++a) x0_soa[a * ld + s] = x0[a];
@@ -218,7 +224,7 @@ extern "C" int32_t ia355_rootinit_fwd(const float *xp, int64_t S, const int64_t 
     rootinit_f32<<<grid_for(ceil_div(S, 16) * 64, kBlock, 256 * 2), kBlock, lds, s>>>(
         xp, S, S_dev, ld, pose, params, B, nb, init_bone, x0);
   else
-    rootinit_bf16<<<grid_for(S, kBlock, 256 * 4), kBlock, 0, s>>>(
+    rootinit_bf16<<<grid_for(S <= kOnePairSamples ? 2 * S : S, kBlock, 256 * 4), kBlock, 0, s>>>(
         xp, S, S_dev, ld, pose, params, B, nb, init_bone, x0);
   return launch_status();
 }

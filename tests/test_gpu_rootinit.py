@@ -86,6 +86,31 @@ def test_rootinit_bones_and_ragged(orc, nb):
         assert (b[n:] == -7).all() and (x[:, n:] == -7.0).all(), n
 
 
+def test_rootinit_bf16_steps():
+    """BF16 calls and device counts around 32,768 samples, where a wave's step
+    goes from 32 samples to 64: each bit-equal to the first samples of the
+    longest, nothing written past the count."""
+    K = _K()
+    w = synth.train_step()
+    S = 33000
+    xp = soa(synth.sample_posed_points(synth.make_skeleton(0), w.B.astype(np.float64), S, 6).astype(np.float32))
+    params, pose, B = up(_params()), up(w.pose_params.reshape(-1)), up(w.B)
+
+    def run(n, cap):
+        bone = torch.full((S,), -7, dtype=torch.int16, device=dev())
+        x0 = torch.full((3, S), -7.0, device=dev())
+        Sd = None if cap == n else torch.tensor([n], dtype=torch.int64, device=dev())
+        K.rootinit_fwd(xp, cap, S, pose, params, B, K.BF16, bone, x0, S_dev=Sd)
+        return host(bone), host(x0)
+
+    fb, fx = run(S, S)
+    for n in (31, 33, 4097, 32767, 32768, 32769, 32801, 32833):
+        for cap in (n, S):
+            b, x = run(n, cap)
+            assert np.array_equal(b[:n], fb[:n]) and np.array_equal(x[:, :n], fx[:, :n]), (n, cap)
+            assert (b[n:] == -7).all() and (x[:, n:] == -7.0).all(), (n, cap)
+
+
 def test_rootinit_bf16_unaligned_params():
     """BF16 initialiser with its parameter block at an address that is not a
     multiple of 16 bytes (the fragments are then gathered one value at a
