@@ -134,30 +134,53 @@ int reg_blocks(int64_t S) {
 // latency of the halo's loads (one row per thread, its loads in flight
 // together).  A thread per output word walking 32 cells x 27 densities left
 // the chip idle: 143 us at G = 64 (r = 1, 8192 threads), 5 us this way.
+//
+// Without a dilation that thread per word read every density once, 32 side by
+// side, where a thread per row has 64 rows in each load: G = 256 took 40 us
+// and 97.  There a row's eight densities are read by eight lanes and the rows'
+// masks are a ballot's bytes; the bricks, which share their 128-byte lines with
+// three neighbours along x, go to the XCDs in eight runs, which takes a quarter
+// off.  G = 256: 24 us, G = 512: 228 (361 by the thread per word, 795 by rows).
 constexpr int kHaloY = 8 + 2 * kMaxDilate, kHaloZ = 16 + 2 * kMaxDilate;
 
-__global__ void __launch_bounds__(kBlock) occ_from_density_kernel(const float *__restrict__ sigma, int G,
-                                                                  float thresh, int r, uint32_t *__restrict__ bits) {
+template <bool kDilate>
+__global__ void __launch_bounds__(kBlock) occ_from_density_kernel(const float *__restrict__ sigma, int G, float thresh,
+                                                                  int r, int64_t nbrick, uint32_t *__restrict__ bits) {
   __shared__ uint32_t row[kHaloZ * kHaloY];  // x-dilated cells 0..7 of each halo row
   __shared__ __attribute__((aligned(4))) uint8_t out[128];
   const int nb = (G + 7) / 8;
-  const int64_t brick = blockIdx.x;
+  const int64_t brick =
+      kDilate ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+  if (brick >= nbrick) return;
   const int x0 = (int)(brick % nb) * 8, y0 = (int)((brick / nb) % nb) * 8, z0 = (int)(brick / ((int64_t)nb * nb)) * 16;
-  const int hy = 8 + 2 * r, hx = 8 + 2 * r, rows = (16 + 2 * r) * hy;
-  for (int i = threadIdx.x; i < rows; i += kBlock) {
-    const int zz = z0 - r + i / hy, yy = y0 - r + i % hy;
-    uint32_t m = 0;
-    if (zz >= 0 && zz < G && yy >= 0 && yy < G) {
-      const float *src = sigma + ((int64_t)zz * G + yy) * G;
+  const int hy = 8 + 2 * r;
+  if constexpr (kDilate) {
+    const int hx = 8 + 2 * r, rows = (16 + 2 * r) * hy;
+    for (int i = threadIdx.x; i < rows; i += kBlock) {
+      const int zz = z0 - r + i / hy, yy = y0 - r + i % hy;
+      uint32_t m = 0;
+      if (zz >= 0 && zz < G && yy >= 0 && yy < G) {
+        const float *src = sigma + ((int64_t)zz * G + yy) * G;
 #pragma unroll
-      for (int j = 0; j < 8 + 2 * kMaxDilate; ++j) {
-        const int xx = x0 - r + j;
-        if (j < hx && xx >= 0 && xx < G && src[xx] > thresh) m |= 1u << j;
+        for (int j = 0; j < 8 + 2 * kMaxDilate; ++j) {
+          const int xx = x0 - r + j;
+          if (j < hx && xx >= 0 && xx < G && src[xx] > thresh) m |= 1u << j;
+        }
       }
+      uint32_t d = m;
+      for (int k = 1; k <= 2 * r; ++k) d |= m >> k;
+      row[i] = d;
     }
-    uint32_t d = m;
-    for (int k = 1; k <= 2 * r; ++k) d |= m >> k;
-    row[i] = d;
+  } else {
+    const int j = threadIdx.x % 8;
+#pragma unroll
+    for (int i = threadIdx.x / 8; i < 128; i += kBlock / 8) {
+      const int zz = z0 + i / 8, yy = y0 + i % 8, xx = x0 + j;
+      const bool in = zz < G && yy < G && xx < G;
+      const float v = sigma[in ? ((int64_t)zz * G + yy) * G + xx : 0];
+      const uint64_t over = __ballot(in && v > thresh);
+      if (j == 0) row[i] = (uint32_t)(over >> threadIdx.x % kWave) & 0xffu;
+    }
   }
   __syncthreads();
   if (threadIdx.x < 128) {
@@ -213,7 +236,9 @@ extern "C" int32_t ia355_occ_from_density(const float *sigma, int32_t G, float s
                                           uint32_t *occ_bits, ia355_stream_t stream) {
   if (G <= 0 || G > 2048 || dilate < 0 || dilate > kMaxDilate || !sigma || !occ_bits) return IA355_ERR_INVALID_ARG;
   const int64_t nbrick = occ_words(G) / 32;
-  occ_from_density_kernel<<<(unsigned)nbrick, kBlock, 0, as_stream(stream)>>>(sigma, G, sigma_thresh, dilate, occ_bits);
+  auto *kernel = dilate > 0 ? occ_from_density_kernel<true> : occ_from_density_kernel<false>;
+  kernel<<<(unsigned)(8 * ceil_div(nbrick, (int64_t)8)), kBlock, 0, as_stream(stream)>>>(sigma, G, sigma_thresh, dilate,
+                                                                                        nbrick, occ_bits);
   return launch_status();
 }
 

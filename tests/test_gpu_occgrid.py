@@ -60,6 +60,13 @@ def test_occ_from_density_bricks_and_halos(G, r):
     assert not got[G:].any() and not got[:, G:].any() and not got[:, :, G:].any()
 
 
+@pytest.mark.parametrize("G", [2, 7, 9, 16, 33, 64, 129])
+def test_occ_from_density_no_dilation_bricks(G):
+    """The undilated grid's own kernel: brick counts that do and do not fill
+    eight runs, grids that end inside a brick, the same densities."""
+    test_occ_from_density_bricks_and_halos(G, 0)
+
+
 def _build(w, G, table, thresh, r, mlp_dtype):
     K = _K()
     Dz, Dy, Dx, nb = w.W.shape
