@@ -376,6 +376,13 @@ def test_hash_encode_fp16_level_turns(orc, S, L, cap):
         assert_mixed(got, ref, TOL, f"hash level turns S={S} L={L}")
 
 
+@pytest.mark.parametrize("S,L", [(1, 20), (4 * 256, 20), (4 * 256 + 1, 20), (3 * 256 - 1, 16), (256, 32)])
+def test_hash_encode_fp16_counts_and_groups(orc, S, L):
+    """Device-side counts that end at, before and after a chunk, with one to
+    three level groups: slots without a chunk leave, the others write all."""
+    test_hash_encode_fp16_level_turns(orc, S, L, 1 << 14)
+
+
 def test_hash_encode_bf16_features(orc):
     K = _K()
     S = 2049
