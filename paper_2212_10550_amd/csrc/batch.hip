@@ -198,7 +198,7 @@ __device__ inline void sample_xp(const WaveMem &wm, int ra, int rb, int j, float
 }
 
 // Decoder weights fetched from the workgroup's LDS as the MFMAs use them
-// (the same bf16 fragments and FP32 biases as the decoder kernel's FragBf).
+// (the same BF16 fragments and FP32 biases as the decoder kernel's FragLds).
 struct LdsMW {
   const Store &st;
   int lane, g;
@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(kW * kWave, kMinGroups * kW / 4) render_kernel
             int bi;
             float off3[3], h1[4][4];
             rid::layer1(xs, wm.c1, st.w1x, g, h1);
-            rid::tile_tail<true>(h1, rid::LdsFragW{st.rw, st.rb2, st.rb3, lane, g}, nb, g, &bi, off3);
+            rid::tile_tail_bf16(h1, rid::LdsFragW{st.rw, st.rb2, st.rb3, lane, g}, nb, g, &bi, off3);
             if (g == t) {
               const int kb = bi < nb ? bi : 0;
               ibone = kb;

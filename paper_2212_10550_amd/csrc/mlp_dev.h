@@ -1,6 +1,8 @@
 // The decoder MLP of Sec. 3.1, Eq. 1-2 (32 -> 64 -> 64 -> 4) in its BF16
-// MFMA form, shared by the decoder kernels and the fused batch renderer so
-// that both compute the same floats (internal).  Layouts: see mlp.hip.
+// MFMA form (internal).  Layouts: see mlp.hip.  The decoder forward and the
+// persistent batch renderer share everything here but the chain of layers
+// (several tiles against one): the same operations in the same order, which
+// the batch tests hold to the same bits.
 #pragma once
 #include <hip/hip_bf16.h>
 
@@ -13,7 +15,6 @@ constexpr int NIN = 32, NH = 64, NOUT = 4;
 constexpr int OFF_W1 = 0, OFF_B1 = OFF_W1 + NH * NIN, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH,
               OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NOUT * NH, NPARAM = OFF_B3 + NOUT;
 static_assert(NPARAM == 6532, "parameter count");
-
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -94,9 +95,6 @@ struct LdsW {
   __device__ __forceinline__ bf16x8 w3(int c) const { return s.mw[12 + c][lane]; }
   __device__ __forceinline__ f32x4 b1(int mt) const { return *reinterpret_cast<const f32x4 *>(s.b1 + 16 * mt + 4 * g); }
   __device__ __forceinline__ f32x4 b2(int mt) const { return *reinterpret_cast<const f32x4 *>(s.b2 + 16 * mt + 4 * g); }
-  __device__ __forceinline__ f32x4 b3() const {
-    return g == 0 ? *reinterpret_cast<const f32x4 *>(s.b3) : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
 };
 
 // A compiler-only barrier inside a loop: the LDS fragment reads after it
@@ -113,10 +111,8 @@ __device__ __forceinline__ bf16x8 pack_act(const f32x4 z[4], int c) {
 }
 
 // The BF16 forward of one 16-sample tile with the weights from a source:
-// w.w1(mt), w.w2(mt, c), w.w3(c) give the A-operand fragments and
-// w.b1(mt), w.b2(mt), w.b3() the accumulator initialisers (biases), so the
-// fragments may live in registers or be fetched from LDS as they are used;
-// the operations are the same either way.
+// w.w1(mt), w.w2(mt, c), w.w3(c) give the A-operand fragments and w.b1(mt),
+// w.b2(mt), w.b3() the accumulator initialisers (biases).
 template <class WSrc>
 __device__ __forceinline__ void fwd_bf_src(const WSrc &w, const bf16x8 &X, f32x4 z1[4], f32x4 z2[4], f32x4 &o) {
 #pragma unroll

@@ -49,8 +49,8 @@ __global__ void __launch_bounds__(kBlock, 1) rootinit_f32(const float *__restric
   __syncthreads();
 
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  rid::Frag<false> f;
-  rid::load_frag<false>(sP, l, r, g, f);
+  rid::Frag f;
+  rid::load_frag(sP, l, r, g, f);
   const int64_t ntile = ceil_div(S, 16);
   const int64_t wstride = (int64_t)gridDim.x * (kBlock / 64);
   for (int64_t tile = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); tile < ntile; tile += wstride) {
@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(kBlock, 1) rootinit_f32(const float *__restric
     }
     int bi;
     float off[3];
-    rid::tile<false>(x, c1, w1x, f, nb, g, &bi, off);
+    rid::tile_f32(x, c1, w1x, f, nb, g, &bi, off);
     if (g == 0 && ok) {
       const int k = bi < nb ? bi : 0;
       bone_out[s] = (int16_t)k;
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restri
       f32x4 z[kPair][4], o[kPair][2];
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        const bf16x8 a0 = w.w2b(mt, 0), a1 = w.w2b(mt, 1);
+        const bf16x8 a0 = w.w2(mt, 0), a1 = w.w2(mt, 1);
         const f32x4 b = w.b2(mt);
 #pragma unroll
         for (int u = 0; u < kPair; ++u) {
@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(kBlock, 4) rootinit_bf16(const float *__restri
         }
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {
-        const bf16x8 a0 = w.w3b(mt, 0), a1 = w.w3b(mt, 1);
+        const bf16x8 a0 = w.w3(mt, 0), a1 = w.w3(mt, 1);
         const f32x4 b = w.b3(mt);
 #pragma unroll
         for (int u = 0; u < kPair; ++u) {

@@ -1,9 +1,11 @@
 // The learned root initialiser (an addition to the root finding of
 // Sec. 3.1): (x', pose) -> nb bone logits and a canonical offset through
-// (3 + 6 nb) -> 64 -> 64 -> (nb + 3), shared by the initialiser kernel and
-// the fused batch renderer so that both compute the same floats (internal).
-// Layer 1's pose part is folded into a per-neuron constant c1 once per pose;
-// layers 2 and 3 run on MFMA with the decoder MLP's layouts.
+// (3 + 6 nb) -> 64 -> 64 -> (nb + 3) (internal).  Layer 1's pose part is
+// folded into a per-neuron constant c1 once per pose; layers 2 and 3 run on
+// MFMA with the decoder MLP's layouts.  The BF16 initialiser kernel and the
+// persistent batch renderer share everything here but the chain of layers
+// (a pair of tiles against one): the same operations in the same order, which
+// the batch tests hold to the same bits.
 #pragma once
 #include <hip/hip_bf16.h>
 
@@ -75,11 +77,9 @@ __device__ __forceinline__ void fold_pose(const float *P, const Layout &l, const
   if (q == 0 && threadIdx.x < 4 * H) c1[n] = acc + P[l.offb1 + n];
 }
 
-// Weight fragments of layers 2 and 3 of lane (r, g).
-template <bool BF16>
+// FP32 weight fragments of layers 2 and 3 of lane (r, g), in registers.
 struct Frag {
-  float w2f[4][16], w3f[2][16];
-  bf16x8 w2b[4][2], w3b[2][2];
+  float w2[4][16], w3[2][16];
   float b2[4][4], b3[2][4];
 };
 
@@ -100,47 +100,28 @@ __host__ __device__ inline int w3b_at(const Layout &l, int mt, int c, int j, int
   return row < l.nout ? l.offW3 + row * H + 16 * (2 * c + j / 4) + 4 * g + (j % 4) : -1;
 }
 
-template <bool BF16>
-__device__ __forceinline__ void load_frag(const float *sP, const Layout &l, int r, int g, Frag<BF16> &f) {
+__device__ __forceinline__ void load_frag(const float *sP, const Layout &l, int r, int g, Frag &f) {
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) f.b2[mt][i] = sP[l.offb2 + 16 * mt + 4 * g + i];
-    if (!BF16) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) f.w2f[mt][k] = sP[w2f_at(l, mt, k, r, g)];
-    } else {
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f.w2b[mt][c][j] = (__bf16)sP[w2b_at(l, mt, c, j, r, g)];
-    }
+    for (int k = 0; k < 16; ++k) f.w2[mt][k] = sP[w2f_at(l, mt, k, r, g)];
   }
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) f.b3[mt][i] = (16 * mt + 4 * g + i) < l.nout ? sP[l.offb3 + 16 * mt + 4 * g + i] : 0.0f;
-    if (!BF16) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const int i = w3f_at(l, mt, k, r, g);
-        f.w3f[mt][k] = i >= 0 ? sP[i] : 0.0f;
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int i = w3b_at(l, mt, c, j, r, g);
-          f.w3b[mt][c][j] = (__bf16)(i >= 0 ? sP[i] : 0.0f);
-        }
+    for (int k = 0; k < 16; ++k) {
+      const int i = w3f_at(l, mt, k, r, g);
+      f.w3[mt][k] = i >= 0 ? sP[i] : 0.0f;
     }
   }
 }
 
 // BF16 fragment q (0-7: layer 2 (mt, c) = (q / 2, q % 2); 8-11: layer 3
-// (mt, c) = ((q - 8) / 2, q % 2)) of lane (r, g), built alone (the same
-// values as load_frag<true>).
+// (mt, c) = ((q - 8) / 2, q % 2)) of lane (r, g), built alone.
 __device__ __forceinline__ bf16x8 frag_bf(const float *P, const Layout &l, int q, int r, int g) {
   bf16x8 v;
 #pragma unroll
@@ -187,64 +168,6 @@ __device__ __forceinline__ void pick(const f32x4 o[2], int nb, int g, int *bone,
   }
 }
 
-// Layers 2-3 and the argmax of one 16-sample tile from the layer-1
-// activations h1 (lane r + 16 g holds neurons 16t + 4g + i of sample r),
-// with the weight fragments from a source: w.w2f(mt, k) / w.w3f(mt, k)
-// (FP32 16x16x4 operands), w.w2b(mt, c) / w.w3b(mt, c) (BF16 16x16x32
-// operands), w.b2(mt) / w.b3(mt) (accumulator initialisers).  The bone
-// (ties: the lowest) and the three offsets land in every lane of sample r.
-template <bool BF16, class WSrc>
-__device__ __forceinline__ void tile_tail(const float h1[4][4], const WSrc &w, int nb, int g, int *bone,
-                                          float off_out[3]) {
-  f32x4 z2[4], o[2];
-  if (!BF16) {
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      f32x4 acc = w.b2(mt);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w2f(mt, 4 * t + i), h1[t][i], acc, 0, 0, 0);
-      z2[mt] = acc;
-    }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      f32x4 acc = w.b3(mt);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w3f(mt, 4 * t + i), relu(z2[t][i]), acc, 0, 0, 0);
-      o[mt] = acc;
-    }
-  } else {
-    bf16x8 ha, hb;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      ha[j] = (__bf16)h1[j / 4][j % 4];
-      hb[j] = (__bf16)h1[2 + j / 4][j % 4];
-    }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      f32x4 acc = w.b2(mt);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w2b(mt, 0), ha, acc, 0, 0, 0);
-      z2[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w2b(mt, 1), hb, acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      ha[j] = (__bf16)relu(z2[j / 4][j % 4]);
-      hb[j] = (__bf16)relu(z2[2 + j / 4][j % 4]);
-    }
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
-      f32x4 acc = w.b3(mt);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w3b(mt, 0), ha, acc, 0, 0, 0);
-      o[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w3b(mt, 1), hb, acc, 0, 0, 0);
-    }
-  }
-  pick(o, nb, g, bone, off_out);
-}
-
 // Layer 1's neuron with constant c and x weights w at point x.
 __device__ __forceinline__ float neuron1(const float x[3], float c, const float *w) {
   return relu(c + w[0] * x[0] + w[1] * x[1] + w[2] * x[2]);
@@ -262,22 +185,6 @@ __device__ __forceinline__ void layer1(const float x[3], const float *c1, const 
     }
 }
 
-// Fragments held in registers (Frag).
-template <bool BF16>
-struct RegFrag {
-  const Frag<BF16> &f;
-  __device__ __forceinline__ float w2f(int mt, int k) const { return f.w2f[mt][k]; }
-  __device__ __forceinline__ float w3f(int mt, int k) const { return f.w3f[mt][k]; }
-  __device__ __forceinline__ bf16x8 w2b(int mt, int c) const { return f.w2b[mt][c]; }
-  __device__ __forceinline__ bf16x8 w3b(int mt, int c) const { return f.w3b[mt][c]; }
-  __device__ __forceinline__ f32x4 b2(int mt) const {
-    return f32x4{f.b2[mt][0], f.b2[mt][1], f.b2[mt][2], f.b2[mt][3]};
-  }
-  __device__ __forceinline__ f32x4 b3(int mt) const {
-    return f32x4{f.b3[mt][0], f.b3[mt][1], f.b3[mt][2], f.b3[mt][3]};
-  }
-};
-
 // BF16 fragments of layers 2-3 read from LDS as each MFMA needs them:
 // rw[q][lane] is fragment q of lane (lane % 16, lane / 16) (q as frag_bf:
 // 0-7 layer 2, 8-11 layer 3), rb2 [64] and rb3 [kMaxOut] the biases
@@ -286,10 +193,8 @@ struct LdsFragW {
   const bf16x8 (*rw)[kWave];
   const float *rb2, *rb3;
   int lane, g;
-  __device__ __forceinline__ float w2f(int, int) const { return 0.0f; }
-  __device__ __forceinline__ float w3f(int, int) const { return 0.0f; }
-  __device__ __forceinline__ bf16x8 w2b(int mt, int c) const { return rw[2 * mt + c][lane]; }
-  __device__ __forceinline__ bf16x8 w3b(int mt, int c) const { return rw[8 + 2 * mt + c][lane]; }
+  __device__ __forceinline__ bf16x8 w2(int mt, int c) const { return rw[2 * mt + c][lane]; }
+  __device__ __forceinline__ bf16x8 w3(int mt, int c) const { return rw[8 + 2 * mt + c][lane]; }
   __device__ __forceinline__ f32x4 b2(int mt) const { return *reinterpret_cast<const f32x4 *>(rb2 + 16 * mt + 4 * g); }
   __device__ __forceinline__ f32x4 b3(int mt) const { return *reinterpret_cast<const f32x4 *>(rb3 + 16 * mt + 4 * g); }
 };
@@ -339,15 +244,63 @@ __device__ __forceinline__ void stage_frag_lds(const float *__restrict__ P, cons
   for (int i = threadIdx.x; i < kMaxOut; i += blockDim.x) rb3[i] = i < l.nout ? P[l.offb3 + i] : 0.0f;
 }
 
-// One 16-sample tile, called by all 64 lanes of a wave (lane r + 16 g holds
-// sample r's point x): the argmax bone (ties: the lowest) and the three
+// One 16-sample tile in FP32, called by all 64 lanes of a wave (lane r + 16 g
+// holds sample r's point x): the argmax bone (ties: the lowest) and the three
 // offsets, in every lane of sample r.  c1 [64] and w1x [64][3] in LDS.
-template <bool BF16>
-__device__ __forceinline__ void tile(const float x[3], const float *c1, const float *w1x, const Frag<BF16> &f, int nb,
-                                     int g, int *bone, float off_out[3]) {
+__device__ __forceinline__ void tile_f32(const float x[3], const float *c1, const float *w1x, const Frag &f, int nb,
+                                         int g, int *bone, float off_out[3]) {
   float h1[4][4];
   layer1(x, c1, w1x, g, h1);
-  tile_tail<BF16>(h1, RegFrag<BF16>{f}, nb, g, bone, off_out);
+  f32x4 z2[4], o[2];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    f32x4 acc{f.b2[mt][0], f.b2[mt][1], f.b2[mt][2], f.b2[mt][3]};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.w2[mt][4 * t + i], h1[t][i], acc, 0, 0, 0);
+    z2[mt] = acc;
+  }
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt) {
+    f32x4 acc{f.b3[mt][0], f.b3[mt][1], f.b3[mt][2], f.b3[mt][3]};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f.w3[mt][4 * t + i], relu(z2[t][i]), acc, 0, 0, 0);
+    o[mt] = acc;
+  }
+  pick(o, nb, g, bone, off_out);
+}
+
+// Layers 2-3 and the argmax of one 16-sample tile in BF16 from the layer-1
+// activations h1 (lane r + 16 g holds neurons 16t + 4g + i of sample r).
+__device__ __forceinline__ void tile_tail_bf16(const float h1[4][4], const LdsFragW &w, int nb, int g, int *bone,
+                                               float off_out[3]) {
+  f32x4 z2[4], o[2];
+  bf16x8 ha, hb;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    ha[j] = (__bf16)h1[j / 4][j % 4];
+    hb[j] = (__bf16)h1[2 + j / 4][j % 4];
+  }
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+    const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w2(mt, 0), ha, w.b2(mt), 0, 0, 0);
+    z2[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w2(mt, 1), hb, acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    ha[j] = (__bf16)relu(z2[j / 4][j % 4]);
+    hb[j] = (__bf16)relu(z2[2 + j / 4][j % 4]);
+  }
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt) {
+    const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w3(mt, 0), ha, w.b3(mt), 0, 0, 0);
+    o[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.w3(mt, 1), hb, acc, 0, 0, 0);
+  }
+  pick(o, nb, g, bone, off_out);
 }
 
 // Broyden start point x0 = B_k^{-1} x' + offset (Bi: [M^-1 | -M^-1 t] of

@@ -378,8 +378,8 @@ def test_hash_encode_fp16_level_turns(orc, S, L, cap):
 
 @pytest.mark.parametrize("S,L", [(1, 20), (4 * 256, 20), (4 * 256 + 1, 20), (3 * 256 - 1, 16), (256, 32)])
 def test_hash_encode_fp16_counts_and_groups(orc, S, L):
-    """Device-side counts that end at, before and after a chunk, with one to
-    three level groups: slots without a chunk leave, the others write all."""
+    """Device-side counts that end at, before and after a chunk, with one or
+    two level groups: slots without a chunk leave, the others write all."""
     test_hash_encode_fp16_level_turns(orc, S, L, 1 << 14)
 
 
