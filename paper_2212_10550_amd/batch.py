@@ -190,13 +190,13 @@ class BatchRenderer:
             return
         main = torch.cuda.current_stream()
         for sl in self.slots:
-            sl.stream.wait_stream(main)
+            K.stream_wait(sl.stream, main)
         for sl, idx in zip(self.slots, self.assign):
             with torch.cuda.stream(sl.stream):
                 for i in idx:
                     self._pose_forward(sl, self.poses[i])
         for sl in self.slots:
-            main.wait_stream(sl.stream)
+            K.stream_wait(main, sl.stream)
 
     def capture(self):
         self.graph = None

@@ -134,6 +134,16 @@ def _stream():
     return _vp(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
+def stream_wait(stream, other):
+    """``stream`` waits for the work queued on ``other``: an edge of a fork or a
+    join, also inside a capture.  Streams come from a pool that hands each out
+    many times, so the two may be one (a side stream and the stream that a
+    graph is captured on): work on it is in order as it is, and no event is
+    recorded and waited for on the same stream."""
+    if stream != other:
+        stream.wait_stream(other)
+
+
 def _p(t, dtype=None, name="tensor"):
     if t is None:
         return None

@@ -249,7 +249,7 @@ class Pipeline:
         table gradient writes every entry itself, so it needs no clear."""
         if self.table_grad_mode == "binned":
             return
-        self.side.wait_stream(torch.cuda.current_stream())
+        K.stream_wait(self.side, torch.cuda.current_stream())
         with torch.cuda.stream(self.side):
             K.zero(self.grad_table)
         self._table_zeroed = True
@@ -314,7 +314,7 @@ class Pipeline:
             main = torch.cuda.current_stream()
             ow = not self._table_zeroed
             if self._table_zeroed:  # the clear was forked to the side stream
-                main.wait_stream(self.side)
+                K.stream_wait(main, self.side)
                 self._table_zeroed = False
             self._mark("hash_bwd_table")
             self._table_grad(S, Sd, overwrite=ow)
@@ -324,7 +324,7 @@ class Pipeline:
             self._mark(None)
             return
         main = torch.cuda.current_stream()
-        self.side.wait_stream(main)
+        K.stream_wait(self.side, main)
         if self.table_grad_mode == "binned":
             # every level in one binned call beside the position gradient,
             # which is queued first: its kernels are the longer chain and fill
@@ -336,9 +336,9 @@ class Pipeline:
             st["deform_bwd"]()
             with torch.cuda.stream(self.side):
                 self._table_grad(S, Sd, overwrite=True)
-            main.wait_stream(self.side)
+            K.stream_wait(main, self.side)
             return
-        self.side2.wait_stream(self.side)  # after the table clear (if any) and the MLP backward
+        K.stream_wait(self.side2, self.side)  # after the table clear (if any) and the MLP backward
         ow = not self._table_zeroed
         with torch.cuda.stream(self.side):
             self._table_grad(S, Sd, overwrite=ow, group=K.TABLE_COARSE)
@@ -347,8 +347,8 @@ class Pipeline:
         self._table_zeroed = False
         st["hash_bwd_x"]()
         st["deform_bwd"]()
-        main.wait_stream(self.side)
-        main.wait_stream(self.side2)
+        K.stream_wait(main, self.side)
+        K.stream_wait(main, self.side2)
 
     def stage_times(self, n=20, backward=True, reps=10):
         """GPU ms per stage (device counts): each stage's calls captured

@@ -97,6 +97,29 @@ def test_batch_pool_serves_smaller_poses():
     _check_replays(br, _single_refs(ws, params, br.poses), "two poses, one slot")
 
 
+@pytest.mark.parametrize("at", [0, 1, 2])
+def test_batch_captured_on_a_slots_stream(small_batch, at):
+    """A stream of the pool may be handed out again: the graph is captured on
+    the stream of one of three slots, and replayed in turn with another
+    renderer's, nothing waiting between."""
+    from paper_2212_10550_amd.batch import BatchRenderer
+    params = _params()
+    brs = [BatchRenderer(small_batch, params, n_streams=3) for _ in range(2)]
+    refs = _single_refs(small_batch, params, brs[0].poses)
+    for br in brs:
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=br.slots[at].stream):
+            br.render()
+        torch.cuda.synchronize()
+        br.graph = g
+    for br in (brs[0], brs[1], brs[0]):
+        br.render()
+    torch.cuda.synchronize()
+    for br in brs:
+        _check_replays(br, refs, f"captured on slot {at}'s stream")
+
+
 # schedules: rays per tile (ragged last tiles, 64 = one lane per ray),
 # samples per segment (256: a 64-ray tile splits into several segments),
 # waves per workgroup, workgroups per CU (every kernel instantiation)

@@ -81,3 +81,61 @@ def test_autograd_front_end_dtype_checks():
         A.hash_encode(torch.zeros(3, 4), torch.zeros(4, dtype=torch.int16), torch.zeros(16, 64, 2).half(), cfg)
     with pytest.raises(TypeError):
         A.mlp(torch.zeros(16, 4, 2).bfloat16(), torch.zeros(4, dtype=torch.int16), torch.zeros(6532))
+
+
+def test_fork_and_join_when_streams_are_one(monkeypatch):
+    """The pool hands a stream out again and again: a renderer's or a step's
+    side stream may be the stream that the work is captured on.  No stream
+    waits for itself, every other fork and join is there, and each pose runs."""
+    import torch
+    from paper_2212_10550_amd.batch import BatchRenderer
+    from paper_2212_10550_amd.pipeline import Pipeline
+    log = []
+
+    class Stream:
+        def __init__(self, n):
+            self.n = n
+
+        def __eq__(self, o):
+            return self.n == o.n
+
+        def __ne__(self, o):
+            return self.n != o.n
+
+        def wait_stream(self, o):
+            log.append(("wait", self.n, o.n))
+
+        def __enter__(self):
+            log.append(("on", self.n))
+
+        def __exit__(self, *a):
+            pass
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream(2))
+    monkeypatch.setattr(torch.cuda, "stream", lambda s: s)
+    r = BatchRenderer.__new__(BatchRenderer)
+    r.graph = r.persistent = None
+    r.poses, r.assign = list("abcd"), [[0], [1], [2], [3]]
+    r.slots = [type("Slot", (), {"stream": Stream(n)})() for n in (1, 2, 3, 4)]
+    r._pose_forward = lambda sl, p: log.append(("pose", p))
+    r.render()
+    waits = [e for e in log if e[0] == "wait"]
+    assert waits == [("wait", n, 2) for n in (1, 3, 4)] + [("wait", 2, n) for n in (1, 3, 4)]
+    assert [e[1] for e in log if e[0] == "pose"] == list("abcd")
+
+    for mode, sides in (("binned", (2, 3)), ("atomic", (2, 3)), ("atomic", (1, 2))):
+        log.clear()
+        p = Pipeline.__new__(Pipeline)
+        p.table_grad_mode, p.timer, p._table_zeroed = mode, None, False
+        p.side, p.side2 = Stream(sides[0]), Stream(sides[1])
+        p.stages = lambda S, Sd: [(n, lambda n=n: log.append(("stage", n)))
+                                  for n in ("loss+render_bwd", "mlp_bwd", "hash_bwd_x", "deform_bwd")]
+        p._mark = lambda name: None
+        p._table_grad = lambda S, Sd, **kw: log.append(("stage", "table"))
+        p.backward(8)
+        waits = [e for e in log if e[0] == "wait"]
+        assert all(a != b for _, a, b in waits)
+        assert len([e for e in log if e == ("stage", "table")]) == (1 if mode == "binned" else 2)
+        if mode == "atomic":
+            other = 3 if sides == (2, 3) else 1  # the side stream that is not the current one
+            assert ("wait", other, 2) in waits and ("wait", 2, other) in waits
