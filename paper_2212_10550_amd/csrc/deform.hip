@@ -8,7 +8,7 @@
 //    the per-pose blended transform of vertex v.  A is a 12-float-per-vertex
 //    grid (3 x float4 per corner) built once per pose, which halves the
 //    gathered bytes and removes the 24-bone blend from every residual.
-//  * solve kernel: eight lanes per posed sample each run a third of the nb
+//  * solve kernel: two, eight or 32 lanes per posed sample share its nb
 //    Broyden solves in FP32 registers and pick the lowest residual with
 //    shuffles; bone inverses are staged in LDS once per block; the blended
 //    grid is read through the vector L1/L2 with float4 gathers, a cell's
@@ -99,9 +99,6 @@ __global__ void __launch_bounds__(kSolveBlock, kHeld ? 2 : 3) solve_kernel(
   }
 }
 
-// Guided solve: one lane per sample starts Broyden at the given x0; an
-// accepted root (residual < tol_valid, inside the canonical box) is final,
-// otherwise the sample index is appended to the fallback queue.
 // Every distinct valid root of each sample (multi-root aggregation, the
 // alternative to keeping only the lowest-residual root): the kGroup lanes of
 // a sample run its inits as in the multi-init solve and put each init's final
@@ -208,6 +205,9 @@ __global__ void __launch_bounds__(256) select_max_kernel(int K, int64_t S, const
   }
 }
 
+// Guided solve: one lane per sample starts Broyden at the given x0; an
+// accepted root (residual < tol_valid, inside the canonical box) is final,
+// otherwise the sample index is appended to the fallback queue.
 // kHeld: each lane holds the corners for itself, where there are few samples
 // and the loop over a wave's cells is a chain of its own: 64 samples 17.0 ->
 // 14.9 us, 36,503 19.3 -> 18.5, 65,536 19.3 -> 18.7, but 131,072 20.3 -> 24.0.

@@ -1,6 +1,6 @@
 // Per-sample arithmetic of the root finding (Sec. 3.1, Eq. 5-7), shared by
-// the deform kernels and the fused batch renderer so that both compute the
-// same floats: the blended transform grid A_v = sum_i W[v][i] B_i, the
+// the deform kernels and the persistent batch renderer so that both compute
+// the same floats: the blended transform grid A_v = sum_i W[v][i] B_i, the
 // residual g(x) = sum_c tri_c (A_c x_h) - x' and its Jacobian on that grid,
 // one Broyden solve and the multi-init search (internal).
 #pragma once
@@ -119,23 +119,25 @@ __device__ __forceinline__ uint32_t cell_base(const Grid &g, const Cell &c) {
 // three rows of corner k.  at() changes the cell of the lanes with `need`; it is
 // called by the whole wave.  Every source gives the same floats.
 //  * HeldCorners keeps the last cell's 96 floats in registers and gathers
-//    only when the cell changes.  The staged multi-init kernels use it: their
-//    time went to the texture path (24 gathers of 16 bytes per residual), and Broyden's
-//    steps shrink so fast that only the start, the first step and a fifth of
-//    the second steps reach a new cell of a 64 x 64 x 32 grid.  It costs 60
-//    to 70 registers (guided solve 91 -> 160, three waves per SIMD; multi-init
-//    solve 121 -> 176, two) and pays all the same: guided solve of 875,600
-//    samples 133 -> 76 us, multi-init solve of 36,503 samples 83 -> 72 us, of
-//    a 64^3 lattice 477 -> 398 us.
+//    only when the cell changes.  The time went to the texture path (24
+//    gathers of 16 bytes per residual), and Broyden's steps shrink so fast
+//    that only the start, the first step and a fifth of the second steps reach
+//    a new cell of a 64 x 64 x 32 grid.  It costs 60 to 70 registers (guided
+//    solve 91 -> 166, three waves per SIMD; multi-init solve 121 -> 174, two)
+//    and pays all the same: against gathering, guided solve of 875,600 samples
+//    133 -> 76 us, multi-init solve of 36,503 83 -> 72, of a 64^3 lattice 477
+//    -> 398.  The root lists, the guided solve's fallback, and the small calls
+//    of the multi-init and of the guided solve use it.
 //  * SharedCorners adds to it: the cells that a wave's lanes lack are loaded
 //    once each into LDS (24 lanes load a cell's 384 bytes directly) and read
 //    from there into the lanes' registers.  After kCellSlots distinct cells
-//    the lanes left gather their own.  The guided solve uses it, whose 64
-//    neighbouring samples lie in few cells: 875,600 samples 75 -> 43 us, of a
+//    the lanes left gather their own.  The guided solve uses it beyond 65,536
+//    samples; a wave's 64 lie in few cells: 875,600 samples 75 -> 43 us, of a
 //    frame 78 -> 65; in random order a whole guided pass takes 124 us as it
 //    did before (24 slots: 132).
-//  * SharedLater gathers the start cells, which differ in nearly every lane of
-//    the multi-init solve, and shares the later ones: 14 cells a wave at the
+//  * SharedLater, which the multi-init solve uses but for few samples of few
+//    bones (168 registers, three waves), gathers the start cells, which differ
+//    in nearly every lane, and shares the later ones: 14 cells a wave at the
 //    first step and 6 at the second (24 slots in place of 12: 36,503 samples
 //    67 us against 64, eight: 65).
 //  * GatherCorners reads them from the blended grid each time: the persistent

@@ -1,22 +1,24 @@
 // Multiresolution hash encoding (Sec. 3.1, Instant-NGP) forward and backward.
 //
 // Forward design (gfx950, 8 XCDs with a private 4 MB L2 each):
-//  * one thread per (sample, level); a block covers 256 consecutive samples
-//    of ONE level, so its gathers stay inside one level's table;
+//  * a lane takes a sample (two in frame-sized calls) and two levels where an
+//    XCD serves several: a block's 256 or 512 consecutive samples read their
+//    positions once for both, and its gathers stay inside two levels' tables;
 //  * workgroups are dispatched round-robin over the 8 XCDs, so block b runs
-//    on XCD b % 8.  Levels are assigned to XCDs by that residue (XCD k gets
-//    levels k, k+8, ...), so each XCD's L2 caches only its own levels'
-//    tables (2 x 2 MiB at T = 2^19 in FP16) instead of all sixteen;
+//    on XCD b % 8, and levels are assigned to XCDs (xcd_level): each XCD's L2
+//    caches the tables of two levels at a time (2 x 2 MiB at T = 2^19 in FP16)
+//    instead of all sixteen.  With an FP32 table an XCD keeps its levels for
+//    the call, with an FP16 one the pairs move on seven times (served_xcd);
 //  * the position scaling u = x N_l is split into a rounded product and its
 //    exact FMA remainder, so the cell and fraction are accurate to FP32
 //    relative precision even at N_l ~ 2000;
 //  * features are written level-major [L][S][F]: each block writes one
-//    contiguous run (coalesced 8-byte / 4-byte stores per lane).
-// Backward: the table gradient is FP32 atomics laid out so that each wave
-// instruction touches few cache lines (see table_grad_kernel); the position
-// gradient runs one wave per 4 samples x 16 levels (lane = level + 16 *
-// sample) and is reduced across the 16 level lanes with shuffles
-// (deterministic).
+//    contiguous run a level (coalesced 8-byte / 4-byte stores per lane).
+// Backward: the table gradient sorts corner pairs by tile of the table and sums
+// each tile in LDS as integers, or, without a workspace, adds FP32 atomics laid
+// out so that each wave instruction touches few cache lines (see
+// table_grad_kernel); the position gradient has the forward's mapping, a level's
+// contributions in a workspace, then their sum in a fixed order (deterministic).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
