@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(kBlendBlock) blend_kernel(const float *__restr
   blend_block(W, B, nb, nvert, A, blockIdx.x, sB, sW);
 }
 
-// kG lanes per sample: eight (three inits each of 24, one after the other), or
+// Lanes per sample: eight (three inits each of 24, one after the other), or
 // 32 for few samples, whose time is a lane's chain of inits and not the chip's
 // rate: 24 bones, 200 samples 31.5 -> 12.1 us, 4096 32.6 -> 17.6, 8192 32.7 ->
 // 26.2, 16,384 45.7 -> 42.6, but 24,576 56.5 -> 58.0; 12 bones (two inits a
@@ -59,14 +59,16 @@ inline int64_t wide_samples(int nb) {
 // samples 16.0 -> 15.2 us, 12 bones 23.3 -> 20.2, but 36,503 48 -> 53).
 inline bool few_inits(int64_t S, int nb) { return S <= 16384 && nb <= 2 * kGroup; }
 
-// lanes: per sample; 32 up to `wide` samples.  kHeld: each lane holds the
-// corners for itself (two waves per SIMD).
-template <bool kHeld>
+// kLanes: per sample; zero, where the count is on the device, 32 up to `wide`
+// samples and eight beyond (constant lanes save 1 to 2 %: 36,503 samples 70.2
+// against 71.3 us).  kHeld: each lane holds the corners for itself (two waves
+// per SIMD).
+template <bool kHeld, int kLanes>
 __global__ void __launch_bounds__(kSolveBlock, kHeld ? 2 : 3) solve_kernel(
     const float *__restrict__ xp_soa, int64_t S, const int64_t *__restrict__ S_dev, int64_t ld,
     const float *__restrict__ B, int nb, const float *__restrict__ A, Grid gr, Box hbox, int max_iter, float tol_stop,
     float tol_valid, float *__restrict__ xc_soa, int16_t *__restrict__ bone_out, float *__restrict__ resid_out,
-    int16_t *__restrict__ steps_out, int lanes, int64_t wide) {
+    int16_t *__restrict__ steps_out, int64_t wide) {
   __shared__ float sBinv[kMaxBones * 12];
   __shared__ int sBok[kMaxBones];
   __shared__ float keep[6 * kSolveBlock];
@@ -74,7 +76,7 @@ __global__ void __launch_bounds__(kSolveBlock, kHeld ? 2 : 3) solve_kernel(
   stage_bone_inverses(B, nb, sBinv, sBok);
   __syncthreads();
   const int64_t Sn = count_of(S, S_dev);
-  if (Sn <= wide) lanes = kWideGroup;
+  const int lanes = kLanes > 0 ? kLanes : Sn <= wide ? kWideGroup : kGroup;
   const int j = threadIdx.x & (lanes - 1), mine = (int)threadIdx.x / lanes, per_block = kSolveBlock / lanes;
   // every lane of a block runs the same iterations, so the groups' shuffles
   // always see all their lanes
@@ -639,11 +641,14 @@ int32_t deform_launch(const float *xp, int64_t S, const int64_t *S_dev, int64_t 
     hb.hi[a] = hash_aabb[3 + a];
   }
   const int64_t wide = wide_samples(nb);
-  const int lanes = nb <= kNarrowGroup ? kNarrowGroup : kGroup;
-  auto *kernel = S > wide && few_inits(S, nb) ? solve_kernel<true> : solve_kernel<false>;
-  kernel<<<stride_grid(ceil_div(S * (S <= wide ? kWideGroup : lanes), kSolveBlock), S_dev != nullptr), kSolveBlock, 0,
-           s>>>(xp, S, S_dev, ld, B, nb, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps, lanes,
-                wide);
+  const bool held = S > wide && few_inits(S, nb), by_count = S_dev && wide > 0;
+  const int lanes = nb <= kNarrowGroup ? kNarrowGroup : S <= wide ? kWideGroup : kGroup;
+  auto *kernel = lanes == kNarrowGroup ? (held ? solve_kernel<true, kNarrowGroup> : solve_kernel<false, kNarrowGroup>)
+                 : lanes == kWideGroup ? solve_kernel<false, kWideGroup>
+                 : by_count            ? (held ? solve_kernel<true, 0> : solve_kernel<false, 0>)
+                                       : (held ? solve_kernel<true, kGroup> : solve_kernel<false, kGroup>);
+  kernel<<<stride_grid(ceil_div(S * lanes, kSolveBlock), S_dev != nullptr), kSolveBlock, 0, s>>>(
+      xp, S, S_dev, ld, B, nb, A, g, hb, max_iter, tol_stop, tol_valid, xc, bone, resid, steps, wide);
   return launch_status();
 }
 
