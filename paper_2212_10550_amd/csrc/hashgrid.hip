@@ -187,12 +187,18 @@ void launch_encode(const EncodeArgs &a, int lv_lane, int sp_lane, unsigned g, hi
 // workspace part [L][3][S].  The second sums the levels in a fixed order.
 constexpr int kBwdBlock = 256;
 constexpr int kBwdMaxLevels = 16;  // the backward's level limit
+// Wave priority: beside the table gradient of a training step the position
+// gradient is the longer chain, and its waves come first where they share a
+// SIMD with the sort's (captured step of 8,192 rays: 332 us without, 327 so,
+// 330 with the first kernel alone; the moments after it are no faster for it).
+constexpr int kXgradPrio = 2;
 
 template <typename TT, int kLv>
 __global__ void __launch_bounds__(kBwdBlock) xgrad_level_kernel(
     const float *__restrict__ gfeat, const float *__restrict__ xc, const int16_t *__restrict__ bone, int64_t S,
     const int64_t *__restrict__ S_dev, int64_t ld, const TT *__restrict__ table, int L, int log2T, Levels lv, Box box,
     float *__restrict__ part, int ngroup) {
+  __builtin_amdgcn_s_setprio(kXgradPrio);
   // the encode's mapping: kLv levels (b % 8) + 8 (kLv g + t) per lane
   const int slot = blockIdx.x / kXcd;
   const int64_t Sn = count_of(S, S_dev);
@@ -266,6 +272,7 @@ void launch_xgrad(int lv_lane, unsigned blocks, hipStream_t s, const float *gfea
 __global__ void __launch_bounds__(kBwdBlock) xgrad_sum_kernel(const float *__restrict__ part, int64_t S,
                                                               const int64_t *__restrict__ S_dev, int L, int64_t ld,
                                                               float *__restrict__ gxc) {
+  __builtin_amdgcn_s_setprio(kXgradPrio);
   const int64_t Sn = count_of(S, S_dev);
   for (int64_t n = (int64_t)blockIdx.x * kBwdBlock + threadIdx.x; n < Sn; n += (int64_t)gridDim.x * kBwdBlock) {
     // all loads first (independent addresses), then the sums in level order
