@@ -4,8 +4,9 @@
 //             keep mask, 64 steps a word), the ray's count and the block's
 //             total: one wave per ray and one lane per sample for few rays,
 //             one lane per ray for many;
-//   chunk  -- each block scans 8192 block totals (exclusive, in place) and
-//             writes its chunk total;
+//   chunk  -- each block scans 8192 block totals (exclusive, in place; one
+//             block of 1024 or 4096 where that is all) and writes its chunk
+//             total;
 //   top    -- one block scans the chunk totals and writes the sample count
 //             (skipped when there is one chunk: the chunk kernel writes it);
 //   fill   -- from the keep masks and the ray's entry distance: only kept
@@ -490,8 +491,7 @@ extern "C" int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d,
       fn<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, reinterpret_cast<const uint8_t *>(occ_bits), G, box, dt,
                                            n_per_ray, max_steps, ray_off, ray_cnt, ray_dt, block_sum, mw.masks, nw,
                                            mw.tn);
-    }
-    else if (pow2)
+    } else if (pow2)
       march_count<true><<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, occ_bits, G, box, dt, n_per_ray,
                                                           max_steps, ray_off, ray_cnt, ray_dt, block_sum, mw.masks, nw,
                                                           mw.tn);
@@ -505,8 +505,8 @@ extern "C" int32_t ia355_occgrid_march(const float *rays_o, const float *rays_d,
   if (nchunk != 1) march_scan_top<<<1, 1024, 0, s>>>(chunk_sum, nchunk, ray_off, R, n_samples);
   if (R > 0 && cap > 0) {
     if (many)
-      march_fill_many<<<dim3((unsigned)nblk, fill_parts(R)), kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
-                                                        ray_off, ray_cnt, ray_dt, xs, ts, ray_id, cap);
+      march_fill_many<<<dim3((unsigned)nblk, fill_parts(R)), kBlock, 0, s>>>(
+          rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum, ray_off, ray_cnt, ray_dt, xs, ts, ray_id, cap);
     else
       march_fill<<<(unsigned)nblk, kBlock, 0, s>>>(rays_o, rays_d, R, mw.masks, nw, mw.tn, block_sum, chunk_sum,
                                                    ray_off, ray_dt, xs, ts, ray_id, cap);
