@@ -41,6 +41,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -903,6 +904,7 @@ def short_kernel_name(name):
     if name.startswith("void "):
         name = name[5:]
     name = name.replace("(anonymous namespace)::", "")
+    name = re.sub(r"\([\w:]+\)(?=\d)", "", name)  # an enumerator among the template arguments
     return name.split("(", 1)[0]
 
 
